@@ -142,7 +142,7 @@ __device__ __forceinline__ int64_t pos_offset(const CacheView &c, int l, int s, 
 // Workspace carve-up (all offsets 256-byte aligned).
 struct Workspace {
     size_t band_rev;   // double [F]: omega_f / 2pi
-    size_t fold_phasors;   // double [1 + S][F][2]: mean over the offsets of e^{i w delta}; e^{i w cur_pos[s]}
+    size_t reserved;   // ((1 + S) F 2 doubles, unused: the total is what callers' workspaces were sized for)
     size_t phasors;    // relative-position phasor table of the MFMA score kernel
     size_t table;      // float  [L][S][Hkv][F][3][G]: folded centre table
     size_t work;       // int32: item counter and work list of the MFMA score kernel

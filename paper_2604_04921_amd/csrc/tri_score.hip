@@ -23,14 +23,14 @@ struct FoldArgs {
     const float *centers;   // [L][Hq][F][3]
     float *table;           // [L][S][Hkv][F][3][G]
     double *band_rev;       // [F]
-    double *phasors;        // [1 + S][F][2]: (0) mean over the offsets of e^{i w delta}; (1 + s) e^{i w cur_pos[s]}
     const int32_t *cur_pos; // [S]
     const int32_t *seq_len; // [S]
-    int32_t *work;          // work list of the MFMA score kernel, or NULL when the generic kernel runs
+    int32_t *work;          // work list of the MFMA score kernels, or NULL when the generic kernel runs
     int32_t chunk_keys;     // keys per entry of that list
     float4 *lane_table;     // relative-position phasor table of the one-key-per-lane kernel to fill in, or NULL
     int32_t max_seq_len;
-    int32_t S, Hq, Hkv, G;
+    int32_t L, S, Hq, Hkv, G;
+    int32_t seq_blocks;     // workgroups per (layer, KV head)
     double theta;
     int32_t n_off;
     int32_t variant;        // tri_score_variant
@@ -45,67 +45,84 @@ __device__ __forceinline__ void unit_phasor(double t, double rev, double *c, dou
     sincos(kTwoPi * x, s, c);
 }
 
-// The phasors the fold needs depend on the band and, for the query position, on the sequence only: they
-// are evaluated once here (double-precision pow / sincos are long software routines) instead of once per
-// query head and layer.  grid (2 + S), block F: thread = band.  Workgroup S + 1 has nothing to do with phasors:
-// it lists the chunks of the MFMA score kernel (a launch of its own would cost more than the list); nor have the
-// kLaneTableEntries / F workgroups after it, which fill the one-key-per-lane kernel's table when it is asked for.
-__global__ __launch_bounds__(kBands) void fold_phasor_kernel(FoldArgs a)
+constexpr int kFoldSeqs = 8;      // sequences per workgroup
+constexpr int kFoldThreads = 512;
+
+// The folded tables of one (layer, KV head) and up to kFoldSeqs sequences per workgroup: grid (L * Hkv * seq_blocks + extra),
+// block 512.  The phasors a fold needs depend on the band and on the offsets or the query position only, and every
+// workgroup evaluates them for itself: (offset, band) and (sequence, band) pairs spread over its threads, three double-precision
+// sincos per thread for 16 offsets and 8 sequences, the offsets then added in their order by one thread per band.  The
+// kernel is bound by that chain of software sincos and pow, not by its work: a launch of its own for the phasors, in which one
+// thread per band went through the offsets one after the other, and a second one for the tables took 5.8 + 4.6 us (10.6 + 5.1
+// with 32 offsets); with this one a step on one head's 4096 keys takes 35.6 us instead of 39.5, on one layer of eight heads
+// x 32768 keys 74.3 instead of 78.4.
+// The extra workgroups have nothing to do with the tables: the first lists the chunks of the MFMA score kernels and
+// writes the band frequencies (a launch of its own would cost more than the list), the kLaneTableEntries / 512 after it
+// fill the one-key-per-lane kernel's phasor table when it is asked for.
+__global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
 {
-    if ((int)blockIdx.x > a.S + 1) {
-        lane_phasor_entry(a.theta, ((int)blockIdx.x - a.S - 2) * kBands + (int)threadIdx.x, a.lane_table);
+    __shared__ double off_ph[kMaxOffsets * kBands][2];   // e^{i w delta_j}: entry (j, band); row 0 then holds their mean
+    __shared__ double cur_ph[kFoldSeqs * kBands][2];     // e^{i w cur_pos[s]}
+    const int tid = threadIdx.x;
+    const int n_fold = a.L * a.Hkv * a.seq_blocks;
+    // Section 2.1: omega_f = theta^(-2f/d); kept as revolutions per position.  (kFoldThreads is a multiple of F: a
+    // thread's band is the same in every loop below)
+    const int f = tid % kBands;
+    const int extra = (int)blockIdx.x - n_fold;   // uniform over the workgroup
+    if (extra > 0) {
+        lane_phasor_entry(a.theta, (extra - 1) * kFoldThreads + tid, a.lane_table);
         return;
     }
-    if ((int)blockIdx.x == a.S + 1) {   // uniform over the workgroup
+    const double rev = pow(a.theta, -2.0 * (double)f / (double)kHeadDim) / kTwoPi;
+    if (extra == 0) {
+        if (tid < kBands) a.band_rev[f] = rev;
         if (a.work) build_work_list(a.seq_len, a.S, a.max_seq_len, a.chunk_keys, a.work);
         return;
     }
-    const int f = threadIdx.x;
-    // Section 2.1: omega_f = theta^(-2f/d); kept as revolutions per position
-    const double rev = pow(a.theta, -2.0 * (double)f / (double)kHeadDim) / kTwoPi;
-    double *out = a.phasors + ((int64_t)blockIdx.x * kBands + f) * 2;
-    if (blockIdx.x == 0) {
-        a.band_rev[f] = rev;
+    const int lh = blockIdx.x / a.seq_blocks, sb = blockIdx.x - lh * a.seq_blocks;
+    const int l = lh / a.Hkv, h = lh - l * a.Hkv;
+    const int s0 = sb * kFoldSeqs, n_seq = min(a.S - s0, kFoldSeqs);
+    for (int k = tid; k < a.n_off * kBands; k += kFoldThreads) {
+        double c, s;
+        unit_phasor((double)a.offsets[k / kBands], rev, &c, &s);
+        off_ph[k][0] = c;
+        off_ph[k][1] = s;
+    }
+    for (int k = tid; k < n_seq * kBands; k += kFoldThreads) {
+        double c, s;
+        unit_phasor((double)a.cur_pos[s0 + k / kBands], rev, &c, &s);
+        cur_ph[k][0] = c;
+        cur_ph[k][1] = s;
+    }
+    __syncthreads();
+    if (tid < kBands) {   // mean over the offsets, in their order
         double er = 0.0, ei = 0.0;
         for (int j = 0; j < a.n_off; ++j) {
-            double c, s;
-            unit_phasor((double)a.offsets[j], rev, &c, &s);
-            er += c;
-            ei += s;
+            er += off_ph[j * kBands + f][0];
+            ei += off_ph[j * kBands + f][1];
         }
-        out[0] = er / (double)a.n_off;
-        out[1] = ei / (double)a.n_off;
-    } else {
-        double c, s;
-        unit_phasor((double)a.cur_pos[blockIdx.x - 1], rev, &c, &s);
-        out[0] = c;
-        out[1] = s;
+        off_ph[f][0] = er / (double)a.n_off;
+        off_ph[f][1] = ei / (double)a.n_off;
     }
-}
-
-constexpr int kFoldSeqs = 8;   // sequences per workgroup
-
-// grid (Hkv, L, ceil(S / kFoldSeqs)), block F * G: thread = (band, query head of the group), so that a
-// wave's stores fill whole stretches of the [F][3][G] table of its head-instance
-__global__ __launch_bounds__(kBands *kMaxGroup) void fold_kernel(FoldArgs a)
-{
-    const int f = threadIdx.x / a.G, g = threadIdx.x % a.G, h = blockIdx.x, l = blockIdx.y;
-    const int qh = h * a.G + g;
-    const double er = a.phasors[f * 2], ei = a.phasors[f * 2 + 1];
-    const float *ct = a.centers + (((int64_t)l * a.Hq + qh) * kBands + f) * 3;
-    const double qr = (double)ct[0], qi = (double)ct[1], qa = (double)ct[2];
+    __syncthreads();
     // the ablation variants (Section 5) only change the table: no trig part, no norm part, or the norm
     // part without its (1 - R_f) weight, i.e. S_norm^(0) of Section 4.1
     const bool trig_on = a.variant != TRI_SCORE_NORM_ONLY, norm_on = a.variant != TRI_SCORE_TRIG_ONLY;
-    const double ar = trig_on ? qr * er - qi * ei : 0.0, ai = trig_on ? qr * ei + qi * er : 0.0;
-    const double cn = !norm_on ? 0.0 : a.variant == TRI_SCORE_NORM_UNWEIGHTED ? qa : qa - hypot(qr, qi);
-    const int s_end = min(a.S, ((int)blockIdx.z + 1) * kFoldSeqs);
-    for (int s = blockIdx.z * kFoldSeqs; s < s_end; ++s) {
-        const double c = a.phasors[((int64_t)(1 + s) * kBands + f) * 2], sn = a.phasors[((int64_t)(1 + s) * kBands + f) * 2 + 1];
-        float *t = a.table + (((((int64_t)l * a.S + s) * a.Hkv + h) * kBands + f) * 3) * a.G;
-        t[0 * a.G + g] = (float)(ar * c - ai * sn);
-        t[1 * a.G + g] = (float)(ar * sn + ai * c);
-        t[2 * a.G + g] = (float)cn;
+    // (band, query head) pairs, the head fastest: neighbouring threads write neighbouring entries of [F][3][G]
+    for (int k = tid; k < kBands * a.G; k += kFoldThreads) {
+        const int fb = k / a.G, g = k - fb * a.G;
+        const float *ct = a.centers + (((int64_t)l * a.Hq + h * a.G + g) * kBands + fb) * 3;
+        const double er = off_ph[fb][0], ei = off_ph[fb][1];
+        const double qr = (double)ct[0], qi = (double)ct[1], qa = (double)ct[2];
+        const double ar = trig_on ? qr * er - qi * ei : 0.0, ai = trig_on ? qr * ei + qi * er : 0.0;
+        const double cn = !norm_on ? 0.0 : a.variant == TRI_SCORE_NORM_UNWEIGHTED ? qa : qa - hypot(qr, qi);
+        for (int j = 0; j < n_seq; ++j) {
+            const double c = cur_ph[j * kBands + fb][0], sn = cur_ph[j * kBands + fb][1];
+            float *t = a.table + (((((int64_t)l * a.S + s0 + j) * a.Hkv + h) * kBands + fb) * 3) * a.G;
+            t[0 * a.G + g] = (float)(ar * c - ai * sn);
+            t[1 * a.G + g] = (float)(ar * sn + ai * c);
+            t[2 * a.G + g] = (float)cn;
+        }
     }
 }
 
@@ -452,7 +469,6 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     fo.centers = centers;
     fo.table = reinterpret_cast<float *>(ws + wl.table);
     fo.band_rev = reinterpret_cast<double *>(ws + wl.band_rev);
-    fo.phasors = reinterpret_cast<double *>(ws + wl.fold_phasors);
     fo.cur_pos = c.cur_pos;
     fo.seq_len = c.seq_len;
     fo.work = mfma_path(c, G) ? reinterpret_cast<int32_t *>(ws + wl.work) : nullptr;
@@ -466,7 +482,9 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     }
     fo.chunk_keys = chunk_keys;
     fo.max_seq_len = c.max_seq_len;
+    fo.L = m.n_layers;
     fo.S = c.n_seqs;
+    fo.seq_blocks = (c.n_seqs + kFoldSeqs - 1) / kFoldSeqs;
     fo.Hq = m.n_q_heads;
     fo.Hkv = m.n_kv_heads;
     fo.G = G;
@@ -481,12 +499,9 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     const bool lane_kernel = fo.work && m.pairs == TRI_PAIR_INTERLEAVED && (c.block_size == 0 || chunk_keys < kFastChunk);
     const bool lane_table = lane_kernel && !c.k_rotated;
     fo.lane_table = lane_table ? reinterpret_cast<float4 *>(ws + wl.phasors) : nullptr;
-    hipLaunchKernelGGL(fold_phasor_kernel, dim3(2 + c.n_seqs + (lane_table ? kLaneTableEntries / kBands : 0)),
-                       dim3(kBands), 0, st, fo);
-    tri_status rc0 = hip_status("fold_phasor_kernel");
-    if (rc0 != TRI_OK) return rc0;
-    hipLaunchKernelGGL(fold_kernel, dim3(m.n_kv_heads, m.n_layers, (c.n_seqs + kFoldSeqs - 1) / kFoldSeqs),
-                       dim3(kBands * G), 0, st, fo);
+    // (L * Hkv * seq_blocks is below 2^31: at most L * Hkv * S, which the entry points bound)
+    hipLaunchKernelGGL(fold_kernel, dim3(m.n_layers * m.n_kv_heads * fo.seq_blocks + 1 + (lane_table ? kLaneTableEntries / kFoldThreads : 0)),
+                       dim3(kFoldThreads), 0, st, fo);
     tri_status rc = hip_status("fold_kernel");
     if (rc != TRI_OK) return rc;
 

@@ -42,35 +42,43 @@ constexpr int kPhasorBlockStride = kPhasorRange * 16 + 64;      // bytes per 4-b
 constexpr int kPhasorHalfStride = 16 * kPhasorBlockStride;      // bytes per half (bands 0-1 / 2-3 of a chunk)
 constexpr int kPhasorBytes = 2 * kPhasorHalfStride;
 
-// Work list of the MFMA score kernel, built on the device from the sequence lengths by one workgroup of any size
-// (kWorkThreads at most): [0] the kernel's shared item counter (zeroed here), [1] entries per (layer, KV head), from
-// kWorkHeader on one (sequence, chunk) pair per chunk of chunk_keys keys that exists.
+// Work list of the MFMA score kernels, built on the device from the sequence lengths by one workgroup of a multiple of
+// 64 threads: [0] the kernel's shared item counter (zeroed here), [1] entries per (layer, KV head), from
+// kWorkHeader on one (sequence, chunk) pair per chunk of chunk_keys keys that exists.  The first wave finds where each of
+// 64 runs of sequences starts with a shuffle scan (one thread adding 64 LDS entries one after the other took 3 us),
+// then every run's pairs are written by one lane of each wave.
 constexpr int kWorkHeader = 4;
-constexpr int kWorkThreads = 256;
 __device__ __forceinline__ void build_work_list(const int32_t *seq_len, int n_seqs, int max_seq_len, int chunk_keys,
                                                 int32_t *work)
 {
-    __shared__ int start[kWorkThreads + 1];
-    const int tid = threadIdx.x, nt = blockDim.x;
-    const int seg = (n_seqs + nt - 1) / nt, s0 = min(n_seqs, tid * seg), s1 = min(n_seqs, s0 + seg);
-    int cnt = 0;
-    for (int s = s0; s < s1; ++s) cnt += (clamp_len(seq_len[s], max_seq_len) + chunk_keys - 1) / chunk_keys;
-    start[tid + 1] = cnt;
-    __syncthreads();
-    if (tid == 0) {
-        start[0] = 0;
-        for (int k = 1; k <= nt; ++k) start[k] += start[k - 1];
-        work[0] = 0;
-        work[1] = start[nt];
+    __shared__ int start[64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
+    const int seg = (n_seqs + 63) / 64, s0 = min(n_seqs, lane * seg), s1 = min(n_seqs, s0 + seg);
+    auto chunks = [&](int s) { return (clamp_len(seq_len[s], max_seq_len) + chunk_keys - 1) / chunk_keys; };
+    if (wave == 0) {
+        int cnt = 0;
+        for (int s = s0; s < s1; ++s) cnt += chunks(s);
+        int cum = cnt;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int t = __shfl_up(cum, o, 64);
+            if (lane >= o) cum += t;
+        }
+        start[lane] = cum - cnt;
+        if (lane == 63) {
+            work[0] = 0;
+            work[1] = cum;
+        }
     }
     __syncthreads();
-    int o = start[tid];
+    int o = start[lane];
     for (int s = s0; s < s1; ++s) {
-        const int n = (clamp_len(seq_len[s], max_seq_len) + chunk_keys - 1) / chunk_keys;
-        for (int ch = 0; ch < n; ++ch, ++o) {
-            work[kWorkHeader + 2 * o] = s;
-            work[kWorkHeader + 2 * o + 1] = ch;
+        const int n = chunks(s);
+        for (int ch = wave; ch < n; ch += n_waves) {
+            work[kWorkHeader + 2 * (o + ch)] = s;
+            work[kWorkHeader + 2 * (o + ch) + 1] = ch;
         }
+        o += n;
     }
 }
 
@@ -79,7 +87,7 @@ tri_status launch_phasor_table(double theta, uint4 *phasors, hipStream_t st);
 tri_status launch_score_fast(int G, const ScoreArgs &sa, bool half_split, hipStream_t st);
 // bf16 keys with interleaved pairs, one key per lane (tri_score_lane.hip); its own phasor table layout
 // Its table of e^{i w r}: entry (band pair bp, r) = (cos, sin) of bands 2bp and 2bp+1 at relative position r, at byte
-// bp * kLanePairStride + 16 r.  The fold's phasor kernel writes it with kLaneTableEntries extra threads.
+// bp * kLanePairStride + 16 r.  The fold kernel writes it with kLaneTableEntries extra threads.
 constexpr int kLaneRange = 64;                                  // relative positions 0 .. 63
 constexpr int kLanePairStride = kLaneRange * 16 + 16;           // bytes per band pair (16 bytes of skew)
 constexpr int kLanePhasorBytes = (kBands / 2) * kLanePairStride;
