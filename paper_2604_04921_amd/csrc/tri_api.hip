@@ -475,7 +475,7 @@ static tri_status run_step(const tri_model *model, const float *centers, const t
     // evicting in place with the fewest moves, the selection's workgroups do the moves themselves where they can
     const FillTail fill{new_seq_len};
     bool filled = false;
-    if ((rc = launch_select(*model, nullptr, reinterpret_cast<const float *>(ws + wl.raw), nullptr,
+    if ((rc = launch_select(*model, nullptr, reinterpret_cast<float *>(ws + wl.raw), nullptr,
                             reinterpret_cast<const double *>(ws + wl.partials), moments,
                             reinterpret_cast<uint32_t *>(ws + wl.final_), *src, budget, kept_idx, kept_cnt,
                             (hipStream_t)stream, dst ? nullptr : &fill, &filled)) != TRI_OK)

@@ -140,7 +140,7 @@ __global__ __launch_bounds__(kFillThreads) void fill_kernel(CompactArgs a)
     __shared__ int32_t n_tail;
     const int inst = blockIdx.x;
     const FillArgs f{a.src, a.new_seq_len, a.budget, a.elem_bytes, a.row16};
-    fill_block(f, inst, read_cnt(a, inst), a.kept_idx + (int64_t)inst * a.budget, moves, kept_bits, wave_tot, &n_tail);
+    fill_block<kFillThreads>(f, inst, read_cnt(a, inst), a.kept_idx + (int64_t)inst * a.budget, moves, kept_bits, wave_tot, &n_tail);
 }
 
 }  // namespace

@@ -1,5 +1,5 @@
 // In-place eviction that moves as few slots as possible (Section 4.3 fixes no slot order), as a routine of one
-// 256-thread workgroup: the kernel of tri_compact_fill calls it, and so does the selection kernel of short sequences at
+// workgroup: the kernel of tri_compact_fill calls it, and so does the selection kernel of short sequences at
 // the end of the fused step, on the kept slots it has just written.
 #pragma once
 #include "tri_internal.h"
@@ -20,8 +20,9 @@ struct FillArgs {
 // at or beyond cnt (ascending).  Sources (>= cnt) and destinations (< cnt) are disjoint, so the moves need no ordering.
 // idx: the head-instance's kept slots, ascending (read into [0, max_seq_len - 1]: device memory the host cannot check).
 // LDS handed in: moves [2][budget] (destination slots, source slots), kept_bits [ceil(cnt / 32)] at least,
-// wave_tot [4], n_tail [1].  Every thread of the workgroup must call it; it starts with a barrier of its own only
+// wave_tot [THREADS / 64], n_tail [1].  Every thread of the workgroup must call it; it starts with a barrier of its own only
 // after its first LDS writes, so the caller synchronises before if the LDS was in other use.
+template <int THREADS>
 __device__ __forceinline__ void fill_block(const FillArgs &a, int inst, int cnt, const int32_t *idx, int32_t *moves,
                                            uint32_t *kept_bits, uint32_t *wave_tot, int32_t *n_tail)
 {
@@ -31,11 +32,11 @@ __device__ __forceinline__ void fill_block(const FillArgs &a, int inst, int cnt,
     if (a.new_seq_len && l == 0 && h == 0 && tid == 0) a.new_seq_len[s] = cnt;
     auto slot = [&](int j) { return min(max(idx[j], 0), a.c.max_seq_len - 1); };
     const int n_words = (cnt + 31) >> 5;
-    for (int w = tid; w < n_words; w += kFillThreads) kept_bits[w] = 0u;
+    for (int w = tid; w < n_words; w += THREADS) kept_bits[w] = 0u;
     if (tid == 0) *n_tail = 0;
     __syncthreads();
     int my_tail = 0;
-    for (int j = tid; j < cnt; j += kFillThreads) {
+    for (int j = tid; j < cnt; j += THREADS) {
         const int n = slot(j);
         if (n < cnt) atomicOr(&kept_bits[n >> 5], 1u << (n & 31));
         else ++my_tail;
@@ -46,7 +47,7 @@ __device__ __forceinline__ void fill_block(const FillArgs &a, int inst, int cnt,
     const int first_tail = cnt - tail;   // idx is ascending: its last `tail` entries lie at or beyond cnt
     // free slots below cnt, in ascending order, paired with the tail survivors
     int done = 0;
-    for (int w0 = 0; w0 < n_words; w0 += kFillThreads) {
+    for (int w0 = 0; w0 < n_words; w0 += THREADS) {
         const int w = w0 + tid;
         uint32_t free_bits = 0u;
         if (w < n_words) {
@@ -63,7 +64,7 @@ __device__ __forceinline__ void fill_block(const FillArgs &a, int inst, int cnt,
         if (lane == 63) wave_tot[wave] = cum;
         __syncthreads();
         uint32_t before = cum - c, total = 0u;
-        for (int k = 0; k < kFillThreads / 64; ++k) {
+        for (int k = 0; k < THREADS / 64; ++k) {
             if (k < wave) before += wave_tot[k];
             total += wave_tot[k];
         }
@@ -81,7 +82,7 @@ __device__ __forceinline__ void fill_block(const FillArgs &a, int inst, int cnt,
         __syncthreads();
     }
     // done == tail moves; 16 bytes of K and of V per thread and move
-    const int rows_per_pass = kFillThreads / a.row16;
+    const int rows_per_pass = THREADS / a.row16;
     const int r = tid / a.row16, part = tid % a.row16;
     char *kb = (char *)a.c.k, *vb = (char *)a.c.v;
     int32_t *pb = const_cast<int32_t *>(a.c.pos);

@@ -180,15 +180,16 @@ struct MomentLayout {
 };
 tri_status launch_score(const tri_model &m, const float *centers, const tri_cache &c, float *final_out,
                         float *raw_out, char *ws, const Workspace &wl, MomentLayout *moments, hipStream_t st);
-// final_scores given: select on them; else form them from the raw scores and either stats (mean, 1/sigma) or, when
-// partials is given, the per-tile moments (scratch: keys of long sequences)
+// final_scores given: select on them; else form them from the raw scores (which may be overwritten) and either stats
+// (mean, 1/sigma) or, when partials is given, the per-tile moments.  hist: the workspace's `final_` area, for the histograms
+// of long sequences' chunks (at most one word per key and 1024 words per 2048 keys).
 // fill given and taken (*fill_taken set): the selection's workgroups also evict their head-instances in place, as
 // launch_compact_fill would afterwards (short sequences only; else the caller launches the fill itself)
 struct FillTail {
     int32_t *new_seq_len;   // [S] or NULL
 };
-tri_status launch_select(const tri_model &m, const float *final_scores, const float *raw, const double *stats,
-                         const double *partials, MomentLayout moments, uint32_t *scratch, const tri_cache &c,
+tri_status launch_select(const tri_model &m, const float *final_scores, float *raw, const double *stats,
+                         const double *partials, MomentLayout moments, uint32_t *hist, const tri_cache &c,
                          int32_t budget, int32_t *kept_idx, int32_t *kept_cnt, hipStream_t st,
                          const FillTail *fill = nullptr, bool *fill_taken = nullptr);
 tri_status launch_compact(const tri_model &m, const tri_cache &src, const tri_cache &dst, int32_t budget,

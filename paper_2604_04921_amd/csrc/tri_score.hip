@@ -29,7 +29,7 @@ struct FoldArgs {
     int32_t chunk_keys;     // keys per entry of that list
     float4 *lane_table;     // relative-position phasor table of the one-key-per-lane kernel to fill in, or NULL
     int32_t max_seq_len;
-    int32_t L, S, Hq, Hkv, G;
+    int32_t S, Hq, Hkv, G;
     int32_t seq_blocks;     // workgroups per (layer, KV head)
     double theta;
     int32_t n_off;
@@ -48,7 +48,7 @@ __device__ __forceinline__ void unit_phasor(double t, double rev, double *c, dou
 constexpr int kFoldSeqs = 8;      // sequences per workgroup
 constexpr int kFoldThreads = 512;
 
-// The folded tables of one (layer, KV head) and up to kFoldSeqs sequences per workgroup: grid (L * Hkv * seq_blocks + extra),
+// The folded tables of one (layer, KV head) and up to kFoldSeqs sequences per workgroup: grid (Hkv * seq_blocks + extra, L),
 // block 512.  The phasors a fold needs depend on the band and on the offsets or the query position only, and every
 // workgroup evaluates them for itself: (offset, band) and (sequence, band) pairs spread over its threads, three double-precision
 // sincos per thread for 16 offsets and 8 sequences, the offsets then added in their order by one thread per band.  The
@@ -56,7 +56,7 @@ constexpr int kFoldThreads = 512;
 // thread per band went through the offsets one after the other, and a second one for the tables took 5.8 + 4.6 us (10.6 + 5.1
 // with 32 offsets); with this one a step on one head's 4096 keys takes 35.6 us instead of 39.5, on one layer of eight heads
 // x 32768 keys 74.3 instead of 78.4.
-// The extra workgroups have nothing to do with the tables: the first lists the chunks of the MFMA score kernels and
+// The extra workgroups of the first layer's row have nothing to do with the tables: the first lists the chunks of the MFMA score kernels and
 // writes the band frequencies (a launch of its own would cost more than the list), the kLaneTableEntries / 512 after it
 // fill the one-key-per-lane kernel's phasor table when it is asked for.
 __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
@@ -64,11 +64,12 @@ __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
     __shared__ double off_ph[kMaxOffsets * kBands][2];   // e^{i w delta_j}: entry (j, band); row 0 then holds their mean
     __shared__ double cur_ph[kFoldSeqs * kBands][2];     // e^{i w cur_pos[s]}
     const int tid = threadIdx.x;
-    const int n_fold = a.L * a.Hkv * a.seq_blocks;
+    const int n_fold = a.Hkv * a.seq_blocks, l = blockIdx.y;
     // Section 2.1: omega_f = theta^(-2f/d); kept as revolutions per position.  (kFoldThreads is a multiple of F: a
     // thread's band is the same in every loop below)
     const int f = tid % kBands;
     const int extra = (int)blockIdx.x - n_fold;   // uniform over the workgroup
+    if (extra >= 0 && l > 0) return;
     if (extra > 0) {
         lane_phasor_entry(a.theta, (extra - 1) * kFoldThreads + tid, a.lane_table);
         return;
@@ -79,8 +80,7 @@ __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
         if (a.work) build_work_list(a.seq_len, a.S, a.max_seq_len, a.chunk_keys, a.work);
         return;
     }
-    const int lh = blockIdx.x / a.seq_blocks, sb = blockIdx.x - lh * a.seq_blocks;
-    const int l = lh / a.Hkv, h = lh - l * a.Hkv;
+    const int h = blockIdx.x / a.seq_blocks, sb = blockIdx.x - h * a.seq_blocks;
     const int s0 = sb * kFoldSeqs, n_seq = min(a.S - s0, kFoldSeqs);
     for (int k = tid; k < a.n_off * kBands; k += kFoldThreads) {
         double c, s;
@@ -482,7 +482,6 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     }
     fo.chunk_keys = chunk_keys;
     fo.max_seq_len = c.max_seq_len;
-    fo.L = m.n_layers;
     fo.S = c.n_seqs;
     fo.seq_blocks = (c.n_seqs + kFoldSeqs - 1) / kFoldSeqs;
     fo.Hq = m.n_q_heads;
@@ -499,8 +498,7 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     const bool lane_kernel = fo.work && m.pairs == TRI_PAIR_INTERLEAVED && (c.block_size == 0 || chunk_keys < kFastChunk);
     const bool lane_table = lane_kernel && !c.k_rotated;
     fo.lane_table = lane_table ? reinterpret_cast<float4 *>(ws + wl.phasors) : nullptr;
-    // (L * Hkv * seq_blocks is below 2^31: at most L * Hkv * S, which the entry points bound)
-    hipLaunchKernelGGL(fold_kernel, dim3(m.n_layers * m.n_kv_heads * fo.seq_blocks + 1 + (lane_table ? kLaneTableEntries / kFoldThreads : 0)),
+    hipLaunchKernelGGL(fold_kernel, dim3(m.n_kv_heads * fo.seq_blocks + 1 + (lane_table ? kLaneTableEntries / kFoldThreads : 0), m.n_layers),
                        dim3(kFoldThreads), 0, st, fo);
     tri_status rc = hip_status("fold_kernel");
     if (rc != TRI_OK) return rc;

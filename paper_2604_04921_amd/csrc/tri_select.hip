@@ -2,22 +2,26 @@
 // image of the float score, then an ordered emit so that the kept slots come out ascending and equal
 // scores at the threshold go to the lower slots.
 //
-// Either kernel takes final scores (tri_select_topk) or takes the raw per-head scores and their
-// per-chunk moments (or ready-made mean / 1/sigma), forms the statistics and S_final = max_g (S~(g) - mu_g) /
-// sigma_g itself (fused step: neither statistics nor final scores then travel through memory).  Sequences of up to 32768 keys keep their
-// integer keys in registers (select_reg_kernel: one histogram over linear score bins, exact ranking of
-// the threshold bin); longer ones use select_kernel (the same steps over keys held in LDS or, beyond
-// 32768 keys, in a workspace area).
+// Final scores (tri_select_topk) or, in the fused step, the raw per-head scores and their per-chunk moments are the input; the
+// statistics and S_final = max_g (S~(g) - mu_g) / sigma_g are then formed here (neither travels through memory).
+// One workgroup selects among a head-instance's keys (select_kernel): up to 32768 keys lie in its LDS, those of longer
+// sequences stay in memory.  Where one workgroup per head-instance would read the raw scores too slowly -- long
+// sequences, batches of few head-instances -- many workgroups turn them into integer keys and histograms first
+// (keys_kernel).
+#include <algorithm>
+
 #include "tri_fill.h"
 
 namespace tri {
 
 namespace {
 
-constexpr int kSelThreads = 1024;
-constexpr int kSelWaves = kSelThreads / 64;
+typedef float float4v __attribute__((ext_vector_type(4)));
+
+constexpr int kSelThreads = 1024;       // threads per workgroup, or
+constexpr int kSelSmallThreads = 256;   // many short sequences
+constexpr int kSelHeldKeys = 32768;     // keys held in LDS at most
 constexpr int kSelBins = 2048;          // linear score bins of the histogram pass
-constexpr int kSelLdsKeys = 32768;      // keys held in LDS at most
 
 // Monotone map float -> uint32 (larger float <=> larger key); -0.0 is folded onto +0.0.
 __device__ __forceinline__ uint32_t order_key(float x)
@@ -29,18 +33,18 @@ __device__ __forceinline__ uint32_t order_key(float x)
 
 struct SelectArgs {
     const float *final_;   // [inst][Nmax] final scores, or NULL when raw + stats are given
-    const float *raw;      // [inst][G][Nmax]
+    float *raw;            // [inst][G][Nmax]; keys_kernel leaves a head-instance's integer keys in its first row
     const double *stats;   // [inst][G][2] = (mean, 1/sigma); unused when partials is given
     const double *partials;   // [inst][n_tiles][2G] per-tile sum and sum of squares of the raw scores, or NULL
     int32_t n_tiles, tile_keys;
-    uint32_t *scratch;     // [inst][Nmax] keys of sequences too long for LDS (raw mode only)
+    uint32_t *hist;        // [inst][n_chunks][kSelBins / 2]: histograms of the keys' chunks, two 16-bit counts per word
     const int32_t *seq_len;
     int32_t *kept_idx;     // [inst][B]
     int32_t *kept_cnt;     // [inst]
-    int32_t n_seqs, n_kv_heads, max_seq_len, budget, lds_keys;
+    int32_t n_seqs, n_kv_heads, max_seq_len, budget;
+    int32_t chunk_keys, n_chunks;   // keys_kernel: keys per workgroup, workgroups per head-instance
     const int32_t *head_budgets;   // [L][Hkv] or NULL: budget of each (layer, KV head), at most `budget`
-    int32_t n_above, n_upto;       // select_kernel: this launch handles the head-instances with n_above < N <= n_upto
-    // 256-thread select_reg_kernel, fill != 0: the workgroup goes on to evict its head-instance in place (fill_block)
+    // fill != 0: the workgroup goes on to evict its head-instance in place (fill_block)
     FillArgs fa;
     int32_t fill;
 };
@@ -53,8 +57,6 @@ __device__ __forceinline__ int instance_budget(const SelectArgs &a, int inst)
     return min(max(a.head_budgets[l * a.n_kv_heads + h], 0), a.budget);
 }
 
-constexpr int kSelCand = 2048;   // keys of the threshold bin ranked in LDS
-
 __device__ __forceinline__ float key_to_float(uint32_t u)
 {
     return __uint_as_float((u & 0x80000000u) ? (u & 0x7fffffffu) : ~u);
@@ -65,241 +67,174 @@ __device__ __forceinline__ int linear_bin(uint32_t u)
     return (int)fminf(fmaxf(x, 0.0f), 2047.0f);
 }
 
-// grid (instances), block 1024.  G = 0: final scores given; G > 0: raw scores of G query heads given.
+// Mean and 1/sigma of a head-instance's heads, as every kernel here takes them: from the moments (block_stats; every thread
+// of the workgroup calls) or ready-made.
 template <int G>
-__global__ __launch_bounds__(kSelThreads) void select_kernel(SelectArgs a)
+__device__ __forceinline__ void load_zparams(const SelectArgs &a, int inst, int N, int tid, double *zpart, double *zst,
+                                             ZParams (&zp)[G])
 {
-    extern __shared__ uint32_t lds_keys[];
-    __shared__ uint32_t hist[kSelBins];
-    __shared__ uint32_t cand_key[kSelCand];
-    __shared__ int32_t cand_idx[kSelCand];
-    __shared__ uint32_t wave_tot[kSelWaves];
-    __shared__ uint32_t sh[36];   // 0: selected bin, 1: need inside it, 2: candidate count, 3: threshold key, 4..35: bit counters / tie count
-    __shared__ uint32_t wg[2][kSelWaves], we[2][kSelWaves];
+    if (a.partials)   // uniform over the launch
+        block_stats<G>(a.partials + (int64_t)inst * a.n_tiles * (2 * G), (N + a.tile_keys - 1) / a.tile_keys, N, tid,
+                       zpart, zst);
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+        zp[g] = a.partials ? z_params(zst[2 * g], zst[2 * g + 1])
+                           : z_params(a.stats[((int64_t)inst * G + g) * 2], a.stats[((int64_t)inst * G + g) * 2 + 1]);
+}
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int inst = blockIdx.x;
-    const int s = (inst / a.n_kv_heads) % a.n_seqs;
-    const int N = clamp_len(a.seq_len[s], a.max_seq_len);
-    if (N <= a.n_above || N > a.n_upto) return;   // the other launch's head-instance (uniform over the workgroup)
-    const int B = instance_budget(a, inst);
-    int32_t *out = a.kept_idx + (int64_t)inst * a.budget;
-    if (tid == 0) a.kept_cnt[inst] = N < B ? N : B;
-    if (B == 0) return;   // a head whose own budget is 0 keeps nothing
-    if (N <= B) {  // nothing to evict: keep every slot
-        for (int n = tid; n < N; n += kSelThreads) out[n] = n;
-        return;
-    }
-    const bool in_lds = N <= a.lds_keys;
-    const float *fs = G == 0 ? a.final_ + (int64_t)inst * a.max_seq_len : nullptr;
-    const float *rw = G > 0 ? a.raw + (int64_t)inst * (G > 0 ? G : 1) * a.max_seq_len : nullptr;
-    uint32_t *gk = (G > 0 && !in_lds) ? a.scratch + (int64_t)inst * a.max_seq_len : nullptr;
-
-    ZParams zp[G > 0 ? G : 1];
-    if constexpr (G > 0) {
-        __shared__ double zst[2 * (G > 0 ? G : 1)], zpart[32 * (G > 0 ? G : 1)];
-        if (a.partials)   // statistics from the moments (uniform over the launch)
-            block_stats<G>(a.partials + (int64_t)inst * a.n_tiles * (2 * G), (N + a.tile_keys - 1) / a.tile_keys, N, tid,
-                           zpart, zst);
+// The threshold among the m candidates (keys of the bin that holds the B-th largest, zeros behind them up to
+// the next multiple of 32): the key of which fewer than `need` are larger and at least `need` as large.  sh[3] = that key,
+// sh[4] = how many are larger.  Eight neighbouring threads share a candidate and read the list 16 bytes at a time: the phase
+// is a chain of LDS latencies (one thread per candidate, one key per read: 40 candidates cost 3 us).  Barriers are the
+// caller's.
+template <int THREADS>
+__device__ __forceinline__ void rank_candidates(const uint32_t *cand_key, uint32_t m, uint32_t need, int tid, uint32_t *sh)
+{
+    const uint4 *quad = reinterpret_cast<const uint4 *>(cand_key);
+    const int part = tid & 7;
+    for (uint32_t c0 = 0; c0 < m; c0 += THREADS / 8) {   // uniform: every lane takes part in the shuffles
+        const uint32_t c = c0 + (uint32_t)(tid >> 3);
+        const uint32_t kc = c < m ? cand_key[c] : 0u;
+        uint32_t gt = 0u, ge = 0u;
+#pragma unroll 2
+        for (uint32_t q = part; 4u * q < m; q += 8u) {
+            const uint4 k = quad[q];
+            gt += (k.x > kc ? 1u : 0u) + (k.y > kc ? 1u : 0u) + (k.z > kc ? 1u : 0u) + (k.w > kc ? 1u : 0u);
+            ge += (k.x >= kc ? 1u : 0u) + (k.y >= kc ? 1u : 0u) + (k.z >= kc ? 1u : 0u) + (k.w >= kc ? 1u : 0u);
+        }
 #pragma unroll
-        for (int g = 0; g < G; ++g)
-            zp[g] = a.partials ? z_params(zst[2 * g], zst[2 * g + 1])
-                               : z_params(a.stats[((int64_t)inst * G + g) * 2], a.stats[((int64_t)inst * G + g) * 2 + 1]);
-    }
-    // key of slot n from its source (first touch)
-    auto make_key = [&](int n) {
-        float f;
-        if constexpr (G > 0) {
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const float z = z_score(__builtin_nontemporal_load(&rw[(int64_t)g * a.max_seq_len + n]), zp[g]);
-                f = g == 0 ? z : fmaxf(f, z);
-            }
-        } else {
-            f = fs[n];
+        for (int o = 1; o < 8; o <<= 1) {
+            gt += __shfl_xor(gt, o, 64);
+            ge += __shfl_xor(ge, o, 64);
         }
-        return order_key(f);
-    };
-    // key of slot n on later passes
-    auto get_key = [&](int n) {
-        if (in_lds) return lds_keys[n];
-        if constexpr (G > 0) return gk[n];
-        else return order_key(fs[n]);
-    };
-
-    // ---- keys to LDS / scratch, histogram of their linear score bins (see select_reg_kernel: the same three
-    // steps, with the keys in memory instead of registers).  Four rows of loads are issued before their updates.
-    for (int k = tid; k < kSelBins; k += kSelThreads) hist[k] = 0u;
-    if (tid < 36) sh[tid] = 0u;
-    __syncthreads();
-    for (int n0 = tid; n0 < N; n0 += 4 * kSelThreads) {
-        uint32_t u[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) u[j] = make_key(min(n0 + j * kSelThreads, N - 1));
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + j * kSelThreads;
-            if (n < N) {
-                if (in_lds) lds_keys[n] = u[j];
-                else if constexpr (G > 0) gk[n] = u[j];
-                atomicAdd(&hist[linear_bin(u[j])], 1u);
-            }
+        if (c < m && gt < need && need <= ge) {   // candidates of equal key write the same values
+            sh[3] = kc;
+            sh[4] = gt;
         }
-    }
-    __syncthreads();
-
-    // ---- the bin holding the B-th largest: thread t owns bins 2047-2t and 2046-2t, running count from the top
-    {
-        const uint32_t v0 = hist[kSelBins - 1 - 2 * tid], v1 = hist[kSelBins - 2 - 2 * tid];
-        uint32_t cum = v0 + v1;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t t = __shfl_up(cum, o, 64);
-            if (lane >= o) cum += t;
-        }
-        if (lane == 63) wave_tot[wave] = cum;
-        __syncthreads();
-        for (int w = 0; w < wave; ++w) cum += wave_tot[w];
-        const uint32_t excl = cum - v0 - v1, want = (uint32_t)B;
-        if (excl < want && want <= excl + v0) {          // exactly one thread and bin holds the B-th key
-            sh[0] = (uint32_t)(kSelBins - 1 - 2 * tid);
-            sh[1] = want - excl;
-        } else if (excl + v0 < want && want <= cum) {
-            sh[0] = (uint32_t)(kSelBins - 2 - 2 * tid);
-            sh[1] = want - excl - v0;
-        }
-    }
-    __syncthreads();
-    const int sel_bin = (int)sh[0];
-    uint32_t need = sh[1];   // how many keys of the selected bin are kept (>= 1)
-
-    // ---- gather the selected bin's keys (any order; the ranks below do not depend on it)
-    for (int n0 = 0; n0 < N; n0 += kSelThreads) {
-        const int n = n0 + tid;
-        const uint32_t u = n < N ? get_key(n) : 0u;
-        const bool hit = n < N && linear_bin(u) == sel_bin;
-        const uint64_t hm = __ballot(hit);
-        if (hm) {
-            uint32_t base = 0u;
-            if (lane == 0) base = atomicAdd(&sh[2], (uint32_t)__popcll(hm));
-            base = __builtin_amdgcn_readfirstlane(base);
-            const uint32_t pos = base + (uint32_t)__popcll(hm & ((1ull << lane) - 1ull));
-            if (hit && pos < (uint32_t)kSelCand) {
-                cand_key[pos] = u;
-                cand_idx[pos] = n;
-            }
-        }
-    }
-    __syncthreads();
-    const uint32_t m = sh[2];
-    uint32_t thr;
-    if (m <= (uint32_t)kSelCand) {
-        // exact rank of every candidate among the candidates: key descending, slot ascending
-        for (uint32_t c = tid; c < m; c += kSelThreads) {
-            const uint32_t kc = cand_key[c];
-            const int32_t ic = cand_idx[c];
-            uint32_t rank = 0u;
-            for (uint32_t o = 0; o < m; ++o) {
-                const uint32_t ko = cand_key[o];
-                rank += (ko > kc || (ko == kc && cand_idx[o] < ic)) ? 1u : 0u;
-            }
-            if (rank == need - 1u) sh[3] = kc;   // the last kept candidate defines the threshold
-        }
-        __syncthreads();
-        thr = sh[3];
-        // threshold ties kept = need - (candidates strictly above the threshold)
-        uint32_t above = 0u;
-        for (uint32_t c = tid; c < m; c += kSelThreads) above += cand_key[c] > thr ? 1u : 0u;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) above += __shfl_xor(above, o, 64);
-        if (lane == 0 && above) atomicAdd(&sh[4], above);
-        __syncthreads();
-        need -= sh[4];
-    } else {
-        // too many keys in one bin (many equal scores): one bit at a time, keys of the bin only
-        uint32_t prefix = 0u, mask = 0u;
-#pragma unroll 1
-        for (int bit = 31; bit >= 0; --bit) {
-            const uint32_t bm = 1u << bit;
-            uint32_t c = 0u;
-            for (int n0 = 0; n0 < N; n0 += kSelThreads) {
-                const int n = n0 + tid;
-                const uint32_t u = n < N ? get_key(n) : 0u;
-                const bool in = n < N && linear_bin(u) == sel_bin;
-                c += (uint32_t)__popcll(__ballot(in && (u & mask) == prefix && (u & bm) != 0u));
-            }
-            if (lane == 0 && c) atomicAdd(&sh[4 + bit], c);
-            __syncthreads();
-            const uint32_t ones = sh[4 + bit];
-            if (ones >= need) prefix |= bm;
-            else need -= ones;
-            mask |= bm;
-        }
-        thr = prefix;
-    }
-    // keys > thr are kept; of the keys == thr the first `need` slots
-
-    // ---- ordered emit
-    uint32_t g_run = 0u, e_run = 0u;
-    int buf = 0;
-    for (int n0 = 0; n0 < N; n0 += kSelThreads, buf ^= 1) {
-        const int n = n0 + tid;
-        uint32_t u = 0u;
-        const bool in = n < N;
-        if (in) u = get_key(n);
-        const bool gt = in && u > thr, eq = in && u == thr;
-        const uint64_t gm = __ballot(gt), em = __ballot(eq);
-        const uint64_t below = (1ull << lane) - 1ull;
-        const uint32_t g_lt = __popcll(gm & below), e_lt = __popcll(em & below);
-        if (lane == 0) {
-            wg[buf][wave] = __popcll(gm);
-            we[buf][wave] = __popcll(em);
-        }
-        __syncthreads();
-        uint32_t g_before = 0u, e_before = 0u, g_tot = 0u, e_tot = 0u;
-#pragma unroll
-        for (int w = 0; w < kSelWaves; ++w) {
-            const uint32_t a_ = wg[buf][w], b_ = we[buf][w];
-            if (w < wave) {
-                g_before += a_;
-                e_before += b_;
-            }
-            g_tot += a_;
-            e_tot += b_;
-        }
-        const uint32_t e_rank = e_run + e_before + e_lt;
-        if (gt || (eq && e_rank < need)) {
-            const uint32_t dst = g_run + g_before + g_lt + (e_rank < need ? e_rank : need);
-            out[dst] = n;
-        }
-        g_run += g_tot;
-        e_run += e_tot;
     }
 }
 
-// Register-resident variant for sequences of at most THREADS * KPT keys: every thread keeps KPT keys
-// (slot n = j * THREADS + tid) in registers.  Built as 256 x 16 (up to 4096 keys: small workgroups, cheap
-// barriers, eight per CU), 1024 x 8 and 1024 x 32.
-//   1. One histogram pass over 2048 *linear* bins of the score on [-4, 12) (monotone in the score, so
-//      a valid coarse partition; z-scores spread over hundreds of bins, whereas the top bits of their
-//      float image share a handful of values and would serialise the LDS atomics).
-//   2. The bin holding the B-th largest score is found with one scan; its few keys are gathered in LDS
-//      and ranked exactly (key descending, slot ascending), which gives the threshold key and the number
-//      of threshold ties to keep.  A bin with more keys than the LDS list holds (many equal scores)
-//      is resolved one bit at a time from the registers instead.
-//   3. Ordered emit with three barriers: per-(row, wave) counts from ballots, one scan, the stores.
-template <int G, int KPT, int THREADS>
-__global__ __launch_bounds__(THREADS) void select_reg_kernel(SelectArgs a)
+// Sum of the first `wave` of W counts (the loads do not wait for one another).
+template <int W>
+__device__ __forceinline__ uint32_t sum_before(const uint32_t *counts, int wave)
+{
+    uint32_t sum = 0u;
+#pragma unroll
+    for (int w = 0; w < W; ++w) sum += w < wave ? counts[w] : 0u;
+    return sum;
+}
+
+// Raw scores -> integer keys (written over the head-instance's first raw row: every key's scores are read by the thread that
+// writes it) and the histogram of each chunk's linear bins.  grid (instances * n_chunks), block 256.  A streaming kernel:
+// 4 G bytes read and 4 written per key, the next keys' loads issued before a key's arithmetic.  VEC: rows of a
+// multiple of four keys, four keys per thread and load.
+constexpr int kKeysThreads = 256;
+template <int G, bool VEC>
+__global__ __launch_bounds__(kKeysThreads) void keys_kernel(SelectArgs a)
+{
+    __shared__ uint32_t hist[kSelBins];
+    __shared__ double zst[2 * G], zpart[32 * G];
+    const int tid = threadIdx.x;
+    const int inst = blockIdx.x / a.n_chunks, chunk = blockIdx.x - inst * a.n_chunks;
+    const int s = (inst / a.n_kv_heads) % a.n_seqs;
+    const int N = clamp_len(a.seq_len[s], a.max_seq_len);
+    const int c0 = chunk * a.chunk_keys, c1 = min(N, c0 + a.chunk_keys);
+    const int B = instance_budget(a, inst);
+    if (c0 >= N || N <= B || B == 0) return;   // (uniform over the workgroup; select_kernel reads nothing of it either)
+    for (int k = tid; k < kSelBins; k += kKeysThreads) hist[k] = 0u;
+    ZParams zp[G];
+    load_zparams<G>(a, inst, N, tid, zpart, zst, zp);
+    __syncthreads();
+    float *rw = a.raw + (int64_t)inst * G * a.max_seq_len;
+    constexpr int kStep = 4 * kKeysThreads;   // keys per iteration
+    // thread's key i of the iteration at n0
+    auto slot = [&](int n0, int i) { return VEC ? n0 + 4 * tid + i : n0 + i * kKeysThreads + tid; };
+    auto load = [&](int n0, float (&v)[G][4]) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const float *row = rw + (int64_t)g * a.max_seq_len;
+            if constexpr (VEC) {   // (a row holds a multiple of four entries: four from a slot below N exist)
+                const float4v t = __builtin_nontemporal_load(reinterpret_cast<const float4v *>(row + min(slot(n0, 0), (N - 1) & ~3)));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[g][i] = t[i];
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[g][i] = __builtin_nontemporal_load(row + min(slot(n0, i), N - 1));
+            }
+        }
+    };
+    auto finish = [&](int n0, const float (&v)[G][4]) {
+        uint32_t u[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float f = z_score(v[0][i], zp[0]);
+#pragma unroll
+            for (int g = 1; g < G; ++g) f = fmaxf(f, z_score(v[g][i], zp[g]));
+            u[i] = order_key(f);
+        }
+        uint32_t *ks = reinterpret_cast<uint32_t *>(rw);
+        if (VEC && slot(n0, 3) < c1) {
+            *reinterpret_cast<uint4 *>(ks + slot(n0, 0)) = make_uint4(u[0], u[1], u[2], u[3]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (slot(n0, i) < c1) ks[slot(n0, i)] = u[i];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (slot(n0, i) < c1) atomicAdd(&hist[linear_bin(u[i])], 1u);
+    };
+    // A clamped load of the iteration past the end may read what another thread has already replaced by keys: its values
+    // are not used.
+    float cur[G][4], nxt[G][4];
+    load(c0, cur);
+    for (int n0 = c0; n0 < c1; n0 += kStep) {
+        load(n0 + kStep, nxt);
+        finish(n0, cur);
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) cur[g][i] = nxt[g][i];
+    }
+    __syncthreads();
+    uint32_t *out = a.hist + ((int64_t)inst * a.n_chunks + chunk) * (kSelBins / 2);
+    for (int k = tid; k < kSelBins / 2; k += kKeysThreads) out[k] = hist[2 * k] | (hist[2 * k + 1] << 16);
+}
+
+// One workgroup selects among a head-instance's keys.  grid (instances).
+//   SRC     G > 0: raw scores of G query heads; 0: final scores; kFromKeys: what keys_kernel left (integer keys, chunk
+//           histograms; not HELD)
+//   HELD    the keys lie in LDS (dynamic, four bytes per key, whole rows of 256) from the first pass on; else every pass reads
+//           them from memory
+//   VEC     16-byte loads of the source (rows of a multiple of four entries)
+// Steps:
+//   1. Histogram over 2048 *linear* bins of the score on [-4, 12) (monotone in the score, so a valid coarse partition; z-scores
+//      spread over hundreds of bins, whereas the top bits of their float image share a handful of values and would
+//      serialise the LDS atomics).
+//   2. One scan finds the bin that holds the B-th largest score; its few keys are gathered and ranked exactly, which gives the
+//      threshold key and the number of threshold ties to keep.  A bin with more keys than the list holds (many equal
+//      scores) is resolved one bit at a time instead.
+//   3. Ordered emit: every wave owns a contiguous stretch of the slots and knows from the gathering pass how many it keeps.
+// Between the passes there are half a dozen barriers, so the kernel is a chain of latencies wherever the batch does not
+// keep several workgroups per CU busy -- that of fetching its instructions among them: code that unrolled the rows to
+// hold the keys in registers was 27 to 40 KB and ran once through; these loops are 7 to 8 KB (the
+// fill's included, 16), and leave two to three times the registers free.  Measured against that variant: 4608 head-instances of 8000 keys,
+// the whole step 3773 -> 3725 us; 2304 of 32768, this launch 342 -> 302 us; one of 4096, 11.4 -> 8.3 us; a step on eight of
+// 32768 70 -> 66 us.
+constexpr int kFromKeys = -1;
+template <int SRC, bool VEC, bool HELD, int THREADS>
+__global__ __launch_bounds__(THREADS, HELD ? (THREADS == kSelThreads ? 4 : 5) : 8) void select_kernel(SelectArgs a, int64_t key_row)
 {
     constexpr int kWaves = THREADS / 64;
     constexpr int kBinsPerThread = kSelBins / THREADS;
-    __shared__ uint32_t hist[kSelBins];
-    __shared__ uint32_t cand_store[2 * kSelCand];   // candidate keys, then their slots (later the fill's move list)
-    uint32_t *const cand_key = cand_store;
-    int32_t *const cand_idx = reinterpret_cast<int32_t *>(cand_store + kSelCand);
-    __shared__ uint32_t row_g[KPT * kWaves], row_e[KPT * kWaves];   // [row j][wave], then exclusive prefixes
-    __shared__ uint32_t scan_tot[2][kWaves];
-    __shared__ uint32_t sh[36];   // 0: selected bin, 1: need inside it, 2: candidate count, 3: threshold key, 4..35: bit counters / tie count
+    constexpr int kHeads = SRC > 0 ? SRC : 1;
+    constexpr int kCand = kSelBins / 2;             // keys of the threshold bin ranked in LDS
+    extern __shared__ __align__(16) uint32_t keys[];   // HELD: the keys; later the fill's move list
+    __shared__ __align__(16) uint32_t bins[kSelBins];   // the histogram, then candidates (first half keys, second half slots)
+    __shared__ uint32_t scan_tot[kWaves];
+    __shared__ uint32_t wave_gt[kWaves], wave_eq[kWaves];
+    __shared__ uint32_t sh[36];   // 0: selected bin, 1: need inside it, 2: candidate count, 3: threshold key, 4..35: bit counters / larger candidates
+    uint32_t *const cand_key = bins, *const cand_idx = bins + kCand;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -309,13 +244,13 @@ __global__ __launch_bounds__(THREADS) void select_reg_kernel(SelectArgs a)
     const int B = instance_budget(a, inst);
     int32_t *out = a.kept_idx + (int64_t)inst * a.budget;
     if (tid == 0) a.kept_cnt[inst] = N < B ? N : B;
-    // the eviction in place that may follow: the histogram and the candidate arrays are free by then
+    // the eviction in place that may follow: keys and histogram are free by then
     auto fill_tail = [&](int cnt) {
-        if constexpr (THREADS == kFillThreads) {
+        if constexpr (HELD && SRC > 0) {
             if (a.fill) {
-                __syncthreads();   // out[] is complete and nobody reads hist or the candidates any more
-                fill_block(a.fa, inst, cnt, out, reinterpret_cast<int32_t *>(cand_store), hist, scan_tot[0],
-                           reinterpret_cast<int32_t *>(&sh[0]));
+                __syncthreads();   // out[] is complete and nobody reads the LDS any more
+                fill_block<THREADS>(a.fa, inst, cnt, out, reinterpret_cast<int32_t *>(keys), bins, scan_tot,
+                                    reinterpret_cast<int32_t *>(&sh[0]));
             }
         }
     };
@@ -328,89 +263,166 @@ __global__ __launch_bounds__(THREADS) void select_reg_kernel(SelectArgs a)
         fill_tail(N);
         return;
     }
-    for (int k = tid; k < kSelBins; k += THREADS) hist[k] = 0u;
+    const float *src = SRC > 0 ? a.raw + (int64_t)inst * kHeads * a.max_seq_len
+                               : SRC == 0 ? a.final_ + (int64_t)inst * a.max_seq_len : nullptr;
+    const uint32_t *ks = SRC == kFromKeys ? reinterpret_cast<const uint32_t *>(a.raw) + inst * key_row : nullptr;
+
+    // ---- HELD, scores: the first loads go out ahead of the statistics, which are a chain of loads and barriers of their own
+    constexpr int kStep = 4 * THREADS;   // keys per iteration of the loading loop
+    auto src_slot = [&](int n0, int i) { return VEC ? n0 + 4 * tid + i : n0 + i * THREADS + tid; };
+    auto load = [&](int n0, float (&v)[kHeads][4]) {
+#pragma unroll
+        for (int g = 0; g < kHeads; ++g) {
+            const float *row = src + (int64_t)g * a.max_seq_len;
+            if constexpr (VEC) {   // (four entries from a slot below N on exist)
+                const float4v t = __builtin_nontemporal_load(reinterpret_cast<const float4v *>(row + min(src_slot(n0, 0), (N - 1) & ~3)));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[g][i] = t[i];
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[g][i] = __builtin_nontemporal_load(row + min(src_slot(n0, i), N - 1));
+            }
+        }
+    };
+    float cur[kHeads][4];
+    if constexpr (HELD) load(0, cur);
+    for (int k = tid; k < kSelBins; k += THREADS) bins[k] = 0u;
     if (tid < 36) sh[tid] = 0u;
-    __shared__ double zst[2 * (G > 0 ? G : 1)], zpart[32 * (G > 0 ? G : 1)];
-    if constexpr (G > 0) {
-        if (a.partials)   // statistics from the moments (uniform over the launch)
-            block_stats<G>(a.partials + (int64_t)inst * a.n_tiles * (2 * G), (N + a.tile_keys - 1) / a.tile_keys, N, tid,
-                           zpart, zst);
+    if (tid < kWaves) wave_gt[tid] = wave_eq[tid] = 0u;
+    ZParams zp[kHeads];
+    if constexpr (SRC > 0) {
+        __shared__ double zst[2 * kHeads], zpart[32 * kHeads];
+        load_zparams<kHeads>(a, inst, N, tid, zpart, zst, zp);
     }
     __syncthreads();
 
-    // ---- keys into registers, histogram of their linear bins.  A slot past the end holds key 0, which no finite
-    // score maps to (the smallest, -inf, is 0x007fffff) and which lies below every threshold: the later phases
-    // need no bounds test, only "key != 0" where a bin is recomputed.
-    uint32_t key[KPT];
-    {
-        const float *rw = G > 0 ? a.raw + (int64_t)inst * (G > 0 ? G : 1) * a.max_seq_len : nullptr;
-        const float *fs = G == 0 ? a.final_ + (int64_t)inst * a.max_seq_len : nullptr;
-        ZParams zp[G > 0 ? G : 1];
-        if constexpr (G > 0) {
+    // ---- keys into LDS (a slot past the end, up to the row's, holds key 0, which no finite score maps to and which lies below
+    // every threshold), histogram of their bins
+    if constexpr (HELD) {
+        for (int n0 = 0; n0 < N; n0 += kStep) {
+            float nxt[kHeads][4];
+            load(n0 + kStep, nxt);   // (past the end: the last key again)
+            uint32_t u[4];
 #pragma unroll
-            for (int g = 0; g < G; ++g)
-                zp[g] = a.partials ? z_params(zst[2 * g], zst[2 * g + 1])
-                                   : z_params(a.stats[((int64_t)inst * G + g) * 2], a.stats[((int64_t)inst * G + g) * 2 + 1]);
-        }
-        // Rows are taken 16 at a time (fewer with many query heads, and in the 256-thread variant, whose occupancy
-        // depends on its register count; measured: 16 rows 729 us on config 3, was 940; 8 rows 216 us at steady state,
-        // was 240): first the keys of the chunk with unconditional loads (a slot past the end
-        // re-reads the last one), so that the compiler may issue the loads of many rows before it waits for the
-        // first -- one row at a time the phase is bound by load latency --, then the chunk's histogram updates,
-        // whose branches also keep the next chunk's loads from being hoisted (registers).
-        constexpr int kChunkMax = THREADS == 256 ? (G > 4 ? 4 : 8) : G > 6 ? 4 : G > 4 ? 8 : 16;
-        constexpr int kChunk = KPT < kChunkMax ? KPT : kChunkMax;
+            for (int i = 0; i < 4; ++i) {
+                float f = cur[0][i];
+                if constexpr (SRC > 0) {
+                    f = z_score(f, zp[0]);
 #pragma unroll
-        for (int j0 = 0; j0 < KPT; j0 += kChunk) {
-#pragma unroll
-            for (int j = j0; j < j0 + kChunk; ++j) {
-                const int n = j * THREADS + tid;
-                const int nc = min(n, N - 1);
-                float f;
-                if constexpr (G > 0) {
-#pragma unroll
-                    for (int g = 0; g < G; ++g) {
-                        // raw scores are read exactly once
-                        const float z = z_score(__builtin_nontemporal_load(&rw[(int64_t)g * a.max_seq_len + nc]), zp[g]);
-                        f = g == 0 ? z : fmaxf(f, z);
-                    }
-                } else {
-                    f = __builtin_nontemporal_load(&fs[nc]);
+                    for (int g = 1; g < kHeads; ++g) f = fmaxf(f, z_score(cur[g][i], zp[g]));
                 }
-                key[j] = n < N ? order_key(f) : 0u;
+                u[i] = src_slot(n0, i) < N ? order_key(f) : 0u;
+                if (u[i] != 0u) atomicAdd(&bins[linear_bin(u[i])], 1u);
+            }
+            const int end = (N + 255) & ~255;
+            if constexpr (VEC) {
+                if (src_slot(n0, 0) < end) *reinterpret_cast<uint4 *>(keys + src_slot(n0, 0)) = make_uint4(u[0], u[1], u[2], u[3]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (src_slot(n0, i) < end) keys[src_slot(n0, i)] = u[i];
             }
 #pragma unroll
-            for (int j = j0; j < j0 + kChunk; ++j)
-                if (key[j] != 0u) atomicAdd(&hist[linear_bin(key[j])], 1u);
+            for (int g = 0; g < kHeads; ++g)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) cur[g][i] = nxt[g][i];
         }
     }
-    __syncthreads();
-
-    // ---- the bin holding the B-th largest: thread t owns bins 2047 - t*kBinsPerThread and the ones just below
-    {
-        uint32_t v[kBinsPerThread];
-        uint32_t cum = 0u;
+    // The wave's stretch [w0, w1) in rows of 256 slots.  f(n0, u): slot n0 + 4 lane + i holds key u[i]; rows in ascending order.
+    constexpr int kRow = 256;
+    const int seg = ((N + kWaves - 1) / kWaves + kRow - 1) / kRow * kRow;
+    const int w0 = min(N, wave * seg), w1 = min(N, w0 + seg);
+    auto load_row = [&](int n0, uint32_t (&u)[4]) {
+        if constexpr (VEC) {
+            const int n = min(n0 + 4 * lane, (N - 1) & ~3);
+            if constexpr (SRC == 0) {
+                const float4 t = *reinterpret_cast<const float4 *>(src + n);
+                u[0] = order_key(t.x), u[1] = order_key(t.y), u[2] = order_key(t.z), u[3] = order_key(t.w);
+            } else {
+                const uint4 t = *reinterpret_cast<const uint4 *>(ks + n);
+                u[0] = t.x, u[1] = t.y, u[2] = t.z, u[3] = t.w;
+            }
+        } else {
 #pragma unroll
-        for (int k = 0; k < kBinsPerThread; ++k) {
-            v[k] = hist[kSelBins - 1 - kBinsPerThread * tid - k];
-            cum += v[k];
+            for (int i = 0; i < 4; ++i) {
+                const int n = min(n0 + 4 * lane + i, N - 1);
+                u[i] = SRC == 0 ? order_key(src[n]) : ks[n];
+            }
         }
-        const uint32_t own = cum;
+    };
+    auto for_rows = [&](auto f) {
+        if constexpr (HELD) {
+#pragma unroll 1
+            for (int n0 = w0; n0 < w1; n0 += kRow) {
+                const uint4 t = *reinterpret_cast<const uint4 *>(keys + n0 + 4 * lane);
+                const uint32_t u[4] = {t.x, t.y, t.z, t.w};
+                f(n0, u);
+            }
+        } else {
+            uint32_t u[4], nxt[4];
+            if (w0 < w1) load_row(w0, u);
+#pragma unroll 1
+            for (int n0 = w0; n0 < w1; n0 += kRow) {
+                load_row(n0 + kRow, nxt);   // the next row is on its way while this one is looked at
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (n0 + 4 * lane + i >= w1) u[i] = 0u;
+                f(n0, u);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) u[i] = nxt[i];
+            }
+        }
+    };
+
+    // ---- the bin holding the B-th largest: thread t owns bins 2047 - t * kBinsPerThread and the ones just below
+    uint32_t v[kBinsPerThread];
+    if constexpr (SRC == kFromKeys) {
+        static_assert(THREADS == kSelThreads, "one thread per word of a chunk's histogram");
+        v[0] = v[1] = 0u;
+        const int chunks = (N + a.chunk_keys - 1) / a.chunk_keys;
+        const uint32_t *h = a.hist + (int64_t)inst * a.n_chunks * (kSelBins / 2) + (kSelBins / 2 - 1 - tid);
+        for (int c0 = 0; c0 < chunks; c0 += 8) {   // eight loads in flight
+            uint32_t t[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) t[c] = h[(int64_t)min(c0 + c, chunks - 1) * (kSelBins / 2)];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                if (c0 + c >= chunks) t[c] = 0u;
+                v[0] += t[c] >> 16;
+                v[1] += t[c] & 0xffffu;
+            }
+        }
+    } else {
+        if constexpr (!HELD)
+            for_rows([&](int, const uint32_t (&u)[4]) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (u[i] != 0u) atomicAdd(&bins[linear_bin(u[i])], 1u);
+            });
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kBinsPerThread; ++k) v[k] = bins[kSelBins - 1 - kBinsPerThread * tid - k];
+    }
+    {
+        uint32_t own = 0u;
+#pragma unroll
+        for (int k = 0; k < kBinsPerThread; ++k) own += v[k];
+        uint32_t cum = own;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
             const uint32_t t = __shfl_up(cum, o, 64);
             if (lane >= o) cum += t;
         }
-        if (lane == 63) scan_tot[0][wave] = cum;
-        __syncthreads();
-        for (int w = 0; w < wave; ++w) cum += scan_tot[0][w];
-        uint32_t excl = cum - own;
-        const uint32_t need = (uint32_t)B;
+        if (lane == 63) scan_tot[wave] = cum;
+        __syncthreads();   // (the histogram has been read: its place now takes the candidates)
+        for (int k = tid; k < kCand; k += THREADS) cand_key[k] = 0u;
+        uint32_t excl = cum - own + sum_before<kWaves>(scan_tot, wave);
+        const uint32_t want = (uint32_t)B;
 #pragma unroll
-        for (int k = 0; k < kBinsPerThread; ++k) {
-            if (excl < need && need <= excl + v[k]) {
+        for (int k = 0; k < kBinsPerThread; ++k) {   // exactly one thread and bin holds the B-th key
+            if (excl < want && want <= excl + v[k]) {
                 sh[0] = (uint32_t)(kSelBins - 1 - kBinsPerThread * tid - k);
-                sh[1] = need - excl;
+                sh[1] = want - excl;
             }
             excl += v[k];
         }
@@ -419,48 +431,39 @@ __global__ __launch_bounds__(THREADS) void select_reg_kernel(SelectArgs a)
     const int sel_bin = (int)sh[0];
     uint32_t need = sh[1];   // how many keys of the selected bin are kept (>= 1)
 
-    // ---- gather the selected bin's keys (any order; ranks below do not depend on it)
+    // ---- gather the selected bin's keys (any order; the ranks below do not depend on it), count the keys above it
+    uint32_t above_bin = 0u;
+    for_rows([&](int n0, const uint32_t (&u)[4]) {
 #pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-        const int n = j * THREADS + tid;
-        const bool hit = key[j] != 0u && linear_bin(key[j]) == sel_bin;
-        const uint64_t hm = __ballot(hit);
-        if (hm) {
-            uint32_t base = 0u;
-            if (lane == 0) base = atomicAdd(&sh[2], (uint32_t)__popcll(hm));
-            base = __builtin_amdgcn_readfirstlane(base);
-            const uint32_t pos = base + (uint32_t)__popcll(hm & ((1ull << lane) - 1ull));
-            if (hit && pos < (uint32_t)kSelCand) {
-                cand_key[pos] = key[j];
-                cand_idx[pos] = n;
+        for (int i = 0; i < 4; ++i) {
+            const int bin = linear_bin(u[i]);
+            above_bin += (u[i] != 0u && bin > sel_bin) ? 1u : 0u;
+            if (u[i] != 0u && bin == sel_bin) {
+                const uint32_t pos = atomicAdd(&sh[2], 1u);
+                if (pos < (uint32_t)kCand) {
+                    cand_key[pos] = u[i];
+                    cand_idx[pos] = (uint32_t)(n0 + 4 * lane + i);
+                }
             }
         }
-    }
+    });
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) above_bin += __shfl_xor(above_bin, o, 64);
+    if (lane == 0) wave_gt[wave] = above_bin;
     __syncthreads();
     const uint32_t m = sh[2];
     uint32_t thr;
-    if (m <= (uint32_t)kSelCand) {
-        // exact rank of every candidate among the candidates: key descending, slot ascending
-        for (uint32_t c = tid; c < m; c += THREADS) {
-            const uint32_t kc = cand_key[c];
-            const int32_t ic = cand_idx[c];
-            uint32_t rank = 0u;
-            for (uint32_t o = 0; o < m; ++o) {
-                const uint32_t ko = cand_key[o];
-                rank += (ko > kc || (ko == kc && cand_idx[o] < ic)) ? 1u : 0u;
-            }
-            if (rank == need - 1u) sh[3] = kc;   // the last kept candidate defines the threshold
-        }
+    if (m <= (uint32_t)kCand) {
+        rank_candidates<THREADS>(cand_key, m, need, tid, sh);
         __syncthreads();
         thr = sh[3];
-        // threshold ties kept = need - (candidates strictly above the threshold)
-        uint32_t above = 0u;
-        for (uint32_t c = tid; c < m; c += THREADS) above += cand_key[c] > thr ? 1u : 0u;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) above += __shfl_xor(above, o, 64);
-        if (lane == 0 && above) atomicAdd(&sh[4], above);
+        need -= sh[4];   // threshold ties kept
+        for (uint32_t c = tid; c < m; c += THREADS) {   // the waves' own counts
+            const int owner = (int)cand_idx[c] / seg;
+            if (cand_key[c] > thr) atomicAdd(&wave_gt[owner], 1u);
+            else if (cand_key[c] == thr) atomicAdd(&wave_eq[owner], 1u);
+        }
         __syncthreads();
-        need -= sh[4];
     } else {
         // too many keys in one bin (many equal scores): one bit at a time, keys of the bin only
         uint32_t prefix = 0u, mask = 0u;
@@ -468,11 +471,13 @@ __global__ __launch_bounds__(THREADS) void select_reg_kernel(SelectArgs a)
         for (int bit = 31; bit >= 0; --bit) {
             const uint32_t bm = 1u << bit;
             uint32_t c = 0u;
+            for_rows([&](int, const uint32_t (&u)[4]) {
 #pragma unroll
-            for (int j = 0; j < KPT; ++j) {
-                const bool in = key[j] != 0u && linear_bin(key[j]) == sel_bin;
-                c += (uint32_t)__popcll(__ballot(in && (key[j] & mask) == prefix && (key[j] & bm) != 0u));
-            }
+                for (int i = 0; i < 4; ++i) {
+                    const bool in = u[i] != 0u && linear_bin(u[i]) == sel_bin;
+                    c += (uint32_t)__popcll(__ballot(in && (u[i] & mask) == prefix && (u[i] & bm) != 0u));
+                }
+            });
             if (lane == 0 && c) atomicAdd(&sh[4 + bit], c);
             __syncthreads();
             const uint32_t ones = sh[4 + bit];
@@ -481,137 +486,144 @@ __global__ __launch_bounds__(THREADS) void select_reg_kernel(SelectArgs a)
             mask |= bm;
         }
         thr = prefix;
+        uint32_t cg = 0u, ce = 0u;
+        for_rows([&](int, const uint32_t (&u)[4]) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                cg += (uint32_t)__popcll(__ballot(u[i] > thr));
+                ce += (uint32_t)__popcll(__ballot(u[i] == thr));
+            }
+        });
+        if (lane == 0) {
+            wave_gt[wave] = cg;
+            wave_eq[wave] = ce;
+        }
+        __syncthreads();
     }
     // keys > thr are kept; of the keys == thr the first `need` slots
 
-    // ---- ordered emit: slot order is row-major (row j, then wave, then lane)
+    // ---- ordered emit: the wave starts behind the kept slots of the waves before it
+    uint32_t g_run = sum_before<kWaves>(wave_gt, wave), e_run = sum_before<kWaves>(wave_eq, wave);
+    const uint64_t below = (1ull << lane) - 1ull;
+    for_rows([&](int n0, const uint32_t (&u)[4]) {
+        uint32_t g_at = g_run, e_at = e_run;   // kept / threshold keys before the lane's first slot
+        uint64_t eq_any = 0ull;
 #pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-        const uint64_t gm = __ballot(key[j] > thr), em = __ballot(key[j] == thr);
-        if (lane == 0) {
-            row_g[j * kWaves + wave] = (uint32_t)__popcll(gm);
-            row_e[j * kWaves + wave] = (uint32_t)__popcll(em);
+        for (int i = 0; i < 4; ++i) {
+            const uint64_t gm = __ballot(u[i] > thr);
+            g_at += (uint32_t)__popcll(gm & below);
+            g_run += (uint32_t)__popcll(gm);
+            eq_any |= __ballot(u[i] == thr);
         }
-    }
-    __syncthreads();
-    {   // exclusive scan over the KPT*16 (row, wave) counts: thread t owns entry t
-        constexpr int kEntries = KPT * kWaves;
-        static_assert(kEntries <= THREADS, "one thread per (row, wave) entry");
-        uint32_t vg = tid < kEntries ? row_g[tid] : 0u, ve = tid < kEntries ? row_e[tid] : 0u;
-        uint32_t cg = vg, ce = ve;
+        if (eq_any) {
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t tg = __shfl_up(cg, o, 64), te = __shfl_up(ce, o, 64);
-            if (lane >= o) {
-                cg += tg;
-                ce += te;
+            for (int i = 0; i < 4; ++i) {
+                const uint64_t em = __ballot(u[i] == thr);
+                e_at += (uint32_t)__popcll(em & below);
+                e_run += (uint32_t)__popcll(em);
             }
         }
-        if (lane == 63) {
-            scan_tot[0][wave] = cg;
-            scan_tot[1][wave] = ce;
-        }
-        __syncthreads();
-        for (int w = 0; w < wave; ++w) {
-            cg += scan_tot[0][w];
-            ce += scan_tot[1][w];
-        }
-        if (tid < kEntries) {
-            row_g[tid] = cg - vg;
-            row_e[tid] = ce - ve;
-        }
-    }
-    __syncthreads();
-    const uint64_t below = (1ull << lane) - 1ull;
 #pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-        const int n = j * THREADS + tid;
-        const bool gt = key[j] > thr, eq = key[j] == thr;
-        const uint64_t gm = __ballot(gt), em = __ballot(eq);
-        const uint32_t g_before = row_g[j * kWaves + wave] + (uint32_t)__popcll(gm & below);
-        const uint32_t e_before = row_e[j * kWaves + wave] + (uint32_t)__popcll(em & below);
-        if (gt || (eq && e_before < need)) out[g_before + (e_before < need ? e_before : need)] = n;
-    }
+        for (int i = 0; i < 4; ++i) {
+            const bool gt = u[i] > thr, eq = u[i] == thr;
+            const uint32_t dst = g_at + min(e_at, need);
+            if ((gt || (eq && e_at < need)) && dst < (uint32_t)B) out[dst] = n0 + 4 * lane + i;   // (below B unless scores are NaN)
+            g_at += gt ? 1u : 0u;
+            e_at += eq ? 1u : 0u;
+        }
+    });
     fill_tail(B);
 }
 
-template <int G>
-tri_status launch_select_g(const SelectArgs &sa, int n_inst, hipStream_t st)
+template <int SRC>
+tri_status launch_held(const SelectArgs &sa, int n_inst, bool small, bool vec, hipStream_t st)
 {
-    if (sa.max_seq_len <= 16 * 256) {   // short sequences: small workgroups, cheap barriers, many per CU
-        hipLaunchKernelGGL((select_reg_kernel<G, 16, 256>), dim3(n_inst), dim3(256), 0, st, sa);
-        return hip_status("select_reg_kernel");
-    }
-    if (sa.max_seq_len <= 8 * kSelThreads) {
-        hipLaunchKernelGGL((select_reg_kernel<G, 8, kSelThreads>), dim3(n_inst), dim3(kSelThreads), 0, st, sa);
-        return hip_status("select_reg_kernel");
-    }
-    if (sa.max_seq_len <= 32 * kSelThreads) {
-        hipLaunchKernelGGL((select_reg_kernel<G, 32, kSelThreads>), dim3(n_inst), dim3(kSelThreads), 0, st, sa);
-        return hip_status("select_reg_kernel");
-    }
-    // Longer than the register-resident kernel takes.  Two launches split the head-instances by length on the
-    // device: those whose keys fit LDS, and the rest, whose keys go through the workspace -- that launch asks for no
-    // dynamic LDS, so two workgroups share a CU and one's load phase overlaps the other's ranking and emit.
-    auto kern = select_kernel<G>;
-    const size_t lds = (size_t)kSelLdsKeys * sizeof(uint32_t);
-    if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+    auto kern = small ? (vec ? select_kernel<SRC, true, true, kSelSmallThreads> : select_kernel<SRC, false, true, kSelSmallThreads>)
+                      : (vec ? select_kernel<SRC, true, true, kSelThreads> : select_kernel<SRC, false, true, kSelThreads>);
+    size_t lds = (size_t)((sa.max_seq_len + 255) / 256 * 256) * sizeof(uint32_t);
+    if (sa.fill) lds = std::max(lds, (size_t)sa.budget * 2 * sizeof(int32_t));
+    if (lds > 48 * 1024 &&
+        hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         return hip_status("hipFuncSetAttribute(select_kernel)");
-    SelectArgs lo = sa, hi = sa;
-    lo.lds_keys = kSelLdsKeys;
-    lo.n_above = -1;
-    lo.n_upto = kSelLdsKeys;
-    hi.lds_keys = 0;
-    hi.n_above = kSelLdsKeys;
-    hi.n_upto = sa.max_seq_len;
-    hipLaunchKernelGGL(kern, dim3(n_inst), dim3(kSelThreads), lds, st, lo);
-    tri_status rc = hip_status("select_kernel");
-    if (rc != TRI_OK) return rc;
-    hipLaunchKernelGGL(kern, dim3(n_inst), dim3(kSelThreads), 0, st, hi);
+    hipLaunchKernelGGL(kern, dim3(n_inst), dim3(small ? kSelSmallThreads : kSelThreads), lds, st, sa, (int64_t)0);
+    return hip_status("select_kernel");
+}
+
+template <int G>
+tri_status launch_select_g(const SelectArgs &sa, int n_inst, int n_cu, hipStream_t st)
+{
+    // (final scores come from the caller: any alignment that floats have)
+    const bool vec = (sa.max_seq_len & 3) == 0 && (G > 0 || ((uintptr_t)sa.final_ & 15) == 0);
+    if (sa.max_seq_len <= kSelHeldKeys) {
+        // Short sequences: small workgroups, cheap barriers, several per CU -- unless there are so few that a CU has one
+        // anyway (one head-instance of 4096 keys, whole step: 32.1 us with 1024 threads, 33.4 with 256; 288 of 2176, score and
+        // selection: 92.4 and 91.7; 1152: equal; 2304: 385.6 and 384.5).
+        const bool small = sa.max_seq_len <= 4096 && n_inst > n_cu / 2;
+        return launch_held<G>(sa, n_inst, small, vec, st);
+    }
+    if constexpr (G > 0) {
+        // Longer ones through keys_kernel: 512 head-instances of 131072 keys, eight heads, 744 us in one launch that kept the
+        // keys in memory -> 486 + 125 us; 768 of 4096 to 65536 keys, four heads, 486 us in two launches split by length -> 152 +
+        // 80 us.  (Up to 32768 keys the extra launch and the keys' way through memory cost what the wider grid
+        // gains: eight head-instances of 32768 keys, whole step, 64.9 us against 66.2; of 8192, 41.7 against 38.5; 512 of
+        // 32768, 1202 against 1153.)
+        SelectArgs sk = sa;
+        sk.chunk_keys = 2048;   // about sixteen chunks per head-instance; a chunk's counts fit 16 bits
+        while (sk.chunk_keys < 32768 && sk.max_seq_len > 16 * sk.chunk_keys) sk.chunk_keys *= 2;
+        sk.n_chunks = (sk.max_seq_len + sk.chunk_keys - 1) / sk.chunk_keys;
+        const dim3 grid((uint32_t)((int64_t)n_inst * sk.n_chunks));
+        if (vec) hipLaunchKernelGGL((keys_kernel<G, true>), grid, dim3(kKeysThreads), 0, st, sk);
+        else hipLaunchKernelGGL((keys_kernel<G, false>), grid, dim3(kKeysThreads), 0, st, sk);
+        tri_status rc = hip_status("keys_kernel");
+        if (rc != TRI_OK) return rc;
+        const int64_t key_row = (int64_t)G * sk.max_seq_len;
+        auto kern = vec ? select_kernel<kFromKeys, true, false, kSelThreads> : select_kernel<kFromKeys, false, false, kSelThreads>;
+        hipLaunchKernelGGL(kern, dim3(n_inst), dim3(kSelThreads), 0, st, sk, key_row);
+        return hip_status("select_kernel");
+    }
+    if constexpr (G == 0) {
+        auto kern = vec ? select_kernel<0, true, false, kSelThreads> : select_kernel<0, false, false, kSelThreads>;
+        hipLaunchKernelGGL(kern, dim3(n_inst), dim3(kSelThreads), 0, st, sa, (int64_t)0);
+    }
     return hip_status("select_kernel");
 }
 
 }  // namespace
 
-tri_status launch_select(const tri_model &m, const float *final_scores, const float *raw, const double *stats,
-                         const double *partials, MomentLayout moments, uint32_t *scratch, const tri_cache &c,
+tri_status launch_select(const tri_model &m, const float *final_scores, float *raw, const double *stats,
+                         const double *partials, MomentLayout moments, uint32_t *hist, const tri_cache &c,
                          int32_t budget, int32_t *kept_idx, int32_t *kept_cnt, hipStream_t st, const FillTail *fill,
                          bool *fill_taken)
 {
     if (fill_taken) *fill_taken = false;
     const int n_inst = m.n_layers * c.n_seqs * m.n_kv_heads;
     if (n_inst <= 0) return TRI_OK;
-    SelectArgs sa{final_scores, raw, stats, partials, moments.n_tiles, moments.tile_keys, scratch, c.seq_len, kept_idx,
-                  kept_cnt, c.n_seqs, m.n_kv_heads,
-                  c.max_seq_len, budget, c.max_seq_len < kSelLdsKeys ? (c.max_seq_len > 0 ? c.max_seq_len : 1) : kSelLdsKeys,
-                  m.head_budgets, -1, c.max_seq_len};
+    SelectArgs sa{final_scores, raw, stats, partials, moments.n_tiles, moments.tile_keys, hist, c.seq_len, kept_idx,
+                  kept_cnt, c.n_seqs, m.n_kv_heads, c.max_seq_len, budget, 1, 1, m.head_budgets};
     sa.fill = 0;
-    // Sequences short enough for the 256-thread kernel, whose workgroup is the fill's: the eviction in place rides
-    // along (its move list takes the candidate arrays' place, so the budget may not exceed their length) -- on small
-    // batches, whose workgroups are all resident at once (eight per CU): there the launch saved counts (one sequence
-    // of 288 head-instances: 0.147 -> 0.142 ms per step, four: 0.299 -> 0.291), whereas 18432 head-instances take
-    // 0.74 ms this way against 0.21 + 0.44 ms as two launches.
+    // Short sequences: the eviction in place rides along (its move list takes the keys' place in LDS) -- on small batches, whose
+    // workgroups are all resident at once (eight of 256 threads per CU): there the launch saved counts (one sequence of 288
+    // head-instances: 0.147 -> 0.142 ms per step, four: 0.299 -> 0.291), whereas 18432 head-instances take 0.74 ms this way
+    // against 0.21 + 0.44 ms as two launches.
     int n_cu = 0;
-    if (fill && fill_taken && c.max_seq_len <= 16 * kFillThreads && budget <= kSelCand) {
-        const tri_status rcu = device_cus(&n_cu);
-        if (rcu != TRI_OK) return rcu;
-    }
-    if (n_cu > 0 && n_inst <= 8 * n_cu) {
+    const tri_status rcu = device_cus(&n_cu);
+    if (rcu != TRI_OK) return rcu;
+    if (!final_scores && fill && fill_taken && c.max_seq_len <= 4096 && budget <= 2048 && n_inst <= 8 * n_cu) {
         sa.fa = FillArgs{make_view(m, c), fill->new_seq_len, budget, c.dtype == TRI_BF16 ? 2 : 4,
                          kHeadDim * (c.dtype == TRI_BF16 ? 2 : 4) / 16};
         sa.fill = 1;
         *fill_taken = true;
     }
-    if (final_scores) return launch_select_g<0>(sa, n_inst, st);
+    if (final_scores) return launch_select_g<0>(sa, n_inst, n_cu, st);
     switch (m.n_q_heads / m.n_kv_heads) {
-        case 1: return launch_select_g<1>(sa, n_inst, st);
-        case 2: return launch_select_g<2>(sa, n_inst, st);
-        case 3: return launch_select_g<3>(sa, n_inst, st);
-        case 4: return launch_select_g<4>(sa, n_inst, st);
-        case 5: return launch_select_g<5>(sa, n_inst, st);
-        case 6: return launch_select_g<6>(sa, n_inst, st);
-        case 7: return launch_select_g<7>(sa, n_inst, st);
-        case 8: return launch_select_g<8>(sa, n_inst, st);
+        case 1: return launch_select_g<1>(sa, n_inst, n_cu, st);
+        case 2: return launch_select_g<2>(sa, n_inst, n_cu, st);
+        case 3: return launch_select_g<3>(sa, n_inst, n_cu, st);
+        case 4: return launch_select_g<4>(sa, n_inst, n_cu, st);
+        case 5: return launch_select_g<5>(sa, n_inst, n_cu, st);
+        case 6: return launch_select_g<6>(sa, n_inst, n_cu, st);
+        case 7: return launch_select_g<7>(sa, n_inst, n_cu, st);
+        case 8: return launch_select_g<8>(sa, n_inst, n_cu, st);
     }
     set_error("group size not built (1 to 8)");
     return TRI_ERR_UNSUPPORTED;
