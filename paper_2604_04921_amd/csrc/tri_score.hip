@@ -27,7 +27,8 @@ struct FoldArgs {
     const int32_t *seq_len; // [S]
     int32_t *work;          // work list of the MFMA score kernels, or NULL when the generic kernel runs
     int32_t chunk_keys;     // keys per entry of that list
-    float4 *lane_table;     // relative-position phasor table of the one-key-per-lane kernel to fill in, or NULL
+    float4 *phasors;        // relative-position phasor table of the MFMA score kernel, filled in by extra workgroups
+    int32_t lane_kernel;    // its layout: the one-key-per-lane kernel's or the sixteen-lane kernel's
     int32_t max_seq_len;
     int32_t S, Hq, Hkv, G;
     int32_t seq_blocks;     // workgroups per (layer, KV head)
@@ -57,8 +58,8 @@ constexpr int kFoldThreads = 512;
 // with 32 offsets); with this one a step on one head's 4096 keys takes 35.6 us instead of 39.5, on one layer of eight heads
 // x 32768 keys 74.3 instead of 78.4.
 // The extra workgroups of the first layer's row have nothing to do with the tables: the first lists the chunks of the MFMA score kernels and
-// writes the band frequencies (a launch of its own would cost more than the list), the kLaneTableEntries / 512 after it
-// fill the one-key-per-lane kernel's phasor table when it is asked for.
+// writes the band frequencies (a launch of its own would cost more than the list), those after it fill the MFMA score
+// kernel's phasor table when it needs one, an entry per thread.
 __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
 {
     __shared__ double off_ph[kMaxOffsets * kBands][2];   // e^{i w delta_j}: entry (j, band); row 0 then holds their mean
@@ -71,7 +72,9 @@ __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
     const int extra = (int)blockIdx.x - n_fold;   // uniform over the workgroup
     if (extra >= 0 && l > 0) return;
     if (extra > 0) {
-        lane_phasor_entry(a.theta, (extra - 1) * kFoldThreads + tid, a.lane_table);
+        const int t = (extra - 1) * kFoldThreads + tid;
+        if (a.lane_kernel) lane_phasor_entry(a.theta, t, a.phasors);
+        else fast_phasor_entry(a.theta, t, a.phasors);
         return;
     }
     const double rev = pow(a.theta, -2.0 * (double)f / (double)kHeadDim) / kTwoPi;
@@ -393,10 +396,6 @@ tri_status launch_score_g(const tri_model &m, const tri_cache &c, ScoreArgs sa, 
     const int tile_keys = fast ? sa.chunk_keys : kScoreTile;
     sa.n_tiles = (c.max_seq_len + tile_keys - 1) / tile_keys;
     tri_status rc = TRI_OK;
-    if (fast && !lane_kernel && !c.k_rotated) {   // (the one-key-per-lane kernel's table came with the fold's phasors)
-        rc = launch_phasor_table(m.rope_theta, const_cast<uint4 *>(sa.phasors), st);
-        if (rc != TRI_OK) return rc;
-    }
     hipEvent_t ev0, ev1;
     const bool timed = timing_next(&ev0, &ev1);
     if (timed) (void)hipEventRecord(ev0, st);
@@ -472,13 +471,15 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     fo.cur_pos = c.cur_pos;
     fo.seq_len = c.seq_len;
     fo.work = mfma_path(c, G) ? reinterpret_cast<int32_t *>(ws + wl.work) : nullptr;
-    // keys per work item: small batches on the one-key-per-lane kernel are cut finer
+    // keys per work item: small batches are cut finer
     int chunk_keys = kFastChunk;
-    if (fo.work && m.pairs == TRI_PAIR_INTERLEAVED) {
+    if (fo.work) {
         int n_cu = 0;
         tri_status rcu = device_cus(&n_cu);
         if (rcu != TRI_OK) return rcu;
-        chunk_keys = lane_chunk_keys(G, (int64_t)m.n_layers * c.n_seqs * m.n_kv_heads, c.max_seq_len, n_cu);
+        const int64_t inst = (int64_t)m.n_layers * c.n_seqs * m.n_kv_heads;
+        chunk_keys = m.pairs == TRI_PAIR_INTERLEAVED ? lane_chunk_keys(inst, c.max_seq_len, n_cu)
+                                                     : fast_chunk_keys(G, inst, c.max_seq_len, n_cu);
     }
     fo.chunk_keys = chunk_keys;
     fo.max_seq_len = c.max_seq_len;
@@ -491,14 +492,16 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     fo.n_off = m.n_offsets;
     fo.variant = m.score_variant;
     for (int j = 0; j < m.n_offsets; ++j) fo.offsets[j] = m.offsets[j];
-    // Interleaved pairs: the kernel with one key per lane.  Paged caches go there only as small batches (work items
-    // below kFastChunk, which only that kernel takes): on large paged batches the kernel that spreads a key over
-    // sixteen lanes is 3 % faster (config 4: 12.2 ms against 12.5 ms per 12-layer slab), as it is the only one for
-    // half-split pairs.
-    const bool lane_kernel = fo.work && m.pairs == TRI_PAIR_INTERLEAVED && (c.block_size == 0 || chunk_keys < kFastChunk);
-    const bool lane_table = lane_kernel && !c.k_rotated;
-    fo.lane_table = lane_table ? reinterpret_cast<float4 *>(ws + wl.phasors) : nullptr;
-    hipLaunchKernelGGL(fold_kernel, dim3(m.n_kv_heads * fo.seq_blocks + 1 + (lane_table ? kLaneTableEntries / kFoldThreads : 0), m.n_layers),
+    // Interleaved pairs: the kernel with one key per lane; half-split pairs: the one that spreads a key over sixteen lanes.
+    // Large paged batches (whole items of kFastChunk) of short sequences or of more than four query heads per KV head, too:
+    // 3072 x 4096 keys 1055 us a step against 1073, 768 x 4096 to 65536 keys at G = 8 2600 against 2684, at G = 5 2447
+    // against 2495, but 2107 against 2058 at G = 4, 1983 against 1959 at G = 2, 3098 against 3064 on 3072 x 9000 keys.
+    const bool lane_kernel = fo.work && m.pairs == TRI_PAIR_INTERLEAVED &&
+                             (c.block_size == 0 || chunk_keys < kFastChunk || (G <= 4 && c.max_seq_len > kFastChunk));
+    const int table_entries = !fo.work || c.k_rotated ? 0 : lane_kernel ? kLaneTableEntries : kFastTableEntries;
+    fo.phasors = reinterpret_cast<float4 *>(ws + wl.phasors);
+    fo.lane_kernel = lane_kernel;
+    hipLaunchKernelGGL(fold_kernel, dim3(m.n_kv_heads * fo.seq_blocks + 1 + table_entries / kFoldThreads, m.n_layers),
                        dim3(kFoldThreads), 0, st, fo);
     tri_status rc = hip_status("fold_kernel");
     if (rc != TRI_OK) return rc;

@@ -21,22 +21,54 @@ struct ScoreArgs {
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-// Keys per work item of the MFMA score kernels (= keys per entry of `partials` on that path): kFastChunk, or for
-// the one-key-per-lane kernel on a small batch a few rounds of its waves (see lane_chunk_keys), kMinChunk at least.
+// Keys per work item of the MFMA score kernels (= keys per entry of `partials` on that path): kFastChunk on large batches, less
+// where that would leave resident workgroups without work (item_keys), kMinChunk at least.
 constexpr int kFastChunk = 8192;
 constexpr int kMinChunk = 512;
-constexpr int lane_waves(int G) { return G > 4 ? 8 : 12; }      // waves per workgroup of the one-key-per-lane kernel
-// A batch with few tiles per CU is cut into items of r rounds (one tile per wave and round) so that every CU gets
-// about four items or more; r = 1 is the smallest item.
-inline int lane_chunk_keys(int G, int64_t instances, int max_seq_len, int n_cu)
+constexpr int kItemCost = 768;
+constexpr int lane_waves(int G) { return G > 4 ? 8 : 12; }   // waves per workgroup of the one-key-per-lane kernel
+// Waves per workgroup of the sixteen-lane kernel: with more than four query heads per KV head a wave needs more than 128
+// registers, so only three waves fit a SIMD; 12-wave workgroups fill them (8-wave ones would leave one of three unused).
+constexpr int fast_waves(int G) { return G > 4 ? 12 : 8; }
+// Resident workgroups take items until none is left, so a batch takes about (items per workgroup, rounded up) x (an item's keys
+// + the item's own cost in keys: its tables, its first loads, its waves' last ones).  Every head-instance is cut into the
+// number of equal pieces that makes this least, in units that keep the waves' tiles whole; batches of eight or more
+// items of kFastChunk keys per workgroup stay with those.  Measured, whole steps (start: kFastChunk for half-split pairs,
+// about four items per CU in rounds of the workgroup's waves for interleaved ones): one layer of eight x 12289 keys, half-split,
+// 150 -> 43.7 us, sixteen layers 206 -> 180; one layer of eight x 32768, interleaved, 66.5 -> 57.8 us, four layers 126 ->
+// 109, 36 layers 693 -> 674; score + selection of 288 x 2176 keys 91.0 -> 89.4, 576 155 -> 134.  An item cost of 128 keys is
+// worse on many short sequences (1152 x 2176: 243 against 219 us), 384 and 1600 on some in between (576 x 2176, G = 4: 143
+// and 134; 160 x 32768: 387 and 397 against 387), 768 nowhere.
+inline int item_keys(int64_t instances, int max_seq_len, int64_t workgroups, int unit)
 {
-    const int round_keys = lane_waves(G) * 64;
-    const int64_t tiles = instances * (((int64_t)max_seq_len + 63) / 64);
-    const int64_t r = tiles / (4 * (int64_t)(n_cu > 0 ? n_cu : 1) * lane_waves(G));
-    if (r * round_keys >= kFastChunk) return kFastChunk;
-    return (int)(r > 1 ? r : 1) * round_keys;
+    if (instances * ((max_seq_len + kFastChunk - 1) / kFastChunk) >= 8 * workgroups) return kFastChunk;
+    const int least = (kMinChunk + unit - 1) / unit * unit;
+    int best = kFastChunk;
+    int64_t best_cost = INT64_MAX;
+    for (int pieces = 1; pieces <= 1024; ++pieces) {
+        int keys = ((max_seq_len + pieces - 1) / pieces + unit - 1) / unit * unit;
+        const bool last = keys <= least;
+        if (last) keys = least;
+        if (keys > kFastChunk) continue;
+        const int64_t items = instances * ((max_seq_len + keys - 1) / keys);
+        const int64_t cost = (items + workgroups - 1) / workgroups * (keys + kItemCost);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = keys;
+        }
+        if (last) break;
+    }
+    return best;
 }
-// Relative positions covered by the phasor table.
+inline int lane_chunk_keys(int64_t instances, int max_seq_len, int n_cu)
+{
+    return item_keys(instances, max_seq_len, n_cu > 0 ? n_cu : 1, 64);
+}
+inline int fast_chunk_keys(int G, int64_t instances, int max_seq_len, int n_cu)
+{
+    return item_keys(instances, max_seq_len, 2 * (int64_t)(n_cu > 0 ? n_cu : 1), fast_waves(G) * 16);
+}
+// Relative positions covered by its phasor table.
 constexpr int kPhasorRange = 128;
 constexpr int kPhasorBlockStride = kPhasorRange * 16 + 64;      // bytes per 4-band chunk (64 B skew)
 constexpr int kPhasorHalfStride = 16 * kPhasorBlockStride;      // bytes per half (bands 0-1 / 2-3 of a chunk)
@@ -82,7 +114,29 @@ __device__ __forceinline__ void build_work_list(const int32_t *seq_len, int n_se
     }
 }
 
-tri_status launch_phasor_table(double theta, uint4 *phasors, hipStream_t st);
+// (cos, sin) of band f at relative position r, in double
+__device__ __forceinline__ void relative_phasor(double theta, int f, int r, float *c, float *s)
+{
+    constexpr double kTwoPiD = 6.283185307179586476925286766559;
+    double x = (double)r * (pow(theta, -2.0 * (double)f / (double)kHeadDim) / kTwoPiD);
+    x -= floor(x);
+    double sd, cd;
+    sincos(kTwoPiD * x, &sd, &cd);
+    *c = (float)cd;
+    *s = (float)sd;
+}
+// Entry t of the sixteen-lane kernel's table, (half hf, chunk b, r) = (cos, sin) of bands 4b+2hf, 4b+2hf+1 at relative position
+// r, at byte hf * kPhasorHalfStride + b * kPhasorBlockStride + 16 r.  The fold kernel writes it with kFastTableEntries extra
+// threads (a launch of its own took 4.6 us).
+constexpr int kFastTableEntries = 2 * 16 * kPhasorRange;
+__device__ __forceinline__ void fast_phasor_entry(double theta, int t, float4 *out)
+{
+    const int r = t % kPhasorRange, b = (t / kPhasorRange) % 16, hf = t / (kPhasorRange * 16), f = 4 * b + 2 * hf;
+    float4 v;
+    relative_phasor(theta, f, r, &v.x, &v.y);
+    relative_phasor(theta, f + 1, r, &v.z, &v.w);
+    out[(hf * kPhasorHalfStride + b * kPhasorBlockStride) / 16 + r] = v;
+}
 // bf16 keys; G in 1..8
 tri_status launch_score_fast(int G, const ScoreArgs &sa, bool half_split, hipStream_t st);
 // bf16 keys with interleaved pairs, one key per lane (tri_score_lane.hip); its own phasor table layout
@@ -94,19 +148,11 @@ constexpr int kLanePhasorBytes = (kBands / 2) * kLanePairStride;
 constexpr int kLaneTableEntries = (kBands / 2) * kLaneRange;
 __device__ __forceinline__ void lane_phasor_entry(double theta, int t, float4 *out)
 {
-    constexpr double kTwoPiD = 6.283185307179586476925286766559;
     const int r = t % kLaneRange, bp = t / kLaneRange;
-    float v[4];
-    for (int k = 0; k < 2; ++k) {
-        const int f = 2 * bp + k;
-        double x = (double)r * (pow(theta, -2.0 * (double)f / (double)kHeadDim) / kTwoPiD);
-        x -= floor(x);
-        double s, c;
-        sincos(kTwoPiD * x, &s, &c);
-        v[2 * k] = (float)c;
-        v[2 * k + 1] = (float)s;
-    }
-    out[bp * (kLanePairStride / 16) + r] = make_float4(v[0], v[1], v[2], v[3]);
+    float4 v;
+    relative_phasor(theta, 2 * bp, r, &v.x, &v.y);
+    relative_phasor(theta, 2 * bp + 1, r, &v.z, &v.w);
+    out[bp * (kLanePairStride / 16) + r] = v;
 }
 tri_status launch_score_lane(int G, const ScoreArgs &sa, hipStream_t st);
 // ints the MFMA kernel's work list takes: a header and one (sequence, chunk) pair per possible chunk

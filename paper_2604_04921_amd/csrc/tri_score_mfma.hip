@@ -28,33 +28,10 @@ namespace tri {
 
 namespace {
 
-constexpr double kTwoPi = 6.283185307179586476925286766559;
 constexpr int kMaxDevices = 64;   // GPUs of one process the occupancy cache distinguishes
-// Workgroup size of the score kernel: with more than four query heads per KV head a wave needs more than 128
-// registers, so only three waves fit a SIMD; 12-wave workgroups fill them (8-wave ones would leave one of three unused).
-constexpr int fast_threads(int G) { return G > 4 ? 768 : 512; }
+constexpr int fast_threads(int G) { return fast_waves(G) * 64; }
 
 typedef float float4v __attribute__((ext_vector_type(4)));
-
-// grid (2*16*R / 256), block 256: entry (half hf, chunk b, r) = (cos, sin) of bands 4b+2hf, 4b+2hf+1
-// at relative position r, in double, stored at byte hf*HalfStride + b*BlockStride + 16*r.
-__global__ __launch_bounds__(256) void phasor_table_kernel(double theta, float4 *out)
-{
-    const int t = blockIdx.x * 256 + threadIdx.x;
-    const int r = t % kPhasorRange, b = (t / kPhasorRange) % 16, hf = t / (kPhasorRange * 16);
-    if (hf >= 2) return;
-    float v[4];
-    for (int k = 0; k < 2; ++k) {
-        const int f = 4 * b + 2 * hf + k;
-        double x = (double)r * (pow(theta, -2.0 * (double)f / (double)kHeadDim) / kTwoPi);
-        x -= floor(x);
-        double s, c;
-        sincos(kTwoPi * x, &s, &c);
-        v[2 * k] = (float)c;
-        v[2 * k + 1] = (float)s;
-    }
-    out[(hf * kPhasorHalfStride + b * kPhasorBlockStride) / 16 + r] = make_float4(v[0], v[1], v[2], v[3]);
-}
 
 __device__ __forceinline__ float row_ror_add(float c, int ctrl_is_8)
 {
@@ -161,7 +138,7 @@ __device__ __forceinline__ void score_step(const uint4 kd, const float (&cs)[4],
 }
 
 // grid = as many workgroups as the GPU holds at once, block 512 (768 for G > 4).  A workgroup stays for the whole launch and
-// takes items -- one (layer, KV head, sequence, chunk of 8192 keys) each, listed by build_work_list() -- from a
+// takes items -- one (layer, KV head, sequence, chunk of chunk_keys keys) each, listed by build_work_list() -- from a
 // shared counter until they run out; the phasor table is loaded once per workgroup, and neither empty chunks of short sequences nor the order
 // in which the hardware hands workgroups to the XCDs cost anything (with one workgroup per chunk slot of the
 // longest sequence, ragged batches lost up to a quarter of the kernel's throughput to the empty ones).  The item's
@@ -526,12 +503,15 @@ template <int G>
 tri_status launch_fast_g(const ScoreArgs &sa, bool half_split, hipStream_t st)
 {
     const bool paged = sa.c.block_shift >= 0;
-    auto pick = [&](auto half) {
-        constexpr bool H = decltype(half)::value;
-        return sa.c.k_rotated ? (paged ? score_mfma_kernel<G, true, true, H> : score_mfma_kernel<G, false, true, H>)
-                              : (paged ? score_mfma_kernel<G, true, false, H> : score_mfma_kernel<G, false, false, H>);
-    };
-    auto kern = half_split ? pick(std::true_type{}) : pick(std::false_type{});
+    // (interleaved pairs in a contiguous cache are the one-key-per-lane kernel's)
+    if (!half_split && !paged) {
+        set_error("score: no sixteen-lane kernel for interleaved pairs in a contiguous cache");
+        return TRI_ERR_UNSUPPORTED;
+    }
+    const bool rot = sa.c.k_rotated != 0;
+    auto kern = !half_split ? (rot ? score_mfma_kernel<G, true, true, false> : score_mfma_kernel<G, true, false, false>)
+                : paged     ? (rot ? score_mfma_kernel<G, true, true, true> : score_mfma_kernel<G, true, false, true>)
+                            : (rot ? score_mfma_kernel<G, false, true, true> : score_mfma_kernel<G, false, false, true>);
     const int lds = sa.c.k_rotated ? 0 : kPhasorBytes;   // no phasor table for post-RoPE keys
     if (lds && hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
         return hip_status("hipFuncSetAttribute(score_mfma_kernel)");
@@ -560,7 +540,7 @@ tri_status launch_fast_g(const ScoreArgs &sa, bool half_split, hipStream_t st)
     }
     const int64_t max_items = (int64_t)sa.n_tiles * sa.c.n_seqs * sa.c.n_kv_heads * sa.n_layers;
     if (max_items > (int64_t)0x7fff0000) {   // the item counter is a 32-bit integer
-        set_error("score: %lld chunks of %d keys exceed the 32-bit work counter", (long long)max_items, kFastChunk);
+        set_error("score: %lld chunks of %d keys exceed the 32-bit work counter", (long long)max_items, sa.chunk_keys);
         return TRI_ERR_UNSUPPORTED;
     }
     const int grid = (int)std::min<int64_t>((int64_t)slots, max_items);
@@ -576,13 +556,6 @@ tri_status launch_fast_g(const ScoreArgs &sa, bool half_split, hipStream_t st)
 }
 
 }  // namespace
-
-tri_status launch_phasor_table(double theta, uint4 *phasors, hipStream_t st)
-{
-    hipLaunchKernelGGL(phasor_table_kernel, dim3(2 * 16 * kPhasorRange / 256), dim3(256), 0, st, theta,
-                       reinterpret_cast<float4 *>(phasors));
-    return hip_status("phasor_table_kernel");
-}
 
 tri_status launch_score_fast(int G, const ScoreArgs &sa, bool half_split, hipStream_t st)
 {
