@@ -51,6 +51,24 @@ constexpr int lane_lds_bytes(int G, bool rotated)
 // keys x 1 piece (the reads) then fall into 16 different groups of four banks.
 __device__ __forceinline__ int stage_offset(int k, int p) { return ((k ^ ((k >> 3) & 1)) << 7) + ((p ^ (k & 7)) << 4); }
 
+// Smallest or largest of the wave's 64 values, by DPP (lane 63 ends up with the whole wave's).
+template <bool MAX>
+__device__ __forceinline__ int wave_extreme(int v)
+{
+    auto step = [&](auto ctrl, auto rows) {
+        const int t = __builtin_amdgcn_update_dpp(v, v, decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
+        v = MAX ? max(v, t) : min(v, t);
+    };
+    using std::integral_constant;
+    step(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});   // row_shr 1, 2, 4, 8
+    step(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});   // row_bcast 15 into rows 1, 3
+    step(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});   // row_bcast 31 into rows 2, 3
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
 // ROTATED: the keys are stored post-RoPE (no rotation, no positions).  PAGED: block_size >= 16.
 template <int G, bool PAGED, bool ROTATED>
 __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArgs a)
@@ -236,20 +254,19 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
             float sgn = 1.f;
             double rel_d = 0.0;
             if constexpr (!ROTATED) {
-                int lo = p_key, hi = p_key;
-#pragma unroll
-                for (int o = 32; o >= 1; o >>= 1) {
-                    lo = min(lo, __shfl_xor(lo, o, 64));
-                    hi = max(hi, __shfl_xor(hi, o, 64));
+                // Usual case: slots in the order of their positions, all within 64 of the first: base = the first, r >= 0.
+                // (The lowest and highest position of every tile through twelve LDS shuffles, each waiting for the one before,
+                // cost 64 x 8 head-instances of 131072 keys at G = 8 1 %.)
+                int base = __builtin_amdgcn_readfirstlane(p_key);
+                if (__builtin_amdgcn_ballot_w64((uint32_t)p_key - (uint32_t)base >= (uint32_t)kLaneRange) != 0ull) {
+                    base = wave_extreme<false>(p_key);
+                    const int64_t span = (int64_t)wave_extreme<true>(p_key) - (int64_t)base;
+                    // positions within 64 of the lowest: base = the lowest, r >= 0.  Else base = the middle and the table
+                    // serves |r| (a negative r flips the sine), as long as the span stays below 127.
+                    mirrored = span >= kLaneRange;
+                    in_table = span < 2 * kLaneRange - 1;
+                    if (mirrored) base = (int)((int64_t)base + (span >> 1));
                 }
-                lo = __builtin_amdgcn_readfirstlane(lo);
-                hi = __builtin_amdgcn_readfirstlane(hi);
-                const int64_t span = (int64_t)hi - (int64_t)lo;
-                // positions within 64 of the lowest: base = the lowest, r >= 0.  Else base = the middle and the table
-                // serves |r| (a negative r flips the sine), as long as the span stays below 127.
-                mirrored = span >= kLaneRange;
-                in_table = span < 2 * kLaneRange - 1;
-                const int base = mirrored ? (int)((int64_t)lo + (span >> 1)) : lo;
                 const int64_t rel = (int64_t)p_key - (int64_t)base;
                 rel_d = (double)rel;
                 sgn = rel < 0 ? -1.f : 1.f;
