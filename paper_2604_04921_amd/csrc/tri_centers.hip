@@ -11,94 +11,106 @@ struct CentersArgs {
     float *out;     // [L][Hq][F][3], or NULL: leave the sums in `sums`
     double *sums;   // [L][Hq][F][3] running sums (streaming calibration), or NULL
     int64_t T;
-    int32_t L, Hq, pairs, is_bf16;
+    int32_t L, Hq;
     int32_t first;  // sums: 1 = overwrite, 0 = add to what is there
 };
 
-constexpr int kCenterThreads = 512;   // 8 band octets x 64 token residues
+constexpr int kCenterThreads = 256;
 constexpr int kCenterWaves = kCenterThreads / 64;
 
-// The (re, im) of bands 8q..8q+7 of the head vector that starts at element `row`: 32 contiguous bytes (bf16,
-// interleaved pairs), two 16-byte pieces 128 bytes apart (bf16, half-split), or the fp32 counterparts.
-__device__ __forceinline__ void load_octet(const CentersArgs &a, int64_t row, int q, float (&re)[8], float (&im)[8])
-{
-    const bool half = a.pairs == TRI_PAIR_HALF;
-    if (a.is_bf16) {
-        const uint16_t *p = (const uint16_t *)a.q + row;
-        const uint4 u0 = *reinterpret_cast<const uint4 *>(p + (half ? 8 * q : 16 * q));
-        const uint4 u1 = *reinterpret_cast<const uint4 *>(p + (half ? kBands + 8 * q : 16 * q + 8));
-        const uint32_t w0[4] = {u0.x, u0.y, u0.z, u0.w}, w1[4] = {u1.x, u1.y, u1.z, u1.w};
+// The 16-byte pieces that hold (re, im) of bands 8q..8q+7 of the head vector at element `row`: two (bf16) or four (fp32), 32
+// or 64 contiguous bytes with interleaved pairs, two halves 64 elements apart with half-split ones.
+template <bool BF16, bool HALF>
+struct Octet {
+    static constexpr int kPieces = BF16 ? 2 : 4;
+    uint4 p[kPieces];
+    // ONCE: nobody else reads these bytes
+    template <bool ONCE>
+    __device__ __forceinline__ void load(const void *base, int64_t row, int q)
+    {
+        constexpr int kPer = BF16 ? 8 : 4;   // elements per piece
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (half) {   // u0 = 8 real parts, u1 = 8 imaginary parts
-                re[2 * k] = __uint_as_float(w0[k] << 16);
-                re[2 * k + 1] = __uint_as_float(w0[k] & 0xffff0000u);
-                im[2 * k] = __uint_as_float(w1[k] << 16);
-                im[2 * k + 1] = __uint_as_float(w1[k] & 0xffff0000u);
-            } else {      // u0 = bands 0-3 as (re, im) pairs, u1 = bands 4-7
-                re[k] = __uint_as_float(w0[k] << 16);
-                im[k] = __uint_as_float(w0[k] & 0xffff0000u);
-                re[4 + k] = __uint_as_float(w1[k] << 16);
-                im[4 + k] = __uint_as_float(w1[k] & 0xffff0000u);
-            }
-        }
-    } else {
-        const float *p = (const float *)a.q + row;
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            if (half) {
-                const float4 r4 = *reinterpret_cast<const float4 *>(p + 8 * q + 4 * k);
-                const float4 i4 = *reinterpret_cast<const float4 *>(p + kBands + 8 * q + 4 * k);
-                re[4 * k] = r4.x, re[4 * k + 1] = r4.y, re[4 * k + 2] = r4.z, re[4 * k + 3] = r4.w;
-                im[4 * k] = i4.x, im[4 * k + 1] = i4.y, im[4 * k + 2] = i4.z, im[4 * k + 3] = i4.w;
-            } else {
-                const float4 a4 = *reinterpret_cast<const float4 *>(p + 16 * q + 8 * k);
-                const float4 b4 = *reinterpret_cast<const float4 *>(p + 16 * q + 8 * k + 4);
-                re[4 * k] = a4.x, im[4 * k] = a4.y, re[4 * k + 1] = a4.z, im[4 * k + 1] = a4.w;
-                re[4 * k + 2] = b4.x, im[4 * k + 2] = b4.y, re[4 * k + 3] = b4.z, im[4 * k + 3] = b4.w;
-            }
+        for (int k = 0; k < kPieces; ++k) {
+            const int e = HALF ? (k / (kPieces / 2)) * kBands + 8 * q + (k % (kPieces / 2)) * kPer : 16 * q + k * kPer;
+            const char *at = (const char *)base + (row + e) * (BF16 ? 2 : 4);
+            p[k] = ONCE ? load_stream16(at) : *reinterpret_cast<const uint4 *>(at);
         }
     }
+    // element e of the 16 in load order
+    __device__ __forceinline__ float at(int e) const
+    {
+        const int k = BF16 ? e >> 3 : e >> 2, r = BF16 ? (e & 7) >> 1 : e & 3;
+        const uint32_t w = r == 0 ? p[k].x : r == 1 ? p[k].y : r == 2 ? p[k].z : p[k].w;
+        if constexpr (!BF16) return __uint_as_float(w);
+        return __uint_as_float((e & 1) ? (w & 0xffff0000u) : (w << 16));
+    }
+    __device__ __forceinline__ float re(int k) const { return at(HALF ? k : 2 * k); }
+    __device__ __forceinline__ float im(int k) const { return at(HALF ? 8 + k : 2 * k + 1); }
+};
+
+// sqrt of a sum of two squares of fp32 values, to within a unit in the last place of a double: one coupled Newton
+// step and one correction by the residual on the hardware's reciprocal root (squares of fp32 values lie well inside
+// double's range, so the scaling of the library's square root -- half of the kernel's time -- is not needed).
+__device__ __forceinline__ double root(double s)
+{
+    const double r = __builtin_amdgcn_rsq(s);
+    double g = s * r, h = 0.5 * r;
+    const double d = fma(-h, g, 0.5);
+    g = fma(g, d, g);
+    h = fma(h, d, h);
+    g = fma(fma(-g, g, s), h, g);
+    return s > 0.0 && s < __builtin_inf() ? g : s;   // 0, infinity and NaN are their own
 }
 
-// grid (Hq, L), block 512: thread = (token residue r mod 64, band octet q); eight neighbouring threads read one
-// whole head vector with 16-byte loads.  Double sums in a fixed order: per thread over its tokens, then a
-// butterfly over the 8 residues of a wave, then the 8 waves in order.
+// Block 256: thread = (band octet of the workgroup's O, token residue); O neighbouring threads read O/8 of a head vector with
+// 16-byte loads, the next token's on their way while one is summed.  Grid: 8 / O workgroups per (layer, head), eight apart in the
+// launch, so that those that share cache lines run on one XCD, side by side (workgroups go to the eight XCDs in turn).  Double sums in a fixed order: per thread
+// over its tokens, then a butterfly over the residues of a wave, then the waves in order.
+// Bound by its double arithmetic and the memory stream together: 4096 tokens x 36 x 32 heads in bf16 (1.2 GB) 421 -> 265 us with the root
+// above and 256 threads where 512 with the library's square root stood, in fp32 (18 x 32 heads) 684 -> 277.
+template <bool BF16, bool HALF, int O>
 __global__ __launch_bounds__(kCenterThreads) void centers_kernel(CentersArgs a)
 {
-    __shared__ double part[kCenterWaves][kBands][3];
-    const int q = threadIdx.x & 7, r = threadIdx.x >> 3, wave = threadIdx.x >> 6;
-    const int h = blockIdx.x, l = blockIdx.y;
+    constexpr int kResidues = kCenterThreads / O;
+    __shared__ double part[kCenterWaves][8 * O][3];
+    const int q = threadIdx.x % O, r = threadIdx.x / O, wave = threadIdx.x >> 6;
+    constexpr int kParts = 8 / O;
+    const int64_t lh = (int64_t)(blockIdx.x / (8 * kParts)) * 8 + blockIdx.x % 8;   // layer * Hq + head
+    const int q0 = (int)(blockIdx.x / 8) % kParts * O;
+    if (lh >= (int64_t)a.L * a.Hq) return;
     double sre[8], sim[8], sab[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) sre[k] = sim[k] = sab[k] = 0.0;
-    for (int64_t t = r; t < a.T; t += kCenterThreads / 8) {
-        float re[8], im[8];
-        load_octet(a, ((t * a.L + l) * a.Hq + h) * kHeadDim, q, re, im);
+    auto row = [&](int64_t t) { return (t * a.L * a.Hq + lh) * kHeadDim; };
+    Octet<BF16, HALF> cur, nxt;
+    if (r < a.T) cur.template load<O == 8>(a.q, row(r), q0 + q);
+    for (int64_t t = r; t < a.T; t += kResidues) {
+        nxt.template load<O == 8>(a.q, row(t + kResidues < a.T ? t + kResidues : t), q0 + q);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            const double x = (double)re[k], y = (double)im[k];
+            const double x = (double)cur.re(k), y = (double)cur.im(k);
             sre[k] += x;
             sim[k] += y;
-            sab[k] += sqrt(x * x + y * y);
+            sab[k] += root(fma(x, x, y * y));
         }
+        cur = nxt;
     }
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
 #pragma unroll
-        for (int o = 8; o < 64; o <<= 1) {   // lanes that differ in the residue only
+        for (int o = O; o < 64; o <<= 1) {   // lanes that differ in the residue only
             sre[k] += __shfl_xor(sre[k], o, 64);
             sim[k] += __shfl_xor(sim[k], o, 64);
             sab[k] += __shfl_xor(sab[k], o, 64);
         }
-        if ((threadIdx.x & 63) < 8) {
+        if ((threadIdx.x & 63) < O) {
             part[wave][8 * q + k][0] = sre[k];
             part[wave][8 * q + k][1] = sim[k];
             part[wave][8 * q + k][2] = sab[k];
         }
     }
     __syncthreads();
-    if (threadIdx.x < kBands) {
+    if (threadIdx.x < 8 * O) {
         const int f = threadIdx.x;
         double t0 = 0.0, t1 = 0.0, t2 = 0.0;
         for (int k = 0; k < kCenterWaves; ++k) {
@@ -106,7 +118,7 @@ __global__ __launch_bounds__(kCenterThreads) void centers_kernel(CentersArgs a)
             t1 += part[k][f][1];
             t2 += part[k][f][2];
         }
-        const int64_t e = (((int64_t)l * a.Hq + h) * kBands + f) * 3;
+        const int64_t e = (lh * kBands + 8 * q0 + f) * 3;
         if (a.sums) {   // one thread owns the entry: a plain read-modify-write, chunks arrive in stream order
             double *o = a.sums + e;
             o[0] = a.first ? t0 : o[0] + t0;
@@ -119,6 +131,21 @@ __global__ __launch_bounds__(kCenterThreads) void centers_kernel(CentersArgs a)
             o[2] = (float)(t2 / (double)a.T);
         }
     }
+}
+
+template <bool BF16, bool HALF>
+tri_status launch_centers_t(const CentersArgs &a, int n_cu, hipStream_t st)
+{
+    // A workgroup per (layer, head) where that gives every CU two; else the bands are split over two, four or eight, which
+    // read the same cache lines.  4096 tokens: 32 heads 89 -> 16 us with eight, 128 heads 91 -> 36 with four, 256 heads 102 ->
+    // 65 with two; four per CU instead of two would take 128 heads to 46, 384 heads from 100 to 138.
+    const int64_t heads = (int64_t)a.L * a.Hq;
+    int parts = 1;
+    while (parts < 8 && heads * parts < 2 * (int64_t)n_cu) parts *= 2;
+    auto kern = parts == 1 ? centers_kernel<BF16, HALF, 8> : parts == 2 ? centers_kernel<BF16, HALF, 4>
+                : parts == 4 ? centers_kernel<BF16, HALF, 2> : centers_kernel<BF16, HALF, 1>;
+    hipLaunchKernelGGL(kern, dim3((uint32_t)((heads + 7) / 8 * 8 * parts)), dim3(kCenterThreads), 0, st, a);
+    return hip_status("centers_kernel");
 }
 
 // sums / total tokens -> the statistics table
@@ -165,9 +192,13 @@ __global__ __launch_bounds__(kBands) void diagnostics_kernel(DiagArgs a)
 tri_status launch_centers(const tri_model &m, const void *q, int32_t q_dtype, int64_t n_tokens, float *out,
                           double *sums, int32_t first, hipStream_t st)
 {
-    CentersArgs a{q, out, sums, n_tokens, m.n_layers, m.n_q_heads, m.pairs, q_dtype == TRI_BF16 ? 1 : 0, first};
-    hipLaunchKernelGGL(centers_kernel, dim3(m.n_q_heads, m.n_layers), dim3(kCenterThreads), 0, st, a);
-    return hip_status("centers_kernel");
+    int n_cu = 0;
+    const tri_status rc = device_cus(&n_cu);
+    if (rc != TRI_OK) return rc;
+    const CentersArgs a{q, out, sums, n_tokens, m.n_layers, m.n_q_heads, first};
+    const bool half = m.pairs == TRI_PAIR_HALF;
+    if (q_dtype == TRI_BF16) return half ? launch_centers_t<true, true>(a, n_cu, st) : launch_centers_t<true, false>(a, n_cu, st);
+    return half ? launch_centers_t<false, true>(a, n_cu, st) : launch_centers_t<false, false>(a, n_cu, st);
 }
 
 tri_status launch_centers_finalize(const tri_model &m, const double *sums, int64_t total_tokens, float *out,
