@@ -28,7 +28,7 @@ struct FoldArgs {
     int32_t *work;          // work list of the MFMA score kernels, or NULL when the generic kernel runs
     int32_t chunk_keys;     // keys per entry of that list
     float4 *phasors;        // relative-position phasor table of the MFMA score kernel, filled in by extra workgroups
-    int32_t lane_kernel;    // its layout: the one-key-per-lane kernel's or the sixteen-lane kernel's
+    int32_t lane_kernel;    // its layout: that of tri_score_lane.hip or the sixteen-lane kernel's
     int32_t max_seq_len;
     int32_t S, Hq, Hkv, G;
     int32_t seq_blocks;     // workgroups per (layer, KV head)
@@ -400,9 +400,9 @@ tri_status launch_score_g(const tri_model &m, const tri_cache &c, ScoreArgs sa, 
     const bool timed = timing_next(&ev0, &ev1);
     if (timed) (void)hipEventRecord(ev0, st);
     if (lane_kernel) {
-        rc = launch_score_lane(G, sa, st);
+        rc = launch_score_lane(G, sa, m.pairs == TRI_PAIR_HALF, st);
     } else if (fast) {
-        rc = launch_score_fast(G, sa, m.pairs == TRI_PAIR_HALF, st);
+        rc = launch_score_fast(G, sa, st);
     } else {
         dim3 grid(sa.n_tiles, c.n_seqs * m.n_kv_heads, m.n_layers);
         rc = (c.dtype == TRI_BF16) ? launch_score_kernel<G, uint16_t>(m, sa, grid, st)
@@ -477,9 +477,7 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
         int n_cu = 0;
         tri_status rcu = device_cus(&n_cu);
         if (rcu != TRI_OK) return rcu;
-        const int64_t inst = (int64_t)m.n_layers * c.n_seqs * m.n_kv_heads;
-        chunk_keys = m.pairs == TRI_PAIR_INTERLEAVED ? lane_chunk_keys(inst, c.max_seq_len, n_cu)
-                                                     : fast_chunk_keys(G, inst, c.max_seq_len, n_cu);
+        chunk_keys = item_keys((int64_t)m.n_layers * c.n_seqs * m.n_kv_heads, c.max_seq_len, n_cu);
     }
     fo.chunk_keys = chunk_keys;
     fo.max_seq_len = c.max_seq_len;
@@ -492,12 +490,15 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     fo.n_off = m.n_offsets;
     fo.variant = m.score_variant;
     for (int j = 0; j < m.n_offsets; ++j) fo.offsets[j] = m.offsets[j];
-    // Interleaved pairs: the kernel with one key per lane; half-split pairs: the one that spreads a key over sixteen lanes.
-    // Large paged batches (whole items of kFastChunk) of short sequences or of more than four query heads per KV head, too:
-    // 3072 x 4096 keys 1055 us a step against 1073, 768 x 4096 to 65536 keys at G = 8 2600 against 2684, at G = 5 2447
-    // against 2495, but 2107 against 2058 at G = 4, 1983 against 1959 at G = 2, 3098 against 3064 on 3072 x 9000 keys.
-    const bool lane_kernel = fo.work && m.pairs == TRI_PAIR_INTERLEAVED &&
-                             (c.block_size == 0 || chunk_keys < kFastChunk || (G <= 4 && c.max_seq_len > kFastChunk));
+    // bf16 keys: the kernel of tri_score_lane.hip, but large paged batches (whole items of kFastChunk) of pre-RoPE keys with
+    // interleaved pairs, of short sequences or of more than four query heads per KV head, go to the one that spreads a key over
+    // sixteen lanes: 3072 x 4096 keys 1055 us a step against 1073, 768 x 4096 to 65536 keys at G = 8 2600 against 2684, at G = 5
+    // 2447 against 2495 -- where it is the slower one: 2107 against 2058 at G = 4, 1983 against 1959 at G = 2, 3098 against
+    // 3064 on 3072 x 9000 keys; half-split pairs, 768 x 4096 to 65536 keys, 2680 against 2664 at G = 8, 2135 against 2078 at
+    // G = 4, 3072 x 4096 keys 1077 against 1068; post-RoPE at G = 8 2368 against 2364.
+    const bool sixteen = m.pairs == TRI_PAIR_INTERLEAVED && c.block_size != 0 && !c.k_rotated && chunk_keys == kFastChunk &&
+                         (G > 4 || c.max_seq_len <= kFastChunk);
+    const bool lane_kernel = fo.work && !sixteen;
     const int table_entries = !fo.work || c.k_rotated ? 0 : lane_kernel ? kLaneTableEntries : kFastTableEntries;
     fo.phasors = reinterpret_cast<float4 *>(ws + wl.phasors);
     fo.lane_kernel = lane_kernel;

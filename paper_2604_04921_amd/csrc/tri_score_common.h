@@ -21,28 +21,30 @@ struct ScoreArgs {
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-// Keys per work item of the MFMA score kernels (= keys per entry of `partials` on that path): kFastChunk on large batches, less
-// where that would leave resident workgroups without work (item_keys), kMinChunk at least.
+// Keys per work item of the MFMA score kernels (= keys per entry of `partials` on that path): kFastChunk on large batches (the
+// sixteen-lane kernel always), less where that would leave resident workgroups without work (item_keys), kMinChunk at least.
 constexpr int kFastChunk = 8192;
 constexpr int kMinChunk = 512;
 constexpr int kItemCost = 768;
-constexpr int lane_waves(int G) { return G > 4 ? 8 : 12; }   // waves per workgroup of the one-key-per-lane kernel
+constexpr int lane_waves(int G) { return G > 4 ? 8 : 12; }   // waves per workgroup of the kernel of tri_score_lane.hip
 // Waves per workgroup of the sixteen-lane kernel: with more than four query heads per KV head a wave needs more than 128
 // registers, so only three waves fit a SIMD; 12-wave workgroups fill them (8-wave ones would leave one of three unused).
 constexpr int fast_waves(int G) { return G > 4 ? 12 : 8; }
 // Resident workgroups take items until none is left, so a batch takes about (items per workgroup, rounded up) x (an item's keys
 // + the item's own cost in keys: its tables, its first loads, its waves' last ones).  Every head-instance is cut into the
-// number of equal pieces that makes this least, in units that keep the waves' tiles whole; batches of eight or more
-// items of kFastChunk keys per workgroup stay with those.  Measured, whole steps (start: kFastChunk for half-split pairs,
-// about four items per CU in rounds of the workgroup's waves for interleaved ones): one layer of eight x 12289 keys, half-split,
-// 150 -> 43.7 us, sixteen layers 206 -> 180; one layer of eight x 32768, interleaved, 66.5 -> 57.8 us, four layers 126 ->
-// 109, 36 layers 693 -> 674; score + selection of 288 x 2176 keys 91.0 -> 89.4, 576 155 -> 134.  An item cost of 128 keys is
-// worse on many short sequences (1152 x 2176: 243 against 219 us), 384 and 1600 on some in between (576 x 2176, G = 4: 143
-// and 134; 160 x 32768: 387 and 397 against 387), 768 nowhere.
-inline int item_keys(int64_t instances, int max_seq_len, int64_t workgroups, int unit)
+// number of equal pieces that makes this least, in whole tiles of 64; batches of eight or more
+// items of kFastChunk keys per workgroup stay with those.  Measured, whole steps (before: about four items per CU in rounds of the workgroup's waves;
+// kFastChunk for half-split pairs): one layer of eight x 32768 keys 66.5 -> 57.8 us, four layers 126 -> 109, 36 layers
+// 693 -> 674; one layer of eight x 12289, half-split, 150 -> 44.5, sixteen layers 207 -> 169; score + selection of 288 x 2176
+// keys 91.0 -> 89.4, 576 155 -> 134.  An item cost of 128 keys is worse on many short sequences (1152 x 2176: 243 against
+// 219 us), 384 and 1600 on some in between (576 x 2176: 143 and 134; 160 x 32768: 387 and 397 against 387), 768 nowhere.
+inline int item_keys(int64_t instances, int max_seq_len, int n_cu)
 {
+    constexpr int unit = 64;                            // a tile
+    const int64_t workgroups = n_cu > 0 ? n_cu : 1;     // one per CU
     if (instances * ((max_seq_len + kFastChunk - 1) / kFastChunk) >= 8 * workgroups) return kFastChunk;
-    const int least = (kMinChunk + unit - 1) / unit * unit;
+    constexpr int least = kMinChunk;
+    static_assert(kMinChunk % unit == 0, "whole tiles");
     int best = kFastChunk;
     int64_t best_cost = INT64_MAX;
     for (int pieces = 1; pieces <= 1024; ++pieces) {
@@ -60,15 +62,7 @@ inline int item_keys(int64_t instances, int max_seq_len, int64_t workgroups, int
     }
     return best;
 }
-inline int lane_chunk_keys(int64_t instances, int max_seq_len, int n_cu)
-{
-    return item_keys(instances, max_seq_len, n_cu > 0 ? n_cu : 1, 64);
-}
-inline int fast_chunk_keys(int G, int64_t instances, int max_seq_len, int n_cu)
-{
-    return item_keys(instances, max_seq_len, 2 * (int64_t)(n_cu > 0 ? n_cu : 1), fast_waves(G) * 16);
-}
-// Relative positions covered by its phasor table.
+// Relative positions covered by the sixteen-lane kernel's phasor table.
 constexpr int kPhasorRange = 128;
 constexpr int kPhasorBlockStride = kPhasorRange * 16 + 64;      // bytes per 4-band chunk (64 B skew)
 constexpr int kPhasorHalfStride = 16 * kPhasorBlockStride;      // bytes per half (bands 0-1 / 2-3 of a chunk)
@@ -137,10 +131,11 @@ __device__ __forceinline__ void fast_phasor_entry(double theta, int t, float4 *o
     relative_phasor(theta, f + 1, r, &v.z, &v.w);
     out[(hf * kPhasorHalfStride + b * kPhasorBlockStride) / 16 + r] = v;
 }
-// bf16 keys; G in 1..8
-tri_status launch_score_fast(int G, const ScoreArgs &sa, bool half_split, hipStream_t st);
-// bf16 keys with interleaved pairs, one key per lane (tri_score_lane.hip); its own phasor table layout
-// Its table of e^{i w r}: entry (band pair bp, r) = (cos, sin) of bands 2bp and 2bp+1 at relative position r, at byte
+// bf16 keys; G in 1..8.  launch_score_lane (tri_score_lane.hip): the general one; launch_score_fast (tri_score_mfma.hip): paged,
+// interleaved pairs, pre-RoPE.  Each has its own phasor table layout.
+tri_status launch_score_fast(int G, const ScoreArgs &sa, hipStream_t st);
+tri_status launch_score_lane(int G, const ScoreArgs &sa, bool half_split, hipStream_t st);
+// The general kernel's table of e^{i w r}: entry (band pair bp, r) = (cos, sin) of bands 2bp and 2bp+1 at relative position r, at byte
 // bp * kLanePairStride + 16 r.  The fold kernel writes it with kLaneTableEntries extra threads.
 constexpr int kLaneRange = 64;                                  // relative positions 0 .. 63
 constexpr int kLanePairStride = kLaneRange * 16 + 16;           // bytes per band pair (16 bytes of skew)
@@ -154,7 +149,6 @@ __device__ __forceinline__ void lane_phasor_entry(double theta, int t, float4 *o
     relative_phasor(theta, 2 * bp + 1, r, &v.z, &v.w);
     out[bp * (kLanePairStride / 16) + r] = v;
 }
-tri_status launch_score_lane(int G, const ScoreArgs &sa, hipStream_t st);
 // ints the MFMA kernel's work list takes: a header and one (sequence, chunk) pair per possible chunk
 inline size_t fast_work_ints(int64_t n_seqs, int64_t max_seq_len)
 {

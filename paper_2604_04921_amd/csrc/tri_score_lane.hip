@@ -1,17 +1,26 @@
-// Score kernel for bf16 keys with interleaved pairs, one key per lane (Sections 4.1-4.2).
+// Score kernel for bf16 keys (Sections 4.1-4.2).
 //
-// A wave takes 64 consecutive slots of a head-instance -- a tile -- and every lane scores one of them against all
-// query heads of the group.  The contraction over (band, component) x query head runs on v_mfma_f32_4x4x1_16b_f32:
-// block b of the instruction holds lanes 4b..4b+3, its rows are those four lanes' keys (operand A: the lane's own
-// rotated component or modulus of the band in turn), its columns four query heads (operand B: lane 4b+j supplies the
-// folded table entry of head j, the same in every block).  The accumulator of lane (b, j) therefore ends up with the
-// scores of keys 4b..4b+3 for head j: no cross-lane reduction, and one 16-byte store per lane writes them.
+// A wave takes 64 consecutive slots of a head-instance -- a tile -- in two steps, and scores them against all query heads of the
+// group.  The contraction over (band, component) x query head runs on v_mfma_f32_4x4x1_16b_f32: block b of the instruction
+// holds lanes 4b..4b+3, its rows are those four lanes' keys (operand A: the lane's own rotated component or modulus of the band
+// in turn), its columns four query heads (operand B: lane 4b+j supplies the folded table entry of head j).  The accumulator of
+// lane (b, j) ends up with the scores of four keys for head j: no cross-lane reduction over keys or heads, and one 16-byte
+// store per lane writes them.  Two ways to hand out the work (rows_layout()):
+//   * half rows: a lane owns one key; step 0 takes bands 0-31 of the 64 keys, step 1 bands 32-63.  Needs the two components of a
+//     band in the same half of the row, i.e. interleaved pairs.
+//   * rows: step 0 takes keys 0-31 of the tile, step 1 keys 32-63, and two lanes share a key: lane l has its bands 0-31 (l < 32)
+//     or 32-63.  The accumulators then hold half of the bands; one lane swap per register adds the halves for both steps'
+//     keys.  With whole rows in LDS the pair layouts differ in which pieces a lane reads and in nothing else.
+// Half-split pairs need the second; post-RoPE keys, which have the registers for it, gain 1 - 2 % from its whole-row loads (24 x 5 x 8
+// ragged head-instances up to 20011 keys, scores only: 848 -> 834 us; 36 x 2 x 8 x 32768, a step: 1261 -> 1245).  Pre-RoPE interleaved
+// keys keep the first: equal or 0.7 % slower in position order, but the second's extra registers spill and cost 1 % at sparse or
+// scattered positions (1362 -> 1377), 1.6 % at G = 8 (5247 -> 5330), 4 % on one sequence at steady state.
 //
 // What it takes to get there:
-//   * K rows reach their lanes through LDS: the wave loads half rows (128 bytes per key, whole cache lines) with
-//     coalesced 16-byte loads, writes them to its own staging area and each lane reads its key back 16 bytes (four
-//     bands) at a time.  The area is XOR-swizzled so that both the writes (16 lanes = 2 keys x 8 pieces) and the reads
-//     (16 lanes = 16 keys, one piece) touch every bank once.
+//   * K rows reach their lanes through LDS: the wave loads half rows (128 bytes per key, whole cache lines) or rows with coalesced
+//     16-byte loads, writes them to its own staging area and each lane reads its key back 16 bytes at a time: four
+//     bands, or the real or imaginary parts of eight.  The area is XOR-swizzled so that both the writes (16 lanes = 2 half
+//     rows or one row) and the reads (16 lanes = 16 keys, one piece) touch every bank once.
 //   * Rotation of the key (Appendix B.2): k e^{i w p} = (k e^{i w r}) e^{i w base} with base a position in the middle of
 //     the tile's positions and |r| < 64.  e^{i w |r|} comes from a table in LDS (one 16-byte read per two bands; a
 //     negative r flips the sign of the sine), e^{-i w base} is folded into the wave's copy of the head-instance's table,
@@ -35,7 +44,8 @@ constexpr int kMaxDevices = 64;
 typedef float float4v __attribute__((ext_vector_type(4)));
 
 constexpr int kTileKeys = 64;
-constexpr int kStageBytes = kTileKeys * 128;                    // one half row per key, swizzled, no padding
+constexpr int kStageBytes = kTileKeys * 128;                    // 64 half rows or 32 rows, swizzled, no padding
+constexpr bool rows_layout(bool rotated, bool half_split) { return rotated || half_split; }
 constexpr int kTabRow = kBands + 4;                             // floats per (component, head) row: 16 bytes of skew
 
 // (lane_waves(G): LDS decides -- 33 KB of phasors + a stage and a table per wave)
@@ -46,10 +56,14 @@ constexpr int lane_lds_bytes(int G, bool rotated)
     return (rotated ? 0 : kLanePhasorBytes) + lane_heads(G) * kTabRow * 4 + lane_waves(G) * lane_wave_bytes(G);
 }
 
-// Byte offset of (key k, 16-byte piece p of its half row) in a wave's staging area.  Rows k and k ^ 1 swap places when
-// bit 3 of k is set and the piece index is XORed with k & 7: 16 lanes that hold 2 keys x 8 pieces (the writes) or 16
-// keys x 1 piece (the reads) then fall into 16 different groups of four banks.
-__device__ __forceinline__ int stage_offset(int k, int p) { return ((k ^ ((k >> 3) & 1)) << 7) + ((p ^ (k & 7)) << 4); }
+// Byte offset of 16-byte piece p of key k in a wave's staging area, such that 16 lanes that hold whole rows or half rows (the
+// writes) or one piece of 16 keys (the reads) fall into 16 different groups of four banks.  Half rows: rows k and k ^ 1 swap
+// places when bit 3 of k is set and the piece index is XORed with k & 7; rows: the piece index is XORed with k & 15.
+template <bool ROWS>
+__device__ __forceinline__ int stage_offset(int k, int p)
+{
+    return ROWS ? (k << 8) + ((p ^ (k & 15)) << 4) : ((k ^ ((k >> 3) & 1)) << 7) + ((p ^ (k & 7)) << 4);
+}
 
 // Smallest or largest of the wave's 64 values, by DPP (lane 63 ends up with the whole wave's).
 template <bool MAX>
@@ -69,12 +83,13 @@ __device__ __forceinline__ int wave_extreme(int v)
     return __builtin_amdgcn_readlane(v, 63);
 }
 
-// ROTATED: the keys are stored post-RoPE (no rotation, no positions).  PAGED: block_size >= 16.
-template <int G, bool PAGED, bool ROTATED>
+// ROTATED: the keys are stored post-RoPE (no rotation, no positions).  PAGED: block_size >= 16.  HALF: half-split pairs.
+template <int G, bool PAGED, bool ROTATED, bool HALF>
 __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArgs a)
 {
     constexpr int NG = (G + 3) / 4, HR = lane_heads(G), W = lane_waves(G), kThreads = W * 64;
     constexpr int kTabBytes = HR * kTabRow * 4;          // one component's rows
+    constexpr bool ROWS = rows_layout(ROTATED, HALF);
     extern __shared__ __align__(16) char lds[];
     __shared__ double red[W][2 * 4 * NG];
     __shared__ double lds_rev[kBands];                    // omega_f / 2pi
@@ -89,7 +104,7 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
     char *const ph_base = lds;                                                  // phasor table (absent when ROTATED)
     char *const cn_base = lds + (ROTATED ? 0 : kLanePhasorBytes);               // norm-term rows, shared by the waves
     char *const my_base = cn_base + kTabBytes + wave * lane_wave_bytes(G);
-    char *const stage = my_base;                                                // this wave's half rows
+    char *const stage = my_base;                                                // this wave's rows
     char *const tab_re = my_base + kStageBytes, *const tab_im = tab_re + kTabBytes;
 
     if constexpr (!ROTATED)
@@ -105,15 +120,19 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
     int next_item = (int)(((uint32_t)blockIdx.x * (uint32_t)a.first_mult) % gridDim.x);
 
     const uint32_t slot_bytes = (uint32_t)c.stride_slot * 2u;
-    // loads: instruction t of a half row brings keys 8t .. 8t+7, eight lanes (128 contiguous bytes) per key
-    const int ld_key = lane >> 3, ld_piece = lane & 7;
+    // loads: instruction t of a step brings its keys 8t .. 8t+7, eight lanes (128 contiguous bytes) per key, or 4t .. 4t+3, sixteen
+    // lanes (256 bytes) per key
+    constexpr int kLoadKeys = ROWS ? 4 : 8;   // keys per load instruction
+    const int ld_key = ROWS ? lane >> 4 : lane >> 3, ld_piece = ROWS ? lane & 15 : lane & 7;
     const int bmask = PAGED ? (1 << c.block_shift) - 1 : 0;
     uint32_t ld_off = (uint32_t)ld_key * slot_bytes + (uint32_t)ld_piece * 16u;   // the lane's part of a load address
-    // where the lane writes its loaded pieces and reads its own key's pieces in the staging area
-    // (load t is written at 1024 t plus one of two offsets, by the parity of t: see stage_offset)
-    const int st_wr0 = stage_offset(ld_key, ld_piece), st_wr1 = stage_offset(8 + ld_key, ld_piece) - 1024;
-    const int st_rd0 = stage_offset(lane, 0);   // piece p of the lane's key lies at st_rd0 ^ (p << 4)
-    const int tab_lane = j * kTabRow * 4;   // byte offset of the lane's head row inside a quad of table rows
+    // where the lane writes its loaded pieces (rows: load t at 1024 t, with 4 (t % 4) XORed into the piece index; half rows: at
+    // 1024 t plus one of two offsets, by the parity of t) and reads its key's (its piece p lies at st_rd ^ (p << 4))
+    const int hh = ROWS ? lane >> 5 : 0;   // rows: which half of the bands
+    const int st_wr0 = stage_offset<ROWS>(ld_key, ld_piece), st_wr1 = ROWS ? 0 : stage_offset<ROWS>(8 + ld_key, ld_piece) - 1024;
+    const int st_rd = ROWS ? stage_offset<ROWS>(lane & 31, HALF ? 4 * hh : 8 * hh) : stage_offset<ROWS>(lane, 0);
+    // byte offset of the lane's head row, from its first band on, inside a quad of table rows
+    const int tab_lane = (j * kTabRow + 32 * hh) * 4;
 
     for (;;) {
         if (tid == 0) lds_item = next_item;
@@ -141,33 +160,36 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                               (PAGED ? 0 : (int64_t)s * c.pos_stride_sb);
         const int32_t *bt = PAGED ? c.block_table + (int64_t)s * c.max_blocks : nullptr;
 
-        // half row `half` of the tile at slot n0 (cnt keys exist): eight 16-byte loads per lane.  For a whole tile every
-        // address is a wave-uniform pointer (a group of eight keys never straddles a block) plus the lane's constant
+        // what step `half` takes of the tile at slot n0 (cnt keys exist): eight 16-byte loads per lane.  For a whole tile every
+        // address is a wave-uniform pointer (sixteen keys never straddle a block) plus the lane's constant
         // offset; in the last, partial tile a key past the end repeats the last one.
         // Paged caches: lane j of `btv` holds the physical block of keys n0 + 16 j .. + 15 (load_blocks; a block holds
         // 16 slots or more), asked for a tile ahead like the positions, so that no load here waits for a block-table
         // entry.
         auto load_half = [&](int n0, int cnt, int half, uint4(&kd)[8], int btv) {
+            const int first_key = ROWS ? 32 * half : 0, byte = ROWS ? 0 : 128 * half;
             if (cnt == kTileKeys) {
+                constexpr int kPer16 = 16 / kLoadKeys;   // instructions per sixteen keys
 #pragma unroll
-                for (int t = 0; t < 8; t += 2) {
-                    const int n = n0 + 8 * t;
+                for (int t = 0; t < 8; t += kPer16) {
+                    const int k0 = first_key + kLoadKeys * t, n = n0 + k0;
                     const char *p;
                     if constexpr (PAGED) {
-                        const int blk = __builtin_amdgcn_readlane(btv, t / 2);
+                        const int blk = __builtin_amdgcn_readlane(btv, k0 / 16);
                         p = krow + (int64_t)blk * c.stride_sb * 2 + (int64_t)(n & bmask) * slot_bytes;
                     } else {
                         p = krow + (int64_t)n * slot_bytes;
                     }
-                    asm volatile("" : "+v"(ld_off));   // keeps (scalar base + 32-bit lane offset) addressing
-                    kd[t] = load_stream16(p + half * 128 + ld_off);
-                    asm volatile("" : "+v"(ld_off));
-                    kd[t + 1] = load_stream16(p + 8 * (int64_t)slot_bytes + half * 128 + ld_off);
+#pragma unroll
+                    for (int i = 0; i < kPer16; ++i) {
+                        asm volatile("" : "+v"(ld_off));   // keeps (scalar base + 32-bit lane offset) addressing
+                        kd[t + i] = load_stream16(p + (int64_t)(kLoadKeys * i) * slot_bytes + byte + ld_off);
+                    }
                 }
             } else {
 #pragma unroll
                 for (int t = 0; t < 8; ++t) {
-                    const int n = n0 + min(8 * t + ld_key, cnt - 1);
+                    const int n = n0 + min(first_key + kLoadKeys * t + ld_key, cnt - 1);
                     const char *p;
                     if constexpr (PAGED) {
                         const int blk = bt[n >> c.block_shift];
@@ -175,7 +197,7 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                     } else {
                         p = krow + (int64_t)n * slot_bytes;
                     }
-                    kd[t] = load_stream16(p + half * 128 + ld_piece * 16);
+                    kd[t] = load_stream16(p + byte + ld_piece * 16);
                 }
             }
         };
@@ -195,7 +217,10 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
         };
         auto stage_half = [&](const uint4(&kd)[8]) {
 #pragma unroll
-            for (int t = 0; t < 8; ++t) *reinterpret_cast<uint4 *>(stage + ((t & 1) ? st_wr1 : st_wr0) + 1024 * t) = kd[t];
+            for (int t = 0; t < 8; ++t) {
+                const int at = ROWS ? st_wr0 ^ (64 * (t & 3)) : (t & 1) ? st_wr1 : st_wr0;
+                *reinterpret_cast<uint4 *>(stage + at + 1024 * t) = kd[t];
+            }
         };
 
         double s1[NG], s2[NG];
@@ -248,16 +273,14 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                 bt_next = load_blocks(m0, min(kTileKeys, c0 + c_len - m0));
             }
 
-            // ---- the tile's base and the lane's relative position
-            int r = 0;
+            // ---- the tile's base
+            int base = 0;
             bool in_table = true, mirrored = false;   // wave-uniform
-            float sgn = 1.f;
-            double rel_d = 0.0;
             if constexpr (!ROTATED) {
                 // Usual case: slots in the order of their positions, all within 64 of the first: base = the first, r >= 0.
                 // (The lowest and highest position of every tile through twelve LDS shuffles, each waiting for the one before,
                 // cost 64 x 8 head-instances of 131072 keys at G = 8 1 %.)
-                int base = __builtin_amdgcn_readfirstlane(p_key);
+                base = __builtin_amdgcn_readfirstlane(p_key);
                 if (__builtin_amdgcn_ballot_w64((uint32_t)p_key - (uint32_t)base >= (uint32_t)kLaneRange) != 0ull) {
                     base = wave_extreme<false>(p_key);
                     const int64_t span = (int64_t)wave_extreme<true>(p_key) - (int64_t)base;
@@ -267,10 +290,6 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                     in_table = span < 2 * kLaneRange - 1;
                     if (mirrored) base = (int)((int64_t)base + (span >> 1));
                 }
-                const int64_t rel = (int64_t)p_key - (int64_t)base;
-                rel_d = (double)rel;
-                sgn = rel < 0 ? -1.f : 1.f;
-                r = in_table ? (int)(rel < 0 ? -rel : rel) : 0;   // (0 keeps the unused table address in range)
                 // fold e^{-i w base} into the wave's table: lane = band
                 const float x = (float)__builtin_amdgcn_fract((double)base * lds_rev[lane]);
                 const float bs = __builtin_amdgcn_sinf(x), bc = __builtin_amdgcn_cosf(x);
@@ -281,25 +300,42 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                     reinterpret_cast<float *>(tab_im)[g * kTabRow + lane] = qi * bc - qr * bs;
                 }
             }
-            const char *ph_lane = ph_base + r * 16;
+            // the lane's relative position: of its key, or (rows) of its key of either step
+            const char *ph_lane = ph_base;
+            float sgn = 1.f;
+            double rel_d = 0.0;
+            auto take_position = [&](int p) {
+                if constexpr (ROTATED) return;
+                const int64_t rel = (int64_t)p - (int64_t)base;
+                rel_d = (double)rel;
+                sgn = rel < 0 ? -1.f : 1.f;
+                const int r = in_table ? (int)(rel < 0 ? -rel : rel) : 0;   // (0 keeps the unused table address in range)
+                ph_lane = ph_base + r * 16 + hh * (16 * kLanePairStride);
+            };
+            if constexpr (!ROWS) take_position(p_key);
 
             float4v acc[NG], acc2[NG];   // two chains, so that consecutive matrix instructions do not depend on each other
-#pragma unroll
-            for (int q = 0; q < NG; ++q) acc[q] = acc2[q] = float4v{0.f, 0.f, 0.f, 0.f};
+            float4v first[NG];           // rows: step 0's scores, over the lane's half of the bands
 
             // Everything a piece (four bands of the lane's key) needs from LDS: the key's 16 bytes, the phasors of its
             // four bands at the lane's relative position, the lane's table entries.  Pieces are fetched one ahead of
             // the piece being scored, in straight-line code, so that the LDS latency hides behind the arithmetic.
             struct Piece {
-                uint4 kq;
+                uint4 kq;   // interleaved: four bands; half-split: the real parts of eight
+                uint4 ki;   // half-split: their imaginary parts
                 float4 e0, e1;
                 float4 br[NG], bi[NG], bc[NG];
             };
-            auto fetch = [&](int half, int pc, auto table_tag) {
+            auto fetch = [&](const Piece &prev, int half, int pc, auto table_tag) {
                 constexpr bool TABLE = decltype(table_tag)::value;
-                const int f0 = 32 * half + 4 * pc;   // first of the piece's four bands
+                const int f0 = (ROWS ? 0 : 32 * half) + 4 * pc;   // first of the piece's four bands (rows: of the lane's 32)
                 Piece o;
-                o.kq = *reinterpret_cast<const uint4 *>(stage + (st_rd0 ^ (pc << 4)));
+                if constexpr (HALF) {
+                    o.kq = pc & 1 ? prev.kq : *reinterpret_cast<const uint4 *>(stage + (st_rd ^ ((pc / 2) << 4)));
+                    o.ki = pc & 1 ? prev.ki : *reinterpret_cast<const uint4 *>(stage + (st_rd ^ ((8 + pc / 2) << 4)));
+                } else {
+                    o.kq = *reinterpret_cast<const uint4 *>(stage + (st_rd ^ (pc << 4)));
+                }
                 if constexpr (TABLE) {
                     o.e0 = *reinterpret_cast<const float4 *>(ph_lane + (f0 / 2) * kLanePairStride);
                     o.e1 = *reinterpret_cast<const float4 *>(ph_lane + (f0 / 2 + 1) * kLanePairStride);
@@ -316,8 +352,9 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
             // The vector instructions of the piece first, then its matrix instructions in one run.
             auto score_piece = [&](const Piece &pz, int half, int pc, auto table_tag, auto mirror_tag) {
                 constexpr bool TABLE = decltype(table_tag)::value, MIRROR = decltype(mirror_tag)::value;
-                const int f0 = 32 * half + 4 * pc;
+                const int f0 = (ROWS ? 0 : 32 * half) + 4 * pc;
                 const uint32_t w[4] = {pz.kq.x, pz.kq.y, pz.kq.z, pz.kq.w};
+                const uint32_t wi[4] = {pz.ki.x, pz.ki.y, pz.ki.z, pz.ki.w};
                 float cs[4] = {1.f, 1.f, 1.f, 1.f}, sn[4] = {0.f, 0.f, 0.f, 0.f};
                 if constexpr (!ROTATED) {
                     if constexpr (TABLE) {
@@ -330,7 +367,7 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                     } else {
 #pragma unroll
                         for (int k = 0; k < 4; ++k) {
-                            const float x = (float)__builtin_amdgcn_fract(rel_d * lds_rev[f0 + k]);
+                            const float x = (float)__builtin_amdgcn_fract(rel_d * lds_rev[32 * hh + f0 + k]);
                             sn[k] = __builtin_amdgcn_sinf(x);
                             cs[k] = __builtin_amdgcn_cosf(x);
                         }
@@ -339,7 +376,15 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                 float kr[4], ki[4], m[4];
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    const float re = bf16_lo(w[k]), im = bf16_hi(w[k]);
+                    float re, im;
+                    if constexpr (HALF) {
+                        const int d = 2 * (pc & 1) + (k >> 1);
+                        re = (k & 1) ? bf16_hi(w[d]) : bf16_lo(w[d]);
+                        im = (k & 1) ? bf16_hi(wi[d]) : bf16_lo(wi[d]);
+                    } else {
+                        re = bf16_lo(w[k]);
+                        im = bf16_hi(w[k]);
+                    }
                     m[k] = __builtin_amdgcn_sqrtf(fmaf(re, re, im * im));
                     kr[k] = ROTATED ? re : re * cs[k] - im * sn[k];
                     ki[k] = ROTATED ? im : re * sn[k] + im * cs[k];
@@ -375,8 +420,15 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
             auto score_tile = [&](auto table_tag, auto mirror_tag) {
 #pragma unroll
                 for (int half = 0; half < 2; ++half) {
-                    stage_half(kd);   // waits for the half row's loads, then 8 LDS writes
-                    // the next loads go out while this half row is scored
+                    stage_half(kd);   // waits for the step's loads, then 8 LDS writes
+                    if constexpr (ROWS && !ROTATED) {
+                        const auto p = __builtin_amdgcn_permlane32_swap((uint32_t)p_key, (uint32_t)p_key, false, false);
+                        take_position((int)p[half]);
+                    }
+                    if (ROWS || half == 0)
+#pragma unroll
+                        for (int q = 0; q < NG; ++q) acc[q] = acc2[q] = float4v{0.f, 0.f, 0.f, 0.f};
+                    // the next loads go out while this step's are scored
                     if (half == 0) {
                         load_half(n0, cnt, 1, kd, bt_cur);
                     } else if (t_idx + W < n_tiles) {
@@ -384,13 +436,18 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                         load_half(m0, mc, 0, kd, bt_next);
                         pos_next = load_pos(m0, mc);
                     }
-                    Piece cur = fetch(half, 0, table_tag);
+                    Piece cur = fetch(Piece{}, half, 0, table_tag);
 #pragma unroll
                     for (int pc = 0; pc < 8; ++pc) {
                         Piece nxt = cur;
-                        if (pc + 1 < 8) nxt = fetch(half, pc + 1, table_tag);
+                        if (pc + 1 < 8) nxt = fetch(cur, half, pc + 1, table_tag);
                         score_piece(cur, half, pc, table_tag, mirror_tag);
                         cur = nxt;
+                    }
+#pragma unroll
+                    for (int q = 0; q < NG; ++q) {
+                        if (ROWS || half == 1) acc[q] += acc2[q];
+                        if (ROWS && half == 0) first[q] = acc[q];
                     }
                 }
             };
@@ -399,8 +456,14 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
             else score_tile(std::true_type{}, std::false_type{});
 
             bt_cur = bt_next;
+            // rows: the two halves of the bands together, step 0's keys in lanes 0-31 and step 1's in lanes 32-63
 #pragma unroll
-            for (int q = 0; q < NG; ++q) acc[q] += acc2[q];
+            for (int q = 0; q < NG; ++q)
+#pragma unroll
+                for (int k = 0; ROWS && k < 4; ++k) {
+                    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(first[q][k]), __float_as_uint(acc[q][k]), false, false);
+                    acc[q][k] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+                }
             // ---- lane (b, j) holds keys n0 + 4b .. + 3 for head 4q + j
 #pragma unroll
             for (int q = 0; q < NG; ++q) {
@@ -453,22 +516,26 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
 }
 
 template <int G>
-tri_status launch_lane_g(const ScoreArgs &sa, hipStream_t st)
+tri_status launch_lane_g(const ScoreArgs &sa, bool half_split, hipStream_t st)
 {
     const bool paged = sa.c.block_shift >= 0, rotated = sa.c.k_rotated != 0;
-    auto kern = rotated ? (paged ? score_lane_kernel<G, true, true> : score_lane_kernel<G, false, true>)
-                        : (paged ? score_lane_kernel<G, true, false> : score_lane_kernel<G, false, false>);
+    auto pick = [&](auto half) {
+        constexpr bool H = decltype(half)::value;
+        return rotated ? (paged ? score_lane_kernel<G, true, true, H> : score_lane_kernel<G, false, true, H>)
+                       : (paged ? score_lane_kernel<G, true, false, H> : score_lane_kernel<G, false, false, H>);
+    };
+    auto kern = half_split ? pick(std::true_type{}) : pick(std::false_type{});
     const int lds = lane_lds_bytes(G, rotated);
     if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
         return hip_status("hipFuncSetAttribute(score_lane_kernel)");
-    static std::atomic<int> resident[2][2][kMaxDevices];
+    static std::atomic<int> resident[2][2][2][kMaxDevices];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) {
         (void)hipGetLastError();
         set_error("score: no current device below %d", kMaxDevices);
         return TRI_ERR_HIP;
     }
-    std::atomic<int> &cached = resident[rotated ? 1 : 0][paged ? 1 : 0][dev];
+    std::atomic<int> &cached = resident[half_split ? 1 : 0][rotated ? 1 : 0][paged ? 1 : 0][dev];
     int slots = cached.load(std::memory_order_relaxed);
     if (slots == 0) {
         int n_cu = 0, per_cu = 0;
@@ -501,17 +568,17 @@ tri_status launch_lane_g(const ScoreArgs &sa, hipStream_t st)
 
 }  // namespace
 
-tri_status launch_score_lane(int G, const ScoreArgs &sa, hipStream_t st)
+tri_status launch_score_lane(int G, const ScoreArgs &sa, bool half_split, hipStream_t st)
 {
     switch (G) {
-        case 1: return launch_lane_g<1>(sa, st);
-        case 2: return launch_lane_g<2>(sa, st);
-        case 3: return launch_lane_g<3>(sa, st);
-        case 4: return launch_lane_g<4>(sa, st);
-        case 5: return launch_lane_g<5>(sa, st);
-        case 6: return launch_lane_g<6>(sa, st);
-        case 7: return launch_lane_g<7>(sa, st);
-        case 8: return launch_lane_g<8>(sa, st);
+        case 1: return launch_lane_g<1>(sa, half_split, st);
+        case 2: return launch_lane_g<2>(sa, half_split, st);
+        case 3: return launch_lane_g<3>(sa, half_split, st);
+        case 4: return launch_lane_g<4>(sa, half_split, st);
+        case 5: return launch_lane_g<5>(sa, half_split, st);
+        case 6: return launch_lane_g<6>(sa, half_split, st);
+        case 7: return launch_lane_g<7>(sa, half_split, st);
+        case 8: return launch_lane_g<8>(sa, half_split, st);
     }
     set_error("group size %d not built (1 to 8)", G);
     return TRI_ERR_UNSUPPORTED;

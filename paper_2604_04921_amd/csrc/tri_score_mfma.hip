@@ -1,7 +1,7 @@
 // Score kernel for bf16 keys with a key spread over sixteen lanes: fp32 MFMA for the contraction over
-// (band, component) x query head, a phasor table in LDS for the rotation of the key.  It takes interleaved or
-// half-split pairs; the launcher in tri_score.hip sends it the half-split caches and the large paged batches
-// (the one-key-per-lane kernel of tri_score_lane.hip takes the rest).
+// (band, component) x query head, a phasor table in LDS for the rotation of the key.  The launcher in tri_score.hip sends it
+// large paged batches of pre-RoPE keys with interleaved pairs, where sequences are short or a KV head serves more than four
+// query heads; the kernel of tri_score_lane.hip takes the rest.
 //
 // Lane layout (wave64): lane = 4*b + i.  In one step a wave scores 4 keys; lane (b, i) loads the
 // 16 bytes holding bands 4b..4b+3 of key i -- exactly the operand layout of
@@ -85,10 +85,8 @@ struct LaneTable {
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 // (K rows are read exactly once: load_stream16, the 16-byte load with the non-temporal hint.)
 
-// ROTATE = false: the key is stored post-RoPE, already k e^{i w p}.
-// HALF = false: kd holds the (re, im) pairs of the lane's four bands; HALF = true (half-split layout):
-// kd = (re of bands 0-1, re of bands 2-3, im of bands 0-1, im of bands 2-3), two bf16 per dword.
-template <int NG, bool ROTATE, bool HALF>
+// kd: the (re, im) pairs of the lane's four bands.
+template <int NG>
 __device__ __forceinline__ void score_step(const uint4 kd, const float (&cs)[4], const float (&sn)[4],
                                            const LaneTable (&tb)[NG], float (&out)[NG])
 {
@@ -100,24 +98,17 @@ __device__ __forceinline__ void score_step(const uint4 kd, const float (&cs)[4],
     float kr[4], ki[4], m[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        float re, im;
-        if constexpr (HALF) {
-            re = (k & 1) ? bf16_hi(w[k >> 1]) : bf16_lo(w[k >> 1]);
-            im = (k & 1) ? bf16_hi(w[2 + (k >> 1)]) : bf16_lo(w[2 + (k >> 1)]);
-        } else {
-            re = bf16_lo(w[k]);
-            im = bf16_hi(w[k]);
-        }
+        const float re = bf16_lo(w[k]), im = bf16_hi(w[k]);
         // |k_f|^2 from the unpacked pair: fp32 multiplications and fused multiply-adds run at twice the rate of the
         // packed bf16 dot product (and of every integer, conversion or cross-lane instruction) on this GPU
         m[k] = __builtin_amdgcn_sqrtf(fmaf(re, re, im * im));
-        kr[k] = ROTATE ? re * cs[k] - im * sn[k] : re;
-        ki[k] = ROTATE ? re * sn[k] + im * cs[k] : im;
+        kr[k] = re * cs[k] - im * sn[k];
+        ki[k] = re * sn[k] + im * cs[k];
     }
     __builtin_amdgcn_sched_barrier(0);
     // the wave's priority drops for its matrix run and rises again for the vector work that follows, so that a wave
     // in its vector part outranks those in their matrix runs (ragged paged batch of 6144 head-instances 12.23 -> 12.03 ms,
-    // half-split pairs on 36 x 16 x 8 x 32768 keys 7.86 -> 7.60 ms, in one process each)
+    // in one process)
     __builtin_amdgcn_s_setprio(0);
     float4v acc[NG];
 #pragma unroll
@@ -143,8 +134,8 @@ __device__ __forceinline__ void score_step(const uint4 kd, const float (&cs)[4],
 // in which the hardware hands workgroups to the XCDs cost anything (with one workgroup per chunk slot of the
 // longest sequence, ragged batches lost up to a quarter of the kernel's throughput to the empty ones).  The item's
 // keys are split evenly over the waves; each wave walks its contiguous share in groups of 16 (4 steps).
-// PAGED: block_size >= 16, so a group never straddles a block.
-template <int G, bool PAGED, bool ROTATED, bool HALF>
+// Paged caches of block_size >= 16: a group never straddles a block.
+template <int G>
 // (the second launch bound keeps every variant at four waves per SIMD for G <= 4, three above: two workgroups per CU)
 __global__ __launch_bounds__(fast_threads(G), G > 4 ? 3 : 4) void score_mfma_kernel(ScoreArgs a)
 {
@@ -161,8 +152,7 @@ __global__ __launch_bounds__(fast_threads(G), G > 4 ? 3 : 4) void score_mfma_ker
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keeps loop control scalar
     const int b = lane >> 2, i = lane & 3;
 
-    if constexpr (!ROTATED)
-        for (int k = tid; k < kPhasorBytes / 16; k += kFastThreads) lds_phasors[k] = a.phasors[k];
+    for (int k = tid; k < kPhasorBytes / 16; k += kFastThreads) lds_phasors[k] = a.phasors[k];
     if (tid < kBands) lds_rev[tid] = a.band_rev[tid];
     const int per_lh = __builtin_amdgcn_readfirstlane(a.work[1]);   // items per (layer, KV head)
     const int n_items = per_lh * a.n_layers * c.n_kv_heads;       // below 2^31: checked on the host
@@ -229,12 +219,10 @@ __global__ __launch_bounds__(fast_threads(G), G > 4 ? 3 : 4) void score_mfma_ker
     // Addresses.  Everything that depends on the group is wave-uniform (scalar registers); a lane
     // adds its own constant offset: key (4t + i) of the group, 16-byte piece b of the row.
     const uint32_t slot_bytes = (uint32_t)c.stride_slot * 2u;
-    const char *krow = (const char *)c.k + ((int64_t)l * c.stride_layer + (int64_t)h * c.stride_head) * 2 +
-                       (PAGED ? 0 : (int64_t)s * c.stride_sb * 2);
-    const int32_t *prow = c.pos + (int64_t)l * c.pos_stride_layer + (int64_t)h * c.pos_stride_head +
-                          (PAGED ? 0 : (int64_t)s * c.pos_stride_sb);
-    const int32_t *bt = PAGED ? c.block_table + (int64_t)s * c.max_blocks : nullptr;
-    const int bmask = PAGED ? (1 << c.block_shift) - 1 : 0;
+    const char *krow = (const char *)c.k + ((int64_t)l * c.stride_layer + (int64_t)h * c.stride_head) * 2;
+    const int32_t *prow = c.pos + (int64_t)l * c.pos_stride_layer + (int64_t)h * c.pos_stride_head;
+    const int32_t *bt = c.block_table + (int64_t)s * c.max_blocks;
+    const int bmask = (1 << c.block_shift) - 1;
     // Loads are issued in the coalesced lane order (lane = 16*key + piece: a wave instruction reads
     // four whole 256-byte rows front to back) and handed to the consumer lane (b, i) = piece b of
     // key i with one cross-lane permute per dword.  Loading straight in consumer order costs the
@@ -247,27 +235,18 @@ __global__ __launch_bounds__(fast_threads(G), G > 4 ? 3 : 4) void score_mfma_ker
     const int perm_k = (16 * i + b) * 4;   // ds_bpermute address: source lane of this lane's K piece
     const int perm_p = i * 4;              // source lane (4t + i) of this lane's position at step t, plus 16*t
 
-    // Paged: the wave's share (at most 1024 keys) spans at most 64 blocks plus one; their ids are read once,
+    // The wave's share (at most 1024 keys) spans at most 64 blocks plus one; their ids are read once,
     // one per lane, so that no group's addresses wait on a block-table load behind the K loads in flight.
-    const int blk0 = PAGED ? (w0 >> c.block_shift) : 0;
-    int blk_ids = 0, blk_ids_hi = 0;
-    if constexpr (PAGED) {
-        blk_ids = bt[min(blk0 + lane, c.max_blocks - 1)];
-        blk_ids_hi = bt[min(blk0 + 64, c.max_blocks - 1)];
-    }
+    const int blk0 = w0 >> c.block_shift;
+    const int blk_ids = bt[min(blk0 + lane, c.max_blocks - 1)], blk_ids_hi = bt[min(blk0 + 64, c.max_blocks - 1)];
 
     // group starting at key n (a multiple of 16): uniform base pointers of its K rows and positions
     auto group_ptrs = [&](int n, const char *&kp, const int32_t *&pq) {
-        if constexpr (PAGED) {
-            const int rel = (n >> c.block_shift) - blk0;
-            const int blk = rel < 64 ? __builtin_amdgcn_readlane(blk_ids, rel) : __builtin_amdgcn_readfirstlane(blk_ids_hi);
-            const int slot = n & bmask;
-            kp = krow + (int64_t)blk * c.stride_sb * 2 + (int64_t)slot * slot_bytes;
-            pq = prow + (int64_t)blk * c.pos_stride_sb + slot;
-        } else {
-            kp = krow + (int64_t)n * slot_bytes;
-            pq = prow + n;
-        }
+        const int rel = (n >> c.block_shift) - blk0;
+        const int blk = rel < 64 ? __builtin_amdgcn_readlane(blk_ids, rel) : __builtin_amdgcn_readfirstlane(blk_ids_hi);
+        const int slot = n & bmask;
+        kp = krow + (int64_t)blk * c.stride_sb * 2 + (int64_t)slot * slot_bytes;
+        pq = prow + (int64_t)blk * c.pos_stride_sb + slot;
     };
 
     // all 16 keys of the group exist: no per-lane address arithmetic at all.  kd[t] = rows 4t..4t+3 in
@@ -283,12 +262,8 @@ __global__ __launch_bounds__(fast_threads(G), G > 4 ? 3 : 4) void score_mfma_ker
             asm volatile("" : "+v"(koff[t]));
             kd[t] = load_stream16(kp + koff[t]);
         }
-        if constexpr (ROTATED) {
-            pp = 0;
-        } else {
-            asm volatile("" : "+v"(pos_off));
-            pp = *reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(pq) + pos_off);
-        }
+        asm volatile("" : "+v"(pos_off));
+        pp = *reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(pq) + pos_off);
     };
 
     // last, partial group: keys past the end repeat the last one (their results are discarded)
@@ -301,36 +276,15 @@ __global__ __launch_bounds__(fast_threads(G), G > 4 ? 3 : 4) void score_mfma_ker
             const int j = min(4 * t + ld_key, cnt - 1);
             kd[t] = load_stream16(kp + (uint32_t)j * slot_bytes + (uint32_t)ld_piece * 16u);
         }
-        pp = ROTATED ? 0 : pq[min(ld_piece, cnt - 1)];
+        pp = pq[min(ld_piece, cnt - 1)];
     };
-
-    // Half-split layout: a row is 64 real parts followed by 64 imaginary parts, so piece p < 8 holds the
-    // real parts of bands 8p..8p+7 and piece 8 + p their imaginary parts.  Consumer (b, i) needs dwords
-    // 2(b&1), 2(b&1)+1 of pieces b>>1 and 8 + (b>>1) of key i.  Four permutes still do: in each, the real
-    // pieces offer one dword and the imaginary pieces another, and even / odd consumers read opposite kinds.
-    const bool ld_im = ld_piece >= 8, odd_b = (b & 1) != 0;
-    const int perm_re = (16 * i + (b >> 1)) * 4, perm_im = perm_re + 8 * 4;
-    const int perm_a = odd_b ? perm_im : perm_re, perm_b = odd_b ? perm_re : perm_im;
 
     // load order -> consumer order
     auto to_consumer = [&](const uint4 &raw) {
-        uint4 v;
-        if constexpr (HALF) {
-            const int r1 = __builtin_amdgcn_ds_bpermute(perm_a, (int)(ld_im ? raw.z : raw.x));
-            const int r2 = __builtin_amdgcn_ds_bpermute(perm_b, (int)(ld_im ? raw.x : raw.z));
-            const int r3 = __builtin_amdgcn_ds_bpermute(perm_a, (int)(ld_im ? raw.w : raw.y));
-            const int r4 = __builtin_amdgcn_ds_bpermute(perm_b, (int)(ld_im ? raw.y : raw.w));
-            v.x = (uint32_t)(odd_b ? r2 : r1);   // re of bands 4b, 4b+1
-            v.y = (uint32_t)(odd_b ? r4 : r3);   // re of bands 4b+2, 4b+3
-            v.z = (uint32_t)(odd_b ? r1 : r2);   // im of bands 4b, 4b+1
-            v.w = (uint32_t)(odd_b ? r3 : r4);   // im of bands 4b+2, 4b+3
-        } else {
-            v.x = (uint32_t)__builtin_amdgcn_ds_bpermute(perm_k, (int)raw.x);
-            v.y = (uint32_t)__builtin_amdgcn_ds_bpermute(perm_k, (int)raw.y);
-            v.z = (uint32_t)__builtin_amdgcn_ds_bpermute(perm_k, (int)raw.z);
-            v.w = (uint32_t)__builtin_amdgcn_ds_bpermute(perm_k, (int)raw.w);
-        }
-        return v;
+        return make_uint4((uint32_t)__builtin_amdgcn_ds_bpermute(perm_k, (int)raw.x),
+                          (uint32_t)__builtin_amdgcn_ds_bpermute(perm_k, (int)raw.y),
+                          (uint32_t)__builtin_amdgcn_ds_bpermute(perm_k, (int)raw.z),
+                          (uint32_t)__builtin_amdgcn_ds_bpermute(perm_k, (int)raw.w));
     };
 
     // fold e^{-i w base} into the lane's table registers
@@ -357,7 +311,7 @@ __global__ __launch_bounds__(fast_threads(G), G > 4 ? 3 : 4) void score_mfma_ker
         const float4 e0 = *reinterpret_cast<const float4 *>(ph0 + r * 16);
         const float4 e1 = *reinterpret_cast<const float4 *>(ph0 + kPhasorHalfStride + r * 16);
         const float cs[4] = {e0.x, e0.z, e1.x, e1.z}, sn[4] = {e0.y, e0.w, e1.y, e1.w};
-        score_step<NG, true, HALF>(kd, cs, sn, tb, out);
+        score_step<NG>(kd, cs, sn, tb, out);
     };
 
     // one step for any four positions: move the base if that brings them into the table, else
@@ -380,7 +334,7 @@ __global__ __launch_bounds__(fast_threads(G), G > 4 ? 3 : 4) void score_mfma_ker
                     sn[k] = __builtin_amdgcn_sinf(x);
                     cs[k] = __builtin_amdgcn_cosf(x);
                 }
-                score_step<NG, true, HALF>(kd, cs, sn, tb, out);
+                score_step<NG>(kd, cs, sn, tb, out);
                 return;
             }
         }
@@ -393,41 +347,35 @@ __global__ __launch_bounds__(fast_threads(G), G > 4 ? 3 : 4) void score_mfma_ker
 #pragma unroll
         for (int t = 0; t < 4; ++t) kd[t] = to_consumer(kraw[t]);
         float out[4][NG];   // per step, block sums not yet finished (reduce_blocks)
-        if constexpr (ROTATED) {   // post-RoPE keys: straight into the contraction
-            const float one[4] = {1.f, 1.f, 1.f, 1.f}, zero[4] = {0.f, 0.f, 0.f, 0.f};
+        // common case: all 16 positions of the group fall in the table around the current base.  The test
+        // and the table index are formed on the positions in load order (every lane holds one of the 16),
+        // before they go to the consumer lanes.
+        int rraw = praw - base;
+        bool fast = __builtin_amdgcn_ballot_w64((unsigned)rraw >= (unsigned)kPhasorRange) == 0ull;
+        if (!fast) {
+            // span of the 16 positions: lanes 0..15 hold one each (one DPP row)
+            int lo = praw, hi = praw;
 #pragma unroll
-            for (int t = 0; t < 4; ++t) score_step<NG, false, HALF>(kd[t], one, zero, tb, out[t]);
+            for (int o = 8; o >= 1; o >>= 1) {
+                lo = min(lo, __shfl_xor(lo, o, 16));
+                hi = max(hi, __shfl_xor(hi, o, 16));
+            }
+            lo = __builtin_amdgcn_readfirstlane(lo);
+            hi = __builtin_amdgcn_readfirstlane(hi);
+            if ((int64_t)hi - (int64_t)lo < kPhasorRange) {
+                move_base(lo);
+                rraw = praw - base;
+                fast = true;
+            }
+        }
+        if (fast) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                step_table(kd[t], __builtin_amdgcn_ds_bpermute(perm_p + 16 * t, rraw), out[t]);
         } else {
-            // common case: all 16 positions of the group fall in the table around the current base.  The test
-            // and the table index are formed on the positions in load order (every lane holds one of the 16),
-            // before they go to the consumer lanes.
-            int rraw = praw - base;
-            bool fast = __builtin_amdgcn_ballot_w64((unsigned)rraw >= (unsigned)kPhasorRange) == 0ull;
-            if (!fast) {
-                // span of the 16 positions: lanes 0..15 hold one each (one DPP row)
-                int lo = praw, hi = praw;
 #pragma unroll
-                for (int o = 8; o >= 1; o >>= 1) {
-                    lo = min(lo, __shfl_xor(lo, o, 16));
-                    hi = max(hi, __shfl_xor(hi, o, 16));
-                }
-                lo = __builtin_amdgcn_readfirstlane(lo);
-                hi = __builtin_amdgcn_readfirstlane(hi);
-                if ((int64_t)hi - (int64_t)lo < kPhasorRange) {
-                    move_base(lo);
-                    rraw = praw - base;
-                    fast = true;
-                }
-            }
-            if (fast) {
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    step_table(kd[t], __builtin_amdgcn_ds_bpermute(perm_p + 16 * t, rraw), out[t]);
-            } else {
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    step_general(kd[t], __builtin_amdgcn_ds_bpermute(perm_p + 16 * t, praw), out[t]);
-            }
+            for (int t = 0; t < 4; ++t)
+                step_general(kd[t], __builtin_amdgcn_ds_bpermute(perm_p + 16 * t, praw), out[t]);
         }
         float kept[NG];   // the lane's own result: step sub
 #pragma unroll
@@ -500,31 +448,22 @@ __global__ __launch_bounds__(fast_threads(G), G > 4 ? 3 : 4) void score_mfma_ker
 }
 
 template <int G>
-tri_status launch_fast_g(const ScoreArgs &sa, bool half_split, hipStream_t st)
+tri_status launch_fast_g(const ScoreArgs &sa, hipStream_t st)
 {
-    const bool paged = sa.c.block_shift >= 0;
-    // (interleaved pairs in a contiguous cache are the one-key-per-lane kernel's)
-    if (!half_split && !paged) {
-        set_error("score: no sixteen-lane kernel for interleaved pairs in a contiguous cache");
-        return TRI_ERR_UNSUPPORTED;
-    }
-    const bool rot = sa.c.k_rotated != 0;
-    auto kern = !half_split ? (rot ? score_mfma_kernel<G, true, true, false> : score_mfma_kernel<G, true, false, false>)
-                : paged     ? (rot ? score_mfma_kernel<G, true, true, true> : score_mfma_kernel<G, true, false, true>)
-                            : (rot ? score_mfma_kernel<G, false, true, true> : score_mfma_kernel<G, false, false, true>);
-    const int lds = sa.c.k_rotated ? 0 : kPhasorBytes;   // no phasor table for post-RoPE keys
-    if (lds && hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+    auto kern = score_mfma_kernel<G>;
+    const int lds = kPhasorBytes;
+    if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
         return hip_status("hipFuncSetAttribute(score_mfma_kernel)");
     // as many workgroups as are resident at once (they stay until the work list is empty), no more than items can exist.
     // The answer is kept per kernel and per GPU; threads that ask at the same time compute the same number.
-    static std::atomic<int> resident[2][2][2][kMaxDevices];
+    static std::atomic<int> resident[kMaxDevices];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) {
         (void)hipGetLastError();
         set_error("score: no current device below %d", kMaxDevices);
         return TRI_ERR_HIP;
     }
-    std::atomic<int> &cached = resident[sa.c.k_rotated ? 1 : 0][paged ? 1 : 0][half_split ? 1 : 0][dev];
+    std::atomic<int> &cached = resident[dev];
     int slots = cached.load(std::memory_order_relaxed);
     if (slots == 0) {
         int n_cu = 0, per_cu = 0;
@@ -557,17 +496,17 @@ tri_status launch_fast_g(const ScoreArgs &sa, bool half_split, hipStream_t st)
 
 }  // namespace
 
-tri_status launch_score_fast(int G, const ScoreArgs &sa, bool half_split, hipStream_t st)
+tri_status launch_score_fast(int G, const ScoreArgs &sa, hipStream_t st)
 {
     switch (G) {
-        case 1: return launch_fast_g<1>(sa, half_split, st);
-        case 2: return launch_fast_g<2>(sa, half_split, st);
-        case 3: return launch_fast_g<3>(sa, half_split, st);
-        case 4: return launch_fast_g<4>(sa, half_split, st);
-        case 5: return launch_fast_g<5>(sa, half_split, st);
-        case 6: return launch_fast_g<6>(sa, half_split, st);
-        case 7: return launch_fast_g<7>(sa, half_split, st);
-        case 8: return launch_fast_g<8>(sa, half_split, st);
+        case 1: return launch_fast_g<1>(sa, st);
+        case 2: return launch_fast_g<2>(sa, st);
+        case 3: return launch_fast_g<3>(sa, st);
+        case 4: return launch_fast_g<4>(sa, st);
+        case 5: return launch_fast_g<5>(sa, st);
+        case 6: return launch_fast_g<6>(sa, st);
+        case 7: return launch_fast_g<7>(sa, st);
+        case 8: return launch_fast_g<8>(sa, st);
     }
     set_error("group size %d not built (1 to 8)", G);
     return TRI_ERR_UNSUPPORTED;
