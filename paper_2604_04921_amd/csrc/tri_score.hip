@@ -158,42 +158,48 @@ __device__ __forceinline__ void band_update(float (&acc)[G], const float *__rest
         acc[g] = fmaf(tb[0 * G + g], kr, fmaf(tb[1 * G + g], ki, fmaf(tb[2 * G + g], m, acc[g])));
 }
 
-// grid (n_tiles, S*Hkv, L), block 256: one key per thread, staged through LDS so that global
-// loads are coalesced 16-byte accesses while each thread ends up owning one whole key.
+// grid (n_tiles, S*Hkv, L), block 1024: a tile of 256 keys, four threads per key (a quarter of the bands each, the quarter the
+// same for a whole wave, so that table entries stay scalar operands), staged through LDS so that global loads are coalesced
+// 16-byte accesses while each thread ends up with its quarter of one key.  LDS (135 KB for fp32 keys) allows one workgroup per
+// CU, and a wave alone issues a dependent vector instruction every 6 - 8 clocks: with one thread per key, i.e. one wave
+// per SIMD, the kernel was bound by that: fp32 keys, G = 4, whole steps: one head of 4096 keys 32.3 -> 25.6 us, 288 heads of 4096
+// 521 -> 286, of 32768 3595 -> 1730.
+constexpr int kScoreSplit = 4;
 template <int G, typename T, int PAIRS>
-__global__ __launch_bounds__(kScoreTile) void score_kernel(ScoreArgs a)
+__global__ __launch_bounds__(kScoreTile *kScoreSplit) void score_kernel(ScoreArgs a)
 {
     constexpr int ROW16 = Elem<T>::kRow16;
     constexpr int STRIDE16 = ROW16 + 1;   // odd number of 16-byte units: conflict-free row reads
-    extern __shared__ uint4 lds[];
+    extern __shared__ uint4 lds[];        // the keys; later the quarters' sums
     __shared__ int64_t row_off[kScoreTile];
     __shared__ double red[4][2 * G];
 
     const CacheView &c = a.c;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, key = tid % kScoreTile;
+    const int quarter = __builtin_amdgcn_readfirstlane(tid / kScoreTile);
     const int tile = blockIdx.x;
     const int s = blockIdx.y / c.n_kv_heads, h = blockIdx.y % c.n_kv_heads;
     const int l = blockIdx.z;
     const int N = clamp_len(c.seq_len[s], c.max_seq_len);
     const int n0 = tile * kScoreTile;
     if (n0 >= N) return;
-    const int n = n0 + tid;
+    const int n = n0 + key;
     const bool valid = n < N;
 
-    row_off[tid] = valid ? kv_offset(c, l, s, h, n) : (int64_t)-1;
+    if (quarter == 0) row_off[key] = valid ? kv_offset(c, l, s, h, n) : (int64_t)-1;
     int p = 0;
     if (valid && !c.k_rotated) p = c.pos[pos_offset(c, l, s, h, n)];   // a post-RoPE key needs no rotation
     __syncthreads();
 
     const T *kbase = (const T *)c.k;
-#pragma unroll 4
-    for (int i = 0; i < ROW16; ++i) {
-        int ci = i * kScoreTile + tid;
-        int key = ci / ROW16, part = ci % ROW16;
-        int64_t off = row_off[key];
+#pragma unroll
+    for (int i = 0; i < ROW16 / kScoreSplit; ++i) {
+        const int ci = i * kScoreTile * kScoreSplit + tid;
+        const int k = ci / ROW16, part = ci % ROW16;
+        const int64_t off = row_off[k];
         uint4 v = make_uint4(0u, 0u, 0u, 0u);
         if (off >= 0) v = reinterpret_cast<const uint4 *>(kbase + off)[part];
-        lds[key * STRIDE16 + part] = v;
+        lds[k * STRIDE16 + part] = v;
     }
     __syncthreads();
 
@@ -204,11 +210,12 @@ __global__ __launch_bounds__(kScoreTile) void score_kernel(ScoreArgs a)
     float acc[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) acc[g] = 0.f;
-    const uint4 *row = lds + tid * STRIDE16;
+    const uint4 *row = lds + key * STRIDE16;
+    constexpr int kBandsEach = kBands / kScoreSplit;
 
     if constexpr (sizeof(T) == 2 && PAIRS == TRI_PAIR_INTERLEAVED) {
 #pragma unroll 2
-        for (int j = 0; j < 16; ++j) {
+        for (int j = quarter * (kBandsEach / 4); j < (quarter + 1) * (kBandsEach / 4); ++j) {
             uint4 q = row[j];
             const uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
@@ -218,8 +225,8 @@ __global__ __launch_bounds__(kScoreTile) void score_kernel(ScoreArgs a)
             }
         }
     } else if constexpr (sizeof(T) == 2) {
-#pragma unroll 2
-        for (int j = 0; j < 8; ++j) {
+#pragma unroll
+        for (int j = quarter * (kBandsEach / 8); j < (quarter + 1) * (kBandsEach / 8); ++j) {
             uint4 qr = row[j], qi = row[j + 8];
             const uint32_t wr[4] = {qr.x, qr.y, qr.z, qr.w}, wi[4] = {qi.x, qi.y, qi.z, qi.w};
 #pragma unroll
@@ -231,7 +238,7 @@ __global__ __launch_bounds__(kScoreTile) void score_kernel(ScoreArgs a)
         }
     } else if constexpr (PAIRS == TRI_PAIR_INTERLEAVED) {
 #pragma unroll 2
-        for (int j = 0; j < 32; ++j) {
+        for (int j = quarter * (kBandsEach / 2); j < (quarter + 1) * (kBandsEach / 2); ++j) {
             uint4 q = row[j];
             int f = 2 * j;
             band_update<G>(acc, tb + f * 3 * G, pd, rev[f], __uint_as_float(q.x), __uint_as_float(q.y));
@@ -239,7 +246,7 @@ __global__ __launch_bounds__(kScoreTile) void score_kernel(ScoreArgs a)
         }
     } else {
 #pragma unroll 2
-        for (int j = 0; j < 16; ++j) {
+        for (int j = quarter * (kBandsEach / 4); j < (quarter + 1) * (kBandsEach / 4); ++j) {
             uint4 qr = row[j], qi = row[j + 16];
             const uint32_t wr[4] = {qr.x, qr.y, qr.z, qr.w}, wi[4] = {qi.x, qi.y, qi.z, qi.w};
 #pragma unroll
@@ -250,27 +257,36 @@ __global__ __launch_bounds__(kScoreTile) void score_kernel(ScoreArgs a)
         }
     }
 
-    // raw scores out, and this tile's sum / sum of squares per query head (double, fixed order)
-    const int Hq = c.n_kv_heads * G;
-    float *rw = a.raw + (((int64_t)l * c.n_seqs + s) * Hq + (int64_t)h * G) * c.max_seq_len + n;
-    double mom[2 * G];
+    // the quarters' sums together, in their order
+    __syncthreads();   // nobody reads the keys any more
+    float *const sums = reinterpret_cast<float *>(lds);   // [quarter - 1][head][key]
+    if (quarter > 0) {
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-        if (valid) rw[(int64_t)g * c.max_seq_len] = acc[g];
-        double v = valid ? (double)acc[g] : 0.0;
-        mom[g] = v;
-        mom[G + g] = v * v;
+        for (int g = 0; g < G; ++g) sums[((quarter - 1) * G + g) * kScoreTile + key] = acc[g];
     }
+    __syncthreads();
+    if (quarter == 0) {
 #pragma unroll
-    for (int i = 0; i < 2 * G; ++i) {
-        double v = mom[i];
+        for (int g = 0; g < G; ++g)
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-        mom[i] = v;
-    }
-    if ((tid & 63) == 0) {
+            for (int q = 1; q < kScoreSplit; ++q) acc[g] += sums[((q - 1) * G + g) * kScoreTile + key];
+        // raw scores out, and this tile's sum / sum of squares per query head (double, fixed order)
+        const int Hq = c.n_kv_heads * G;
+        float *rw = a.raw + (((int64_t)l * c.n_seqs + s) * Hq + (int64_t)h * G) * c.max_seq_len + n;
 #pragma unroll
-        for (int i = 0; i < 2 * G; ++i) red[tid >> 6][i] = mom[i];
+        for (int g = 0; g < G; ++g) {
+            if (valid) rw[(int64_t)g * c.max_seq_len] = acc[g];
+            double v1 = valid ? (double)acc[g] : 0.0, v2 = v1 * v1;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                v1 += __shfl_xor(v1, o, 64);
+                v2 += __shfl_xor(v2, o, 64);
+            }
+            if ((tid & 63) == 0) {
+                red[tid >> 6][g] = v1;
+                red[tid >> 6][G + g] = v2;
+            }
+        }
     }
     __syncthreads();
     if (tid < 2 * G) {
@@ -369,13 +385,13 @@ tri_status launch_score_kernel(const tri_model &m, const ScoreArgs &sa, dim3 gri
         if (lds > 48 * 1024 &&
             hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
             return hip_status("hipFuncSetAttribute(score_kernel)");
-        hipLaunchKernelGGL(kern, grid, dim3(kScoreTile), lds, st, sa);
+        hipLaunchKernelGGL(kern, grid, dim3(kScoreTile * kScoreSplit), lds, st, sa);
     } else {
         auto kern = score_kernel<G, T, TRI_PAIR_HALF>;
         if (lds > 48 * 1024 &&
             hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
             return hip_status("hipFuncSetAttribute(score_kernel)");
-        hipLaunchKernelGGL(kern, grid, dim3(kScoreTile), lds, st, sa);
+        hipLaunchKernelGGL(kern, grid, dim3(kScoreTile * kScoreSplit), lds, st, sa);
     }
     return hip_status("score_kernel");
 }
