@@ -9,6 +9,7 @@
 // The fold kernel builds (Re Qhat, Im Qhat, c) per (layer, sequence, query head, band) in double;
 // the score kernel then needs, per key and band, one rotation of the key by its own position,
 // one modulus, and three FMAs per query head -- independent of |D|.
+#include <algorithm>
 #include <atomic>
 
 #include "tri_score_common.h"
@@ -31,6 +32,7 @@ struct FoldArgs {
     int32_t lane_kernel;    // its layout: that of tri_score_lane.hip or the sixteen-lane kernel's
     int32_t max_seq_len;
     int32_t S, Hq, Hkv, G;
+    int32_t fold_seqs;      // sequences per workgroup
     int32_t seq_blocks;     // workgroups per (layer, KV head)
     double theta;
     int32_t n_off;
@@ -46,10 +48,10 @@ __device__ __forceinline__ void unit_phasor(double t, double rev, double *c, dou
     sincos(kTwoPi * x, s, c);
 }
 
-constexpr int kFoldSeqs = 8;      // sequences per workgroup
+constexpr int kFoldSeqs = 8;      // sequences per workgroup, more (up to 32) where workgroups abound
 constexpr int kFoldThreads = 512;
 
-// The folded tables of one (layer, KV head) and up to kFoldSeqs sequences per workgroup: grid (Hkv * seq_blocks + extra, L),
+// The folded tables of one (layer, KV head) and fold_seqs sequences per workgroup: grid (Hkv * seq_blocks + extra, L),
 // block 512.  The phasors a fold needs depend on the band and on the offsets or the query position only, and every
 // workgroup evaluates them for itself: (offset, band) and (sequence, band) pairs spread over its threads, three double-precision
 // sincos per thread for 16 offsets and 8 sequences, the offsets then added in their order by one thread per band.  The
@@ -62,8 +64,9 @@ constexpr int kFoldThreads = 512;
 // kernel's phasor table when it needs one, an entry per thread.
 __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
 {
-    __shared__ double off_ph[kMaxOffsets * kBands][2];   // e^{i w delta_j}: entry (j, band); row 0 then holds their mean
-    __shared__ double cur_ph[kFoldSeqs * kBands][2];     // e^{i w cur_pos[s]}
+    extern __shared__ __align__(16) double fold_lds[];
+    double (*const off_ph)[2] = reinterpret_cast<double (*)[2]>(fold_lds);   // e^{i w delta_j}: entry (j, band); row 0 then holds their mean
+    double (*const cur_ph)[2] = off_ph + a.n_off * kBands;                   // e^{i w cur_pos[s]}
     const int tid = threadIdx.x;
     const int n_fold = a.Hkv * a.seq_blocks, l = blockIdx.y;
     // Section 2.1: omega_f = theta^(-2f/d); kept as revolutions per position.  (kFoldThreads is a multiple of F: a
@@ -84,7 +87,7 @@ __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
         return;
     }
     const int h = blockIdx.x / a.seq_blocks, sb = blockIdx.x - h * a.seq_blocks;
-    const int s0 = sb * kFoldSeqs, n_seq = min(a.S - s0, kFoldSeqs);
+    const int s0 = sb * a.fold_seqs, n_seq = min(a.S - s0, a.fold_seqs);
     for (int k = tid; k < a.n_off * kBands; k += kFoldThreads) {
         double c, s;
         unit_phasor((double)a.offsets[k / kBands], rev, &c, &s);
@@ -340,7 +343,10 @@ struct FinalArgs {
     int32_t key_blocks;   // workgroups per head-instance
 };
 
-// grid (instances * ceil(Nmax/1024)), block 256: S_final(k) = max_g (S~(g)(k) - mu_g) / sigma_g.
+// grid (instances * ceil(Nmax/1024)), block 256: S_final(k) = max_g (S~(g)(k) - mu_g) / sigma_g.  Four keys per thread, all their
+// scores loaded before the first is used: rows of an odd length, which allow no 16-byte loads, were read one score at a time
+// (24 x 5 x 8 head-instances of up to 20011 keys, scores: 834 -> 806 us).  (The statistics formed here as well, instead of by
+// stats_kernel: 288 x 2176 keys equal, 9216 x 2176 76 + 9 -> 93 us.)
 template <int G>
 __global__ __launch_bounds__(256) void final_kernel(FinalArgs a)
 {
@@ -349,30 +355,38 @@ __global__ __launch_bounds__(256) void final_kernel(FinalArgs a)
     const int N = clamp_len(a.seq_len[s], a.max_seq_len);
     const int n = (kb * 256 + threadIdx.x) * 4;
     if (n >= N) return;
-    const float *rw = a.raw + (int64_t)inst * G * a.max_seq_len + n;
+    const bool vec = (a.max_seq_len & 3) == 0;   // (four entries from a slot below N on exist)
+    const float *rw = a.raw + (int64_t)inst * G * a.max_seq_len;
+    float v[G][4];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const float *row = rw + (int64_t)g * a.max_seq_len;
+        if (vec) {
+            const float4 t = *reinterpret_cast<const float4 *>(row + n);
+            v[g][0] = t.x, v[g][1] = t.y, v[g][2] = t.z, v[g][3] = t.w;
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[g][k] = row[min(n + k, N - 1)];
+        }
+    }
     const double *st = a.stats + (int64_t)inst * G * 2;
     float best[4];
-    if (n + 3 < N && (a.max_seq_len & 3) == 0) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const float4 v = *reinterpret_cast<const float4 *>(rw + (int64_t)g * a.max_seq_len);
-            const ZParams zp = z_params(st[2 * g], st[2 * g + 1]);
-            const float z[4] = {z_score(v.x, zp), z_score(v.y, zp), z_score(v.z, zp), z_score(v.w, zp)};
+    for (int g = 0; g < G; ++g) {
+        const ZParams zp = z_params(st[2 * g], st[2 * g + 1]);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) best[k] = (g == 0) ? z[k] : fmaxf(best[k], z[k]);
+        for (int k = 0; k < 4; ++k) {
+            const float z = z_score(v[g][k], zp);
+            best[k] = (g == 0) ? z : fmaxf(best[k], z);
         }
-        *reinterpret_cast<float4 *>(a.final_ + (int64_t)inst * a.max_seq_len + n) =
-            make_float4(best[0], best[1], best[2], best[3]);
+    }
+    float *out = a.final_ + (int64_t)inst * a.max_seq_len + n;
+    if (vec && n + 3 < N) {
+        *reinterpret_cast<float4 *>(out) = make_float4(best[0], best[1], best[2], best[3]);
     } else {
-        for (int k = 0; k < 4 && n + k < N; ++k) {
-            float b = 0.f;
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                float z = z_score(rw[(int64_t)g * a.max_seq_len + k], z_params(st[2 * g], st[2 * g + 1]));
-                b = (g == 0) ? z : fmaxf(b, z);
-            }
-            a.final_[(int64_t)inst * a.max_seq_len + n + k] = b;
-        }
+        for (int k = 0; k < 4; ++k)
+            if (n + k < N) out[k] = best[k];
     }
 }
 
@@ -435,16 +449,14 @@ tri_status launch_score_g(const tri_model &m, const tri_cache &c, ScoreArgs sa, 
                  tile_keys, c.max_seq_len};
     hipLaunchKernelGGL(stats_kernel, dim3(n_inst), dim3(256), 0, st, ta);
     if ((rc = hip_status("stats_kernel")) != TRI_OK) return rc;
-    if (final_out) {
-        FinalArgs fb = fa;
-        fb.key_blocks = (c.max_seq_len + 1023) / 1024;
-        if ((int64_t)fb.key_blocks * n_inst > (int64_t)0x7fffffff) {
-            set_error("tri_score: %d head-instances x %d key blocks exceed the grid", n_inst, fb.key_blocks);
-            return TRI_ERR_UNSUPPORTED;
-        }
-        hipLaunchKernelGGL(final_kernel<G>, dim3((uint32_t)((int64_t)fb.key_blocks * n_inst)), dim3(256), 0, st, fb);
-        rc = hip_status("final_kernel");
+    FinalArgs fb = fa;
+    fb.key_blocks = (c.max_seq_len + 1023) / 1024;
+    if ((int64_t)fb.key_blocks * n_inst > (int64_t)0x7fffffff) {
+        set_error("tri_score: %d head-instances x %d key blocks exceed the grid", n_inst, fb.key_blocks);
+        return TRI_ERR_UNSUPPORTED;
     }
+    hipLaunchKernelGGL(final_kernel<G>, dim3((uint32_t)((int64_t)fb.key_blocks * n_inst)), dim3(256), 0, st, fb);
+    rc = hip_status("final_kernel");
     return rc;
 }
 
@@ -488,17 +500,20 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     fo.seq_len = c.seq_len;
     fo.work = mfma_path(c, G) ? reinterpret_cast<int32_t *>(ws + wl.work) : nullptr;
     // keys per work item: small batches are cut finer
+    int n_cu = 0;
+    tri_status rc = device_cus(&n_cu);
+    if (rc != TRI_OK) return rc;
     int chunk_keys = kFastChunk;
     if (fo.work) {
-        int n_cu = 0;
-        tri_status rcu = device_cus(&n_cu);
-        if (rcu != TRI_OK) return rcu;
         chunk_keys = item_keys((int64_t)m.n_layers * c.n_seqs * m.n_kv_heads, c.max_seq_len, n_cu);
     }
     fo.chunk_keys = chunk_keys;
     fo.max_seq_len = c.max_seq_len;
     fo.S = c.n_seqs;
-    fo.seq_blocks = (c.n_seqs + kFoldSeqs - 1) / kFoldSeqs;
+    fo.fold_seqs = kFoldSeqs;
+    while (fo.fold_seqs < 32 && (int64_t)m.n_layers * m.n_kv_heads * ((c.n_seqs + 2 * fo.fold_seqs - 1) / (2 * fo.fold_seqs)) >= 2 * n_cu)
+        fo.fold_seqs *= 2;
+    fo.seq_blocks = (c.n_seqs + fo.fold_seqs - 1) / fo.fold_seqs;
     fo.Hq = m.n_q_heads;
     fo.Hkv = m.n_kv_heads;
     fo.G = G;
@@ -518,10 +533,13 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     const int table_entries = !fo.work || c.k_rotated ? 0 : lane_kernel ? kLaneTableEntries : kFastTableEntries;
     fo.phasors = reinterpret_cast<float4 *>(ws + wl.phasors);
     fo.lane_kernel = lane_kernel;
+    const size_t fold_lds = (size_t)(m.n_offsets + std::min(fo.fold_seqs, c.n_seqs)) * kBands * 2 * sizeof(double);
+    if (fold_lds > 48 * 1024 &&
+        hipFuncSetAttribute((const void *)fold_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fold_lds) != hipSuccess)
+        return hip_status("hipFuncSetAttribute(fold_kernel)");
     hipLaunchKernelGGL(fold_kernel, dim3(m.n_kv_heads * fo.seq_blocks + 1 + table_entries / kFoldThreads, m.n_layers),
-                       dim3(kFoldThreads), 0, st, fo);
-    tri_status rc = hip_status("fold_kernel");
-    if (rc != TRI_OK) return rc;
+                       dim3(kFoldThreads), fold_lds, st, fo);
+    if ((rc = hip_status("fold_kernel")) != TRI_OK) return rc;
 
     ScoreArgs sa{};
     sa.c = make_view(m, c);
@@ -533,8 +551,14 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     sa.work = reinterpret_cast<int32_t *>(ws + wl.work);
     sa.n_layers = m.n_layers;
     sa.chunk_keys = chunk_keys;
-    FinalArgs fa{sa.raw, reinterpret_cast<double *>(ws + wl.stats), final_out, c.seq_len, c.n_seqs,
-                 m.n_kv_heads, c.max_seq_len, 0};
+    FinalArgs fa{};
+    fa.raw = sa.raw;
+    fa.stats = reinterpret_cast<double *>(ws + wl.stats);
+    fa.final_ = final_out;
+    fa.seq_len = c.seq_len;
+    fa.n_seqs = c.n_seqs;
+    fa.n_kv_heads = m.n_kv_heads;
+    fa.max_seq_len = c.max_seq_len;
     switch (G) {
         case 1: return launch_score_g<1>(m, c, sa, fa, final_out, moments, lane_kernel, st);
         case 2: return launch_score_g<2>(m, c, sa, fa, final_out, moments, lane_kernel, st);

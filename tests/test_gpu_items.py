@@ -55,3 +55,25 @@ def test_positions(oracle, pairs, spread, shuffled):
                 w[name] = np.ascontiguousarray(np.concatenate([x[..., 0::2], x[..., 1::2]], axis=-1))
 
     run_and_check(oracle, cfg, pairs=pairs, mutate=mutate)
+
+
+@pytest.mark.parametrize("pairs", [0, 1])
+@pytest.mark.parametrize("dtype,block,group,lens", [
+    ("f32", 0, 4, [1025, 1022, 300]),   # rows of an odd length
+    ("f32", 0, 8, [513, 256, 1]),    # tile edges, four threads per key
+    ("f32", 0, 1, [255]),
+    ("bf16", 4, 3, [700, 257]),      # paged blocks below 16: the same kernel on bf16
+    ("bf16", 8, 8, [512, 3]),
+])
+def test_generic_kernel(oracle, dtype, block, group, lens, pairs):
+    cfg = recipe.scaled(recipe.CONFIGS["c4_paged" if block else "c2_layer"], n_layers=1, n_seqs=len(lens), n_q_heads=group,
+                        n_kv_heads=1, seq_len=max(lens), min_seq_len=min(lens), budget=100, n_calib=64, positions="dense",
+                        block_size=block, dtype=dtype, n_offsets=4, seed=9 + group)
+
+    def mutate(w):
+        if pairs:
+            for name in ("k", "q_samples"):
+                x = w[name]
+                w[name] = np.ascontiguousarray(np.concatenate([x[..., 0::2], x[..., 1::2]], axis=-1))
+
+    run_and_check(oracle, cfg, paged=bool(block), inplace=bool(block), pairs=pairs, mutate=mutate)
