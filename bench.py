@@ -120,13 +120,12 @@ def main():
     if args.fill and step_bytes:   # only the kept keys stored beyond the new length move
         step_bytes = 260 * keys + 1032 * sum(p_["moved"] for p_ in parts)
     # which of the three score kernels ran (the library's dispatch rule, restated for the label only): bf16 keys in
-    # blocks of 16 or more go to an MFMA kernel; of those, interleaved pairs to the one-key-per-lane kernel unless the
-    # cache is paged and the batch large enough for 8192-key work items
+    # blocks of 16 or more go to an MFMA kernel, score_lane_kernel but for large paged batches of pre-RoPE keys with interleaved
+    # pairs whose sequences are short or whose KV heads serve more than four query heads
     mfma_path = eb == 2 and (cfg.block_size == 0 or cfg.block_size >= 16)
-    waves = 8 if Hq // Hkv > 4 else 12
-    rounds = (L * S * Hkv * ((cfg.seq_len + 63) // 64)) // (4 * torch.cuda.get_device_properties(0).multi_processor_count * waves)
-    small_items = rounds * waves * 64 < 8192
-    lane = mfma_path and not args.half_split and (cfg.block_size == 0 or small_items)
+    large = L * S * Hkv * ((cfg.seq_len + 8191) // 8192) >= 8 * torch.cuda.get_device_properties(0).multi_processor_count
+    lane = mfma_path and not (paged and large and not args.half_split and not args.post_rope and
+                              (Hq // Hkv > 4 or cfg.seq_len <= 8192))
     kernel = "score_lane_kernel" if lane else "score_mfma_kernel" if mfma_path else "score_kernel"
     roofline = {"bound": "hbm", "kernel": kernel, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),

@@ -76,3 +76,27 @@ def test_threshold_bin_longer_than_the_list(oracle, n, kind):
     for h in range(heads):
         assert int(cnt[0, 0, h]) == budget
         np.testing.assert_array_equal(idx[0, 0, h].cpu().numpy(), oracle.topk(f[h].astype(np.float64), budget))
+
+
+@pytest.mark.parametrize("layers", [1, 33])   # 4 and 132 head-instances: 1024 and 256 threads per workgroup
+@pytest.mark.parametrize("n,budget", [(300, 128), (2176, 2048)])
+def test_eviction_at_the_end_of_the_selection(layers, n, budget):
+    """The fused step's eviction in place (moves made by the selection's workgroup) against selection and tri_compact_fill."""
+    cfg = recipe.scaled(recipe.CONFIGS["c2_layer"], n_layers=layers, n_seqs=2, n_q_heads=8, n_kv_heads=2, seq_len=n,
+                        min_seq_len=budget - 1, budget=budget, n_calib=64)
+    run = H.GpuRun(cfg, recipe.generate(cfg))
+    run.build_centers()
+    B, before = run.B, [t.clone() for t in (run.k, run.v, run.pos)]
+    run.score(want_raw=False)
+    run.select()
+    B.tri_compact_fill(run.model, run.cache, budget, run.kept_idx, run.kept_cnt, run.new_len)
+    torch.cuda.synchronize()
+    want = [t.clone() for t in (run.k, run.v, run.pos, run.kept_idx, run.kept_cnt, run.new_len)]
+    for t, b in zip((run.k, run.v, run.pos), before):
+        t.copy_(b)
+    for t in (run.kept_idx, run.kept_cnt, run.new_len):
+        t.fill_(-1)
+    B.tri_compress_step(run.model, run.centers, run.cache, None, budget, run.kept_idx, run.kept_cnt, run.new_len, run.ws)
+    torch.cuda.synchronize()
+    for t, w in zip((run.k, run.v, run.pos, run.kept_idx, run.kept_cnt, run.new_len), want):
+        assert torch.equal(t, w)
