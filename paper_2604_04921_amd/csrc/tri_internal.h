@@ -143,13 +143,13 @@ __device__ __forceinline__ int64_t pos_offset(const CacheView &c, int l, int s, 
 struct Workspace {
     size_t band_rev;   // double [F]: omega_f / 2pi
     size_t reserved;   // ((1 + S) F 2 doubles, unused: the total is what callers' workspaces were sized for)
-    size_t phasors;    // relative-position phasor table of the MFMA score kernel
+    size_t phasors;    // relative-position phasor table of the MFMA score kernels
     size_t table;      // float  [L][S][Hkv][F][3][G]: folded centre table
-    size_t work;       // int32: item counter and work list of the MFMA score kernel
+    size_t work;       // int32: item counter and work list of the MFMA score kernels
     size_t partials;   // double [L][S][Hkv][n_tiles][2G]: per-tile sum and sum of squares
     size_t stats;      // double [L][S][Hkv][G][2]: mean and 1/sigma
     size_t raw;        // float  [L][S][Hq][Nmax] (used when the caller passes no raw_out)
-    size_t final_;     // float  [L][S][Hkv][Nmax] (tri_compress_step only)
+    size_t final_;     // [L][S][Hkv][Nmax] words (tri_compress_step only): histograms of long sequences' chunks
     size_t total;
 };
 Workspace workspace_layout(const tri_model &m, const tri_cache &c, int32_t budget);

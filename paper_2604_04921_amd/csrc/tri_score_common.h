@@ -42,17 +42,17 @@ inline int item_keys(int64_t instances, int max_seq_len, int n_cu)
 {
     constexpr int unit = 64;                            // a tile
     const int64_t workgroups = n_cu > 0 ? n_cu : 1;     // one per CU
-    if (instances * ((max_seq_len + kFastChunk - 1) / kFastChunk) >= 8 * workgroups) return kFastChunk;
+    const int64_t len = max_seq_len, fewest = (len + kFastChunk - 1) / kFastChunk;
+    if (instances * fewest >= 8 * workgroups) return kFastChunk;
     constexpr int least = kMinChunk;
     static_assert(kMinChunk % unit == 0, "whole tiles");
     int best = kFastChunk;
     int64_t best_cost = INT64_MAX;
-    for (int pieces = 1; pieces <= 1024; ++pieces) {
-        int keys = ((max_seq_len + pieces - 1) / pieces + unit - 1) / unit * unit;
+    for (int64_t pieces = fewest; pieces < fewest + 1024; ++pieces) {
+        int keys = (int)(((len + pieces - 1) / pieces + unit - 1) / unit * unit);   // kFastChunk at most
         const bool last = keys <= least;
         if (last) keys = least;
-        if (keys > kFastChunk) continue;
-        const int64_t items = instances * ((max_seq_len + keys - 1) / keys);
+        const int64_t items = instances * ((len + keys - 1) / keys);
         const int64_t cost = (items + workgroups - 1) / workgroups * (keys + kItemCost);
         if (cost < best_cost) {
             best_cost = cost;

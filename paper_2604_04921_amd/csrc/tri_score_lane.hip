@@ -316,6 +316,10 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
 
             float4v acc[NG], acc2[NG];   // two chains, so that consecutive matrix instructions do not depend on each other
             float4v first[NG];           // rows: step 0's scores, over the lane's half of the bands
+            // rows: the first sixteen bands of a step.  The kernel that had these caches before added four bands at a time and
+            // those in a tree; chains of 32 bands left final scores further from 64-bit ones than it did (2.0e-7 against 1.4e-7 on
+            // scattered half-split keys, 1.6e-7 against 1.2e-7 post-RoPE), chains of sixteen 1.8e-7 and 1.3e-7, for 0.3 % of the time.
+            float4v middle[NG];
 
             // Everything a piece (four bands of the lane's key) needs from LDS: the key's 16 bytes, the phasors of its
             // four bands at the lane's relative position, the lane's table entries.  Pieces are fetched one ahead of
@@ -443,10 +447,18 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                         if (pc + 1 < 8) nxt = fetch(cur, half, pc + 1, table_tag);
                         score_piece(cur, half, pc, table_tag, mirror_tag);
                         cur = nxt;
+                        if (ROWS && pc == 3) {   // (sums of sixteen bands at most: see `middle`)
+#pragma unroll
+                            for (int q = 0; q < NG; ++q) {
+                                middle[q] = acc[q] + acc2[q];
+                                acc[q] = acc2[q] = float4v{0.f, 0.f, 0.f, 0.f};
+                            }
+                        }
                     }
 #pragma unroll
                     for (int q = 0; q < NG; ++q) {
                         if (ROWS || half == 1) acc[q] += acc2[q];
+                        if (ROWS) acc[q] += middle[q];
                         if (ROWS && half == 0) first[q] = acc[q];
                     }
                 }
