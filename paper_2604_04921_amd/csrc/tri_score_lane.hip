@@ -281,7 +281,8 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                 // (The lowest and highest position of every tile through twelve LDS shuffles, each waiting for the one before,
                 // cost 64 x 8 head-instances of 131072 keys at G = 8 1 %.)
                 base = __builtin_amdgcn_readfirstlane(p_key);
-                if (__builtin_amdgcn_ballot_w64((uint32_t)p_key - (uint32_t)base >= (uint32_t)kLaneRange) != 0ull) {
+                // (The difference of two int32 positions fits 32 bits without a sign once none lies below the first.)
+                if (__builtin_amdgcn_ballot_w64(p_key < base || (uint32_t)p_key - (uint32_t)base >= (uint32_t)kLaneRange) != 0ull) {
                     base = wave_extreme<false>(p_key);
                     const int64_t span = (int64_t)wave_extreme<true>(p_key) - (int64_t)base;
                     // positions within 64 of the lowest: base = the lowest, r >= 0.  Else base = the middle and the table
