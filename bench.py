@@ -37,6 +37,27 @@ def kernel_sources_sha16():
     return h.hexdigest()[:16]
 
 
+def score_kernel_name(group, instances, n, n_cu, mfma, half_split, paged, post_rope):
+    """Which of the three score kernels runs: the library's rules (csrc/tri_items.h) restated for the label only.  mfma: bf16 keys,
+    contiguous or in blocks of 16 or more."""
+    if not mfma:
+        return "score_kernel"
+    chunk, tile, fewest = 8192, 64, -(-n // 8192)
+    large = instances * fewest >= 8 * n_cu
+    item, best = chunk, None
+    for pieces in range(fewest, 0 if large else fewest + 1024):   # keys per work item: the number of equal pieces that costs least
+        keys = -(-(-(-n // pieces)) // tile) * tile
+        last = keys <= 512
+        keys = max(keys, 512)
+        cost = -(-instances * -(-n // keys) // n_cu) * (keys + 768)
+        if best is None or cost < best:
+            item, best = keys, cost
+        if last:
+            break
+    sixteen = paged and not half_split and not post_rope and item == chunk and (group > 4 or (n <= chunk and large))
+    return "score_mfma_kernel" if sixteen else "score_lane_kernel"
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -119,14 +140,8 @@ def main():
     step_bytes = int(sum(STEP_BYTES(int(n), B) for n in lens)) * L_all * Hkv if eb == 2 else None
     if args.fill and step_bytes:   # only the kept keys stored beyond the new length move
         step_bytes = 260 * keys + 1032 * sum(p_["moved"] for p_ in parts)
-    # which of the three score kernels ran (the library's dispatch rule, restated for the label only): bf16 keys in
-    # blocks of 16 or more go to an MFMA kernel, score_lane_kernel but for large paged batches of pre-RoPE keys with interleaved
-    # pairs whose sequences are short or whose KV heads serve more than four query heads
-    mfma_path = eb == 2 and (cfg.block_size == 0 or cfg.block_size >= 16)
-    large = L * S * Hkv * ((cfg.seq_len + 8191) // 8192) >= 8 * torch.cuda.get_device_properties(0).multi_processor_count
-    lane = mfma_path and not (paged and large and not args.half_split and not args.post_rope and
-                              (Hq // Hkv > 4 or cfg.seq_len <= 8192))
-    kernel = "score_lane_kernel" if lane else "score_mfma_kernel" if mfma_path else "score_kernel"
+    kernel = score_kernel_name(Hq // Hkv, L * S * Hkv, cfg.seq_len, torch.cuda.get_device_properties(0).multi_processor_count,
+                               eb == 2 and (cfg.block_size == 0 or cfg.block_size >= 16), args.half_split, paged, args.post_rope)
     roofline = {"bound": "hbm", "kernel": kernel, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": measured_traffic(cfg.name, mode, args),

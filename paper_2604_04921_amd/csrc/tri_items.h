@@ -1,0 +1,73 @@
+// Host-side rules of the score kernels: how a batch is cut into work items, and which kernel takes it.  Plain C++: the CPU tests
+// compile this file by itself.
+#pragma once
+#include <stdint.h>
+
+namespace tri {
+
+// Keys per work item of the MFMA score kernels (= keys per entry of `partials` on that path): kFastChunk on large batches (the
+// sixteen-lane kernel always), less where that would leave resident workgroups without work (item_keys), kMinChunk at least.
+constexpr int kFastChunk = 8192;
+constexpr int kMinChunk = 512;
+constexpr int kItemCost = 768;
+constexpr int lane_waves(int G) { return G > 4 ? 8 : 12; }   // waves per workgroup of the kernel of tri_score_lane.hip
+// Waves per workgroup of the sixteen-lane kernel: with more than four query heads per KV head a wave needs more than 128
+// registers, so only three waves fit a SIMD; 12-wave workgroups fill them (8-wave ones would leave one of three unused).
+constexpr int fast_waves(int G) { return G > 4 ? 12 : 8; }
+
+// Eight or more items of kFastChunk keys per CU.
+inline bool large_batch(int64_t instances, int max_seq_len, int n_cu)
+{
+    return instances * (((int64_t)max_seq_len + kFastChunk - 1) / kFastChunk) >= 8 * (int64_t)(n_cu > 0 ? n_cu : 1);
+}
+
+// Resident workgroups take items until none is left, so a batch takes about (items per workgroup, rounded up) x (an item's keys
+// + the item's own cost in keys: its tables, its first loads, its waves' last ones).  Every head-instance is cut into the
+// number of equal pieces that makes this least, in whole tiles of 64; large batches stay with kFastChunk.  Measured, whole steps
+// (before: about four items per CU in rounds of the workgroup's waves; kFastChunk for half-split pairs): one layer of eight x 32768 keys 66.5 -> 57.8 us, four layers 126 -> 109, 36 layers
+// 693 -> 674; one layer of eight x 12289, half-split, 150 -> 44.5, sixteen layers 207 -> 169; score + selection of 288 x 2176
+// keys 91.0 -> 89.4, 576 155 -> 134.  An item cost of 128 keys is worse on many short sequences (1152 x 2176: 243 against
+// 219 us), 384 and 1600 on some in between (576 x 2176: 143 and 134; 160 x 32768: 387 and 397 against 387), 768 nowhere.
+inline int item_keys(int64_t instances, int max_seq_len, int n_cu)
+{
+    constexpr int unit = 64;                            // a tile
+    const int64_t workgroups = n_cu > 0 ? n_cu : 1;     // one per CU
+    const int64_t len = max_seq_len, fewest = (len + kFastChunk - 1) / kFastChunk;
+    if (large_batch(instances, max_seq_len, n_cu)) return kFastChunk;
+    constexpr int least = kMinChunk;
+    static_assert(kMinChunk % unit == 0, "whole tiles");
+    int best = kFastChunk;
+    int64_t best_cost = INT64_MAX;
+    for (int64_t pieces = fewest; pieces < fewest + 1024; ++pieces) {
+        int keys = (int)(((len + pieces - 1) / pieces + unit - 1) / unit * unit);   // kFastChunk at most
+        const bool last = keys <= least;
+        if (last) keys = least;
+        const int64_t items = instances * ((len + keys - 1) / keys);
+        const int64_t cost = (items + workgroups - 1) / workgroups * (keys + kItemCost);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = keys;
+        }
+        if (last) break;
+    }
+    return best;
+}
+
+// Which kernel takes bf16 keys (item: item_keys() of the batch): that of tri_score_lane.hip, but paged pre-RoPE keys with
+// interleaved pairs in items of kFastChunk go to the one that spreads a key over sixteen lanes where it is the faster one.
+// More than four query heads per KV head, whole steps: 768 x 4096 to 65536 keys at G = 8 2600 us against 2684, at G = 5 2447 against
+// 2495; batches whose cost model ends at kFastChunk as well (one item per CU and more): 32 x 65536 at G = 8 206 against 215, 64 x
+// 32768 205 against 218, 128 x 16384 225 against 235 (G = 5: 218 against 225), 512 x 8192 528 against 550.
+// Up to four: large batches of short sequences, 3072 x 4096 keys at G = 4 1055 against 1073, 4608 x 2176 2538 against 2559; it is
+// the slower one on smaller batches (256 x 8192 at G = 4 257 against 252, at G = 1 250 against 236; 768 x 8192 745 against 712) and
+// on longer sequences (768 x 4096 to 65536 keys 2107 against 2058 at G = 4, 1983 against 1959 at G = 2; 3072 x 9000 3098 against
+// 3064).
+// Half-split pairs: 768 x 4096 to 65536 keys 2680 against 2664 at G = 8, 2135 against 2078 at G = 4, 3072 x 4096 keys 1077 against
+// 1068; post-RoPE at G = 8 2368 against 2364: never.
+inline bool sixteen_lane_kernel(int G, int item, int64_t instances, int max_seq_len, int n_cu, bool half_split, bool paged, bool rotated)
+{
+    if (!paged || half_split || rotated || item != kFastChunk) return false;
+    return G > 4 || (max_seq_len <= kFastChunk && large_batch(instances, max_seq_len, n_cu));
+}
+
+}  // namespace tri

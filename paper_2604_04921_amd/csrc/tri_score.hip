@@ -521,14 +521,8 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     fo.n_off = m.n_offsets;
     fo.variant = m.score_variant;
     for (int j = 0; j < m.n_offsets; ++j) fo.offsets[j] = m.offsets[j];
-    // bf16 keys: the kernel of tri_score_lane.hip, but large paged batches (whole items of kFastChunk) of pre-RoPE keys with
-    // interleaved pairs, of short sequences or of more than four query heads per KV head, go to the one that spreads a key over
-    // sixteen lanes: 3072 x 4096 keys 1055 us a step against 1073, 768 x 4096 to 65536 keys at G = 8 2600 against 2684, at G = 5
-    // 2447 against 2495 -- where it is the slower one: 2107 against 2058 at G = 4, 1983 against 1959 at G = 2, 3098 against
-    // 3064 on 3072 x 9000 keys; half-split pairs, 768 x 4096 to 65536 keys, 2680 against 2664 at G = 8, 2135 against 2078 at
-    // G = 4, 3072 x 4096 keys 1077 against 1068; post-RoPE at G = 8 2368 against 2364.
-    const bool sixteen = m.pairs == TRI_PAIR_INTERLEAVED && c.block_size != 0 && !c.k_rotated && chunk_keys == kFastChunk &&
-                         (G > 4 || c.max_seq_len <= kFastChunk);
+    const bool sixteen = sixteen_lane_kernel(G, chunk_keys, (int64_t)m.n_layers * c.n_seqs * m.n_kv_heads, c.max_seq_len, n_cu,
+                                             m.pairs == TRI_PAIR_HALF, c.block_size != 0, c.k_rotated != 0);
     const bool lane_kernel = fo.work && !sixteen;
     const int table_entries = !fo.work || c.k_rotated ? 0 : lane_kernel ? kLaneTableEntries : kFastTableEntries;
     fo.phasors = reinterpret_cast<float4 *>(ws + wl.phasors);

@@ -1,6 +1,7 @@
 // Declarations shared by the two score kernels (generic and MFMA).
 #pragma once
 #include "tri_internal.h"
+#include "tri_items.h"
 
 namespace tri {
 
@@ -21,47 +22,6 @@ struct ScoreArgs {
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-// Keys per work item of the MFMA score kernels (= keys per entry of `partials` on that path): kFastChunk on large batches (the
-// sixteen-lane kernel always), less where that would leave resident workgroups without work (item_keys), kMinChunk at least.
-constexpr int kFastChunk = 8192;
-constexpr int kMinChunk = 512;
-constexpr int kItemCost = 768;
-constexpr int lane_waves(int G) { return G > 4 ? 8 : 12; }   // waves per workgroup of the kernel of tri_score_lane.hip
-// Waves per workgroup of the sixteen-lane kernel: with more than four query heads per KV head a wave needs more than 128
-// registers, so only three waves fit a SIMD; 12-wave workgroups fill them (8-wave ones would leave one of three unused).
-constexpr int fast_waves(int G) { return G > 4 ? 12 : 8; }
-// Resident workgroups take items until none is left, so a batch takes about (items per workgroup, rounded up) x (an item's keys
-// + the item's own cost in keys: its tables, its first loads, its waves' last ones).  Every head-instance is cut into the
-// number of equal pieces that makes this least, in whole tiles of 64; batches of eight or more
-// items of kFastChunk keys per workgroup stay with those.  Measured, whole steps (before: about four items per CU in rounds of the workgroup's waves;
-// kFastChunk for half-split pairs): one layer of eight x 32768 keys 66.5 -> 57.8 us, four layers 126 -> 109, 36 layers
-// 693 -> 674; one layer of eight x 12289, half-split, 150 -> 44.5, sixteen layers 207 -> 169; score + selection of 288 x 2176
-// keys 91.0 -> 89.4, 576 155 -> 134.  An item cost of 128 keys is worse on many short sequences (1152 x 2176: 243 against
-// 219 us), 384 and 1600 on some in between (576 x 2176: 143 and 134; 160 x 32768: 387 and 397 against 387), 768 nowhere.
-inline int item_keys(int64_t instances, int max_seq_len, int n_cu)
-{
-    constexpr int unit = 64;                            // a tile
-    const int64_t workgroups = n_cu > 0 ? n_cu : 1;     // one per CU
-    const int64_t len = max_seq_len, fewest = (len + kFastChunk - 1) / kFastChunk;
-    if (instances * fewest >= 8 * workgroups) return kFastChunk;
-    constexpr int least = kMinChunk;
-    static_assert(kMinChunk % unit == 0, "whole tiles");
-    int best = kFastChunk;
-    int64_t best_cost = INT64_MAX;
-    for (int64_t pieces = fewest; pieces < fewest + 1024; ++pieces) {
-        int keys = (int)(((len + pieces - 1) / pieces + unit - 1) / unit * unit);   // kFastChunk at most
-        const bool last = keys <= least;
-        if (last) keys = least;
-        const int64_t items = instances * ((len + keys - 1) / keys);
-        const int64_t cost = (items + workgroups - 1) / workgroups * (keys + kItemCost);
-        if (cost < best_cost) {
-            best_cost = cost;
-            best = keys;
-        }
-        if (last) break;
-    }
-    return best;
-}
 // Relative positions covered by the sixteen-lane kernel's phasor table.
 constexpr int kPhasorRange = 128;
 constexpr int kPhasorBlockStride = kPhasorRange * 16 + 64;      // bytes per 4-band chunk (64 B skew)

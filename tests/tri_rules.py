@@ -1,0 +1,46 @@
+"""The score kernels' host-side rules as the library has them: csrc/tri_items.h, compiled by itself."""
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+WRAPPER = """
+#include "tri_items.h"
+extern "C" {
+int item_keys(long long instances, int n, int n_cu) { return tri::item_keys(instances, n, n_cu); }
+int large_batch(long long instances, int n, int n_cu) { return tri::large_batch(instances, n, n_cu); }
+int sixteen_lane_kernel(int group, long long instances, int n, int n_cu, int half_split, int paged, int rotated)
+{
+    return tri::sixteen_lane_kernel(group, tri::item_keys(instances, n, n_cu), instances, n, n_cu, half_split, paged, rotated);
+}
+}
+"""
+
+
+@functools.lru_cache(maxsize=None)
+def library():
+    with tempfile.TemporaryDirectory(prefix="tri_rules_") as tmp:
+        src, so = os.path.join(tmp, "rules.cpp"), os.path.join(tmp, "rules.so")
+        with open(src, "w") as f:
+            f.write(WRAPPER)
+        subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC",
+                        "-I" + os.path.join(ROOT, "paper_2604_04921_amd", "csrc"), src, "-o", so], check=True)
+        lib = ctypes.CDLL(so)
+    lib.item_keys.argtypes = lib.large_batch.argtypes = [ctypes.c_longlong, ctypes.c_int, ctypes.c_int]
+    lib.sixteen_lane_kernel.argtypes = [ctypes.c_int, ctypes.c_longlong] + [ctypes.c_int] * 5
+    return lib
+
+
+def item_keys(instances, n, n_cu):
+    return library().item_keys(instances, n, n_cu)
+
+
+def large_batch(instances, n, n_cu):
+    return bool(library().large_batch(instances, n, n_cu))
+
+
+def sixteen_lane_kernel(group, instances, n, n_cu, half_split=False, paged=True, rotated=False):
+    return bool(library().sixteen_lane_kernel(group, instances, n, n_cu, half_split, paged, rotated))
