@@ -314,17 +314,21 @@ __global__ __launch_bounds__(fast_threads(G), G > 4 ? 3 : 4) void score_mfma_ker
         score_step<NG>(kd, cs, sn, tb, out);
     };
 
+    // Positions p that the table does not cover from the base in force.  (Compared as well as subtracted: the difference of the
+    // two ends of int32 is small in 32 bits.)
+    auto outside_table = [&](int p) {
+        return __builtin_amdgcn_ballot_w64(p < base || (uint32_t)p - (uint32_t)base >= (uint32_t)kPhasorRange) != 0ull;
+    };
+
     // one step for any four positions: move the base if that brings them into the table, else
     // evaluate the phasors directly (phase in double, relative to the base in force)
     auto step_general = [&](const uint4 &kd, int p, float(&out)[NG]) {
-        int r = p - base;
-        if (__builtin_amdgcn_ballot_w64((unsigned)r >= (unsigned)kPhasorRange) != 0ull) {
+        if (outside_table(p)) {
             const int p0 = __builtin_amdgcn_readlane(p, 0), p1 = __builtin_amdgcn_readlane(p, 1);
             const int p2 = __builtin_amdgcn_readlane(p, 2), p3 = __builtin_amdgcn_readlane(p, 3);
             const int lo = min(min(p0, p1), min(p2, p3)), hi = max(max(p0, p1), max(p2, p3));
             if ((int64_t)hi - (int64_t)lo < kPhasorRange) {
                 move_base(lo);
-                r = p - base;
             } else {
                 const double pd = (double)((int64_t)p - (int64_t)base);
                 float cs[4], sn[4];
@@ -338,7 +342,7 @@ __global__ __launch_bounds__(fast_threads(G), G > 4 ? 3 : 4) void score_mfma_ker
                 return;
             }
         }
-        step_table(kd, r, out);
+        step_table(kd, p - base, out);
     };
 
     auto process_group = [&](int n, const uint4(&kraw)[4], int praw, auto full_tag) {
@@ -350,8 +354,7 @@ __global__ __launch_bounds__(fast_threads(G), G > 4 ? 3 : 4) void score_mfma_ker
         // common case: all 16 positions of the group fall in the table around the current base.  The test
         // and the table index are formed on the positions in load order (every lane holds one of the 16),
         // before they go to the consumer lanes.
-        int rraw = praw - base;
-        bool fast = __builtin_amdgcn_ballot_w64((unsigned)rraw >= (unsigned)kPhasorRange) == 0ull;
+        bool fast = !outside_table(praw);
         if (!fast) {
             // span of the 16 positions: lanes 0..15 hold one each (one DPP row)
             int lo = praw, hi = praw;
@@ -364,11 +367,11 @@ __global__ __launch_bounds__(fast_threads(G), G > 4 ? 3 : 4) void score_mfma_ker
             hi = __builtin_amdgcn_readfirstlane(hi);
             if ((int64_t)hi - (int64_t)lo < kPhasorRange) {
                 move_base(lo);
-                rraw = praw - base;
                 fast = true;
             }
         }
         if (fast) {
+            const int rraw = praw - base;
 #pragma unroll
             for (int t = 0; t < 4; ++t)
                 step_table(kd[t], __builtin_amdgcn_ds_bpermute(perm_p + 16 * t, rraw), out[t]);

@@ -9,6 +9,7 @@ from workload import recipe
 
 import tri_harness as H
 import tri_rules as R
+from test_gpu_position_range import KINDS, positions as ends_of_int32
 
 pytestmark = pytest.mark.gpu
 
@@ -94,3 +95,15 @@ def test_wild_positions(oracle, group):
                 p[:, s] = np.arange(n) // 37 * 3
         w["cur_pos"][:] = 1 << 28
     score_batch(oracle, group, SHORT, set_positions=set_positions)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("group", [4, 5])
+def test_position_range(oracle, group, kind):
+    """Negative positions, and both ends of int32 in one group of sixteen keys or in the step of four."""
+    def set_positions(w):
+        w["pos"][:] = ends_of_int32(kind, w["pos"].shape[-1]).astype(np.int32)
+        if kind in ("high_then_low", "low_then_high"):   # the lone end in a step's second key
+            w["pos"][:, 1::2] = np.roll(w["pos"][:, 1::2], 1, axis=-1)
+        w["cur_pos"][:] = -3
+    score_batch(oracle, group, [1000, 1023, 777, 640, 300, 17, 0, 901], set_positions=set_positions)
