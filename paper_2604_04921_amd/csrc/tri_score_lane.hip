@@ -46,6 +46,15 @@ typedef float float4v __attribute__((ext_vector_type(4)));
 constexpr int kTileKeys = 64;
 constexpr int kStageBytes = kTileKeys * 128;                    // 64 half rows or 32 rows, swizzled, no padding
 constexpr bool rows_layout(bool rotated, bool half_split) { return rotated || half_split; }
+// Where a kernel took caches over from the sixteen-lane one, its fp32 sums are kept as short as that kernel's, which added four
+// bands and then those in a tree; a lane's 64 or 32 bands in one chain left scores further from 64-bit ones.  The moduli's products
+// (small, of one sign) have a chain of their own, and the others' end after chain_pieces() pieces of four bands.  Distance of final
+// scores from 64 bits x 1e7, sixteen-lane kernel / chains of 64 or 32 bands / now, G = 4: half-split dense 1.48 / 1.62 / 1.40,
+// scattered 1.32 / 1.73 / 1.29, post-RoPE 1.25 / 1.42 / 1.16, paged interleaved 1.50 / 2.23 / 1.45, scattered 1.30 / 2.14 / 1.27.  Steps take
+// the same time (9216 x 2176 half-split scattered keys 1392 and 1391 us, dense 1229 and 1227, 768 x 4096 to 65536 paged 2060 and 2049); chains
+// of four bands spill (1930 us), a centred phase on the direct path does as well as shorter chains there but costs 2 %.
+constexpr bool short_chains(bool paged, bool rotated, bool half_split) { return paged || rotated || half_split; }
+constexpr int chain_pieces(bool rotated, bool half_split, bool table) { return rotated || (!half_split && !table) ? 2 : 3; }
 constexpr int kTabRow = kBands + 4;                             // floats per (component, head) row: 16 bytes of skew
 
 // (lane_waves(G): LDS decides -- 33 KB of phasors + a stage and a table per wave)
@@ -89,7 +98,7 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
 {
     constexpr int NG = (G + 3) / 4, HR = lane_heads(G), W = lane_waves(G), kThreads = W * 64;
     constexpr int kTabBytes = HR * kTabRow * 4;          // one component's rows
-    constexpr bool ROWS = rows_layout(ROTATED, HALF);
+    constexpr bool ROWS = rows_layout(ROTATED, HALF), kShortChains = short_chains(PAGED, ROTATED, HALF);
     extern __shared__ __align__(16) char lds[];
     __shared__ double red[W][2 * 4 * NG];
     __shared__ double lds_rev[kBands];                    // omega_f / 2pi
@@ -290,9 +299,13 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                     mirrored = span >= kLaneRange;
                     in_table = span < 2 * kLaneRange - 1;
                     if (mirrored) base = (int)((int64_t)base + (span >> 1));
+                    // the direct path takes any base: with 0 the folded table keeps its own rounding only
+                    if (!in_table) base = 0;
                 }
-                // fold e^{-i w base} into the wave's table: lane = band
-                const float x = (float)__builtin_amdgcn_fract((double)base * lds_rev[lane]);
+                // fold e^{-i w base} into the wave's table: lane = band.  (The phase in [-1/2, 1/2] revolutions: in fp32 twice
+                // as fine as in [0, 1].)
+                const double turns = (double)base * lds_rev[lane];
+                const float x = (float)(turns - __builtin_rint(turns));
                 const float bs = __builtin_amdgcn_sinf(x), bc = __builtin_amdgcn_cosf(x);
 #pragma unroll
                 for (int g = 0; g < G; ++g) {
@@ -316,11 +329,9 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
             if constexpr (!ROWS) take_position(p_key);
 
             float4v acc[NG], acc2[NG];   // two chains, so that consecutive matrix instructions do not depend on each other
+            float4v acc_m[NG];           // kShortChains: the moduli's products, a third chain
+            float4v sum[NG];             // kShortChains: the chains ended so far
             float4v first[NG];           // rows: step 0's scores, over the lane's half of the bands
-            // rows: the first sixteen bands of a step.  The kernel that had these caches before added four bands at a time and
-            // those in a tree; chains of 32 bands left final scores further from 64-bit ones than it did (2.0e-7 against 1.4e-7 on
-            // scattered half-split keys, 1.6e-7 against 1.2e-7 post-RoPE), chains of sixteen 1.8e-7 and 1.3e-7, for 0.3 % of the time.
-            float4v middle[NG];
 
             // Everything a piece (four bands of the lane's key) needs from LDS: the key's 16 bytes, the phasors of its
             // four bands at the lane's relative position, the lane's table entries.  Pieces are fetched one ahead of
@@ -416,13 +427,16 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
 #pragma unroll
                     for (int q = 0; q < NG; ++q) {
                         const float t_[4] = {pz.bc[q].x, pz.bc[q].y, pz.bc[q].z, pz.bc[q].w};
-                        acc[q] = __builtin_amdgcn_mfma_f32_4x4x1f32(m[k], t_[k], acc[q], 0, 0, 0);
+                        float4v &to = kShortChains ? acc_m[q] : acc[q];
+                        to = __builtin_amdgcn_mfma_f32_4x4x1f32(m[k], t_[k], to, 0, 0, 0);
                     }
                 }
                 __builtin_amdgcn_s_setprio(2);
                 __builtin_amdgcn_sched_barrier(0x4 | 0x20 | 0x100);
             };
             auto score_tile = [&](auto table_tag, auto mirror_tag) {
+                constexpr int kPieces = ROWS ? 8 : 16;   // of a sum
+                constexpr int kChain = chain_pieces(ROTATED, HALF, decltype(table_tag)::value);
 #pragma unroll
                 for (int half = 0; half < 2; ++half) {
                     stage_half(kd);   // waits for the step's loads, then 8 LDS writes
@@ -432,7 +446,7 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                     }
                     if (ROWS || half == 0)
 #pragma unroll
-                        for (int q = 0; q < NG; ++q) acc[q] = acc2[q] = float4v{0.f, 0.f, 0.f, 0.f};
+                        for (int q = 0; q < NG; ++q) acc[q] = acc2[q] = acc_m[q] = float4v{0.f, 0.f, 0.f, 0.f};
                     // the next loads go out while this step's are scored
                     if (half == 0) {
                         load_half(n0, cnt, 1, kd, bt_cur);
@@ -448,18 +462,19 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                         if (pc + 1 < 8) nxt = fetch(cur, half, pc + 1, table_tag);
                         score_piece(cur, half, pc, table_tag, mirror_tag);
                         cur = nxt;
-                        if (ROWS && pc == 3) {   // (sums of sixteen bands at most: see `middle`)
+                        const int done = (ROWS ? 0 : 8 * half) + pc + 1;   // pieces of this sum scored so far
+                        if (kShortChains && (done % kChain == 0 || done == kPieces)) {
 #pragma unroll
                             for (int q = 0; q < NG; ++q) {
-                                middle[q] = acc[q] + acc2[q];
+                                const float4v chain = acc[q] + acc2[q];
+                                sum[q] = done == kChain ? chain : sum[q] + chain;
                                 acc[q] = acc2[q] = float4v{0.f, 0.f, 0.f, 0.f};
                             }
                         }
                     }
 #pragma unroll
                     for (int q = 0; q < NG; ++q) {
-                        if (ROWS || half == 1) acc[q] += acc2[q];
-                        if (ROWS) acc[q] += middle[q];
+                        if (ROWS || half == 1) acc[q] = kShortChains ? sum[q] + acc_m[q] : acc[q] + acc2[q];
                         if (ROWS && half == 0) first[q] = acc[q];
                     }
                 }
