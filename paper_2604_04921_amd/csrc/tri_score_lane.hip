@@ -24,8 +24,9 @@
 //   * Rotation of the key (Appendix B.2): k e^{i w p} = (k e^{i w r}) e^{i w base} with base a position in the middle of
 //     the tile's positions and |r| < 64.  e^{i w |r|} comes from a table in LDS (one 16-byte read per two bands; a
 //     negative r flips the sign of the sine), e^{-i w base} is folded into the wave's copy of the head-instance's table,
-//     which it rewrites for every tile (lane = band: one sine / cosine pair and 2 G complex products per lane).  A tile
-//     whose positions span 127 or more takes the direct path (phase in double, v_sin_f32 / v_cos_f32 per lane and band).
+//     which it rewrites for every tile (lane = band: one sine / cosine pair and 2 G complex products per lane) or, rows, for a
+//     step.  A tile (rows: also either step) whose positions span 127 or more takes the direct path (phase in double, v_sin_f32 /
+//     v_cos_f32 per lane and band).
 //   * Operand B is read from that copy in LDS, four bands per read.
 // The vector instructions of four bands are issued first and their twelve (24) matrix instructions in one run after
 // them: a wave that alternates between the two kinds loses about 3.5 clocks per matrix instruction.
@@ -74,9 +75,12 @@ __device__ __forceinline__ int stage_offset(int k, int p)
     return ROWS ? (k << 8) + ((p ^ (k & 15)) << 4) : ((k ^ ((k >> 3) & 1)) << 7) + ((p ^ (k & 7)) << 4);
 }
 
-// Smallest or largest of the wave's 64 values, by DPP (lane 63 ends up with the whole wave's).
+// Smallest or largest of lanes 0-31 and of lanes 32-63, by DPP.
+struct HalfExtremes {
+    int v[2];
+};
 template <bool MAX>
-__device__ __forceinline__ int wave_extreme(int v)
+__device__ __forceinline__ HalfExtremes half_extremes(int v)
 {
     auto step = [&](auto ctrl, auto rows) {
         const int t = __builtin_amdgcn_update_dpp(v, v, decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
@@ -88,8 +92,7 @@ __device__ __forceinline__ int wave_extreme(int v)
     step(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
     step(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
     step(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});   // row_bcast 15 into rows 1, 3
-    step(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});   // row_bcast 31 into rows 2, 3
-    return __builtin_amdgcn_readlane(v, 63);
+    return {{__builtin_amdgcn_readlane(v, 31), __builtin_amdgcn_readlane(v, 63)}};
 }
 
 // ROTATED: the keys are stored post-RoPE (no rotation, no positions).  PAGED: block_size >= 16.  HALF: half-split pairs.
@@ -283,27 +286,11 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
             }
 
             // ---- the tile's base
-            int base = 0;
+            int base = 0, base1 = 0;   // rows: step 1's may be one of its own
             bool in_table = true, mirrored = false;   // wave-uniform
-            if constexpr (!ROTATED) {
-                // Usual case: slots in the order of their positions, all within 64 of the first: base = the first, r >= 0.
-                // (The lowest and highest position of every tile through twelve LDS shuffles, each waiting for the one before,
-                // cost 64 x 8 head-instances of 131072 keys at G = 8 1 %.)
-                base = __builtin_amdgcn_readfirstlane(p_key);
-                // (The difference of two int32 positions fits 32 bits without a sign once none lies below the first.)
-                if (__builtin_amdgcn_ballot_w64(p_key < base || (uint32_t)p_key - (uint32_t)base >= (uint32_t)kLaneRange) != 0ull) {
-                    base = wave_extreme<false>(p_key);
-                    const int64_t span = (int64_t)wave_extreme<true>(p_key) - (int64_t)base;
-                    // positions within 64 of the lowest: base = the lowest, r >= 0.  Else base = the middle and the table
-                    // serves |r| (a negative r flips the sine), as long as the span stays below 127.
-                    mirrored = span >= kLaneRange;
-                    in_table = span < 2 * kLaneRange - 1;
-                    if (mirrored) base = (int)((int64_t)base + (span >> 1));
-                    // the direct path takes any base: with 0 the folded table keeps its own rounding only
-                    if (!in_table) base = 0;
-                }
-                // fold e^{-i w base} into the wave's table: lane = band.  (The phase in [-1/2, 1/2] revolutions: in fp32 twice
-                // as fine as in [0, 1].)
+            // fold e^{-i w base} into the wave's table: lane = band.  (The phase in [-1/2, 1/2] revolutions: in fp32 twice as
+            // fine as in [0, 1].)
+            auto fold_base = [&]() {
                 const double turns = (double)base * lds_rev[lane];
                 const float x = (float)(turns - __builtin_rint(turns));
                 const float bs = __builtin_amdgcn_sinf(x), bc = __builtin_amdgcn_cosf(x);
@@ -313,6 +300,41 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                     reinterpret_cast<float *>(tab_re)[g * kTabRow + lane] = qr * bc + qi * bs;
                     reinterpret_cast<float *>(tab_im)[g * kTabRow + lane] = qi * bc - qr * bs;
                 }
+            };
+            if constexpr (!ROTATED) {
+                // Usual case: slots in the order of their positions, all within 64 of the first: base = the first, r >= 0.
+                // (The lowest and highest position of every tile through twelve LDS shuffles, each waiting for the one before,
+                // cost 64 x 8 head-instances of 131072 keys at G = 8 1 %.)
+                base = base1 = __builtin_amdgcn_readfirstlane(p_key);
+                // (The difference of two int32 positions fits 32 bits without a sign once none lies below the first.)
+                if (__builtin_amdgcn_ballot_w64(p_key < base || (uint32_t)p_key - (uint32_t)base >= (uint32_t)kLaneRange) != 0ull) {
+                    const HalfExtremes lo = half_extremes<false>(p_key), hi = half_extremes<true>(p_key);
+                    base = min(lo.v[0], lo.v[1]);
+                    const int64_t span = (int64_t)max(hi.v[0], hi.v[1]) - (int64_t)base;
+                    // positions within 64 of the lowest: base = the lowest, r >= 0.  Else base = the middle and the table
+                    // serves |r| (a negative r flips the sine), as long as the span stays below 127.
+                    mirrored = span >= kLaneRange;
+                    in_table = span < 2 * kLaneRange - 1;
+                    if (mirrored) base = (int)((int64_t)base + (span >> 1));
+                    base1 = base;
+                    if (!in_table) {
+                        // the direct path takes any base: with 0 the folded table keeps its own rounding only
+                        base = base1 = 0;
+                        if constexpr (ROWS) {
+                            // A step's 32 keys may fit the table by themselves: a middle each, the table folded again between
+                            // the steps.  9216 x 2176 half-split keys, scores and selection, one position in 2 / 3 / 4 / 6 kept: 1370,
+                            // 1436, 1441, 1444 us with a base per tile, 1305, 1320, 1407, 1451 so (1323, 1336, 1359, 1404 on the
+                            // sixteen-lane kernel, which takes a base per sixteen keys; from one in 8 on it is the slower one).
+                            const int64_t span0 = (int64_t)hi.v[0] - lo.v[0], span1 = (int64_t)hi.v[1] - lo.v[1];
+                            if (max(span0, span1) < 2 * kLaneRange - 1) {
+                                in_table = true;
+                                base = (int)(lo.v[0] + (span0 >> 1));
+                                base1 = (int)(lo.v[1] + (span1 >> 1));
+                            }
+                        }
+                    }
+                }
+                fold_base();
             }
             // the lane's relative position: of its key, or (rows) of its key of either step
             const char *ph_lane = ph_base;
@@ -441,6 +463,10 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                 for (int half = 0; half < 2; ++half) {
                     stage_half(kd);   // waits for the step's loads, then 8 LDS writes
                     if constexpr (ROWS && !ROTATED) {
+                        if (half == 1 && base1 != base) {   // wave-uniform
+                            base = base1;
+                            fold_base();
+                        }
                         const auto p = __builtin_amdgcn_permlane32_swap((uint32_t)p_key, (uint32_t)p_key, false, false);
                         take_position((int)p[half]);
                     }

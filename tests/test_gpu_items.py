@@ -35,11 +35,11 @@ def test_half_split_items(oracle, group, lens, paged, rotated):
 
 
 @pytest.mark.parametrize("pairs", [0, 1])
-@pytest.mark.parametrize("spread", [1, 2, 40, 1 << 14, 1 << 20])
+@pytest.mark.parametrize("spread", [1, 2, 3, 4, 40, 1 << 14, 1 << 20])
 @pytest.mark.parametrize("shuffled", [False, True])
 def test_positions(oracle, pairs, spread, shuffled):
-    """A tile of 64 keys spans 63 (the table), about 126 (mirrored table or direct), 2500, 2^20 (direct) and 2^26 positions
-    (direct); shuffled, the whole sequence's range instead."""
+    """A tile of 64 keys spans 63 positions (the table), about 126 (mirrored table or direct), 189 (direct; half-split: mirrored with
+    a base per 32 keys), 252 (there either), 2500, 2^20 and 2^26 (direct); shuffled, the whole sequence's range instead."""
     cfg = recipe.scaled(recipe.CONFIGS["c2_layer"], n_layers=1, n_seqs=1, n_q_heads=8, n_kv_heads=2, seq_len=700,
                         min_seq_len=700, budget=100, n_calib=64, positions="dense", seed=5)
 
