@@ -1,5 +1,7 @@
 // Eviction as compaction (Section 4.3, "evict the rest"): slot j <- slot kept_idx[j] for K, V
 // and the key positions.  Pure byte moves, 16 bytes per lane.
+#include <algorithm>
+
 #include "tri_fill.h"
 
 namespace tri {
@@ -171,8 +173,11 @@ tri_status launch_compact_fill(const tri_model &m, const tri_cache &c, int32_t b
     a.elem_bytes = c.dtype == TRI_BF16 ? 2 : 4;
     a.row16 = kHeadDim * a.elem_bytes / 16;
     const size_t lds = (size_t)budget * 8;
-    if (lds > 48 * 1024 &&
-        hipFuncSetAttribute((const void *)fill_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+    // The most any call can have, beside the kernel's static arrays, not this call's share: the limit belongs to the process, and
+    // another thread may set it between.  (A larger move list does not fit a CU: the runtime's refusal is returned.)
+    constexpr size_t kLdsLimit = 160 * 1024 - (kFillMaxWords * sizeof(uint32_t) + 256);
+    if (lds > 48 * 1024 && hipFuncSetAttribute((const void *)fill_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               (int)std::max(lds, kLdsLimit)) != hipSuccess)
         return hip_status("hipFuncSetAttribute(fill_kernel)");
     hipLaunchKernelGGL(fill_kernel, dim3(n_inst), dim3(kFillThreads), lds, st, a);
     return hip_status("fill_kernel");

@@ -48,7 +48,8 @@ __device__ __forceinline__ void unit_phasor(double t, double rev, double *c, dou
     sincos(kTwoPi * x, s, c);
 }
 
-constexpr int kFoldSeqs = 8;      // sequences per workgroup, more (up to 32) where workgroups abound
+constexpr int kFoldSeqs = 8;      // sequences per workgroup, more where workgroups abound,
+constexpr int kFoldSeqsMost = 32; // at most this many
 constexpr int kFoldThreads = 512;
 
 // The folded tables of one (layer, KV head) and fold_seqs sequences per workgroup: grid (Hkv * seq_blocks + extra, L),
@@ -511,7 +512,7 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     fo.max_seq_len = c.max_seq_len;
     fo.S = c.n_seqs;
     fo.fold_seqs = kFoldSeqs;
-    while (fo.fold_seqs < 32 && (int64_t)m.n_layers * m.n_kv_heads * ((c.n_seqs + 2 * fo.fold_seqs - 1) / (2 * fo.fold_seqs)) >= 2 * n_cu)
+    while (fo.fold_seqs < kFoldSeqsMost && (int64_t)m.n_layers * m.n_kv_heads * ((c.n_seqs + 2 * fo.fold_seqs - 1) / (2 * fo.fold_seqs)) >= 2 * n_cu)
         fo.fold_seqs *= 2;
     fo.seq_blocks = (c.n_seqs + fo.fold_seqs - 1) / fo.fold_seqs;
     fo.Hq = m.n_q_heads;
@@ -528,8 +529,9 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     fo.phasors = reinterpret_cast<float4 *>(ws + wl.phasors);
     fo.lane_kernel = lane_kernel;
     const size_t fold_lds = (size_t)(m.n_offsets + std::min(fo.fold_seqs, c.n_seqs)) * kBands * 2 * sizeof(double);
+    constexpr int kFoldLdsLimit = (kMaxOffsets + kFoldSeqsMost) * kBands * 2 * (int)sizeof(double);   // the most any call asks for
     if (fold_lds > 48 * 1024 &&
-        hipFuncSetAttribute((const void *)fold_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fold_lds) != hipSuccess)
+        hipFuncSetAttribute((const void *)fold_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kFoldLdsLimit) != hipSuccess)
         return hip_status("hipFuncSetAttribute(fold_kernel)");
     hipLaunchKernelGGL(fold_kernel, dim3(m.n_kv_heads * fo.seq_blocks + 1 + table_entries / kFoldThreads, m.n_layers),
                        dim3(kFoldThreads), fold_lds, st, fo);

@@ -542,8 +542,9 @@ tri_status launch_held(const SelectArgs &sa, int n_inst, bool small, bool vec, h
                       : (vec ? select_kernel<SRC, true, true, kSelThreads> : select_kernel<SRC, false, true, kSelThreads>);
     size_t lds = (size_t)((sa.max_seq_len + 255) / 256 * 256) * sizeof(uint32_t);
     if (sa.fill) lds = std::max(lds, (size_t)sa.budget * 2 * sizeof(int32_t));
-    if (lds > 48 * 1024 &&
-        hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+    // (the most any call asks for, not this call's share: the limit belongs to the process, and another thread may set it between)
+    constexpr int kLdsLimit = kSelHeldKeys * (int)sizeof(uint32_t);
+    if (lds > 48 * 1024 && hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit) != hipSuccess)
         return hip_status("hipFuncSetAttribute(select_kernel)");
     hipLaunchKernelGGL(kern, dim3(n_inst), dim3(small ? kSelSmallThreads : kSelThreads), lds, st, sa, (int64_t)0);
     return hip_status("select_kernel");

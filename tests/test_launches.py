@@ -1,0 +1,27 @@
+"""Launches as the library would make them, seen through a fake HIP runtime (no GPU needed)."""
+import pytest
+
+import launch_probe
+
+
+def test_lds_limits_do_not_depend_on_the_call():
+    """The limit on a kernel's dynamic LDS is an attribute of the process: were it each call's own size, a second thread with a
+    smaller call could lower it between another's setting and launch."""
+    calls = [dict(entry="select", n=n) for n in (1000, 13000, 20000, 32768, 40000)]
+    for n in (1000, 4096, 13000, 32768, 40000):
+        for offsets in (1, 16, 40, 64):
+            calls.append(dict(entry="step", n=n, offsets=offsets, seqs=1 + n % 40, group=4, kv_heads=2, fill=n == 4096, budget=900))
+    calls += [dict(entry="step", n=20000, fill=1, budget=b) for b in (1000, 6500, 9000, 16384)]
+    calls += [dict(entry="score", group=g, dtype=0, n=600) for g in (1, 8)]
+    limits = {}
+    for status, launches, set_ in launch_probe.run(calls):
+        assert status == 0 and launches
+        for name, value in set_:
+            limits.setdefault(name, set()).add(value)
+        for name, _, _, lds in launches:
+            if lds > 48 * 1024:
+                assert max(v for k, v in set_ if k == name) >= lds, name
+    assert len(limits) > 4
+    for name, values in limits.items():
+        assert len(values) == 1, "%s: %s" % (name, sorted(values))
+        assert max(values) <= 160 * 1024
