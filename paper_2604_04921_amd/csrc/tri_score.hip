@@ -356,7 +356,9 @@ __global__ __launch_bounds__(256) void final_kernel(FinalArgs a)
     const int N = clamp_len(a.seq_len[s], a.max_seq_len);
     const int n = (kb * 256 + threadIdx.x) * 4;
     if (n >= N) return;
-    const bool vec = (a.max_seq_len & 3) == 0;   // (four entries from a slot below N on exist)
+    // 16-byte accesses: rows of a multiple of four entries (four from a slot below N on exist) from an aligned start (both arrays may
+    // be the caller's, who owes floats' alignment only)
+    const bool vec = (a.max_seq_len & 3) == 0 && (((uintptr_t)a.raw | (uintptr_t)a.final_) & 15) == 0;
     const float *rw = a.raw + (int64_t)inst * G * a.max_seq_len;
     float v[G][4];
 #pragma unroll
