@@ -1,5 +1,7 @@
 // Offline calibration (Section 4.1; Appendix B.5): per (layer, query head, band) the complex mean
 // of the pre-RoPE query samples and the mean of their moduli.
+#include <algorithm>
+
 #include "tri_internal.h"
 
 namespace tri {
@@ -11,7 +13,8 @@ struct CentersArgs {
     float *out;     // [L][Hq][F][3], or NULL: leave the sums in `sums`
     double *sums;   // [L][Hq][F][3] running sums (streaming calibration), or NULL
     int64_t T;
-    int32_t L, Hq;
+    int64_t heads;      // L * Hq
+    int64_t first_head; // of this launch
     int32_t first;  // sums: 1 = overwrite, 0 = add to what is there
 };
 
@@ -75,13 +78,13 @@ __global__ __launch_bounds__(kCenterThreads) void centers_kernel(CentersArgs a)
     __shared__ double part[kCenterWaves][8 * O][3];
     const int q = threadIdx.x % O, r = threadIdx.x / O, wave = threadIdx.x >> 6;
     constexpr int kParts = 8 / O;
-    const int64_t lh = (int64_t)(blockIdx.x / (8 * kParts)) * 8 + blockIdx.x % 8;   // layer * Hq + head
+    const int64_t lh = a.first_head + (int64_t)(blockIdx.x / (8 * kParts)) * 8 + blockIdx.x % 8;   // layer * Hq + head
     const int q0 = (int)(blockIdx.x / 8) % kParts * O;
-    if (lh >= (int64_t)a.L * a.Hq) return;
+    if (lh >= a.heads) return;
     double sre[8], sim[8], sab[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) sre[k] = sim[k] = sab[k] = 0.0;
-    auto row = [&](int64_t t) { return (t * a.L * a.Hq + lh) * kHeadDim; };
+    auto row = [&](int64_t t) { return (t * a.heads + lh) * kHeadDim; };
     Octet<BF16, HALF> cur, nxt;
     if (r < a.T) cur.template load<O == 8>(a.q, row(r), q0 + q);
     for (int64_t t = r; t < a.T; t += kResidues) {
@@ -134,18 +137,24 @@ __global__ __launch_bounds__(kCenterThreads) void centers_kernel(CentersArgs a)
 }
 
 template <bool BF16, bool HALF>
-tri_status launch_centers_t(const CentersArgs &a, int n_cu, hipStream_t st)
+tri_status launch_centers_t(CentersArgs a, int n_cu, hipStream_t st)
 {
     // A workgroup per (layer, head) where that gives every CU two; else the bands are split over two, four or eight, which
     // read the same cache lines.  4096 tokens: 32 heads 89 -> 16 us with eight, 128 heads 91 -> 36 with four, 256 heads 102 ->
     // 65 with two; four per CU instead of two would take 128 heads to 46, 384 heads from 100 to 138.
-    const int64_t heads = (int64_t)a.L * a.Hq;
     int parts = 1;
-    while (parts < 8 && heads * parts < 2 * (int64_t)n_cu) parts *= 2;
+    while (parts < 8 && a.heads * parts < 2 * (int64_t)n_cu) parts *= 2;
     auto kern = parts == 1 ? centers_kernel<BF16, HALF, 8> : parts == 2 ? centers_kernel<BF16, HALF, 4>
                 : parts == 4 ? centers_kernel<BF16, HALF, 2> : centers_kernel<BF16, HALF, 1>;
-    hipLaunchKernelGGL(kern, dim3((uint32_t)((heads + 7) / 8 * 8 * parts)), dim3(kCenterThreads), 0, st, a);
-    return hip_status("centers_kernel");
+    // (a launch takes fewer than 2^32 threads along x: more heads than that, in turn)
+    constexpr int64_t kMostHeads = (int64_t)1 << 23;
+    for (a.first_head = 0; a.first_head < a.heads; a.first_head += kMostHeads) {
+        const int64_t heads = std::min(a.heads - a.first_head, kMostHeads);
+        hipLaunchKernelGGL(kern, dim3((uint32_t)((heads + 7) / 8 * 8 * parts)), dim3(kCenterThreads), 0, st, a);
+        const tri_status rc = hip_status("centers_kernel");
+        if (rc != TRI_OK) return rc;
+    }
+    return TRI_OK;
 }
 
 // sums / total tokens -> the statistics table
@@ -195,7 +204,7 @@ tri_status launch_centers(const tri_model &m, const void *q, int32_t q_dtype, in
     int n_cu = 0;
     const tri_status rc = device_cus(&n_cu);
     if (rc != TRI_OK) return rc;
-    const CentersArgs a{q, out, sums, n_tokens, m.n_layers, m.n_q_heads, first};
+    const CentersArgs a{q, out, sums, n_tokens, (int64_t)m.n_layers * m.n_q_heads, 0, first};
     const bool half = m.pairs == TRI_PAIR_HALF;
     if (q_dtype == TRI_BF16) return half ? launch_centers_t<true, true>(a, n_cu, st) : launch_centers_t<true, false>(a, n_cu, st);
     return half ? launch_centers_t<false, true>(a, n_cu, st) : launch_centers_t<false, false>(a, n_cu, st);

@@ -25,3 +25,15 @@ def test_lds_limits_do_not_depend_on_the_call():
     for name, values in limits.items():
         assert len(values) == 1, "%s: %s" % (name, sorted(values))
         assert max(values) <= 160 * 1024
+
+
+@pytest.mark.parametrize("layers,heads", [(1, 1), (36, 32), (1, 1 << 23), (65536, 256), (40000, 1024)])
+def test_calibration_launches_fit_the_grid(layers, heads):
+    """Every (layer, head) has its workgroups, and no launch 2^32 threads along x (the runtime refuses those)."""
+    [(status, launches, _)] = launch_probe.run([dict(entry="centers", layers=layers, kv_heads=heads, group=1, tokens=3)])
+    assert status == 0
+    covered = 0
+    for name, (x, y, z), threads, _ in launches:
+        assert "centers_kernel" in name and x * threads < 2 ** 32 and y == z == 1
+        covered += x
+    assert covered >= layers * heads
