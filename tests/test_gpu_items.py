@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("group,lens,paged,rotated", [
     (4, [1537, 1536, 513, 512, 1], False, False),
-    (8, [1153, 577, 576], False, False),        # twelve waves per workgroup
+    (8, [1153, 1025, 1024, 513, 512], False, False),   # eight waves per workgroup
     (3, [2100, 128, 129], True, False),
     (5, [700, 1664], True, True),
     (4, [3000, 1024], False, True),
@@ -23,6 +23,8 @@ def test_half_split_items(oracle, group, lens, paged, rotated):
     cfg = recipe.scaled(recipe.CONFIGS["c4_paged" if paged else "c2_layer"], n_layers=1, n_seqs=len(lens), n_q_heads=2 * group,
                         n_kv_heads=2, seq_len=max(lens), min_seq_len=min(lens), budget=300, n_calib=64, positions="dense",
                         block_size=16 if paged else 0, seed=77 + group)
+
+    assert H.item_keys(2 * len(lens), max(lens)) == 512
 
     def mutate(w):
         for name in ("k", "q_samples"):

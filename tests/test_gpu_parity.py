@@ -114,7 +114,7 @@ def test_group_of_eight(oracle):
 
 def test_wild_positions(oracle):
     """Positions that defeat the relative-position table: unsorted, gaps of up to 2^28, one sequence
-    with long runs of equal positions.  Exercises the direct path and the base moves of the MFMA kernel."""
+    with long runs of equal positions.  Exercises the direct path of the score kernel and the tables' bases."""
     cfg = recipe.scaled(recipe.CONFIGS["c2_layer"], n_layers=1, n_seqs=3, n_q_heads=8, n_kv_heads=2, seq_len=700,
                         budget=100, n_calib=128)
 
@@ -224,8 +224,8 @@ def test_sequence_lengths_outside_the_host_bound_are_clamped():
 def test_fused_step_agrees_with_the_three_calls(seq_len, min_len, budget, ties):
     """tri_compress_step forms the final scores inside the selection; tri_score writes them out for tri_select_topk.
     Both go through the same z-score arithmetic, so the kept sets are identical, not merely within the tie band.
-    Beyond 32768 keys the fused selection keeps its integer keys in LDS (sequences up to 32768 keys) or in the
-    workspace (longer ones); the ragged lengths here exercise both.  ties: stretches of the cache hold copies of one
+    Where sequences may be longer than 32768 keys the fused selection leaves its integer keys in memory, in the raw scores' place
+    (else they lie in LDS); the ragged lengths here exercise both.  ties: stretches of the cache hold copies of one
     key at one position, i.e. hundreds of equal final scores, some of them around the budget's threshold."""
     cfg = recipe.scaled(recipe.CONFIGS["c2_layer"], n_layers=1 if seq_len > 5000 else 2, n_seqs=3, n_q_heads=8,
                         n_kv_heads=2, seq_len=seq_len, min_seq_len=min_len, budget=budget, n_calib=128)
@@ -324,7 +324,7 @@ def test_offset_sets(oracle, kind):
 
 
 def test_many_short_sequences(oracle):
-    """More sequences than the work-list builder has threads (each thread then lists several sequences), lengths from
+    """More sequences than the work-list builder has lanes (each then lists several sequences), lengths from
     0 to a few groups: the score kernel's items are one per existing (sequence, chunk) pair, empty sequences have none."""
     cfg = recipe.scaled(recipe.CONFIGS["c2_layer"], n_layers=1, n_seqs=300, n_q_heads=8, n_kv_heads=2, seq_len=70,
                         min_seq_len=0, budget=20, n_calib=128)
@@ -334,27 +334,48 @@ def test_many_short_sequences(oracle):
 
 
 def test_chunk_boundaries(oracle):
-    """Sequence lengths around the work items of the score kernel.  A batch this small is cut into items of one round
-    of the kernel's waves (768 keys): one key short of an item, exactly one, one more; and lengths around 8192 keys and
-    two of them plus a ragged tail."""
+    """Sequence lengths around the smallest work items (512 keys: a batch this small is cut as finely as it goes) and around
+    multiples of them: one key short of an item, exactly one, one more, sixteen of them, and a ragged tail."""
     cfg = recipe.scaled(recipe.CONFIGS["c2_layer"], n_layers=1, n_seqs=7, n_q_heads=8, n_kv_heads=1, seq_len=16901,
                         min_seq_len=16901, budget=500, n_calib=128)
+    k = H.item_keys(7, cfg.seq_len)
+    assert k == 512
+
     def lens(w):
-        w["seq_len"][:] = np.array([767, 768, 769, 8191, 8192, 8193, 16901], dtype=np.int32)
+        w["seq_len"][:] = np.array([k - 1, k, k + 1, 16 * k - 1, 16 * k, 16 * k + 1, 16901], dtype=np.int32)
     run_and_check(oracle, cfg, mutate=lens)
 
 
 def test_work_items_of_two_rounds(oracle):
-    """A batch large enough for work items of two rounds (1536 keys) and small enough not to reach the full 8192:
-    2 layers x 16 sequences x 8 KV heads of up to 6200 keys, lengths around the item size; a dozen head-instances go
-    through the oracle, all of them through the compaction check's index rules."""
+    """Work items of whole sequences (as many head-instances as CUs): 2 layers x 16 sequences x 8 KV heads of up to 6200 keys,
+    lengths around two, four and six rounds of a workgroup's twelve waves (768 keys each); a dozen head-instances go through
+    the oracle, all of them through the compaction check's index rules."""
     cfg = recipe.scaled(recipe.CONFIGS["c2_layer"], n_layers=2, n_seqs=16, n_q_heads=32, n_kv_heads=8, seq_len=6200,
                         min_seq_len=6200, budget=300, n_calib=128)
+    assert H.item_keys(256, cfg.seq_len) >= cfg.seq_len
+
     def lens(w):
         w["seq_len"][:] = np.array([1535, 1536, 1537, 3071, 3072, 3073, 4608, 6200, 6144, 100, 0, 1600, 5000, 2999, 64, 6199],
                                    dtype=np.int32)
     picks = [(l, s, (3 * s + l) % 8) for l in range(2) for s in (0, 1, 2, 5, 7, 8)]
     run_and_check(oracle, cfg, mutate=lens, instances=picks)
+
+
+@pytest.mark.parametrize("group,rotated", [(4, False), (4, True), (8, False)])
+def test_work_items_between_the_extremes(oracle, group, rotated):
+    """A batch large enough for work items above 512 keys and small enough not to reach 8192 or whole sequences (10 x 8
+    head-instances of up to 6200 keys: three items of 2112 on 256 CUs), lengths on either side of one and two items."""
+    cfg = recipe.scaled(recipe.CONFIGS["c2_layer"], n_layers=1, n_seqs=10, n_q_heads=8 * group, n_kv_heads=8, seq_len=6200,
+                        min_seq_len=6200, budget=300, n_calib=64)
+    k = H.item_keys(80, cfg.seq_len)
+    assert 512 < k < 8192 and 2 * k + 1 < cfg.seq_len
+
+    def mutate(w):
+        w["seq_len"][:] = np.array([k - 1, k, k + 1, 2 * k - 1, 2 * k, 2 * k + 1, 6200, 64, 0, k + 500], dtype=np.int32)
+        if rotated:
+            w["k"] = H.to_post_rope(w["k"], w["pos"], cfg.rope_theta, 0, cfg.dtype)
+    picks = [(0, s, (3 * s) % 8) for s in range(10)]
+    run_and_check(oracle, cfg, mutate=mutate, instances=picks, rotated=rotated)
 
 
 def test_all_sequences_empty():
@@ -378,12 +399,13 @@ def test_all_sequences_empty():
 def test_repeated_calls_give_the_same_bits():
     """Work items reach the workgroups through a shared counter, in an order that differs from launch to launch; the
     raw and final scores, the moments behind them and the kept sets must not depend on it.  4 x 16 x 8 head-instances
-    of ragged lengths up to 20000 keys generated on the device (work items of 8192 keys and shorter last ones, about six
-    per workgroup the GPU holds), five calls of tri_score and of the fused step compared bit for bit."""
+    of ragged lengths up to 20000 keys generated on the device (up to three work items per sequence, about four per workgroup
+    the GPU holds), five calls of tri_score and of the fused step compared bit for bit."""
     from paper_2604_04921_amd import binding as B
     from workload import device
     cfg = recipe.scaled(recipe.CONFIGS["c2_layer"], n_layers=4, n_seqs=16, n_q_heads=32, n_kv_heads=8, seq_len=20000,
                         min_seq_len=3000, budget=1024, n_calib=128)
+    assert -(-cfg.seq_len // H.item_keys(cfg.n_layers * cfg.n_seqs * cfg.n_kv_heads, cfg.seq_len)) >= 3
     w = device.generate(cfg, positions="sparse", layers=cfg.n_layers)
     L, S, Hq, Hkv, d, Bk = cfg.n_layers, cfg.n_seqs, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, cfg.budget
     model = B.Model(L, Hq, Hkv, d, cfg.rope_theta, cfg.offsets)

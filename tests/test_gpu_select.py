@@ -1,5 +1,5 @@
 """tri_select_topk on crafted score arrays against the oracle's full stable sort: heavy ties, all-equal scores,
-signed zeros, outliers far outside the z-score range, every kernel variant (<= 8192, <= 32768, longer), ragged
+signed zeros, outliers far outside the z-score range, every kernel variant (keys in LDS up to 32768, in memory beyond), ragged
 lengths including N <= B and N = 0.  Index sets must match bit for bit (integer work on identical inputs)."""
 import zlib
 

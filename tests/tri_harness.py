@@ -5,9 +5,16 @@ import torch
 
 from workload import recipe
 
+import tri_rules
+
 RAW_RTOL = 1e-3      # raw score: |gpu - ref| <= RAW_RTOL * max(|ref|, rms(ref))
 FINAL_RTOL = 1e-3    # final score (unit scale by construction): <= FINAL_RTOL * max(|ref|, 1)
 GAP_RTOL = 1e-3      # index sets must be identical when the B-th and (B+1)-th oracle scores differ by more
+
+
+def item_keys(instances, n):
+    """Keys per work item of the score kernels on this GPU, for a batch of bf16 caches of at most n keys."""
+    return tri_rules.item_keys(instances, n, torch.cuda.get_device_properties(0).multi_processor_count)
 
 
 def to_torch(a, dtype, device="cuda"):
