@@ -463,10 +463,11 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                 for (int half = 0; half < 2; ++half) {
                     stage_half(kd);   // waits for the step's loads, then 8 LDS writes
                     if constexpr (ROWS && !ROTATED) {
-                        if (half == 1 && base1 != base) {   // wave-uniform
-                            base = base1;
-                            fold_base();
-                        }
+                        if constexpr (decltype(mirror_tag)::value)   // (nowhere else do the steps' bases differ)
+                            if (half == 1 && base1 != base) {        // wave-uniform
+                                base = base1;
+                                fold_base();
+                            }
                         const auto p = __builtin_amdgcn_permlane32_swap((uint32_t)p_key, (uint32_t)p_key, false, false);
                         take_position((int)p[half]);
                     }
