@@ -24,10 +24,11 @@ inline bool large_batch(int64_t instances, int max_seq_len, int n_cu)
 // Resident workgroups take items until none is left, so a batch takes about (items per workgroup, rounded up) x (an item's keys
 // + the item's own cost in keys: its tables, its first loads, its waves' last ones).  Every head-instance is cut into the
 // number of equal pieces that makes this least, in whole tiles of 64; large batches stay with kFastChunk.  Measured, whole steps
-// (before: about four items per CU in rounds of the workgroup's waves; kFastChunk for half-split pairs): one layer of eight x 32768 keys 66.5 -> 57.8 us, four layers 126 -> 109, 36 layers
-// 693 -> 674; one layer of eight x 12289, half-split, 150 -> 44.5, sixteen layers 207 -> 169; score + selection of 288 x 2176
-// keys 91.0 -> 89.4, 576 155 -> 134.  An item cost of 128 keys is worse on many short sequences (1152 x 2176: 243 against
-// 219 us), 384 and 1600 on some in between (576 x 2176: 143 and 134; 160 x 32768: 387 and 397 against 387), 768 nowhere.
+// (before: about four items per CU in rounds of the workgroup's waves; kFastChunk for half-split pairs): one layer of eight x
+// 32768 keys 66.5 -> 57.8 us, four layers 126 -> 109, 36 layers 693 -> 674; one layer of eight x 12289, half-split, 150 -> 44.5,
+// sixteen layers 207 -> 169; score + selection of 288 x 2176 keys 91.0 -> 89.4, 576 155 -> 134.  An item cost of 128 keys is worse
+// on many short sequences (1152 x 2176: 243 against 219 us), 384 and 1600 on some in between (576 x 2176: 143 and 134; 160 x
+// 32768: 387 and 397 against 387), 768 nowhere.
 inline int item_keys(int64_t instances, int max_seq_len, int n_cu)
 {
     constexpr int unit = 64;                            // a tile

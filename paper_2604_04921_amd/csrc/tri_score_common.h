@@ -15,7 +15,7 @@ struct ScoreArgs {
     int32_t n_tiles;         // tiles per head-instance in `partials`
     int32_t n_layers;
     int32_t first_mult;      // MFMA kernel only: workgroup b starts on item (b * first_mult) mod grid size
-    int32_t *work;           // MFMA kernel only: item counter and work list (kFastWorkInts(S, Nmax) ints)
+    int32_t *work;           // MFMA kernel only: item counter and work list (fast_work_ints(S, Nmax) ints)
     int32_t chunk_keys;      // MFMA kernels only: keys per work item (= keys per entry of `partials`)
 };
 

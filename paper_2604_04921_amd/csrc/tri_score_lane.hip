@@ -14,7 +14,9 @@
 // Half-split pairs need the second; post-RoPE keys, which have the registers for it, gain 1 - 2 % from its whole-row loads (24 x 5 x 8
 // ragged head-instances up to 20011 keys, scores only: 848 -> 834 us; 36 x 2 x 8 x 32768, a step: 1261 -> 1245).  Pre-RoPE interleaved
 // keys keep the first: equal or 0.7 % slower in position order, but the second's extra registers spill and cost 1 % at sparse or
-// scattered positions (1362 -> 1377), 1.6 % at G = 8 (5247 -> 5330), 4 % on one sequence at steady state.
+// scattered positions (1362 -> 1377), 1.6 % at G = 8 (5247 -> 5330), 4 % on one sequence at steady state.  Half-split pre-RoPE kernels
+// have no choice and do spill: 10 - 26 of their 168 registers at G <= 4 (19 contiguous, 22 paged at G = 4), 2 - 4 of 256 above;
+// paged interleaved ones 6 - 9 and 4 - 6; all others none.
 //
 // What it takes to get there:
 //   * K rows reach their lanes through LDS: the wave loads half rows (128 bytes per key, whole cache lines) or rows with coalesced
@@ -48,12 +50,13 @@ constexpr int kTileKeys = 64;
 constexpr int kStageBytes = kTileKeys * 128;                    // 64 half rows or 32 rows, swizzled, no padding
 constexpr bool rows_layout(bool rotated, bool half_split) { return rotated || half_split; }
 // Where a kernel took caches over from the sixteen-lane one, its fp32 sums are kept as short as that kernel's, which added four
-// bands and then those in a tree; a lane's 64 or 32 bands in one chain left scores further from 64-bit ones.  The moduli's products
+// bands and then those in a tree; sums of 16 (rows) or 64 bands in a chain left scores further from 64-bit ones.  The moduli's products
 // (small, of one sign) have a chain of their own, and the others' end after chain_pieces() pieces of four bands.  Distance of final
-// scores from 64 bits x 1e7, sixteen-lane kernel / chains of 64 or 32 bands / now, G = 4: half-split dense 1.48 / 1.62 / 1.40,
-// scattered 1.32 / 1.73 / 1.29, post-RoPE 1.25 / 1.42 / 1.16, paged interleaved 1.50 / 2.23 / 1.45, scattered 1.30 / 2.14 / 1.27.  Steps take
-// the same time (9216 x 2176 half-split scattered keys 1392 and 1391 us, dense 1229 and 1227, 768 x 4096 to 65536 paged 2060 and 2049); chains
-// of four bands spill (1930 us), a centred phase on the direct path does as well as shorter chains there but costs 2 %.
+// scores from 64 bits x 1e7, sixteen-lane kernel / those chains / now, G = 4: half-split dense 1.48 / 1.62 / 1.40,
+// scattered 1.32 / 1.73 / 1.29, post-RoPE 1.25 / 1.42 / 1.16, paged interleaved 1.50 / 2.23 / 1.45, scattered 1.30 / 2.14 / 1.27.  Steps
+// take the same time (9216 x 2176 half-split scattered keys 1373 us with the longer chains and 1374, dense 1214 and 1212, 768 x 4096 to
+// 65536 paged 2067 and 2050); chains of four bands spill (dense 1931), a centred phase on the direct path does as well as shorter chains
+// there but costs 2 %.
 constexpr bool short_chains(bool paged, bool rotated, bool half_split) { return paged || rotated || half_split; }
 constexpr int chain_pieces(bool rotated, bool half_split, bool table) { return rotated || (!half_split && !table) ? 2 : 3; }
 constexpr int kTabRow = kBands + 4;                             // floats per (component, head) row: 16 bytes of skew

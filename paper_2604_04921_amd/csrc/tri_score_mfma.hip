@@ -1,7 +1,7 @@
 // Score kernel for bf16 keys with a key spread over sixteen lanes: fp32 MFMA for the contraction over
-// (band, component) x query head, a phasor table in LDS for the rotation of the key.  The launcher in tri_score.hip sends it
-// large paged batches of pre-RoPE keys with interleaved pairs, where sequences are short or a KV head serves more than four
-// query heads; the kernel of tri_score_lane.hip takes the rest.
+// (band, component) x query head, a phasor table in LDS for the rotation of the key.  It takes paged batches of pre-RoPE keys
+// with interleaved pairs in work items of 8192 keys, where a KV head serves more than four query heads or a large batch holds
+// short sequences (sixteen_lane_kernel(), tri_items.h); the kernel of tri_score_lane.hip takes the rest.
 //
 // Lane layout (wave64): lane = 4*b + i.  In one step a wave scores 4 keys; lane (b, i) loads the
 // 16 bytes holding bands 4b..4b+3 of key i -- exactly the operand layout of
