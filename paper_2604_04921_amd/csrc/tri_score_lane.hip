@@ -15,8 +15,8 @@
 // ragged head-instances up to 20011 keys, scores only: 848 -> 834 us; 36 x 2 x 8 x 32768, a step: 1261 -> 1245).  Pre-RoPE interleaved
 // keys keep the first: equal or 0.7 % slower in position order, but the second's extra registers spill and cost 1 % at sparse or
 // scattered positions (1362 -> 1377), 1.6 % at G = 8 (5247 -> 5330), 4 % on one sequence at steady state.  Half-split pre-RoPE kernels
-// have no choice and do spill: 10 - 26 of their 168 registers at G <= 4 (19 contiguous, 22 paged at G = 4), 2 - 4 of 256 above;
-// paged interleaved ones 6 - 9 and 4 - 6; all others none.
+// have no choice and do spill at G <= 4: 17 - 22 of their 168 registers contiguous, 4 - 6 paged (up to 2 of 256 above); paged
+// interleaved ones 2; all others none.
 //
 // What it takes to get there:
 //   * K rows reach their lanes through LDS: the wave loads half rows (128 bytes per key, whole cache lines) or rows with coalesced
@@ -122,17 +122,28 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
     char *const stage = my_base;                                                // this wave's rows
     char *const tab_re = my_base + kStageBytes, *const tab_im = tab_re + kTabBytes;
 
-    if constexpr (!ROTATED)
-        for (int k = tid; k < kLanePhasorBytes / 16; k += kThreads)
-            reinterpret_cast<uint4 *>(ph_base)[k] = a.phasors[k];
-    if (tid < kBands) lds_rev[tid] = a.band_rev[tid];
+    // the phasor table: all of a thread's entries asked for at once, stored further down
+    constexpr int kPhasors = ROTATED ? 0 : (kLanePhasorBytes / 16 + kThreads - 1) / kThreads;
+    uint4v ph[kPhasors + 1];
+#pragma unroll
+    for (int k = 0; k < kPhasors; ++k) ph[k] = reinterpret_cast<const uint4v *>(a.phasors)[min(tid + k * kThreads, kLanePhasorBytes / 16 - 1)];
+    const double rev = a.band_rev[tid % kBands];
     // rows of heads that do not exist (G not a multiple of four) stay zero for the whole launch
     for (int k = lane; k < 2 * HR * kTabRow; k += 64) reinterpret_cast<float *>(tab_re)[k] = 0.f;
     for (int k = tid; k < HR * kTabRow; k += kThreads) reinterpret_cast<float *>(cn_base)[k] = 0.f;
 
-    const int per_lh = __builtin_amdgcn_readfirstlane(a.work[1]);
+    // (constant for the whole launch, unlike the counter in front of it: scalar loads)
+    typedef const __attribute__((address_space(4))) int32_t *ConstInts;
+    const ConstInts work_list = (ConstInts)a.work, seq_len = (ConstInts)c.seq_len;
+    const int per_lh = work_list[1];
     const int n_items = per_lh * a.n_layers * c.n_kv_heads;
-    int next_item = (int)(((uint32_t)blockIdx.x * (uint32_t)a.first_mult) % gridDim.x);
+    // A workgroup's first two items are its own: a permutation of its index, and the same behind the grid's first ones; the others come
+    // from the counter.
+    const int first_item = (int)(((uint32_t)blockIdx.x * (uint32_t)a.first_mult) % gridDim.x);
+    int later_item = 0;   // (thread 0's) the counter's answer for the item after the next
+    // (zero, which the compiler does not know to be uniform: it would wait for the counter's answer at once to hand it to all lanes)
+    int own_zero = 0;
+    asm volatile("" : "+v"(own_zero));
 
     const uint32_t slot_bytes = (uint32_t)c.stride_slot * 2u;
     // loads: instruction t of a step brings its keys 8t .. 8t+7, eight lanes (128 contiguous bytes) per key, or 4t .. 4t+3, sixteen
@@ -149,144 +160,183 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
     // byte offset of the lane's head row, from its first band on, inside a quad of table rows
     const int tab_lane = (j * kTabRow + 32 * hh) * 4;
 
-    for (;;) {
-        if (tid == 0) lds_item = next_item;
-        __syncthreads();
-        const int item = __builtin_amdgcn_readfirstlane(lds_item);
-        if (item >= n_items) break;
-        if (tid == 0) next_item = (int)gridDim.x + atomicAdd(&a.work[0], 1);
-        const int lh = item / per_lh, wi = item - lh * per_lh;
+    // A work item: a chunk of a head-instance's slots.  Everything here is wave-uniform.
+    struct Item {
+        const char *krow;
+        const int32_t *prow, *bt;
+        int64_t inst;
+        int chunk, c0, c_len, n_tiles, rot;   // n_tiles 0: none
+        __device__ int tile_at(int t) const { const int u = t + rot; return u >= n_tiles ? u - n_tiles : u; }
+    };
+    auto item_of = [&](int id) {
+        Item it{};
+        if (id >= n_items) return it;
+        const int lh = id / per_lh, wi = id - lh * per_lh;
         const int l = lh / c.n_kv_heads, h = lh - l * c.n_kv_heads;
-        const int s = __builtin_amdgcn_readfirstlane(a.work[kWorkHeader + 2 * wi]);
-        const int chunk = __builtin_amdgcn_readfirstlane(a.work[kWorkHeader + 2 * wi + 1]);
-        const int N = clamp_len(c.seq_len[s], c.max_seq_len);
-        const int64_t inst = ((int64_t)l * c.n_seqs + s) * c.n_kv_heads + h;
-        const float *tbl = a.table + inst * (kBands * 3 * G);   // [F][3][G]
-
-        const int c0 = chunk * a.chunk_keys, c_len = min(N - c0, a.chunk_keys);
-        const int n_tiles = (c_len + kTileKeys - 1) / kTileKeys;
-        const int Hq = c.n_kv_heads * G;
-        float *rw = a.raw + (((int64_t)l * c.n_seqs + s) * Hq + (int64_t)h * G) * c.max_seq_len;
-        const bool vec_store = (c.max_seq_len & 3) == 0 && ((uintptr_t)a.raw & 15) == 0;
-
-        const char *krow = (const char *)c.k + ((int64_t)l * c.stride_layer + (int64_t)h * c.stride_head) * 2 +
-                           (PAGED ? 0 : (int64_t)s * c.stride_sb * 2);
-        const int32_t *prow = c.pos + (int64_t)l * c.pos_stride_layer + (int64_t)h * c.pos_stride_head +
-                              (PAGED ? 0 : (int64_t)s * c.pos_stride_sb);
-        const int32_t *bt = PAGED ? c.block_table + (int64_t)s * c.max_blocks : nullptr;
-
-        // what step `half` takes of the tile at slot n0 (cnt keys exist): eight 16-byte loads per lane.  For a whole tile every
-        // address is a wave-uniform pointer (sixteen keys never straddle a block) plus the lane's constant
-        // offset; in the last, partial tile a key past the end repeats the last one.
-        // Paged caches: lane j of `btv` holds the physical block of keys n0 + 16 j .. + 15 (load_blocks; a block holds
-        // 16 slots or more), asked for a tile ahead like the positions, so that no load here waits for a block-table
-        // entry.
-        auto load_half = [&](int n0, int cnt, int half, uint4(&kd)[8], int btv) {
-            const int first_key = ROWS ? 32 * half : 0, byte = ROWS ? 0 : 128 * half;
-            if (cnt == kTileKeys) {
-                constexpr int kPer16 = 16 / kLoadKeys;   // instructions per sixteen keys
-#pragma unroll
-                for (int t = 0; t < 8; t += kPer16) {
-                    const int k0 = first_key + kLoadKeys * t, n = n0 + k0;
-                    const char *p;
-                    if constexpr (PAGED) {
-                        const int blk = __builtin_amdgcn_readlane(btv, k0 / 16);
-                        p = krow + (int64_t)blk * c.stride_sb * 2 + (int64_t)(n & bmask) * slot_bytes;
-                    } else {
-                        p = krow + (int64_t)n * slot_bytes;
-                    }
-#pragma unroll
-                    for (int i = 0; i < kPer16; ++i) {
-                        asm volatile("" : "+v"(ld_off));   // keeps (scalar base + 32-bit lane offset) addressing
-                        kd[t + i] = load_stream16(p + (int64_t)(kLoadKeys * i) * slot_bytes + byte + ld_off);
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const int n = n0 + min(first_key + kLoadKeys * t + ld_key, cnt - 1);
-                    const char *p;
-                    if constexpr (PAGED) {
-                        const int blk = bt[n >> c.block_shift];
-                        p = krow + (int64_t)blk * c.stride_sb * 2 + (int64_t)(n & bmask) * slot_bytes;
-                    } else {
-                        p = krow + (int64_t)n * slot_bytes;
-                    }
-                    kd[t] = load_stream16(p + byte + ld_piece * 16);
-                }
-            }
-        };
-        auto load_blocks = [&](int n0, int cnt) -> int {
-            if constexpr (!PAGED) return 0;
-            return bt[(n0 + min(16 * (lane & 3), cnt - 1)) >> c.block_shift];
-        };
-        auto load_pos = [&](int n0, int cnt) -> int {
-            if constexpr (ROTATED) return 0;
-            const int n = n0 + min(lane, cnt - 1);
-            if constexpr (PAGED) {
-                const int blk = bt[n >> c.block_shift];
-                return prow[(int64_t)blk * c.pos_stride_sb + (n & bmask)];
-            } else {
-                return prow[n];
-            }
-        };
-        auto stage_half = [&](const uint4(&kd)[8]) {
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const int at = ROWS ? st_wr0 ^ (64 * (t & 3)) : (t & 1) ? st_wr1 : st_wr0;
-                *reinterpret_cast<uint4 *>(stage + at + 1024 * t) = kd[t];
-            }
-        };
-
-        double s1[NG], s2[NG];
-#pragma unroll
-        for (int q = 0; q < NG; ++q) s1[q] = s2[q] = 0.0;
-
-        int t_idx = wave;
+        const int s = work_list[kWorkHeader + 2 * wi];
+        it.chunk = work_list[kWorkHeader + 2 * wi + 1];
+        it.inst = ((int64_t)l * c.n_seqs + s) * c.n_kv_heads + h;
+        it.krow = (const char *)c.k + ((int64_t)l * c.stride_layer + (int64_t)h * c.stride_head) * 2 + (PAGED ? 0 : (int64_t)s * c.stride_sb * 2);
+        it.prow = c.pos + (int64_t)l * c.pos_stride_layer + (int64_t)h * c.pos_stride_head + (PAGED ? 0 : (int64_t)s * c.pos_stride_sb);
+        it.bt = PAGED ? c.block_table + (int64_t)s * c.max_blocks : nullptr;
+        it.c0 = it.chunk * a.chunk_keys;
+        it.c_len = min(clamp_len(seq_len[s], c.max_seq_len) - it.c0, a.chunk_keys);
+        it.n_tiles = (it.c_len + kTileKeys - 1) / kTileKeys;
         // Item i takes its tiles in an order rotated by 5 i: workgroups that run side by side work on neighbouring
         // chunks and would otherwise read the same offset of their chunk (addresses one chunk apart) at the same
         // time, all the way through.  Measured on 36 x 16 x 8 head-instances of 32768 keys in one process: 8.13 ->
         // 7.97 ms and 7.74 -> 7.53 ms (steps of 2 to 6 tiles alike, 1, 11 to 37 less, 7 and 9 little or nothing); with more
         // than four query heads the kernel is bound by its arithmetic and the rotation costs 0.7 %, so it stays off.
-        const int rot = G <= 4 && n_tiles > 0 ? (int)(((unsigned)item * 5u) % (unsigned)n_tiles) : 0;
-        auto tile_at = [&](int t) { const int u = t + rot; return u >= n_tiles ? u - n_tiles : u; };
-        uint4 kd[8];
-        int pos_next = 0, bt_cur = 0, bt_next = 0;
-        if (t_idx < n_tiles) {
-            const int n0 = c0 + tile_at(t_idx) * kTileKeys;
-            bt_cur = load_blocks(n0, min(kTileKeys, c0 + c_len - n0));
-            load_half(n0, min(kTileKeys, c0 + c_len - n0), 0, kd, bt_cur);
-            pos_next = load_pos(n0, min(kTileKeys, c0 + c_len - n0));
-        }
-        // (the first tile's loads are on their way)  Norm-term rows of this head-instance, shared by the waves, and the
-        // folded table per band
-        for (int k = tid; k < kBands * G; k += kThreads) {
-            const int f = k / G, g = k - f * G;
-            reinterpret_cast<float *>(cn_base)[g * kTabRow + f] = tbl[(f * 3 + 2) * G + g];
-        }
-        for (int k = tid; k < kBands * G; k += kThreads) {
-            const int f = k / G, g = k - f * G;
-            const float re = tbl[(f * 3 + 0) * G + g], im = tbl[(f * 3 + 1) * G + g];
-            q_tab[0][g][f] = re;
-            q_tab[1][g][f] = im;
-            if constexpr (ROTATED) {   // no base to fold in: every wave's copy is written once per item
-                for (int w = 0; w < W; ++w) {
-                    char *const wb = cn_base + kTabBytes + w * lane_wave_bytes(G) + kStageBytes;
-                    reinterpret_cast<float *>(wb)[g * kTabRow + f] = re;
-                    reinterpret_cast<float *>(wb + kTabBytes)[g * kTabRow + f] = im;
+        it.rot = G <= 4 ? (int)(((unsigned)id * 5u) % (unsigned)it.n_tiles) : 0;
+        return it;
+    };
+    // A tile of an item: where its rows, positions and block-table entries are, its first slot, its keys that exist.
+    struct Tile {
+        const char *krow;
+        const int32_t *prow, *bt;
+        int n0, cnt;
+    };
+    auto tile_of = [&](const Item &it, int t) {
+        const int n0 = it.c0 + it.tile_at(t) * kTileKeys;
+        return Tile{it.krow, it.prow, it.bt, n0, min(kTileKeys, it.c0 + it.c_len - n0)};
+    };
+
+    // what step `half` takes of the tile at slot n0 (cnt keys exist): eight 16-byte loads per lane.  For a whole tile every
+    // address is a wave-uniform pointer (sixteen keys never straddle a block) plus the lane's constant
+    // offset; in the last, partial tile a key past the end repeats the last one (paged: sixteen keys past the end the last ones; what
+    // lies in a block beyond the length is scored and dropped).
+    // Paged caches: lane j of `btv` holds the physical block of keys n0 + 16 j .. + 15 (load_blocks; a block holds
+    // 16 slots or more), asked for a tile ahead like the positions, so that no load here waits for a block-table
+    // entry.
+    auto load_half = [&](const Tile &ti, int half, uint4(&kd)[8], int btv) {
+        const int first_key = ROWS ? 32 * half : 0, byte = ROWS ? 0 : 128 * half;
+        if (PAGED || ti.cnt == kTileKeys) {
+            constexpr int kPer16 = 16 / kLoadKeys;   // instructions per sixteen keys
+#pragma unroll
+            for (int t = 0; t < 8; t += kPer16) {
+                const int k0 = first_key + kLoadKeys * t, n = ti.n0 + k0;
+                const char *p;
+                if constexpr (PAGED) {
+                    const int blk = __builtin_amdgcn_readlane(btv, k0 / 16);
+                    p = ti.krow + (int64_t)blk * c.stride_sb * 2 + (int64_t)(n & bmask) * slot_bytes;
+                } else {
+                    p = ti.krow + (int64_t)n * slot_bytes;
+                }
+#pragma unroll
+                for (int i = 0; i < kPer16; ++i) {
+                    asm volatile("" : "+v"(ld_off));   // keeps (scalar base + 32-bit lane offset) addressing
+                    kd[t + i] = load_stream16(p + (int64_t)(kLoadKeys * i) * slot_bytes + byte + ld_off);
                 }
             }
-        }
-        __syncthreads();
-
-        for (; t_idx < n_tiles; t_idx += W) {
-            const int n0 = c0 + tile_at(t_idx) * kTileKeys;
-            const int cnt = min(kTileKeys, c0 + c_len - n0);
-            const int p_key = pos_next;
-            if (t_idx + W < n_tiles) {   // the next tile's blocks: needed when its first loads go out, half a tile from now
-                const int m0 = c0 + tile_at(t_idx + W) * kTileKeys;
-                bt_next = load_blocks(m0, min(kTileKeys, c0 + c_len - m0));
+            asm volatile("; whole tile");   // (two different ends, see below)
+        } else {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const uint32_t k = min(first_key + kLoadKeys * t + ld_key, ti.cnt - 1);   // (64 rows fit 32 bits: mfma_path)
+                kd[t] = load_stream16(ti.krow + (int64_t)ti.n0 * slot_bytes + byte + (k * slot_bytes + (uint32_t)ld_piece * 16u));
             }
+            // The compiler would let both branches end in one common last load, whose registers it takes for pending: it then waits for
+            // the seven loads just issued before it issues the eighth, once per tile.
+            asm volatile("; last tile");
+        }
+    };
+    auto load_blocks = [&](const Tile &ti) -> int {
+        if constexpr (!PAGED) return 0;
+        return ti.bt[(ti.n0 + min(16 * (lane & 3), ti.cnt - 1)) >> c.block_shift];
+    };
+    auto load_pos = [&](const Tile &ti, int btv) -> int {
+        if constexpr (ROTATED) return 0;
+        const int k = min(lane, ti.cnt - 1), n = ti.n0 + k;
+        if constexpr (PAGED) return ti.prow[(int64_t)__shfl(btv, k >> 4, 64) * c.pos_stride_sb + (n & bmask)];
+        return ti.prow[n];
+    };
+    auto stage_half = [&](const uint4(&kd)[8]) {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const int at = ROWS ? st_wr0 ^ (64 * (t & 3)) : (t & 1) ? st_wr1 : st_wr0;
+            *reinterpret_cast<uint4 *>(stage + at + 1024 * t) = kd[t];
+        }
+    };
+
+    // The folded table of a head-instance, [F][3][G], spread over the workgroup's threads.
+    constexpr int kTabEach = (kBands * 3 * G + kThreads - 1) / kThreads;
+    uint4 kd[8];
+    int pos_next = 0, bt_cur = 0, bt_next = 0;
+    const bool whole_lines = (c.max_seq_len & 31) == 0 && ((uintptr_t)a.raw & 127) == 0;   // a tile's 64 scores start on a 128-byte line
+    // Items follow one another without a gap: while one is scored, the next one's table entries and every wave's first tile of it
+    // are on their way, so that between two items there are two barriers and no wait for memory.  (Asking for an item, its chunk, its
+    // rows and its table one after the other cost about as much as twelve tiles of an idle CU.)  9216 x 2176 keys, scores and selection:
+    // 1428 -> 1365 us half-split scattered, 1248 -> 1181 in slot order; 288 x 2176 93 -> 81; 64 x 8 x 131072 at G = 8, a step, 5262 -> 5000
+    // (with the waits that load_half and the stores below speak of).
+    float tab[kTabEach];
+    auto load_table = [&](const Item &it) {
+        const float *tbl = a.table + it.inst * (kBands * 3 * G);
+#pragma unroll
+        for (int k = 0; k < kTabEach; ++k) tab[k] = tbl[min(tid + k * kThreads, kBands * 3 * G - 1)];
+    };
+    // the norm-term rows, shared by the waves, and the folded table per band
+    auto store_table = [&]() {
+#pragma unroll
+        for (int k = 0; k < kTabEach; ++k) {
+            const int e = tid + k * kThreads, f = e / (3 * G), comp = e / G - 3 * f, g = e % G;
+            if (kBands * 3 * G % kThreads != 0 && e >= kBands * 3 * G) break;
+            if (comp == 2) {
+                reinterpret_cast<float *>(cn_base)[g * kTabRow + f] = tab[k];
+            } else if constexpr (ROTATED) {   // no base to fold in: every wave's copy is written once per item
+                for (int w = 0; w < W; ++w) {
+                    char *const wb = cn_base + kTabBytes + w * lane_wave_bytes(G) + kStageBytes + comp * kTabBytes;
+                    reinterpret_cast<float *>(wb)[g * kTabRow + f] = tab[k];
+                }
+            } else {
+                q_tab[comp][g][f] = tab[k];
+            }
+        }
+    };
+    auto load_first = [&](const Tile &ti) {
+        bt_cur = load_blocks(ti);
+        pos_next = load_pos(ti, bt_cur);   // (ahead of the rows: needed first)
+        load_half(ti, 0, kd, bt_cur);
+    };
+    Item cur = item_of(first_item);
+    if (cur.n_tiles == 0) return;   // (the whole workgroup)
+    load_table(cur);
+    load_first(tile_of(cur, min(wave, cur.n_tiles - 1)));   // (a wave without a tile: no branch that the wait for the table would have to allow for)
+#pragma unroll
+    for (int k = 0; k < kPhasors; ++k) reinterpret_cast<uint4v *>(ph_base)[min(tid + k * kThreads, kLanePhasorBytes / 16 - 1)] = ph[k];
+    if (tid < kBands) lds_rev[tid] = rev;
+    __syncthreads();   // (the zeros are written)
+    store_table();
+    if (tid == 0) lds_item = (int)gridDim.x + first_item;
+    __syncthreads();
+    for (;;) {
+        const Item nxt = item_of(__builtin_amdgcn_readfirstlane(lds_item));
+        if (nxt.n_tiles > 0) load_table(nxt);
+        double s1[NG], s2[NG];
+#pragma unroll
+        for (int q = 0; q < NG; ++q) s1[q] = s2[q] = 0.0;
+        float *rw = a.raw + cur.inst * G * c.max_seq_len;
+        // (16-byte stores need floats' alignment only; the rows' bytes fit 32 bits with room above them: mfma_path)
+        constexpr uint32_t kNowhere = 0xffffffe0u;
+        constexpr int kNonTemporal = 2;
+        const __amdgpu_buffer_rsrc_t raw_rows = __builtin_amdgcn_make_buffer_rsrc(rw, 0, (uint32_t)G * (uint32_t)c.max_seq_len * 4u, 0x00027000);
+        if (wave >= cur.n_tiles) {
+            // No tile of this item to load the next one's first behind.  (What is asked for here is waited for here, where the wave has
+            // nothing else to do: left pending, it would have to be waited for wherever the other waves' path joins this one.)
+            if (wave < nxt.n_tiles) load_first(tile_of(nxt, wave));
+            __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+        } else for (int t_idx = wave;;) {
+            const Tile now = tile_of(cur, t_idx);
+            const int n0 = now.n0, cnt = now.cnt;
+            int p_key = pos_next;
+            // the wave's next tile: of this item, or its first of the next one
+            const bool last = t_idx + W >= cur.n_tiles, ahead = !last || wave < nxt.n_tiles;
+            const Tile nt = last ? tile_of(nxt, wave) : tile_of(cur, t_idx + W);
+            asm volatile("" : "+v"(p_key));   // (waits for the position here, and not for a copy between registers further down)
+            if (ahead) {
+                if constexpr (PAGED) bt_next = load_blocks(nt);   // needed when its first loads go out, half a tile from now
+                else pos_next = load_pos(nt, 0);
+            }
+            if (tid == 0 && last) later_item = atomicAdd(a.work + own_zero, 1);
 
             // ---- the tile's base
             int base = 0, base1 = 0;   // rows: step 1's may be one of its own
@@ -479,11 +529,10 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                         for (int q = 0; q < NG; ++q) acc[q] = acc2[q] = acc_m[q] = float4v{0.f, 0.f, 0.f, 0.f};
                     // the next loads go out while this step's are scored
                     if (half == 0) {
-                        load_half(n0, cnt, 1, kd, bt_cur);
-                    } else if (t_idx + W < n_tiles) {
-                        const int m0 = c0 + tile_at(t_idx + W) * kTileKeys, mc = min(kTileKeys, c0 + c_len - m0);
-                        load_half(m0, mc, 0, kd, bt_next);
-                        pos_next = load_pos(m0, mc);
+                        load_half(now, 1, kd, bt_cur);
+                    } else if (ahead) {
+                        if constexpr (PAGED) pos_next = load_pos(nt, bt_next);   // (ahead of the rows: needed first)
+                        load_half(nt, 0, kd, bt_next);
                     }
                     Piece cur = fetch(Piece{}, half, 0, table_tag);
 #pragma unroll
@@ -525,29 +574,31 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
             // ---- lane (b, j) holds keys n0 + 4b .. + 3 for head 4q + j
 #pragma unroll
             for (int q = 0; q < NG; ++q) {
-                const int g = 4 * q + j;
-                if (g < G) {
-                    float *dst = rw + (int64_t)g * c.max_seq_len + n0 + 4 * b;
-                    const int live = min(4, cnt - 4 * b);   // keys of this lane that exist
-                    if (live == 4 && vec_store) {
-                        // the selection reads the raw scores from HBM whatever the cache policy of this store; with
-                        // the non-temporal hint the launch is 1 % faster (36 x 16 x 8 x 32768 keys: 7.71 -> 7.63 ms where
-                        // the stores hurt most, equal where they hurt least; post-RoPE keys 6.80 -> 6.60).  Four-byte
-                        // stores do not take the hint well: the sixteen-lane kernel is 3 - 4 % slower with it.
-                        __builtin_nontemporal_store(acc[q], reinterpret_cast<float4v *>(dst));
-                    } else {
+                const int g = 4 * q + j, live = g < G ? min(4, cnt - 4 * b) : 0;   // keys of this lane that exist
+                // One store for all lanes on every path, so that the compiler can count it (a lane with nothing to store lies beyond the
+                // buffer): the wait for the next tile's loads, which went out before, then does not wait for this store too.
+                const uint32_t at = ((uint32_t)g * (uint32_t)c.max_seq_len + (uint32_t)(n0 + 4 * b)) * 4u, to = live == 4 ? at : kNowhere;
+                // The selection reads the raw scores from HBM whatever the cache policy of this store.  Where tiles cover whole cache lines
+                // the non-temporal hint gains 1 % (36 x 16 x 8 x 32768 keys: 7.71 -> 7.63 ms where the stores hurt most, equal where they
+                // hurt least; post-RoPE keys 6.80 -> 6.60); where neighbouring tiles share lines it costs 2 - 6 %, since the halves then
+                // go to memory one by one (6 x 8 x 8 x 30001 keys, a step: 830 us with it, 778 without, 812 with 4-byte stores; 30008: 817, 769).
+                const uint4v scores = __builtin_bit_cast(uint4v, acc[q]);
+                if (whole_lines) __builtin_amdgcn_raw_buffer_store_b128(scores, raw_rows, to, 0, kNonTemporal);
+                else __builtin_amdgcn_raw_buffer_store_b128(scores, raw_rows, to, 0, 0);
+                if (cnt != kTileKeys) {   // (wave-uniform)
 #pragma unroll
-                        for (int k = 0; k < 4; ++k)
-                            if (k < live) dst[k] = acc[q][k];
-                    }
+                    for (int k = 0; k < 3; ++k)
+                        if (live < 4 && k < live) rw[at / 4 + k] = acc[q][k];
+                }
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const double v = k < live ? (double)acc[q][k] : 0.0;
-                        s1[q] += v;
-                        s2[q] += v * v;
-                    }
+                for (int k = 0; k < 4; ++k) {
+                    const double v = k < live ? (double)acc[q][k] : 0.0;
+                    s1[q] += v;
+                    s2[q] += v * v;
                 }
             }
+            if (last) break;
+            t_idx += W;
         }
 
         // per-head sums over the wave's keys: lanes with equal lane % 4 hold the same head
@@ -563,13 +614,18 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                 red[wave][(4 * q + lane) * 2 + 1] = s2[q];
             }
         }
-        __syncthreads();
+        __syncthreads();   // nobody reads this item's table any more
         if (tid < 2 * G) {
             const int g = tid % G, which = tid / G;
             double v = 0.0;
             for (int w_ = 0; w_ < W; ++w_) v += red[w_][g * 2 + which];
-            a.partials[(inst * a.n_tiles + chunk) * (2 * G) + tid] = v;
+            a.partials[(cur.inst * a.n_tiles + cur.chunk) * (2 * G) + tid] = v;
         }
+        if (nxt.n_tiles == 0) break;
+        cur = nxt;
+        store_table();
+        if (tid == 0) lds_item = 2 * (int)gridDim.x + later_item;
+        __syncthreads();
     }
 }
 
