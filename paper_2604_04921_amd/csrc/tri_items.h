@@ -9,7 +9,7 @@ namespace tri {
 // sixteen-lane kernel always), less where that would leave resident workgroups without work (item_keys), kMinChunk at least.
 constexpr int kFastChunk = 8192;
 constexpr int kMinChunk = 512;
-constexpr int kItemCost = 768;
+constexpr int kItemCost = 448;
 constexpr int lane_waves(int G) { return G > 4 ? 8 : 12; }   // waves per workgroup of the kernel of tri_score_lane.hip
 // Waves per workgroup of the sixteen-lane kernel: with more than four query heads per KV head a wave needs more than 128
 // registers, so only three waves fit a SIMD; 12-wave workgroups fill them (8-wave ones would leave one of three unused).
@@ -22,13 +22,14 @@ inline bool large_batch(int64_t instances, int max_seq_len, int n_cu)
 }
 
 // Resident workgroups take items until none is left, so a batch takes about (items per workgroup, rounded up) x (an item's keys
-// + the item's own cost in keys: its tables, its first loads, its waves' last ones).  Every head-instance is cut into the
-// number of equal pieces that makes this least, in whole tiles of 64; large batches stay with kFastChunk.  Measured, whole steps
-// (before: about four items per CU in rounds of the workgroup's waves; kFastChunk for half-split pairs): one layer of eight x
-// 32768 keys 66.5 -> 57.8 us, four layers 126 -> 109, 36 layers 693 -> 674; one layer of eight x 12289, half-split, 150 -> 44.5,
-// sixteen layers 207 -> 169; score + selection of 288 x 2176 keys 91.0 -> 89.4, 576 155 -> 134.  An item cost of 128 keys is worse
-// on many short sequences (1152 x 2176: 243 against 219 us), 384 and 1600 on some in between (576 x 2176: 143 and 134; 160 x
-// 32768: 387 and 397 against 387), 768 nowhere.
+// + the item's own cost in keys: its last tiles, for which there are fewer than the workgroup has waves, and two barriers).  Every
+// head-instance is cut into the number of equal pieces that makes this least, in whole tiles of 64; large batches stay with
+// kFastChunk.  Measured against about four items per CU, whole steps: one layer of eight x 32768 keys 66.5 -> 57.8 us, four layers
+// 126 -> 109, 36 layers 693 -> 674; one layer of eight x 12289, half-split, 150 -> 44.5.  The cost was 768 keys while an item also
+// waited for its list entry, table and first rows; with those asked for an item ahead 448 is the better one: 144 x 2176 keys, scores
+// and selection, 53.1 -> 47.8 us, 576 129.5 -> 122, 288 x 1400 70.4 -> 62.4, 288 x 3000 97.7 -> 91.6, 288 x 17000, a step, 393 -> 385, the
+// others of 27 shapes equal; 256 is equal everywhere.  Counting an item's waves without a last tile as half or as whole idle ones takes 288 x
+// 2176 from 81.0 to 76.2, but 576 from 122 to 130, 288 x 3000 from 91.6 to 98 and 288 x 32768, a step, from 640 to 658.
 inline int item_keys(int64_t instances, int max_seq_len, int n_cu)
 {
     constexpr int unit = 64;                            // a tile

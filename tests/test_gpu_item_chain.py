@@ -1,0 +1,61 @@
+"""Work items that follow one another in a workgroup: thousands of head-instances of ragged lengths, so that every workgroup takes
+several items, many of them with fewer tiles than the workgroup has waves, and rows of raw scores that start on cache lines
+or do not.  Raw and final scores of every length against the oracle.  The layers share one layer's keys (stride 0) and differ in
+their query statistics."""
+import numpy as np
+import pytest
+import torch
+
+from workload import recipe
+
+import tri_harness as H
+
+pytestmark = pytest.mark.gpu
+
+LENS = [1, 64, 65, 129, 0, 511, 640, 700, 767, 768, 769, 900, 1023, 1024, 300, 1000]
+
+
+@pytest.mark.parametrize("group,pairs,paged,rotated,n", [(4, 0, False, False, 1024), (4, 1, False, False, 1031), (3, 1, True, False, 1028),
+                                                         (1, 0, True, False, 1056), (8, 0, False, False, 1025), (6, 1, True, True, 1024),
+                                                         (4, 0, False, True, 1030)])
+def test_chained_items(oracle, group, pairs, paged, rotated, n):
+    from paper_2604_04921_amd import binding as T
+    kv_heads, S, n_cu = 4, len(LENS), torch.cuda.get_device_properties(0).multi_processor_count
+    layers = -(-6 * n_cu // (S * kv_heads))   # six head-instances per CU
+    cfg = recipe.scaled(recipe.CONFIGS["c4_paged"], n_layers=1, n_seqs=S, n_q_heads=kv_heads * group, n_kv_heads=kv_heads, seq_len=n,
+                        min_seq_len=None, budget=40, n_calib=64, positions="sparse" if group == 4 else "dense", block_size=16, seed=77 + group)
+    w = recipe.generate(cfg)
+    w["seq_len"] = np.array(LENS, dtype=np.int32)
+    if pairs:
+        for name in ("k", "q_samples"):
+            w[name] = np.ascontiguousarray(np.concatenate([w[name][..., 0::2], w[name][..., 1::2]], axis=-1))
+    base = oracle.centers(w["q_samples"], pairs=pairs)[0]
+    stats = np.stack([np.roll(base, 5 * l, axis=0) for l in range(layers)])
+    k = H.to_post_rope(w["k"], w["pos"], cfg.rope_theta, pairs, cfg.dtype) if rotated else w["k"]
+    bt = None
+    if paged:
+        bt, nb = recipe.paged_layout(cfg, w["seq_len"])
+        kt = H.to_torch(recipe.to_paged(k, w["seq_len"], bt, nb, 16), "bf16")
+        pos = torch.from_numpy(recipe.to_paged(w["pos"][..., None], w["seq_len"], bt, nb, 16)[..., 0].copy()).cuda()
+        bt = torch.from_numpy(bt).cuda()
+    else:
+        kt, pos = H.to_torch(k, "bf16"), torch.from_numpy(w["pos"]).cuda()
+    kt, pos = kt.expand(layers, *kt.shape[1:]), pos.expand(layers, *pos.shape[1:])
+    model = T.Model(layers, kv_heads * group, kv_heads, 128, cfg.rope_theta, cfg.offsets, pairs)
+    cache = T.Cache(kt, None, pos, torch.from_numpy(w["seq_len"]).cuda(), torch.from_numpy(w["cur_pos"]).cuda(), n, bt, k_rotated=rotated)
+    ws = torch.empty(T.tri_workspace_size(model, cache, 40), dtype=torch.uint8, device="cuda")
+    final = torch.full((layers, S, kv_heads, n), float("nan"), device="cuda")
+    raw = torch.full((layers, S, kv_heads * group, n), float("nan"), device="cuda")
+    T.tri_score(model, torch.from_numpy(stats).cuda(), cache, final, raw, ws)
+    torch.cuda.synchronize()
+    for s, m in enumerate(LENS):
+        assert torch.isnan(raw[:, s, :, m:]).all() and torch.isnan(final[:, s, :, m:]).all()   # nothing past the end
+        if m == 0:
+            continue
+        for l in {0, layers // 2, layers - 1}:
+            h = (s + l) % kv_heads
+            ref = oracle.head_instance(stats[l, h * group:(h + 1) * group], k[0, s, h, :m], w["pos"][0, s, h, :m], int(w["cur_pos"][s]),
+                                       cfg.rope_theta, cfg.offsets, 40, threads=8, pairs=pairs, rotated=rotated)
+            H.check_raw(raw[l, s, h * group:(h + 1) * group, :m].cpu().numpy(), ref["raw"])
+            if m > 1:
+                H.check_final(final[l, s, h, :m].cpu().numpy(), ref["final"])
