@@ -26,9 +26,8 @@ constexpr int kSelBins = 2048;          // linear score bins of the histogram pa
 // Monotone map float -> uint32 (larger float <=> larger key); -0.0 is folded onto +0.0.
 __device__ __forceinline__ uint32_t order_key(float x)
 {
-    uint32_t b = __float_as_uint(x);
-    if (b == 0x80000000u) b = 0u;
-    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+    const uint32_t b = __float_as_uint(x + 0.0f);   // (-0 + 0 = +0)
+    return b ^ ((uint32_t)((int32_t)b >> 31) | 0x80000000u);
 }
 
 struct SelectArgs {
@@ -59,13 +58,12 @@ __device__ __forceinline__ int instance_budget(const SelectArgs &a, int inst)
 
 __device__ __forceinline__ float key_to_float(uint32_t u)
 {
-    return __uint_as_float((u & 0x80000000u) ? (u & 0x7fffffffu) : ~u);
+    return __uint_as_float(u ^ ((uint32_t)((int32_t)~u >> 31) | 0x80000000u));
 }
-__device__ __forceinline__ int linear_bin(uint32_t u)
-{
-    const float x = (key_to_float(u) + 4.0f) * 128.0f;   // 2048 bins over [-4, 12)
-    return (int)fminf(fmaxf(x, 0.0f), 2047.0f);
-}
+// 2048 bins over [-4, 12): where a score lies in them, and its bin (scores beyond go to the first and the last one)
+__device__ __forceinline__ float bin_place(float score) { return fmaf(score, 128.0f, 512.0f); }
+__device__ __forceinline__ int linear_bin(float score) { return (int)__builtin_amdgcn_fmed3f(bin_place(score), 0.0f, 2047.0f); }
+__device__ __forceinline__ int linear_bin(uint32_t u) { return linear_bin(key_to_float(u)); }
 
 // Mean and 1/sigma of a head-instance's heads, as every kernel here takes them: from the moments (block_stats; every thread
 // of the workgroup calls) or ready-made.
@@ -112,6 +110,12 @@ __device__ __forceinline__ void rank_candidates(const uint32_t *cand_key, uint32
             sh[4] = gt;
         }
     }
+}
+
+// `add` and how many lanes below this one are set in the mask
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask, uint32_t add)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, add));
 }
 
 // Sum of the first `wave` of W counts (the loads do not wait for one another).
@@ -165,12 +169,14 @@ __global__ __launch_bounds__(kKeysThreads) void keys_kernel(SelectArgs a)
     };
     auto finish = [&](int n0, const float (&v)[G][4]) {
         uint32_t u[4];
+        int bin[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             float f = z_score(v[0][i], zp[0]);
 #pragma unroll
             for (int g = 1; g < G; ++g) f = fmaxf(f, z_score(v[g][i], zp[g]));
             u[i] = order_key(f);
+            bin[i] = linear_bin(f);
         }
         uint32_t *ks = reinterpret_cast<uint32_t *>(rw);
         if (VEC && slot(n0, 3) < c1) {
@@ -182,7 +188,7 @@ __global__ __launch_bounds__(kKeysThreads) void keys_kernel(SelectArgs a)
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            if (slot(n0, i) < c1) atomicAdd(&hist[linear_bin(u[i])], 1u);
+            if (slot(n0, i) < c1) atomicAdd(&hist[bin[i]], 1u);
     };
     // A clamped load of the iteration past the end may read what another thread has already replaced by keys: its values
     // are not used.
@@ -312,7 +318,7 @@ __global__ __launch_bounds__(THREADS, HELD ? (THREADS == kSelThreads ? 4 : 5) : 
                     for (int g = 1; g < kHeads; ++g) f = fmaxf(f, z_score(cur[g][i], zp[g]));
                 }
                 u[i] = src_slot(n0, i) < N ? order_key(f) : 0u;
-                if (u[i] != 0u) atomicAdd(&bins[linear_bin(u[i])], 1u);
+                if (src_slot(n0, i) < N) atomicAdd(&bins[linear_bin(f)], 1u);
             }
             const int end = (N + 255) & ~255;
             if constexpr (VEC) {
@@ -433,12 +439,15 @@ __global__ __launch_bounds__(THREADS, HELD ? (THREADS == kSelThreads ? 4 : 5) : 
 
     // ---- gather the selected bin's keys (any order; the ranks below do not depend on it), count the keys above it
     uint32_t above_bin = 0u;
+    // (places below the first bin and beyond the last one belong to them; a slot past the end, key 0, is no number and no score's)
+    const float bin_lo = sel_bin == 0 ? -__builtin_inff() : (float)sel_bin, bin_hi = sel_bin == kSelBins - 1 ? __builtin_inff() : (float)(sel_bin + 1);
+    const bool last_bin = sel_bin == kSelBins - 1;
     for_rows([&](int n0, const uint32_t (&u)[4]) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int bin = linear_bin(u[i]);
-            above_bin += (u[i] != 0u && bin > sel_bin) ? 1u : 0u;
-            if (u[i] != 0u && bin == sel_bin) {
+            const float place = bin_place(key_to_float(u[i]));
+            above_bin += place >= bin_hi && !last_bin ? 1u : 0u;
+            if (place >= bin_lo && (place < bin_hi || last_bin)) {
                 const uint32_t pos = atomicAdd(&sh[2], 1u);
                 if (pos < (uint32_t)kCand) {
                     cand_key[pos] = u[i];
@@ -504,14 +513,13 @@ __global__ __launch_bounds__(THREADS, HELD ? (THREADS == kSelThreads ? 4 : 5) : 
 
     // ---- ordered emit: the wave starts behind the kept slots of the waves before it
     uint32_t g_run = sum_before<kWaves>(wave_gt, wave), e_run = sum_before<kWaves>(wave_eq, wave);
-    const uint64_t below = (1ull << lane) - 1ull;
     for_rows([&](int n0, const uint32_t (&u)[4]) {
         uint32_t g_at = g_run, e_at = e_run;   // kept / threshold keys before the lane's first slot
         uint64_t eq_any = 0ull;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const uint64_t gm = __ballot(u[i] > thr);
-            g_at += (uint32_t)__popcll(gm & below);
+            g_at = lanes_below(gm, g_at);
             g_run += (uint32_t)__popcll(gm);
             eq_any |= __ballot(u[i] == thr);
         }
@@ -519,7 +527,7 @@ __global__ __launch_bounds__(THREADS, HELD ? (THREADS == kSelThreads ? 4 : 5) : 
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const uint64_t em = __ballot(u[i] == thr);
-                e_at += (uint32_t)__popcll(em & below);
+                e_at = lanes_below(em, e_at);
                 e_run += (uint32_t)__popcll(em);
             }
         }
