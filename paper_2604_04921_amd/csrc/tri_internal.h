@@ -79,20 +79,38 @@ __device__ __forceinline__ void moments_to_stats(double s1, double s2, int N, do
 }
 
 // Statistics of a head-instance's G query heads inside a workgroup of at least 32 G threads: pt = the
-// head-instance's [tiles][2G] moments, part = 32 G doubles and zst = 2 G doubles of LDS; on return (after a barrier)
-// zst[2g], zst[2g + 1] = mean and 1/sigma of head g.
+// head-instance's [tiles][2G] moments (room for `most`), part = 32 G doubles and zst = 2 G doubles of LDS; on return (after a barrier)
+// zst[2g], zst[2g + 1] = mean and 1/sigma of head g.  The first 64 tiles' moments are asked for by moments_ahead, whatever the length,
+// so that they arrive together with it.
+struct Moments {
+    double v[4];
+};
 template <int G>
-__device__ __forceinline__ void block_stats(const double *pt, int tiles, int N, int tid, double *part, double *zst)
+__device__ __forceinline__ Moments moments_ahead(const double *pt, int most, int tid)
+{
+    Moments m{};
+    if (tid < 2 * G * 16) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) m.v[j] = pt[(int64_t)min((tid & 15) + 16 * j, most - 1) * (2 * G) + (tid >> 4)];
+    }
+    return m;
+}
+template <int G>
+__device__ __forceinline__ void block_stats(const Moments &ahead, const double *pt, int tiles, int N, int tid, double *part, double *zst)
 {
     if (tid < 2 * G * 16) {
         const int col = tid >> 4, k = tid & 15;
         double acc = 0.0;
-        for (int t = k; t < tiles; t += 16) acc += pt[(int64_t)t * (2 * G) + col];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (k + 16 * j < tiles) acc += ahead.v[j];
+        for (int t = k + 64; t < tiles; t += 16) acc += pt[(int64_t)t * (2 * G) + col];
         part[col * 16 + k] = acc;
     }
     __syncthreads();
     if (tid < G) {
         double s1 = 0.0, s2 = 0.0;
+#pragma unroll
         for (int k = 0; k < 16; ++k) {
             s1 += part[tid * 16 + k];
             s2 += part[(G + tid) * 16 + k];

@@ -45,7 +45,7 @@ __device__ __forceinline__ void unit_phasor(double t, double rev, double *c, dou
 {
     double x = t * rev;
     x -= floor(x);
-    sincos(kTwoPi * x, s, c);
+    sincospi(2.0 * x, s, c);   // (no reduction of large arguments, which the general function carries along)
 }
 
 constexpr int kFoldSeqs = 8;      // sequences per workgroup, more where workgroups abound,
@@ -88,6 +88,12 @@ __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
         return;
     }
     const int h = blockIdx.x / a.seq_blocks, sb = blockIdx.x - h * a.seq_blocks;
+    // the thread's (band, query head) pair, the head fastest: neighbouring threads write neighbouring entries of [F][3][G].  Its
+    // statistics are asked for ahead of the phasors.
+    static_assert(kBands * kMaxGroup <= kFoldThreads, "a pair per thread");
+    const int fb = min(tid / a.G, kBands - 1), g = tid - tid / a.G * a.G;
+    const float *ct = a.centers + (((int64_t)l * a.Hq + h * a.G + g) * kBands + fb) * 3;
+    const float c0 = ct[0], c1 = ct[1], c2 = ct[2];
     const int s0 = sb * a.fold_seqs, n_seq = min(a.S - s0, a.fold_seqs);
     for (int k = tid; k < a.n_off * kBands; k += kFoldThreads) {
         double c, s;
@@ -104,6 +110,7 @@ __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
     __syncthreads();
     if (tid < kBands) {   // mean over the offsets, in their order
         double er = 0.0, ei = 0.0;
+#pragma unroll 8
         for (int j = 0; j < a.n_off; ++j) {
             er += off_ph[j * kBands + f][0];
             ei += off_ph[j * kBands + f][1];
@@ -115,12 +122,9 @@ __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
     // the ablation variants (Section 5) only change the table: no trig part, no norm part, or the norm
     // part without its (1 - R_f) weight, i.e. S_norm^(0) of Section 4.1
     const bool trig_on = a.variant != TRI_SCORE_NORM_ONLY, norm_on = a.variant != TRI_SCORE_TRIG_ONLY;
-    // (band, query head) pairs, the head fastest: neighbouring threads write neighbouring entries of [F][3][G]
-    for (int k = tid; k < kBands * a.G; k += kFoldThreads) {
-        const int fb = k / a.G, g = k - fb * a.G;
-        const float *ct = a.centers + (((int64_t)l * a.Hq + h * a.G + g) * kBands + fb) * 3;
+    if (tid < kBands * a.G) {
         const double er = off_ph[fb][0], ei = off_ph[fb][1];
-        const double qr = (double)ct[0], qi = (double)ct[1], qa = (double)ct[2];
+        const double qr = (double)c0, qi = (double)c1, qa = (double)c2;
         const double ar = trig_on ? qr * er - qi * ei : 0.0, ai = trig_on ? qr * ei + qi * er : 0.0;
         const double cn = !norm_on ? 0.0 : a.variant == TRI_SCORE_NORM_UNWEIGHTED ? qa : qa - hypot(qr, qi);
         for (int j = 0; j < n_seq; ++j) {

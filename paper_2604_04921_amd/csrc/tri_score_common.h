@@ -75,7 +75,7 @@ __device__ __forceinline__ void relative_phasor(double theta, int f, int r, floa
     double x = (double)r * (pow(theta, -2.0 * (double)f / (double)kHeadDim) / kTwoPiD);
     x -= floor(x);
     double sd, cd;
-    sincos(kTwoPiD * x, &sd, &cd);
+    sincospi(2.0 * x, &sd, &cd);
     *c = (float)cd;
     *s = (float)sd;
 }

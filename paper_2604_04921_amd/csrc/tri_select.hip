@@ -68,11 +68,16 @@ __device__ __forceinline__ int linear_bin(uint32_t u) { return linear_bin(key_to
 // Mean and 1/sigma of a head-instance's heads, as every kernel here takes them: from the moments (block_stats; every thread
 // of the workgroup calls) or ready-made.
 template <int G>
-__device__ __forceinline__ void load_zparams(const SelectArgs &a, int inst, int N, int tid, double *zpart, double *zst,
+__device__ __forceinline__ Moments load_moments(const SelectArgs &a, int inst, int tid)
+{
+    return a.partials ? moments_ahead<G>(a.partials + (int64_t)inst * a.n_tiles * (2 * G), a.n_tiles, tid) : Moments{};
+}
+template <int G>
+__device__ __forceinline__ void load_zparams(const SelectArgs &a, const Moments &ahead, int inst, int N, int tid, double *zpart, double *zst,
                                              ZParams (&zp)[G])
 {
     if (a.partials)   // uniform over the launch
-        block_stats<G>(a.partials + (int64_t)inst * a.n_tiles * (2 * G), (N + a.tile_keys - 1) / a.tile_keys, N, tid,
+        block_stats<G>(ahead, a.partials + (int64_t)inst * a.n_tiles * (2 * G), (N + a.tile_keys - 1) / a.tile_keys, N, tid,
                        zpart, zst);
 #pragma unroll
     for (int g = 0; g < G; ++g)
@@ -141,13 +146,14 @@ __global__ __launch_bounds__(kKeysThreads) void keys_kernel(SelectArgs a)
     const int tid = threadIdx.x;
     const int inst = blockIdx.x / a.n_chunks, chunk = blockIdx.x - inst * a.n_chunks;
     const int s = (inst / a.n_kv_heads) % a.n_seqs;
+    const Moments ahead = load_moments<G>(a, inst, tid);
     const int N = clamp_len(a.seq_len[s], a.max_seq_len);
     const int c0 = chunk * a.chunk_keys, c1 = min(N, c0 + a.chunk_keys);
     const int B = instance_budget(a, inst);
     if (c0 >= N || N <= B || B == 0) return;   // (uniform over the workgroup; select_kernel reads nothing of it either)
     for (int k = tid; k < kSelBins; k += kKeysThreads) hist[k] = 0u;
     ZParams zp[G];
-    load_zparams<G>(a, inst, N, tid, zpart, zst, zp);
+    load_zparams<G>(a, ahead, inst, N, tid, zpart, zst, zp);
     __syncthreads();
     float *rw = a.raw + (int64_t)inst * G * a.max_seq_len;
     constexpr int kStep = 4 * kKeysThreads;   // keys per iteration
@@ -246,6 +252,8 @@ __global__ __launch_bounds__(THREADS, HELD ? (THREADS == kSelThreads ? 4 : 5) : 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int inst = blockIdx.x;
     const int s = (inst / a.n_kv_heads) % a.n_seqs;
+    Moments ahead{};
+    if constexpr (SRC > 0) ahead = load_moments<kHeads>(a, inst, tid);
     const int N = clamp_len(a.seq_len[s], a.max_seq_len);
     const int B = instance_budget(a, inst);
     int32_t *out = a.kept_idx + (int64_t)inst * a.budget;
@@ -298,7 +306,7 @@ __global__ __launch_bounds__(THREADS, HELD ? (THREADS == kSelThreads ? 4 : 5) : 
     ZParams zp[kHeads];
     if constexpr (SRC > 0) {
         __shared__ double zst[2 * kHeads], zpart[32 * kHeads];
-        load_zparams<kHeads>(a, inst, N, tid, zpart, zst, zp);
+        load_zparams<kHeads>(a, ahead, inst, N, tid, zpart, zst, zp);
     }
     __syncthreads();
 
