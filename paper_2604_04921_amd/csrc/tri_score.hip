@@ -76,9 +76,9 @@ __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
     const int extra = (int)blockIdx.x - n_fold;   // uniform over the workgroup
     if (extra >= 0 && l > 0) return;
     if (extra > 0) {
-        const int t = (extra - 1) * kFoldThreads + tid;
-        if (a.lane_kernel) lane_phasor_entry(a.theta, t, a.phasors);
-        else fast_phasor_entry(a.theta, t, a.phasors);
+        const int t = (extra - 1) * kFoldThreads + tid;   // (an entry holds two bands: a thread each)
+        if (a.lane_kernel) lane_phasor(a.theta, t, reinterpret_cast<float2 *>(a.phasors));
+        else fast_phasor(a.theta, t, reinterpret_cast<float2 *>(a.phasors));
         return;
     }
     const double rev = pow(a.theta, -2.0 * (double)f / (double)kHeadDim) / kTwoPi;
@@ -360,17 +360,17 @@ __global__ __launch_bounds__(256) void final_kernel(FinalArgs a)
     const int N = clamp_len(a.seq_len[s], a.max_seq_len);
     const int n = (kb * 256 + threadIdx.x) * 4;
     if (n >= N) return;
-    // 16-byte accesses: rows of a multiple of four entries (four from a slot below N on exist) from an aligned start (both arrays may
-    // be the caller's, who owes floats' alignment only)
-    const bool vec = (a.max_seq_len & 3) == 0 && (((uintptr_t)a.raw | (uintptr_t)a.final_) & 15) == 0;
+    // 16-byte accesses within a row (both arrays may be the caller's, who owes floats' alignment only: the hardware asks for no more)
+    typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+    const bool vec = n + 3 < a.max_seq_len;
     const float *rw = a.raw + (int64_t)inst * G * a.max_seq_len;
     float v[G][4];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         const float *row = rw + (int64_t)g * a.max_seq_len;
         if (vec) {
-            const float4 t = *reinterpret_cast<const float4 *>(row + n);
-            v[g][0] = t.x, v[g][1] = t.y, v[g][2] = t.z, v[g][3] = t.w;
+            const float4u t = *reinterpret_cast<const float4u *>(row + n);
+            v[g][0] = t[0], v[g][1] = t[1], v[g][2] = t[2], v[g][3] = t[3];
         } else {
 #pragma unroll
             for (int k = 0; k < 4; ++k) v[g][k] = row[min(n + k, N - 1)];
@@ -388,8 +388,8 @@ __global__ __launch_bounds__(256) void final_kernel(FinalArgs a)
         }
     }
     float *out = a.final_ + (int64_t)inst * a.max_seq_len + n;
-    if (vec && n + 3 < N) {
-        *reinterpret_cast<float4 *>(out) = make_float4(best[0], best[1], best[2], best[3]);
+    if (n + 3 < N) {
+        *reinterpret_cast<float4u *>(out) = float4u{best[0], best[1], best[2], best[3]};
     } else {
 #pragma unroll
         for (int k = 0; k < 4; ++k)
@@ -531,7 +531,7 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     const bool sixteen = sixteen_lane_kernel(G, chunk_keys, (int64_t)m.n_layers * c.n_seqs * m.n_kv_heads, c.max_seq_len, n_cu,
                                              m.pairs == TRI_PAIR_HALF, c.block_size != 0, c.k_rotated != 0);
     const bool lane_kernel = fo.work && !sixteen;
-    const int table_entries = !fo.work || c.k_rotated ? 0 : lane_kernel ? kLaneTableEntries : kFastTableEntries;
+    const int table_entries = !fo.work || c.k_rotated ? 0 : lane_kernel ? kLaneTablePhasors : kFastTablePhasors;
     fo.phasors = reinterpret_cast<float4 *>(ws + wl.phasors);
     fo.lane_kernel = lane_kernel;
     const size_t fold_lds = (size_t)(m.n_offsets + std::min(fo.fold_seqs, c.n_seqs)) * kBands * 2 * sizeof(double);

@@ -80,34 +80,32 @@ __device__ __forceinline__ void relative_phasor(double theta, int f, int r, floa
     *s = (float)sd;
 }
 // Entry t of the sixteen-lane kernel's table, (half hf, chunk b, r) = (cos, sin) of bands 4b+2hf, 4b+2hf+1 at relative position
-// r, at byte hf * kPhasorHalfStride + b * kPhasorBlockStride + 16 r.  The fold kernel writes it with kFastTableEntries extra
-// threads (a launch of its own took 4.6 us).
-constexpr int kFastTableEntries = 2 * 16 * kPhasorRange;
-__device__ __forceinline__ void fast_phasor_entry(double theta, int t, float4 *out)
+// r, at byte hf * kPhasorHalfStride + b * kPhasorBlockStride + 16 r.  The fold kernel writes it with kFastTablePhasors extra
+// threads (a launch of its own took 4.6 us), a phasor each (neighbouring bands in neighbouring threads).
+constexpr int kFastTablePhasors = 4 * 16 * kPhasorRange;
+__device__ __forceinline__ void fast_phasor(double theta, int t, float2 *out)
 {
-    const int r = t % kPhasorRange, b = (t / kPhasorRange) % 16, hf = t / (kPhasorRange * 16), f = 4 * b + 2 * hf;
-    float4 v;
+    const int e = t / 2, r = e % kPhasorRange, b = (e / kPhasorRange) % 16, hf = e / (kPhasorRange * 16), f = 4 * b + 2 * hf + t % 2;
+    float2 v;
     relative_phasor(theta, f, r, &v.x, &v.y);
-    relative_phasor(theta, f + 1, r, &v.z, &v.w);
-    out[(hf * kPhasorHalfStride + b * kPhasorBlockStride) / 16 + r] = v;
+    out[((hf * kPhasorHalfStride + b * kPhasorBlockStride) / 16 + r) * 2 + t % 2] = v;
 }
 // bf16 keys; G in 1..8.  launch_score_lane (tri_score_lane.hip): the general one; launch_score_fast (tri_score_mfma.hip): paged,
 // interleaved pairs, pre-RoPE.  Each has its own phasor table layout.
 tri_status launch_score_fast(int G, const ScoreArgs &sa, hipStream_t st);
 tri_status launch_score_lane(int G, const ScoreArgs &sa, bool half_split, hipStream_t st);
 // The general kernel's table of e^{i w r}: entry (band pair bp, r) = (cos, sin) of bands 2bp and 2bp+1 at relative position r, at byte
-// bp * kLanePairStride + 16 r.  The fold kernel writes it with kLaneTableEntries extra threads.
+// bp * kLanePairStride + 16 r.  The fold kernel writes it with kLaneTablePhasors extra threads.
 constexpr int kLaneRange = 64;                                  // relative positions 0 .. 63
 constexpr int kLanePairStride = kLaneRange * 16 + 16;           // bytes per band pair (16 bytes of skew)
 constexpr int kLanePhasorBytes = (kBands / 2) * kLanePairStride;
-constexpr int kLaneTableEntries = (kBands / 2) * kLaneRange;
-__device__ __forceinline__ void lane_phasor_entry(double theta, int t, float4 *out)
+constexpr int kLaneTablePhasors = kBands * kLaneRange;
+__device__ __forceinline__ void lane_phasor(double theta, int t, float2 *out)
 {
-    const int r = t % kLaneRange, bp = t / kLaneRange;
-    float4 v;
-    relative_phasor(theta, 2 * bp, r, &v.x, &v.y);
-    relative_phasor(theta, 2 * bp + 1, r, &v.z, &v.w);
-    out[bp * (kLanePairStride / 16) + r] = v;
+    const int e = t / 2, r = e % kLaneRange, bp = e / kLaneRange;
+    float2 v;
+    relative_phasor(theta, 2 * bp + t % 2, r, &v.x, &v.y);
+    out[(bp * (kLanePairStride / 16) + r) * 2 + t % 2] = v;
 }
 // ints the MFMA kernel's work list takes: a header and one (sequence, chunk) pair per possible chunk
 inline size_t fast_work_ints(int64_t n_seqs, int64_t max_seq_len)

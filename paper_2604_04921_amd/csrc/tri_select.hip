@@ -16,7 +16,9 @@ namespace tri {
 
 namespace {
 
-typedef float float4v __attribute__((ext_vector_type(4)));
+// 16 bytes wherever floats may lie: the hardware asks for no more than a dword's alignment
+typedef float float4v __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t word4v __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int kSelThreads = 1024;       // threads per workgroup, or
 constexpr int kSelSmallThreads = 256;   // many short sequences
@@ -135,10 +137,10 @@ __device__ __forceinline__ uint32_t sum_before(const uint32_t *counts, int wave)
 
 // Raw scores -> integer keys (written over the head-instance's first raw row: every key's scores are read by the thread that
 // writes it) and the histogram of each chunk's linear bins.  grid (instances * n_chunks), block 256.  A streaming kernel:
-// 4 G bytes read and 4 written per key, the next keys' loads issued before a key's arithmetic.  VEC: rows of a
-// multiple of four keys, four keys per thread and load.
+// 4 G bytes read and 4 written per key, the next keys' loads issued before a key's arithmetic.  (Four keys per thread and load, whatever the
+// rows' alignment: what a load brings from behind a row's end lies in the workspace too and is not used.)
 constexpr int kKeysThreads = 256;
-template <int G, bool VEC>
+template <int G>
 __global__ __launch_bounds__(kKeysThreads) void keys_kernel(SelectArgs a)
 {
     __shared__ uint32_t hist[kSelBins];
@@ -158,19 +160,14 @@ __global__ __launch_bounds__(kKeysThreads) void keys_kernel(SelectArgs a)
     float *rw = a.raw + (int64_t)inst * G * a.max_seq_len;
     constexpr int kStep = 4 * kKeysThreads;   // keys per iteration
     // thread's key i of the iteration at n0
-    auto slot = [&](int n0, int i) { return VEC ? n0 + 4 * tid + i : n0 + i * kKeysThreads + tid; };
+    auto slot = [&](int n0, int i) { return n0 + 4 * tid + i; };
     auto load = [&](int n0, float (&v)[G][4]) {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const float *row = rw + (int64_t)g * a.max_seq_len;
-            if constexpr (VEC) {   // (a row holds a multiple of four entries: four from a slot below N exist)
-                const float4v t = __builtin_nontemporal_load(reinterpret_cast<const float4v *>(row + min(slot(n0, 0), (N - 1) & ~3)));
+            const float4v t = __builtin_nontemporal_load(reinterpret_cast<const float4v *>(row + min(slot(n0, 0), (N - 1) & ~3)));
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[g][i] = t[i];
-            } else {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[g][i] = __builtin_nontemporal_load(row + min(slot(n0, i), N - 1));
-            }
+            for (int i = 0; i < 4; ++i) v[g][i] = t[i];
         }
     };
     auto finish = [&](int n0, const float (&v)[G][4]) {
@@ -185,8 +182,8 @@ __global__ __launch_bounds__(kKeysThreads) void keys_kernel(SelectArgs a)
             bin[i] = linear_bin(f);
         }
         uint32_t *ks = reinterpret_cast<uint32_t *>(rw);
-        if (VEC && slot(n0, 3) < c1) {
-            *reinterpret_cast<uint4 *>(ks + slot(n0, 0)) = make_uint4(u[0], u[1], u[2], u[3]);
+        if (slot(n0, 3) < c1) {
+            *reinterpret_cast<word4v *>(ks + slot(n0, 0)) = word4v{u[0], u[1], u[2], u[3]};
         } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
@@ -218,7 +215,8 @@ __global__ __launch_bounds__(kKeysThreads) void keys_kernel(SelectArgs a)
 //           histograms; not HELD)
 //   HELD    the keys lie in LDS (dynamic, four bytes per key, whole rows of 256) from the first pass on; else every pass reads
 //           them from memory
-//   VEC     16-byte loads of the source (rows of a multiple of four entries)
+//   VEC     16-byte loads of the source: always of the workspace's rows (see keys_kernel); of final scores, which are the caller's, where
+//           four entries from a slot below N on exist (rows of a multiple of four)
 // Steps:
 //   1. Histogram over 2048 *linear* bins of the score on [-4, 12) (monotone in the score, so a valid coarse partition; z-scores
 //      spread over hundreds of bins, whereas the top bits of their float image share a handful of values and would
@@ -288,7 +286,7 @@ __global__ __launch_bounds__(THREADS, HELD ? (THREADS == kSelThreads ? 4 : 5) : 
 #pragma unroll
         for (int g = 0; g < kHeads; ++g) {
             const float *row = src + (int64_t)g * a.max_seq_len;
-            if constexpr (VEC) {   // (four entries from a slot below N on exist)
+            if constexpr (VEC) {
                 const float4v t = __builtin_nontemporal_load(reinterpret_cast<const float4v *>(row + min(src_slot(n0, 0), (N - 1) & ~3)));
 #pragma unroll
                 for (int i = 0; i < 4; ++i) v[g][i] = t[i];
@@ -350,11 +348,13 @@ __global__ __launch_bounds__(THREADS, HELD ? (THREADS == kSelThreads ? 4 : 5) : 
         if constexpr (VEC) {
             const int n = min(n0 + 4 * lane, (N - 1) & ~3);
             if constexpr (SRC == 0) {
-                const float4 t = *reinterpret_cast<const float4 *>(src + n);
-                u[0] = order_key(t.x), u[1] = order_key(t.y), u[2] = order_key(t.z), u[3] = order_key(t.w);
+                const float4v t = *reinterpret_cast<const float4v *>(src + n);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) u[i] = order_key(t[i]);
             } else {
-                const uint4 t = *reinterpret_cast<const uint4 *>(ks + n);
-                u[0] = t.x, u[1] = t.y, u[2] = t.z, u[3] = t.w;
+                const word4v t = *reinterpret_cast<const word4v *>(ks + n);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) u[i] = t[i];
             }
         } else {
 #pragma unroll
@@ -554,8 +554,9 @@ __global__ __launch_bounds__(THREADS, HELD ? (THREADS == kSelThreads ? 4 : 5) : 
 template <int SRC>
 tri_status launch_held(const SelectArgs &sa, int n_inst, bool small, bool vec, hipStream_t st)
 {
-    auto kern = small ? (vec ? select_kernel<SRC, true, true, kSelSmallThreads> : select_kernel<SRC, false, true, kSelSmallThreads>)
-                      : (vec ? select_kernel<SRC, true, true, kSelThreads> : select_kernel<SRC, false, true, kSelThreads>);
+    auto kern = small ? select_kernel<SRC, true, true, kSelSmallThreads> : select_kernel<SRC, true, true, kSelThreads>;
+    if constexpr (SRC == 0)
+        if (!vec) kern = small ? select_kernel<SRC, false, true, kSelSmallThreads> : select_kernel<SRC, false, true, kSelThreads>;
     size_t lds = (size_t)((sa.max_seq_len + 255) / 256 * 256) * sizeof(uint32_t);
     if (sa.fill) lds = std::max(lds, (size_t)sa.budget * 2 * sizeof(int32_t));
     // (the most any call asks for, not this call's share: the limit belongs to the process, and another thread may set it between)
@@ -569,8 +570,7 @@ tri_status launch_held(const SelectArgs &sa, int n_inst, bool small, bool vec, h
 template <int G>
 tri_status launch_select_g(const SelectArgs &sa, int n_inst, int n_cu, hipStream_t st)
 {
-    // (final scores come from the caller: any alignment that floats have)
-    const bool vec = (sa.max_seq_len & 3) == 0 && (G > 0 || ((uintptr_t)sa.final_ & 15) == 0);
+    const bool vec = G > 0 || (sa.max_seq_len & 3) == 0;
     if (sa.max_seq_len <= kSelHeldKeys) {
         // Short sequences: small workgroups, cheap barriers, several per CU -- unless there are so few that a CU has one
         // anyway (one head-instance of 4096 keys, whole step: 32.1 us with 1024 threads, 33.4 with 256; 288 of 2176, score and
@@ -589,13 +589,11 @@ tri_status launch_select_g(const SelectArgs &sa, int n_inst, int n_cu, hipStream
         while (sk.chunk_keys < 32768 && sk.max_seq_len > 16 * sk.chunk_keys) sk.chunk_keys *= 2;
         sk.n_chunks = (sk.max_seq_len + sk.chunk_keys - 1) / sk.chunk_keys;
         const dim3 grid((uint32_t)((int64_t)n_inst * sk.n_chunks));
-        if (vec) hipLaunchKernelGGL((keys_kernel<G, true>), grid, dim3(kKeysThreads), 0, st, sk);
-        else hipLaunchKernelGGL((keys_kernel<G, false>), grid, dim3(kKeysThreads), 0, st, sk);
+        hipLaunchKernelGGL(keys_kernel<G>, grid, dim3(kKeysThreads), 0, st, sk);
         tri_status rc = hip_status("keys_kernel");
         if (rc != TRI_OK) return rc;
         const int64_t key_row = (int64_t)G * sk.max_seq_len;
-        auto kern = vec ? select_kernel<kFromKeys, true, false, kSelThreads> : select_kernel<kFromKeys, false, false, kSelThreads>;
-        hipLaunchKernelGGL(kern, dim3(n_inst), dim3(kSelThreads), 0, st, sk, key_row);
+        hipLaunchKernelGGL((select_kernel<kFromKeys, true, false, kSelThreads>), dim3(n_inst), dim3(kSelThreads), 0, st, sk, key_row);
         return hip_status("select_kernel");
     }
     if constexpr (G == 0) {
