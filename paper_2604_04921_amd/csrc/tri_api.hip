@@ -168,7 +168,7 @@ Workspace workspace_layout(const tri_model &m, const tri_cache &c, int32_t budge
     w.reserved = o;
     o = align256(o + ((size_t)c.n_seqs + 1) * kBands * 2 * sizeof(double));
     w.phasors = o;
-    o = align256(o + 128 * 1024);
+    o = align256(o + kPhasorAreaBytes);
     w.table = o;
     o = align256(o + inst * kBands * 3 * G * sizeof(float));
     w.work = o;
@@ -410,7 +410,7 @@ tri_status tri_select_topk(const tri_model *model, const float *final_scores, co
         return TRI_ERR_INVALID_ARG;
     }
     if ((rc = check_limits(*model, *cache, budget, "tri_select_topk")) != TRI_OK) return rc;
-    return launch_select(*model, final_scores, nullptr, nullptr, nullptr, MomentLayout{1, 1}, nullptr, *cache, budget,
+    return launch_select(*model, final_scores, nullptr, nullptr, nullptr, MomentLayout{1, 1, nullptr}, nullptr, *cache, budget,
                          kept_idx, kept_cnt,
                          (hipStream_t)stream);
 }
@@ -469,14 +469,14 @@ static tri_status run_step(const tri_model *model, const float *centers, const t
 {
     tri_status rc;
     // raw scores and their moments stay in the workspace; the selection forms statistics and final scores itself
-    MomentLayout moments{1, 1};
+    MomentLayout moments{1, 1, nullptr};
     if ((rc = launch_score(*model, centers, *src, nullptr, nullptr, ws, wl, &moments, (hipStream_t)stream)) != TRI_OK)
         return rc;
     // evicting in place with the fewest moves, the selection's workgroups do the moves themselves where they can
     const FillTail fill{new_seq_len};
     bool filled = false;
     if ((rc = launch_select(*model, nullptr, reinterpret_cast<float *>(ws + wl.raw), nullptr,
-                            reinterpret_cast<const double *>(ws + wl.partials), moments,
+                            moments.partials, moments,
                             reinterpret_cast<uint32_t *>(ws + wl.final_), *src, budget, kept_idx, kept_cnt,
                             (hipStream_t)stream, dst ? nullptr : &fill, &filled)) != TRI_OK)
         return rc;

@@ -11,7 +11,8 @@ namespace tri {
 
 constexpr int kHeadDim = 128;
 constexpr int kBands = 64;        // F = head_dim / 2
-constexpr int kScoreTile = 256;   // keys scored by one workgroup
+constexpr int kScoreTile = 256;   // keys scored by one workgroup of the generic kernel, at most (an entry of the moments' area)
+constexpr int64_t kPhasorAreaBytes = 128 * 1024;
 constexpr int kMaxOffsets = 64;
 constexpr int kMaxGroup = 8;
 
@@ -190,11 +191,12 @@ tri_status launch_centers_finalize(const tri_model &m, const double *sums, int64
                                    hipStream_t st);
 tri_status launch_diagnostics(const tri_model &m, const float *q_centers, const float *k_centers, float *mrl,
                               float *contrib, int32_t top_k, int32_t *top, hipStream_t st);
-// final_out == NULL (fused step): the moments stay in the workspace's `partials` (layout returned through
+// final_out == NULL (fused step): the moments stay in the workspace (place and layout returned through
 // moments) and no statistics are formed here: the selection does that itself.
 struct MomentLayout {
     int32_t n_tiles;     // entries per head-instance
     int32_t tile_keys;   // keys per entry
+    const double *partials;   // where they are
 };
 tri_status launch_score(const tri_model &m, const float *centers, const tri_cache &c, float *final_out,
                         float *raw_out, char *ws, const Workspace &wl, MomentLayout *moments, hipStream_t st);

@@ -149,9 +149,9 @@ struct Elem<uint16_t> {
 };
 
 // One band of one key: rotate the key by its own position, take its modulus, and add the
-// three products per query head.  tb points at this band's [3][G] table entries (wave-uniform).
+// three products per query head.  tb: this band's [3][G] table entries, in LDS.
 template <int G>
-__device__ __forceinline__ void band_update(float (&acc)[G], const float *__restrict__ tb, double pd,
+__device__ __forceinline__ void band_update(float (&acc)[G], const float *tb, double pd,
                                             double rev, float re, float im)
 {
     double xr = pd * rev;
@@ -166,55 +166,73 @@ __device__ __forceinline__ void band_update(float (&acc)[G], const float *__rest
         acc[g] = fmaf(tb[0 * G + g], kr, fmaf(tb[1 * G + g], ki, fmaf(tb[2 * G + g], m, acc[g])));
 }
 
-// grid (n_tiles, S*Hkv, L), block 1024: a tile of 256 keys, four threads per key (a quarter of the bands each, the quarter the
-// same for a whole wave, so that table entries stay scalar operands), staged through LDS so that global loads are coalesced
-// 16-byte accesses while each thread ends up with its quarter of one key.  LDS (135 KB for fp32 keys) allows one workgroup per
-// CU, and a wave alone issues a dependent vector instruction every 6 - 8 clocks: with one thread per key, i.e. one wave
-// per SIMD, the kernel was bound by that: fp32 keys, G = 4, whole steps: one head of 4096 keys 32.3 -> 25.6 us, 288 heads of 4096
-// 521 -> 286, of 32768 3595 -> 1730.
-constexpr int kScoreSplit = 4;
+// grid (n_tiles, S*Hkv, L), block 512: a tile of one or two parts of 128 keys, four threads per key (a quarter of the bands each, the
+// quarter the same for a whole wave, so that the table entries, in LDS, are read by a wave at one address).  Keys are staged through
+// LDS so that global loads are coalesced 16-byte accesses while each thread ends up with its quarter of one key.  The 68 KB that 128
+// fp32 keys take let two workgroups share a CU: one's loads overlap the other's arithmetic, and the second part's loads go out ahead of the
+// first part's arithmetic.
+// Against 256 keys in one workgroup of 1024 threads, alone on its CU, with the table as scalar operands (whose loads a wave waited for every
+// other band): fp32, whole steps, 192 heads of 32768 keys 1258 -> 863 us at G = 4, 1045 -> 706 at G = 1, 1591 -> 1297 at G = 8; scores and selection
+// of 288 heads of 2176 144 -> 99; scores of 320 ragged ones up to 20011 857 -> 550.  (That one: one thread per key, one wave per SIMD,
+// 3595 us for 288 heads of 32768 keys; four 1730.)
+constexpr int kScoreSplit = 4, kPartKeys = 128, kScoreThreads = kPartKeys * kScoreSplit;
 template <int G, typename T, int PAIRS>
-__global__ __launch_bounds__(kScoreTile *kScoreSplit) void score_kernel(ScoreArgs a)
+__global__ __launch_bounds__(kScoreThreads, 4) void score_kernel(ScoreArgs a)
 {
-    constexpr int ROW16 = Elem<T>::kRow16;
+    constexpr int ROW16 = Elem<T>::kRow16, kLoads = kPartKeys * ROW16 / kScoreThreads;
     constexpr int STRIDE16 = ROW16 + 1;   // odd number of 16-byte units: conflict-free row reads
-    extern __shared__ uint4 lds[];        // the keys; later the quarters' sums
-    __shared__ int64_t row_off[kScoreTile];
-    __shared__ double red[4][2 * G];
+    extern __shared__ uint4 lds[];        // a part's keys; later its quarters' sums
+    __shared__ __align__(16) float tab[kBands * 3 * G];
+    __shared__ double rev[kBands];
+    __shared__ double red[kPartKeys / 64][2 * G];
 
     const CacheView &c = a.c;
-    const int tid = threadIdx.x, key = tid % kScoreTile;
-    const int quarter = __builtin_amdgcn_readfirstlane(tid / kScoreTile);
+    const int tid = threadIdx.x, key = tid % kPartKeys;
+    const int quarter = __builtin_amdgcn_readfirstlane(tid / kPartKeys);
     const int tile = blockIdx.x;
     const int s = blockIdx.y / c.n_kv_heads, h = blockIdx.y % c.n_kv_heads;
     const int l = blockIdx.z;
     const int N = clamp_len(c.seq_len[s], c.max_seq_len);
-    const int n0 = tile * kScoreTile;
+    const int n0 = tile * a.chunk_keys, n1 = min(N, n0 + a.chunk_keys);
     if (n0 >= N) return;
-    const int n = n0 + key;
-    const bool valid = n < N;
-
-    if (quarter == 0) row_off[key] = valid ? kv_offset(c, l, s, h, n) : (int64_t)-1;
-    int p = 0;
-    if (valid && !c.k_rotated) p = c.pos[pos_offset(c, l, s, h, n)];   // a post-RoPE key needs no rotation
-    __syncthreads();
+    const int64_t inst = ((int64_t)l * c.n_seqs + s) * c.n_kv_heads + h;
 
     const T *kbase = (const T *)c.k;
+    uint4 kd[kLoads];
+    int p_next = 0;
+    auto load = [&](int m0) {
 #pragma unroll
-    for (int i = 0; i < ROW16 / kScoreSplit; ++i) {
-        const int ci = i * kScoreTile * kScoreSplit + tid;
-        const int k = ci / ROW16, part = ci % ROW16;
-        const int64_t off = row_off[k];
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (off >= 0) v = reinterpret_cast<const uint4 *>(kbase + off)[part];
-        lds[k * STRIDE16 + part] = v;
+        for (int i = 0; i < kLoads; ++i) {
+            const int ci = i * kScoreThreads + tid, n = m0 + ci / ROW16;
+            kd[i] = make_uint4(0u, 0u, 0u, 0u);
+            if (n < N) kd[i] = reinterpret_cast<const uint4 *>(kbase + kv_offset(c, l, s, h, n))[ci % ROW16];
+        }
+        if (m0 + key < N && !c.k_rotated) p_next = c.pos[pos_offset(c, l, s, h, m0 + key)];   // a post-RoPE key needs no rotation
+    };
+    load(n0);
+    {
+        const float *src = a.table + inst * (kBands * 3 * G);
+        for (int k = tid; k < kBands * 3 * G; k += kScoreThreads) tab[k] = src[k];
+        if (tid < kBands) rev[tid] = a.band_rev[tid];
     }
+    double v1[G], v2[G];   // quarter 0: sums of the scores and of their squares
+#pragma unroll
+    for (int g = 0; g < G; ++g) v1[g] = v2[g] = 0.0;
+    const int Hq = c.n_kv_heads * G;
+    float *rw = a.raw + (((int64_t)l * c.n_seqs + s) * Hq + (int64_t)h * G) * c.max_seq_len;
+    const float *const tb = tab;
+    for (int m0 = n0; m0 < n1; m0 += kPartKeys) {
+    if (m0 > n0) __syncthreads();   // the sums of the part before have been read
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+        const int ci = i * kScoreThreads + tid;
+        lds[ci / ROW16 * STRIDE16 + ci % ROW16] = kd[i];
+    }
+    const double pd = (double)p_next;
     __syncthreads();
-
-    const int64_t inst = ((int64_t)l * c.n_seqs + s) * c.n_kv_heads + h;
-    const float *__restrict__ tb = a.table + inst * (kBands * 3 * G);
-    const double *__restrict__ rev = a.band_rev;
-    const double pd = (double)p;
+    if (m0 + kPartKeys < n1) load(m0 + kPartKeys);   // on its way during this part's arithmetic
+    const int n = m0 + key;
+    const bool valid = n < N;
     float acc[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) acc[g] = 0.f;
@@ -270,37 +288,39 @@ __global__ __launch_bounds__(kScoreTile *kScoreSplit) void score_kernel(ScoreArg
     float *const sums = reinterpret_cast<float *>(lds);   // [quarter - 1][head][key]
     if (quarter > 0) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) sums[((quarter - 1) * G + g) * kScoreTile + key] = acc[g];
+        for (int g = 0; g < G; ++g) sums[((quarter - 1) * G + g) * kPartKeys + key] = acc[g];
     }
     __syncthreads();
     if (quarter == 0) {
 #pragma unroll
-        for (int g = 0; g < G; ++g)
+        for (int g = 0; g < G; ++g) {
 #pragma unroll
-            for (int q = 1; q < kScoreSplit; ++q) acc[g] += sums[((q - 1) * G + g) * kScoreTile + key];
-        // raw scores out, and this tile's sum / sum of squares per query head (double, fixed order)
-        const int Hq = c.n_kv_heads * G;
-        float *rw = a.raw + (((int64_t)l * c.n_seqs + s) * Hq + (int64_t)h * G) * c.max_seq_len + n;
+            for (int q = 1; q < kScoreSplit; ++q) acc[g] += sums[((q - 1) * G + g) * kPartKeys + key];
+            if (valid) {
+                rw[(int64_t)g * c.max_seq_len + n] = acc[g];
+                v1[g] += (double)acc[g];
+                v2[g] += (double)acc[g] * (double)acc[g];
+            }
+        }
+    }
+    }
+    // the tile's sum and sum of squares per query head (double, fixed order)
+    if (quarter == 0) {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            if (valid) rw[(int64_t)g * c.max_seq_len] = acc[g];
-            double v1 = valid ? (double)acc[g] : 0.0, v2 = v1 * v1;
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) {
-                v1 += __shfl_xor(v1, o, 64);
-                v2 += __shfl_xor(v2, o, 64);
+                v1[g] += __shfl_xor(v1[g], o, 64);
+                v2[g] += __shfl_xor(v2[g], o, 64);
             }
             if ((tid & 63) == 0) {
-                red[tid >> 6][g] = v1;
-                red[tid >> 6][G + g] = v2;
+                red[tid >> 6][g] = v1[g];
+                red[tid >> 6][G + g] = v2[g];
             }
         }
     }
     __syncthreads();
-    if (tid < 2 * G) {
-        double v = red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid];
-        a.partials[(inst * a.n_tiles + tile) * (2 * G) + tid] = v;
-    }
+    if (tid < 2 * G) a.partials[(inst * a.n_tiles + tile) * (2 * G) + tid] = red[0][tid] + red[1][tid];
 }
 
 struct StatsArgs {
@@ -400,19 +420,19 @@ __global__ __launch_bounds__(256) void final_kernel(FinalArgs a)
 template <int G, typename T>
 tri_status launch_score_kernel(const tri_model &m, const ScoreArgs &sa, dim3 grid, hipStream_t st)
 {
-    const size_t lds = (size_t)kScoreTile * (Elem<T>::kRow16 + 1) * 16;
+    const size_t lds = (size_t)kPartKeys * (Elem<T>::kRow16 + 1) * 16;
     if (m.pairs == TRI_PAIR_INTERLEAVED) {
         auto kern = score_kernel<G, T, TRI_PAIR_INTERLEAVED>;
         if (lds > 48 * 1024 &&
             hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
             return hip_status("hipFuncSetAttribute(score_kernel)");
-        hipLaunchKernelGGL(kern, grid, dim3(kScoreTile * kScoreSplit), lds, st, sa);
+        hipLaunchKernelGGL(kern, grid, dim3(kScoreThreads), lds, st, sa);
     } else {
         auto kern = score_kernel<G, T, TRI_PAIR_HALF>;
         if (lds > 48 * 1024 &&
             hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
             return hip_status("hipFuncSetAttribute(score_kernel)");
-        hipLaunchKernelGGL(kern, grid, dim3(kScoreTile * kScoreSplit), lds, st, sa);
+        hipLaunchKernelGGL(kern, grid, dim3(kScoreThreads), lds, st, sa);
     }
     return hip_status("score_kernel");
 }
@@ -430,7 +450,17 @@ tri_status launch_score_g(const tri_model &m, const tri_cache &c, ScoreArgs sa, 
 {
     const int n_inst = m.n_layers * c.n_seqs * m.n_kv_heads;
     const bool fast = mfma_path(c, G);
-    const int tile_keys = fast ? sa.chunk_keys : kScoreTile;
+    // generic kernel: one part per workgroup where the moments of so many tiles have room (in the area of the phasor table, which is not
+    // needed then; the workspace's own has an entry per 256 keys): one head of 4096 keys, a step, 24.6 -> 23.4 us
+    int tile_keys = fast ? sa.chunk_keys : kScoreTile;
+    if (!fast) {
+        const int64_t parts = (c.max_seq_len + kPartKeys - 1) / kPartKeys;
+        if (n_inst * parts * 2 * G * (int64_t)sizeof(double) <= kPhasorAreaBytes) {
+            tile_keys = kPartKeys;
+            sa.partials = reinterpret_cast<double *>(const_cast<uint4 *>(sa.phasors));
+        }
+        sa.chunk_keys = tile_keys;
+    }
     sa.n_tiles = (c.max_seq_len + tile_keys - 1) / tile_keys;
     tri_status rc = TRI_OK;
     hipEvent_t ev0, ev1;
@@ -450,6 +480,7 @@ tri_status launch_score_g(const tri_model &m, const tri_cache &c, ScoreArgs sa, 
     if (moments) {
         moments->n_tiles = sa.n_tiles;
         moments->tile_keys = tile_keys;
+        moments->partials = sa.partials;
     }
     if (!final_out) return rc;   // fused step: the selection forms the statistics from the moments itself
     StatsArgs ta{sa.partials, const_cast<double *>(fa.stats), c.seq_len, c.n_seqs, m.n_kv_heads, sa.n_tiles, G,
@@ -497,7 +528,7 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
                         float *raw_out, char *ws, const Workspace &wl, MomentLayout *moments, hipStream_t st)
 {
     const int G = m.n_q_heads / m.n_kv_heads;
-    if (moments) *moments = MomentLayout{1, 1};
+    if (moments) *moments = MomentLayout{1, 1, reinterpret_cast<const double *>(ws + wl.partials)};
     if (c.max_seq_len <= 0 || c.n_seqs <= 0) return TRI_OK;
     FoldArgs fo{};
     fo.centers = centers;
