@@ -623,7 +623,9 @@ tri_status launch_select(const tri_model &m, const float *final_scores, float *r
     int n_cu = 0;
     const tri_status rcu = device_cus(&n_cu);
     if (rcu != TRI_OK) return rcu;
-    if (!final_scores && fill && fill_taken && c.max_seq_len <= 4096 && budget <= 2048 && n_inst <= 8 * n_cu) {
+    // (not where the new lengths are written over the old ones, which other workgroups of the launch still read)
+    const bool aliased = fill && fill->new_seq_len && fill->new_seq_len < c.seq_len + c.n_seqs && c.seq_len < fill->new_seq_len + c.n_seqs;
+    if (!final_scores && fill && fill_taken && !aliased && c.max_seq_len <= 4096 && budget <= 2048 && n_inst <= 8 * n_cu) {
         sa.fa = FillArgs{make_view(m, c), fill->new_seq_len, budget, c.dtype == TRI_BF16 ? 2 : 4,
                          kHeadDim * (c.dtype == TRI_BF16 ? 2 : 4) / 16};
         sa.fill = 1;
