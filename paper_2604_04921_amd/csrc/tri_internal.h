@@ -60,8 +60,8 @@ __device__ __forceinline__ ZParams z_params(double mu, double inv_sigma)
 __device__ __forceinline__ float z_score(float raw, const ZParams &p) { return ((raw - p.mu_hi) - p.mu_lo) * p.rs; }
 
 // Section 4.3, mu_g and 1/sigma_g of one query head from the per-tile sums of its raw scores and of their squares.
-// The tiles are added in sixteen interleaved groups (one thread each) and the groups in order, in stats_kernel and
-// in the selection kernels (block_stats) alike, so both get the same bits.
+// The tiles are added in sixteen interleaved groups (one thread each) and the groups in order, by block_stats for the final scores
+// and for the selection alike, so both get the same bits.
 __device__ __forceinline__ void moments_to_stats(double s1, double s2, int N, double *mean_out, double *rsig_out)
 {
     double mean = 0.0, rsig = 0.0;
@@ -166,7 +166,7 @@ struct Workspace {
     size_t table;      // float  [L][S][Hkv][F][3][G]: folded centre table
     size_t work;       // int32: item counter and work list of the MFMA score kernels
     size_t partials;   // double [L][S][Hkv][n_tiles][2G]: per-tile sum and sum of squares
-    size_t stats;      // double [L][S][Hkv][G][2]: mean and 1/sigma
+    size_t unused;     // (double [L][S][Hkv][G][2]: the total is what callers' workspaces were sized for)
     size_t raw;        // float  [L][S][Hq][Nmax] (used when the caller passes no raw_out)
     size_t final_;     // [L][S][Hkv][Nmax] words (tri_compress_step only): histograms of long sequences' chunks
     size_t total;
@@ -200,16 +200,15 @@ struct MomentLayout {
 };
 tri_status launch_score(const tri_model &m, const float *centers, const tri_cache &c, float *final_out,
                         float *raw_out, char *ws, const Workspace &wl, MomentLayout *moments, hipStream_t st);
-// final_scores given: select on them; else form them from the raw scores (which may be overwritten) and either stats
-// (mean, 1/sigma) or, when partials is given, the per-tile moments.  hist: the workspace's `final_` area, for the histograms
+// final_scores given: select on them; else form them from the raw scores (which may be overwritten) and the per-tile
+// moments.  hist: the workspace's `final_` area, for the histograms
 // of long sequences' chunks (at most one word per key and 1024 words per 2048 keys).
 // fill given and taken (*fill_taken set): the selection's workgroups also evict their head-instances in place, as
 // launch_compact_fill would afterwards (short sequences only; else the caller launches the fill itself)
 struct FillTail {
     int32_t *new_seq_len;   // [S] or NULL
 };
-tri_status launch_select(const tri_model &m, const float *final_scores, float *raw, const double *stats,
-                         const double *partials, MomentLayout moments, uint32_t *hist, const tri_cache &c,
+tri_status launch_select(const tri_model &m, const float *final_scores, float *raw, const double *partials, MomentLayout moments, uint32_t *hist, const tri_cache &c,
                          int32_t budget, int32_t *kept_idx, int32_t *kept_cnt, hipStream_t st,
                          const FillTail *fill = nullptr, bool *fill_taken = nullptr);
 tri_status launch_compact(const tri_model &m, const tri_cache &src, const tri_cache &dst, int32_t budget,

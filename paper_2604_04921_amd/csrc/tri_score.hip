@@ -323,63 +323,32 @@ __global__ __launch_bounds__(kScoreThreads, 4) void score_kernel(ScoreArgs a)
     if (tid < 2 * G) a.partials[(inst * a.n_tiles + tile) * (2 * G) + tid] = red[0][tid] + red[1][tid];
 }
 
-struct StatsArgs {
-    const double *partials;
-    double *stats;  // [inst][G][2] = (mean, 1/sigma)
-    const int32_t *seq_len;
-    int32_t n_seqs, n_kv_heads, n_tiles, G, tile_keys, max_seq_len;
-};
-
-// grid (instances), block 256: Section 4.3, mu_g and sigma_g over the N keys (population sigma).
-__global__ __launch_bounds__(256) void stats_kernel(StatsArgs a)
-{
-    __shared__ double part[16][16];
-    const int inst = blockIdx.x;
-    const int s = (inst / a.n_kv_heads) % a.n_seqs;
-    const int N = clamp_len(a.seq_len[s], a.max_seq_len);
-    const int tiles = (N + a.tile_keys - 1) / a.tile_keys;
-    const int i = threadIdx.x & 15, r = threadIdx.x >> 4;
-    const int W = 2 * a.G;
-    double acc = 0.0;
-    if (i < W)
-        for (int t = r; t < tiles; t += 16) acc += a.partials[((int64_t)inst * a.n_tiles + t) * W + i];
-    part[r][i] = acc;
-    __syncthreads();
-    if (threadIdx.x < a.G) {   // (the same order of additions as block_stats)
-        const int g = threadIdx.x;
-        double s1 = 0.0, s2 = 0.0;
-        for (int k = 0; k < 16; ++k) {
-            s1 += part[k][g];
-            s2 += part[k][a.G + g];
-        }
-        double mean, rsig;
-        moments_to_stats(s1, s2, N, &mean, &rsig);
-        a.stats[((int64_t)inst * a.G + g) * 2 + 0] = mean;
-        a.stats[((int64_t)inst * a.G + g) * 2 + 1] = rsig;
-    }
-}
-
 struct FinalArgs {
     const float *raw;     // [inst][G][Nmax]  (instance-major because Hq = Hkv * G)
-    const double *stats;  // [inst][G][2]
     float *final_;        // [inst][Nmax]
     const int32_t *seq_len;
     int32_t n_seqs, n_kv_heads, max_seq_len;
     int32_t key_blocks;   // workgroups per head-instance
+    const double *partials;   // [inst][n_tiles][2G]: moments of tile_keys keys each
+    int32_t n_tiles, tile_keys;
 };
 
-// grid (instances * ceil(Nmax/1024)), block 256: S_final(k) = max_g (S~(g)(k) - mu_g) / sigma_g.  Four keys per thread, all their
-// scores loaded before the first is used: rows of an odd length, which allow no 16-byte loads, were read one score at a time
-// (24 x 5 x 8 head-instances of up to 20011 keys, scores: 834 -> 806 us).  (The statistics formed here as well, instead of by
-// stats_kernel: 288 x 2176 keys equal, 9216 x 2176 76 + 9 -> 93 us.)
+// grid (instances * ceil(Nmax/1024)), block 256: Section 4.3, mu_g and sigma_g over the N keys (population sigma) from the moments, which
+// every workgroup adds up for itself, and S_final(k) = max_g (S~(g)(k) - mu_g) / sigma_g.  Four keys per thread, all their scores
+// and the moments loaded before the first is used: rows of an odd length read one score at a time took 24 x 5 x 8 head-instances of
+// up to 20011 keys, scores, 834 us against 806.  The statistics in a launch of their own ahead of this one: scores and selection of
+// 288 x 2176 keys 76.0 us against 74.1, 32 x 2176 28.0 / 26.0, 2304 x 2176 336.8 / 334.4, 9216 1323.5 / 1322.2.
 template <int G>
 __global__ __launch_bounds__(256) void final_kernel(FinalArgs a)
 {
+    __shared__ double zst[2 * G], zpart[32 * G];
     const int inst = blockIdx.x / a.key_blocks, kb = blockIdx.x - inst * a.key_blocks;
     const int s = (inst / a.n_kv_heads) % a.n_seqs;
+    const double *pt = a.partials + (int64_t)inst * a.n_tiles * (2 * G);
+    const Moments ahead = moments_ahead<G>(pt, a.n_tiles, threadIdx.x);
     const int N = clamp_len(a.seq_len[s], a.max_seq_len);
-    const int n = (kb * 256 + threadIdx.x) * 4;
-    if (n >= N) return;
+    if (kb * 1024 >= N) return;
+    const int n0 = (kb * 256 + threadIdx.x) * 4, n = min(n0, N - 1);   // (every thread takes part in block_stats)
     // 16-byte accesses within a row (both arrays may be the caller's, who owes floats' alignment only: the hardware asks for no more)
     typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
     const bool vec = n + 3 < a.max_seq_len;
@@ -396,11 +365,12 @@ __global__ __launch_bounds__(256) void final_kernel(FinalArgs a)
             for (int k = 0; k < 4; ++k) v[g][k] = row[min(n + k, N - 1)];
         }
     }
-    const double *st = a.stats + (int64_t)inst * G * 2;
+    block_stats<G>(ahead, pt, (N + a.tile_keys - 1) / a.tile_keys, N, threadIdx.x, zpart, zst);
+    if (n0 >= N) return;
     float best[4];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-        const ZParams zp = z_params(st[2 * g], st[2 * g + 1]);
+        const ZParams zp = z_params(zst[2 * g], zst[2 * g + 1]);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const float z = z_score(v[g][k], zp);
@@ -483,17 +453,17 @@ tri_status launch_score_g(const tri_model &m, const tri_cache &c, ScoreArgs sa, 
         moments->partials = sa.partials;
     }
     if (!final_out) return rc;   // fused step: the selection forms the statistics from the moments itself
-    StatsArgs ta{sa.partials, const_cast<double *>(fa.stats), c.seq_len, c.n_seqs, m.n_kv_heads, sa.n_tiles, G,
-                 tile_keys, c.max_seq_len};
-    hipLaunchKernelGGL(stats_kernel, dim3(n_inst), dim3(256), 0, st, ta);
-    if ((rc = hip_status("stats_kernel")) != TRI_OK) return rc;
     FinalArgs fb = fa;
     fb.key_blocks = (c.max_seq_len + 1023) / 1024;
     if ((int64_t)fb.key_blocks * n_inst > (int64_t)0x7fffffff) {
         set_error("tri_score: %d head-instances x %d key blocks exceed the grid", n_inst, fb.key_blocks);
         return TRI_ERR_UNSUPPORTED;
     }
-    hipLaunchKernelGGL(final_kernel<G>, dim3((uint32_t)((int64_t)fb.key_blocks * n_inst)), dim3(256), 0, st, fb);
+    const dim3 final_grid((uint32_t)((int64_t)fb.key_blocks * n_inst));
+    fb.partials = sa.partials;
+    fb.n_tiles = sa.n_tiles;
+    fb.tile_keys = tile_keys;
+    hipLaunchKernelGGL(final_kernel<G>, final_grid, dim3(256), 0, st, fb);
     rc = hip_status("final_kernel");
     return rc;
 }
@@ -586,7 +556,6 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     sa.chunk_keys = chunk_keys;
     FinalArgs fa{};
     fa.raw = sa.raw;
-    fa.stats = reinterpret_cast<double *>(ws + wl.stats);
     fa.final_ = final_out;
     fa.seq_len = c.seq_len;
     fa.n_seqs = c.n_seqs;

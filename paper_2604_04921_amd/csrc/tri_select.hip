@@ -33,10 +33,9 @@ __device__ __forceinline__ uint32_t order_key(float x)
 }
 
 struct SelectArgs {
-    const float *final_;   // [inst][Nmax] final scores, or NULL when raw + stats are given
+    const float *final_;   // [inst][Nmax] final scores, or NULL when raw scores and their moments are given
     float *raw;            // [inst][G][Nmax]; keys_kernel leaves a head-instance's integer keys in its first row
-    const double *stats;   // [inst][G][2] = (mean, 1/sigma); unused when partials is given
-    const double *partials;   // [inst][n_tiles][2G] per-tile sum and sum of squares of the raw scores, or NULL
+    const double *partials;   // [inst][n_tiles][2G] per-tile sum and sum of squares of the raw scores
     int32_t n_tiles, tile_keys;
     uint32_t *hist;        // [inst][n_chunks][kSelBins / 2]: histograms of the keys' chunks, two 16-bit counts per word
     const int32_t *seq_len;
@@ -67,24 +66,19 @@ __device__ __forceinline__ float bin_place(float score) { return fmaf(score, 128
 __device__ __forceinline__ int linear_bin(float score) { return (int)__builtin_amdgcn_fmed3f(bin_place(score), 0.0f, 2047.0f); }
 __device__ __forceinline__ int linear_bin(uint32_t u) { return linear_bin(key_to_float(u)); }
 
-// Mean and 1/sigma of a head-instance's heads, as every kernel here takes them: from the moments (block_stats; every thread
-// of the workgroup calls) or ready-made.
+// Mean and 1/sigma of a head-instance's heads from the moments (block_stats; every thread of the workgroup calls).
 template <int G>
 __device__ __forceinline__ Moments load_moments(const SelectArgs &a, int inst, int tid)
 {
-    return a.partials ? moments_ahead<G>(a.partials + (int64_t)inst * a.n_tiles * (2 * G), a.n_tiles, tid) : Moments{};
+    return moments_ahead<G>(a.partials + (int64_t)inst * a.n_tiles * (2 * G), a.n_tiles, tid);
 }
 template <int G>
 __device__ __forceinline__ void load_zparams(const SelectArgs &a, const Moments &ahead, int inst, int N, int tid, double *zpart, double *zst,
                                              ZParams (&zp)[G])
 {
-    if (a.partials)   // uniform over the launch
-        block_stats<G>(ahead, a.partials + (int64_t)inst * a.n_tiles * (2 * G), (N + a.tile_keys - 1) / a.tile_keys, N, tid,
-                       zpart, zst);
+    block_stats<G>(ahead, a.partials + (int64_t)inst * a.n_tiles * (2 * G), (N + a.tile_keys - 1) / a.tile_keys, N, tid, zpart, zst);
 #pragma unroll
-    for (int g = 0; g < G; ++g)
-        zp[g] = a.partials ? z_params(zst[2 * g], zst[2 * g + 1])
-                           : z_params(a.stats[((int64_t)inst * G + g) * 2], a.stats[((int64_t)inst * G + g) * 2 + 1]);
+    for (int g = 0; g < G; ++g) zp[g] = z_params(zst[2 * g], zst[2 * g + 1]);
 }
 
 // The threshold among the m candidates (keys of the bin that holds the B-th largest, zeros behind them up to
@@ -605,15 +599,15 @@ tri_status launch_select_g(const SelectArgs &sa, int n_inst, int n_cu, hipStream
 
 }  // namespace
 
-tri_status launch_select(const tri_model &m, const float *final_scores, float *raw, const double *stats,
-                         const double *partials, MomentLayout moments, uint32_t *hist, const tri_cache &c,
+tri_status launch_select(const tri_model &m, const float *final_scores, float *raw, const double *partials,
+                         MomentLayout moments, uint32_t *hist, const tri_cache &c,
                          int32_t budget, int32_t *kept_idx, int32_t *kept_cnt, hipStream_t st, const FillTail *fill,
                          bool *fill_taken)
 {
     if (fill_taken) *fill_taken = false;
     const int n_inst = m.n_layers * c.n_seqs * m.n_kv_heads;
     if (n_inst <= 0) return TRI_OK;
-    SelectArgs sa{final_scores, raw, stats, partials, moments.n_tiles, moments.tile_keys, hist, c.seq_len, kept_idx,
+    SelectArgs sa{final_scores, raw, partials, moments.n_tiles, moments.tile_keys, hist, c.seq_len, kept_idx,
                   kept_cnt, c.n_seqs, m.n_kv_heads, c.max_seq_len, budget, 1, 1, m.head_budgets};
     sa.fill = 0;
     // Short sequences: the eviction in place rides along (its move list takes the keys' place in LDS) -- on small batches, whose
