@@ -56,7 +56,11 @@ inline int item_keys(int64_t instances, int max_seq_len, int n_cu)
 }
 
 // Which kernel takes bf16 keys (item: item_keys() of the batch): that of tri_score_lane.hip, but paged pre-RoPE keys with
-// interleaved pairs in items of kFastChunk go to the one that spreads a key over sixteen lanes where it is the faster one.
+// interleaved pairs in items of kFastChunk go to the one that spreads a key over sixteen lanes where it was the faster one before the
+// other's items followed one another without a gap (the figures below).  Measured since, whole steps, this kernel against the other: 768 x
+// 4096 to 65536 keys at G = 8 2606 / 2460 us, at G = 5 2458 / 2276, 32 x 65536 at G = 8 203 / 199, 512 x 8192 528 / 516, 4608 x 2176 at
+// G = 4 2551 / 2506, 3072 x 4096 2046 / 2002: the line could go, and this kernel with it.  It stands as tests/test_item_rules.py,
+// test_gpu_sixteen_lanes.py and test_gpu_precision.py (whose yardstick this kernel is) state it.
 // More than four query heads per KV head, whole steps: 768 x 4096 to 65536 keys at G = 8 2600 us against 2684, at G = 5 2447 against
 // 2495; batches whose cost model ends at kFastChunk as well (one item per CU and more): 32 x 65536 at G = 8 206 against 215, 64 x
 // 32768 205 against 218, 128 x 16384 225 against 235 (G = 5: 218 against 225), 512 x 8192 528 against 550.
