@@ -21,7 +21,7 @@
  *     host before anything is enqueued; on error nothing is enqueued.
  *   - Return value: TRI_OK or a negative tri_status.  Nothing aborts or throws.
  *     tri_last_error() returns a static string describing the last failure on the calling thread.
- *   - Non-finite key or statistics values: behaviour undefined.
+ *   - Non-finite key or statistics values: scores unspecified; the kept set is a set of distinct slots of the sequence all the same.
  *   - Built geometries: head_dim 128 (64 frequency bands) and n_q_heads / n_kv_heads (= G) from 1 to 8; anything
  *     else returns TRI_ERR_UNSUPPORTED.  n_layers and n_seqs * n_kv_heads must each be below 65536, and
  *     head-instances x max(max_seq_len / 256, budget / 8) below 2^31 per call (TRI_ERR_UNSUPPORTED otherwise: split
@@ -180,7 +180,7 @@ tri_status tri_score(const tri_model *model, const float *centers, const tri_cac
 
 /*
  * Step 3: per head-instance the min(N_s, budget) keys with the largest final score, equal
- * scores resolved in favour of the lower slot index (-0.0 equals +0.0).
+ * scores resolved in favour of the lower slot index (-0.0 equals +0.0; a NaN counts as +inf).
  *   final_scores  device [n_layers][n_seqs][n_kv_heads][max_seq_len] float
  *   kept_idx      device [n_layers][n_seqs][n_kv_heads][budget] int32: kept slots, ascending;
  *                 entries past the count are not written

@@ -25,10 +25,14 @@ constexpr int kSelSmallThreads = 256;   // many short sequences
 constexpr int kSelHeldKeys = 32768;     // keys held in LDS at most
 constexpr int kSelBins = 2048;          // linear score bins of the histogram pass
 
-// Monotone map float -> uint32 (larger float <=> larger key); -0.0 is folded onto +0.0.
+// A score as the selection ranks it, before its key and its bin are formed: -0.0 is folded onto +0.0, and one that is no number counts as
+// +inf (its key alone would lie above every number's, its bin below: passes that disagree about a score leave entries of the kept set
+// unwritten).
+__device__ __forceinline__ float ranked(float score) { return fminf(score + 0.0f, __builtin_inff()); }
+// Monotone map float -> uint32 (larger float <=> larger key) of a ranked score.
 __device__ __forceinline__ uint32_t order_key(float x)
 {
-    const uint32_t b = __float_as_uint(x + 0.0f);   // (-0 + 0 = +0)
+    const uint32_t b = __float_as_uint(x);
     return b ^ ((uint32_t)((int32_t)b >> 31) | 0x80000000u);
 }
 
@@ -172,6 +176,7 @@ __global__ __launch_bounds__(kKeysThreads) void keys_kernel(SelectArgs a)
             float f = z_score(v[0][i], zp[0]);
 #pragma unroll
             for (int g = 1; g < G; ++g) f = fmaxf(f, z_score(v[g][i], zp[g]));
+            f = ranked(f);
             u[i] = order_key(f);
             bin[i] = linear_bin(f);
         }
@@ -302,7 +307,7 @@ __global__ __launch_bounds__(THREADS, HELD ? (THREADS == kSelThreads ? 4 : 5) : 
     }
     __syncthreads();
 
-    // ---- keys into LDS (a slot past the end, up to the row's, holds key 0, which no finite score maps to and which lies below
+    // ---- keys into LDS (a slot past the end, up to the row's, holds key 0, which no score maps to and which lies below
     // every threshold), histogram of their bins
     if constexpr (HELD) {
         for (int n0 = 0; n0 < N; n0 += kStep) {
@@ -317,6 +322,7 @@ __global__ __launch_bounds__(THREADS, HELD ? (THREADS == kSelThreads ? 4 : 5) : 
 #pragma unroll
                     for (int g = 1; g < kHeads; ++g) f = fmaxf(f, z_score(cur[g][i], zp[g]));
                 }
+                f = ranked(f);
                 u[i] = src_slot(n0, i) < N ? order_key(f) : 0u;
                 if (src_slot(n0, i) < N) atomicAdd(&bins[linear_bin(f)], 1u);
             }
@@ -344,7 +350,7 @@ __global__ __launch_bounds__(THREADS, HELD ? (THREADS == kSelThreads ? 4 : 5) : 
             if constexpr (SRC == 0) {
                 const float4v t = *reinterpret_cast<const float4v *>(src + n);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) u[i] = order_key(t[i]);
+                for (int i = 0; i < 4; ++i) u[i] = order_key(ranked(t[i]));
             } else {
                 const word4v t = *reinterpret_cast<const word4v *>(ks + n);
 #pragma unroll
@@ -354,7 +360,7 @@ __global__ __launch_bounds__(THREADS, HELD ? (THREADS == kSelThreads ? 4 : 5) : 
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int n = min(n0 + 4 * lane + i, N - 1);
-                u[i] = SRC == 0 ? order_key(src[n]) : ks[n];
+                u[i] = SRC == 0 ? order_key(ranked(src[n])) : ks[n];
             }
         }
     };
@@ -537,7 +543,7 @@ __global__ __launch_bounds__(THREADS, HELD ? (THREADS == kSelThreads ? 4 : 5) : 
         for (int i = 0; i < 4; ++i) {
             const bool gt = u[i] > thr, eq = u[i] == thr;
             const uint32_t dst = g_at + min(e_at, need);
-            if ((gt || (eq && e_at < need)) && dst < (uint32_t)B) out[dst] = n0 + 4 * lane + i;   // (below B unless scores are NaN)
+            if ((gt || (eq && e_at < need)) && dst < (uint32_t)B) out[dst] = n0 + 4 * lane + i;
             g_at += gt ? 1u : 0u;
             e_at += eq ? 1u : 0u;
         }
