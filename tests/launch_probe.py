@@ -46,7 +46,7 @@ def call(T, lib, c):
     if c["entry"] == "centers":
         return lib.tri_build_centers(m, ANY, g("dtype", 1), g("tokens", 1), ANY, None)
     cache = ctypes.byref(T.TriCache(ANY, ANY, ANY, g("dtype", 1), g("seqs", 1), ANY, ANY, n, block, ANY if block else 0,
-                                    -(-n // block) if block else 0, 1 << 12, 1 << 12, 1 << 12, 128, 0, 0, 0, g("rotated", 0)))
+                                    -(-n // block) if block else 0, 1 << 12, 1 << 12, 1 << 12, g("stride", 128), 0, 0, 0, g("rotated", 0)))
     if c["entry"] == "select":
         return lib.tri_select_topk(m, ANY + g("offset", 0), cache, budget, ANY, ANY, None, 0, None)
     ws = lib.tri_workspace_size(m, cache, budget)
