@@ -416,23 +416,26 @@ bool mfma_path(const tri_cache &c, int G)
 
 template <int G>
 tri_status launch_score_g(const tri_model &m, const tri_cache &c, ScoreArgs sa, const FinalArgs &fa,
-                          float *final_out, MomentLayout *moments, bool lane_kernel, hipStream_t st)
+                          float *final_out, MomentLayout *moments, bool lane_kernel, int n_cu, hipStream_t st)
 {
     const int n_inst = m.n_layers * c.n_seqs * m.n_kv_heads;
     const bool fast = mfma_path(c, G);
-    // generic kernel: one part per workgroup where the moments of so many tiles have room (in the area of the phasor table, which is not
-    // needed then; the workspace's own has an entry per 256 keys): one head of 4096 keys, a step, 24.6 -> 23.4 us
+    // Generic kernel: one part per workgroup where tiles of two would leave CUs without any (fp32, scores: 8 heads of 8192 keys, a tile
+    // per CU, 19.3 us in tiles of two parts, 18.1 in tiles of one; one of 32768 at G = 8 26.1 / 22.6; a step on one of 4096 26.1 /
+    // 22.9).  With more of them there are only more moments to add up (8 heads of 12288 23.8 / 25.1; one of 98304 at G = 8 36.0 /
+    // 39.8, of 131072 39.8 / 47.0).  The moments of so many tiles lie in the area of the phasor table, which is not needed then: the
+    // workspace's own has an entry per 256 keys.
+    tri_status rc = TRI_OK;
     int tile_keys = fast ? sa.chunk_keys : kScoreTile;
     if (!fast) {
-        const int64_t parts = (c.max_seq_len + kPartKeys - 1) / kPartKeys;
-        if (n_inst * parts * 2 * G * (int64_t)sizeof(double) <= kPhasorAreaBytes) {
+        const int64_t parts = (c.max_seq_len + kPartKeys - 1) / kPartKeys, tiles = (c.max_seq_len + kScoreTile - 1) / kScoreTile;
+        if (n_inst * tiles <= n_cu && n_inst * parts * 2 * G * (int64_t)sizeof(double) <= kPhasorAreaBytes) {
             tile_keys = kPartKeys;
             sa.partials = reinterpret_cast<double *>(const_cast<uint4 *>(sa.phasors));
         }
         sa.chunk_keys = tile_keys;
     }
     sa.n_tiles = (c.max_seq_len + tile_keys - 1) / tile_keys;
-    tri_status rc = TRI_OK;
     hipEvent_t ev0, ev1;
     const bool timed = timing_next(&ev0, &ev1);
     if (timed) (void)hipEventRecord(ev0, st);
@@ -562,14 +565,14 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     fa.n_kv_heads = m.n_kv_heads;
     fa.max_seq_len = c.max_seq_len;
     switch (G) {
-        case 1: return launch_score_g<1>(m, c, sa, fa, final_out, moments, lane_kernel, st);
-        case 2: return launch_score_g<2>(m, c, sa, fa, final_out, moments, lane_kernel, st);
-        case 3: return launch_score_g<3>(m, c, sa, fa, final_out, moments, lane_kernel, st);
-        case 4: return launch_score_g<4>(m, c, sa, fa, final_out, moments, lane_kernel, st);
-        case 5: return launch_score_g<5>(m, c, sa, fa, final_out, moments, lane_kernel, st);
-        case 6: return launch_score_g<6>(m, c, sa, fa, final_out, moments, lane_kernel, st);
-        case 7: return launch_score_g<7>(m, c, sa, fa, final_out, moments, lane_kernel, st);
-        case 8: return launch_score_g<8>(m, c, sa, fa, final_out, moments, lane_kernel, st);
+        case 1: return launch_score_g<1>(m, c, sa, fa, final_out, moments, lane_kernel, n_cu, st);
+        case 2: return launch_score_g<2>(m, c, sa, fa, final_out, moments, lane_kernel, n_cu, st);
+        case 3: return launch_score_g<3>(m, c, sa, fa, final_out, moments, lane_kernel, n_cu, st);
+        case 4: return launch_score_g<4>(m, c, sa, fa, final_out, moments, lane_kernel, n_cu, st);
+        case 5: return launch_score_g<5>(m, c, sa, fa, final_out, moments, lane_kernel, n_cu, st);
+        case 6: return launch_score_g<6>(m, c, sa, fa, final_out, moments, lane_kernel, n_cu, st);
+        case 7: return launch_score_g<7>(m, c, sa, fa, final_out, moments, lane_kernel, n_cu, st);
+        case 8: return launch_score_g<8>(m, c, sa, fa, final_out, moments, lane_kernel, n_cu, st);
     }
     set_error("group size %d not built (1 to 8)", G);
     return TRI_ERR_UNSUPPORTED;
