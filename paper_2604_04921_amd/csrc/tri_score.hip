@@ -184,6 +184,7 @@ __global__ __launch_bounds__(kScoreThreads, 4) void score_kernel(ScoreArgs a)
     extern __shared__ uint4 lds[];        // a part's keys; later its quarters' sums
     __shared__ __align__(16) float tab[kBands * 3 * G];
     __shared__ double rev[kBands];
+    __shared__ int64_t k_at[kScoreTile], p_at[kScoreTile];   // paged: where the tile's keys and positions are
     __shared__ double red[kPartKeys / 64][2 * G];
 
     const CacheView &c = a.c;
@@ -198,6 +199,21 @@ __global__ __launch_bounds__(kScoreThreads, 4) void score_kernel(ScoreArgs a)
     const int64_t inst = ((int64_t)l * c.n_seqs + s) * c.n_kv_heads + h;
 
     const T *kbase = (const T *)c.k;
+    // Contiguous keys are a product away from the first; paged ones are looked up by one thread each.  (A lookup and two 64-bit products
+    // by each of the sixteen or thirty-two threads that load a row: 288 heads of 16384 bf16 keys in blocks of 8, scores, 430 us at G = 1
+    // against 311 now, 525 / 410 at G = 4; fp32 ones 676 / 528 and 785 / 597.)
+    const bool paged = c.block_shift >= 0;
+    const int64_t k_base = (int64_t)l * c.stride_layer + (int64_t)h * c.stride_head + (paged ? 0 : (int64_t)s * c.stride_sb);
+    const int64_t p_base = (int64_t)l * c.pos_stride_layer + (int64_t)h * c.pos_stride_head + (paged ? 0 : (int64_t)s * c.pos_stride_sb);
+    if (paged) {
+        const int n = n0 + tid;
+        if (tid < kScoreTile && n < n1) {
+            const int b = c.block_table[(int64_t)s * c.max_blocks + (n >> c.block_shift)], in = n & ((1 << c.block_shift) - 1);
+            k_at[tid] = (int64_t)b * c.stride_sb + slot_offset(c, in);
+            p_at[tid] = (int64_t)b * c.pos_stride_sb + in;
+        }
+        __syncthreads();
+    }
     uint4 kd[kLoads];
     int p_next = 0;
     auto load = [&](int m0) {
@@ -205,9 +221,10 @@ __global__ __launch_bounds__(kScoreThreads, 4) void score_kernel(ScoreArgs a)
         for (int i = 0; i < kLoads; ++i) {
             const int ci = i * kScoreThreads + tid, n = m0 + ci / ROW16;
             kd[i] = make_uint4(0u, 0u, 0u, 0u);
-            if (n < N) kd[i] = reinterpret_cast<const uint4 *>(kbase + kv_offset(c, l, s, h, n))[ci % ROW16];
+            if (n < N) kd[i] = reinterpret_cast<const uint4 *>(kbase + k_base + (paged ? k_at[n - n0] : slot_offset(c, n)))[ci % ROW16];
         }
-        if (m0 + key < N && !c.k_rotated) p_next = c.pos[pos_offset(c, l, s, h, m0 + key)];   // a post-RoPE key needs no rotation
+        const int n = m0 + key;
+        if (n < N && !c.k_rotated) p_next = c.pos[p_base + (paged ? p_at[n - n0] : n)];   // a post-RoPE key needs no rotation
     };
     load(n0);
     {
