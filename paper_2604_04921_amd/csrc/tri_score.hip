@@ -441,16 +441,17 @@ tri_status launch_score_g(const tri_model &m, const tri_cache &c, ScoreArgs sa, 
 {
     const int n_inst = m.n_layers * c.n_seqs * m.n_kv_heads;
     const bool fast = mfma_path(c, G);
-    // Generic kernel: one part per workgroup where tiles of two would leave CUs without any (fp32, scores: 8 heads of 8192 keys, a tile
-    // per CU, 19.3 us in tiles of two parts, 18.1 in tiles of one; one of 32768 at G = 8 26.1 / 22.6; a step on one of 4096 26.1 /
-    // 22.9).  With more of them there are only more moments to add up (8 heads of 12288 23.8 / 25.1; one of 98304 at G = 8 36.0 /
-    // 39.8, of 131072 39.8 / 47.0).  The moments of so many tiles lie in the area of the phasor table, which is not needed then: the
-    // workspace's own has an entry per 256 keys.
+    // Generic kernel: one part per workgroup where tiles of two would leave CUs without any, or a few with twice the others' (scores: 8
+    // heads of 8192 fp32 keys, a tile per CU, 19.4 us in tiles of two parts, 18.4 in tiles of one; one of 4096, a step, 26.2 / 22.9; 9 / 8 of
+    // a tile: 32 bf16 heads of 2176 in blocks of 8, a step, 30.4 / 29.5, one of 80000 23.4 / 22.7, fp32 ones at G = 1 18.8 / 18.2, at G = 8 28.3 /
+    // 29.8).  With more of them there are only more moments to add up (8 fp32 heads of 12288 23.9 / 24.9, of 16384 26.6 / 29.2, at G = 8 29.5 /
+    // 31.8 and 32.1 / 36.7; bf16 21.4 / 21.7 and 22.3 / 26.6).  The moments of so many tiles lie in the area of the phasor table, which is
+    // not needed then: the workspace's own has an entry per 256 keys.
     tri_status rc = TRI_OK;
     int tile_keys = fast ? sa.chunk_keys : kScoreTile;
     if (!fast) {
         const int64_t parts = (c.max_seq_len + kPartKeys - 1) / kPartKeys, tiles = (c.max_seq_len + kScoreTile - 1) / kScoreTile;
-        if (n_inst * tiles <= n_cu && n_inst * parts * 2 * G * (int64_t)sizeof(double) <= kPhasorAreaBytes) {
+        if (4 * n_inst * tiles <= 5 * n_cu && n_inst * parts * 2 * G * (int64_t)sizeof(double) <= kPhasorAreaBytes) {
             tile_keys = kPartKeys;
             sa.partials = reinterpret_cast<double *>(const_cast<uint4 *>(sa.phasors));
         }
