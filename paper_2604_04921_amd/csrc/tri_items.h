@@ -15,11 +15,11 @@ constexpr int lane_waves(int G) { return G > 4 ? 8 : 12; }   // waves per workgr
 // registers, so only three waves fit a SIMD; 12-wave workgroups fill them (8-wave ones would leave one of three unused).
 constexpr int fast_waves(int G) { return G > 4 ? 12 : 8; }
 
-// Rows that a tile with cnt (1 to 64) of its keys in the sequence is loaded from, sixteen keys at a time (which never straddle a block):
-// sixteen keys from `first` on lie in those from tile_group on, and row r of them is read at row tile_row.  Keys past the end repeat
-// rows of the sequence: a slot beyond the length need not exist, not even in the block that the last one is in.
-constexpr int tile_group(int first, int cnt) { return first < cnt ? first : (cnt - 1) & ~15; }
-constexpr int tile_row(int r, int group, int cnt) { return r < cnt - group ? r : cnt - 1 - group; }
+// Rows that a tile with cnt (1 to 64) of its keys in the sequence is loaded from, a group of `rows` keys at a time: row r of the group that
+// begins at key `first` is row min(r, tile_last) from key tile_first on.  Keys past the end repeat the sequence's last one: a slot beyond
+// the length need not exist, not even in the block that the last one is in.
+constexpr int tile_first(int first, int cnt) { return first < cnt ? first : cnt - 1; }
+constexpr int tile_last(int rows, int first, int cnt) { return first + rows < cnt ? rows - 1 : cnt - 1 - tile_first(first, cnt); }
 
 // Eight or more items of kFastChunk keys per CU.
 inline bool large_batch(int64_t instances, int max_seq_len, int n_cu)

@@ -15,8 +15,8 @@
 // ragged head-instances up to 20011 keys, scores only: 848 -> 834 us; 36 x 2 x 8 x 32768, a step: 1261 -> 1245).  Pre-RoPE interleaved
 // keys keep the first: equal or 0.7 % slower in position order, but the second's extra registers spill and cost 1 % at sparse or
 // scattered positions (1362 -> 1377), 1.6 % at G = 8 (5247 -> 5330), 4 % on one sequence at steady state.  Half-split pre-RoPE kernels
-// have no choice and do spill at G <= 4: 4 - 6 of their 168 registers contiguous, 1 - 7 paged; paged interleaved ones 2 - 4; all
-// others none.
+// have no choice and do spill: 3 - 6 of their 168 registers at G <= 4 contiguous, 1 - 7 paged, 2 of 256 contiguous at G > 5; paged
+// interleaved ones 2 - 4 at G <= 4; all others none.
 //
 // What it takes to get there:
 //   * K rows reach their lanes through LDS: the wave loads half rows (128 bytes per key, whole cache lines) or rows with coalesced
@@ -201,51 +201,68 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
         return Tile{it.krow, it.prow, it.bt, n0, min(kTileKeys, it.c0 + it.c_len - n0)};
     };
 
-    // what step `half` takes of the tile at slot n0 (cnt keys exist): eight 16-byte loads per lane.  Every address is a wave-uniform
-    // pointer (sixteen keys never straddle a block) plus an offset of the lane's: its constant; in the last, partial tile keys past the
-    // end repeat rows of the sequence (tile_group, tile_row), which takes one minimum.  Paged caches, whose kernels have the fewest
-    // registers to spare, go that way with every tile (a branch of its own for the last one: 13 - 17 registers spilled, 1.5 - 2 % half-split, 0.5 % interleaved,
-    // 3.5 % on two sequences).
+    // what step `half` takes of the tile at slot n0 (cnt keys exist): eight 16-byte loads per lane.  For a whole tile every address is a
+    // wave-uniform pointer (sixteen keys never straddle a block) plus the lane's constant offset; in the last, partial tile a key past
+    // the end repeats the last one.  Kernels short of registers keep that constant and cut it off at the last row (tile_first,
+    // tile_last), a minimum per load, instead of a row number per load: half-split contiguous ones spill 3 - 6 registers so, not 17 - 22
+    // (9216 x 2176 scattered, scores and selection, 1336 -> 1318 us, 288 x 2170 85.7 -> 78.7, one layer of 8 x 12289 36.7 -> 34.9); the others lose
+    // 0.3 us with it on small calls.  Paged ones, the shortest, go that way with every tile (a branch of its own for the last one: 13 - 17
+    // registers spilled, 1.5 - 2 % half-split, 0.5 % interleaved).
     // Paged caches: lane j of `btv` holds the physical block of keys n0 + 16 j .. + 15 (load_blocks; a block holds
     // 16 slots or more), asked for a tile ahead like the positions, so that no load here waits for a block-table
     // entry.
     auto load_half = [&](const Tile &ti, int half, uint4(&kd)[8], int btv) {
         const int first_key = ROWS ? 32 * half : 0, byte = ROWS ? 0 : 128 * half;
         constexpr int kPer16 = 16 / kLoadKeys;   // instructions per sixteen keys
-        auto sixteen = [&](int k0) {             // where keys k0 .. k0 + 15 of the tile are
-            const int n = ti.n0 + k0;
+        constexpr bool kMinForm = HALF && !ROTATED && G <= 4;   // (of the contiguous kernels)
+        // where key k of the tile is, which lies in the block of key `in`
+        auto row = [&](int in, int k) {
+            const int n = ti.n0 + k;
             if constexpr (PAGED) {
-                const int blk = __builtin_amdgcn_readlane(btv, k0 / 16);
-                return ti.krow + (int64_t)blk * c.stride_sb * 2 + (int64_t)(n & bmask) * slot_bytes;
+                const int blk = __builtin_amdgcn_readlane(btv, in / 16);
+                return ti.krow + (int64_t)blk * c.stride_sb * 2 + (int64_t)(n & bmask) * slot_bytes + byte;
             }
-            return ti.krow + (int64_t)n * slot_bytes;
+            return ti.krow + (int64_t)n * slot_bytes + byte;
         };
-        if (PAGED || ti.cnt != kTileKeys) {
+        // the instructions t0 .. of a group of kRows keys, any of which may lie past the end
+        auto load_group = [&](int t0, auto rows) {
+            constexpr int kRows = decltype(rows)::value;
+            const int first = first_key + kLoadKeys * t0;
+            const char *p = row(first, tile_first(first, ti.cnt));
+            const uint32_t last = (uint32_t)tile_last(kRows, first, ti.cnt) * slot_bytes + (uint32_t)ld_piece * 16u;   // (32 rows fit 32 bits: mfma_path)
 #pragma unroll
-            for (int t = 0; t < 8; t += kPer16) {
-                const int k0 = tile_group(first_key + kLoadKeys * t, ti.cnt);
-                const char *p = sixteen(k0);
-                const uint32_t last = (uint32_t)tile_row(15, k0, ti.cnt) * slot_bytes + (uint32_t)ld_piece * 16u;   // (sixteen rows fit 32 bits: mfma_path)
-#pragma unroll
-                for (int i = 0; i < kPer16; ++i) {
-                    asm volatile("" : "+v"(ld_off));   // keeps (scalar base + 32-bit lane offset) addressing
-                    kd[t + i] = load_stream16(p + byte + min(ld_off + (uint32_t)(kLoadKeys * i) * slot_bytes, last));
-                }
+            for (int i = 0; i < kRows / kLoadKeys; ++i) {
+                asm volatile("" : "+v"(ld_off));   // keeps (scalar base + 32-bit lane offset) addressing
+                kd[t0 + i] = load_stream16(p + min(ld_off + (uint32_t)(kLoadKeys * i) * slot_bytes, last));
             }
-            // The compiler would let both branches end in one common last load, whose registers it takes for pending: it then waits for
-            // the seven loads just issued before it issues the eighth, once per tile.
-            asm volatile("; last tile");
-        } else {
+        };
+        if constexpr (PAGED) {
+#pragma unroll
+            for (int t = 0; t < 8; t += kPer16) load_group(t, std::integral_constant<int, 16>{});
+        } else if (ti.cnt == kTileKeys) {
 #pragma unroll
             for (int t = 0; t < 8; t += kPer16) {
-                const char *p = sixteen(first_key + kLoadKeys * t);
+                const char *p = row(0, first_key + kLoadKeys * t);
 #pragma unroll
                 for (int i = 0; i < kPer16; ++i) {
                     asm volatile("" : "+v"(ld_off));
-                    kd[t + i] = load_stream16(p + (int64_t)(kLoadKeys * i) * slot_bytes + byte + ld_off);
+                    kd[t + i] = load_stream16(p + (int64_t)(kLoadKeys * i) * slot_bytes + ld_off);
                 }
             }
-            asm volatile("; whole tile");   // (a different end)
+            // The compiler would let the branches end in one common last load, whose registers it takes for pending: it then waits for
+            // the seven loads just issued before it issues the eighth, once per tile.
+            asm volatile("; whole tile");
+        } else {
+            if constexpr (kMinForm) {
+                load_group(0, std::integral_constant<int, 32>{});
+            } else {
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const uint32_t k = min(first_key + kLoadKeys * t + ld_key, ti.cnt - 1);   // (64 rows fit 32 bits: mfma_path)
+                    kd[t] = load_stream16(row(0, 0) + (k * slot_bytes + (uint32_t)ld_piece * 16u));
+                }
+            }
+            asm volatile("; last tile");
         }
     };
     auto load_blocks = [&](const Tile &ti) -> int {

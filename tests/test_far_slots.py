@@ -1,6 +1,6 @@
-"""Slots far apart (a token's keys of all layers and sequences next to one another): the score kernels address sixteen rows with 32 bits,
-so bf16 caches with slots up to 2^26 elements apart stay on the matrix kernels.  Which kernel runs is seen without a GPU; on one, the
-scores are the oracle's."""
+"""Slots far apart (a token's keys of all layers and sequences next to one another): the score kernels address sixteen rows of a block, or a
+tile's 64 without blocks, with 32 bits, so bf16 caches with slots up to 2^26, or 2^25, elements apart stay on the matrix kernels.  Which
+kernel runs is seen without a GPU; on one, the scores are the oracle's."""
 import numpy as np
 import pytest
 import torch
@@ -12,17 +12,17 @@ import tri_harness as H
 
 
 def test_kernel_by_slot_stride():
-    strides = [128, 1 << 24, 1 << 25, (1 << 26) - 8, 1 << 26, 1 << 30]
-    for block in (0, 16):
+    strides = [128, 1 << 24, (1 << 25) - 8, 1 << 25, (1 << 26) - 8, 1 << 26, 1 << 30]
+    for block, limit in ((0, 1 << 25), (16, 1 << 26)):
         calls = [dict(entry="score", group=4, kv_heads=2, n=3000, block=block, stride=stride) for stride in strides]
         for stride, (status, launches, _) in zip(strides, launch_probe.run(calls)):
             lane = [name for name, *_ in launches if "score_lane_kernel" in name]
             generic = [name for name, *_ in launches if "12score_kernel" in name]
-            assert status == 0 and len(lane) == (stride < 1 << 26) and len(generic) == (stride >= 1 << 26), (block, stride)
+            assert status == 0 and len(lane) == (stride < limit) and len(generic) == (stride >= limit), (block, stride)
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("stride", [(1 << 25) + 8, (1 << 26) - 8, 1 << 26])
+@pytest.mark.parametrize("stride", [(1 << 25) - 8, (1 << 25) + 8, (1 << 26) - 8, 1 << 26])
 @pytest.mark.parametrize("paged,pairs", [(False, 0), (False, 1), (True, 0), (True, 1)])
 def test_scores(oracle, stride, paged, pairs):
     from paper_2604_04921_amd import binding as T

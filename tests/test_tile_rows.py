@@ -6,11 +6,11 @@ import tri_rules as R
 def test_rows_of_a_partial_tile():
     lib = R.library()
     for cnt in range(1, 65):
-        for first in range(0, 64, 16):
-            group = lib.tile_group(first, cnt)
-            assert group % 16 == 0 and 0 <= group < cnt
-            for r in range(16):
-                row = lib.tile_row(r, group, cnt)
-                assert 0 <= row < 16 and group + row < cnt
-                if first + r < cnt:
-                    assert group + row == first + r
+        for rows in (16, 32):
+            for first in range(0, 64, rows):
+                start, last = lib.tile_first(first, cnt), lib.tile_last(rows, first, cnt)
+                assert start // 16 <= first // 16   # a block that has been looked up: the group's own or, past the end, the last key's
+                assert 0 <= last < rows and 0 <= start <= start + last < cnt
+                for r in range(rows):
+                    if first + r < cnt:
+                        assert start + min(r, last) == first + r

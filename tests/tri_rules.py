@@ -16,8 +16,8 @@ int sixteen_lane_kernel(int group, long long instances, int n, int n_cu, int hal
 {
     return tri::sixteen_lane_kernel(group, tri::item_keys(instances, n, n_cu), instances, n, n_cu, half_split, paged, rotated);
 }
-int tile_group(int first, int cnt) { return tri::tile_group(first, cnt); }
-int tile_row(int row, int group, int cnt) { return tri::tile_row(row, group, cnt); }
+int tile_first(int first, int cnt) { return tri::tile_first(first, cnt); }
+int tile_last(int rows, int first, int cnt) { return tri::tile_last(rows, first, cnt); }
 }
 """
 
