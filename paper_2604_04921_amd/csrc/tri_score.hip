@@ -444,17 +444,23 @@ tri_status launch_score_g(const tri_model &m, const tri_cache &c, ScoreArgs sa, 
 {
     const int n_inst = m.n_layers * c.n_seqs * m.n_kv_heads;
     const bool fast = mfma_path(c, G);
-    // Generic kernel: one part per workgroup where tiles of two would leave CUs without any, or a few with twice the others' (scores: 8
+    // Generic kernel: one part per workgroup where tiles of two would leave CUs without any or give a few twice the others' (scores: 8
     // heads of 8192 fp32 keys, a tile per CU, 19.4 us in tiles of two parts, 18.4 in tiles of one; one of 4096, a step, 26.2 / 22.9; 9 / 8 of
     // a tile: 32 bf16 heads of 2176 in blocks of 8, a step, 30.4 / 29.5, one of 80000 23.4 / 22.7, fp32 ones at G = 1 18.8 / 18.2, at G = 8 28.3 /
-    // 29.8).  With more of them there are only more moments to add up (8 fp32 heads of 12288 23.9 / 24.9, of 16384 26.6 / 29.2, at G = 8 29.5 /
-    // 31.8 and 32.1 / 36.7; bf16 21.4 / 21.7 and 22.3 / 26.6).  The moments of so many tiles lie in the area of the phasor table, which is
-    // not needed then: the workspace's own has an entry per 256 keys.
+    // 29.8; with one or two query heads, which leave the CU more to wait for than to do, up to 3 / 2: 48 of 1900 at G = 2 22.6 / 21.6, 40 of
+    // 2176 at G = 1 20.4 / 19.5, at G = 4 24.3 / 24.6), or need a longer last round of the two workgroups that a CU holds (128 of 1100 keys at
+    // G = 4, 640 tiles of two or 1152 of one, 33.6 / 31.7, bf16 31.0 / 28.4; 48 of 2934 32.1 / 31.6).  Elsewhere there are only more moments to
+    // add up and more workgroups (8 fp32 heads of 12288 23.9 / 24.9, of 16384 26.6 / 29.2, at G = 8 29.5 / 31.8 and 32.1 / 36.7; 56 of 2176 at
+    // G = 8 31.9 / 35.5; bf16 27.7 / 30.7).  The moments of so many tiles lie in the area of the phasor table, which is not needed then: the
+    // workspace's own has an entry per 256 keys.
     tri_status rc = TRI_OK;
     int tile_keys = fast ? sa.chunk_keys : kScoreTile;
     if (!fast) {
-        const int64_t parts = (c.max_seq_len + kPartKeys - 1) / kPartKeys, tiles = (c.max_seq_len + kScoreTile - 1) / kScoreTile;
-        if (4 * n_inst * tiles <= 5 * n_cu && n_inst * parts * 2 * G * (int64_t)sizeof(double) <= kPhasorAreaBytes) {
+        const int64_t parts = (int64_t)n_inst * ((c.max_seq_len + kPartKeys - 1) / kPartKeys);
+        const int64_t tiles = (int64_t)n_inst * ((c.max_seq_len + kScoreTile - 1) / kScoreTile);
+        const int64_t slots = 2 * n_cu, part_rounds = (parts + slots - 1) / slots, tile_rounds = (tiles + slots - 1) / slots;
+        const bool one = tiles * 4 <= (int64_t)n_cu * (G <= 2 ? 6 : 5) || part_rounds < 2 * tile_rounds;
+        if (one && parts * 2 * G * (int64_t)sizeof(double) <= kPhasorAreaBytes) {
             tile_keys = kPartKeys;
             sa.partials = reinterpret_cast<double *>(const_cast<uint4 *>(sa.phasors));
         }
