@@ -152,6 +152,9 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
     const int ld_key = ROWS ? lane >> 4 : lane >> 3, ld_piece = ROWS ? lane & 15 : lane & 7;
     const int bmask = PAGED ? (1 << c.block_shift) - 1 : 0;
     uint32_t ld_off = (uint32_t)ld_key * slot_bytes + (uint32_t)ld_piece * 16u;   // the lane's part of a load address
+    uint32_t ld_more[16 / kLoadKeys];   // that of each instruction of sixteen keys (paged, where registers allow: 0.3 % at G = 8)
+#pragma unroll
+    for (int i = 0; i < 16 / kLoadKeys; ++i) ld_more[i] = ld_off + (uint32_t)(kLoadKeys * i) * slot_bytes;
     // where the lane writes its loaded pieces (rows: load t at 1024 t, with 4 (t % 4) XORed into the piece index; half rows: at
     // 1024 t plus one of two offsets, by the parity of t) and reads its key's (its piece p lies at st_rd ^ (p << 4))
     const int hh = ROWS ? lane >> 5 : 0;   // rows: which half of the bands
@@ -232,8 +235,13 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
             const uint32_t last = (uint32_t)tile_last(kRows, first, ti.cnt) * slot_bytes + (uint32_t)ld_piece * 16u;   // (32 rows fit 32 bits: mfma_path)
 #pragma unroll
             for (int i = 0; i < kRows / kLoadKeys; ++i) {
-                asm volatile("" : "+v"(ld_off));   // keeps (scalar base + 32-bit lane offset) addressing
-                kd[t0 + i] = load_stream16(p + min(ld_off + (uint32_t)(kLoadKeys * i) * slot_bytes, last));
+                if constexpr (PAGED && G > 4) {
+                    asm volatile("" : "+v"(ld_more[i]));   // keeps (scalar base + 32-bit lane offset) addressing
+                    kd[t0 + i] = load_stream16(p + min(ld_more[i], last));
+                } else {
+                    asm volatile("" : "+v"(ld_off));
+                    kd[t0 + i] = load_stream16(p + min(ld_off + (uint32_t)(kLoadKeys * i) * slot_bytes, last));
+                }
             }
         };
         if constexpr (PAGED) {
@@ -245,7 +253,7 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                 const char *p = row(0, first_key + kLoadKeys * t);
 #pragma unroll
                 for (int i = 0; i < kPer16; ++i) {
-                    asm volatile("" : "+v"(ld_off));
+                    asm volatile("" : "+v"(ld_off));   // (see above)
                     kd[t + i] = load_stream16(p + (int64_t)(kLoadKeys * i) * slot_bytes + ld_off);
                 }
             }
