@@ -1,15 +1,20 @@
 """The fused step with the new lengths written over the old ones (new_seq_len = seq_len): the same result as into an array of its own.
-An eviction that rides along with the selection must not replace a length that other workgroups still read."""
+An eviction that rides along with the selection must not replace a length that other workgroups still read.  In a batch that fills that
+path's limit of eight head-instances per compute unit some do so late: a workgroup's 25 KB of LDS let a unit hold six, so a quarter of them begin
+when others, those that write the lengths among them, have ended."""
 import pytest
 import torch
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("layers,n,budget", [(12, 2176, 2048), (3, 5000, 700)])   # the eviction inside the selection, and in a launch of its own
+# the eviction inside the selection, all head-instances at once and as many as that takes; and in a launch of its own
+@pytest.mark.parametrize("layers,n,budget", [(12, 2176, 2048), ("most", 2176, 2048), (3, 5000, 700)])
 def test_new_lengths_over_the_old_ones(layers, n, budget):
     from paper_2604_04921_amd import binding as T
     heads, S, i32 = 4, 3, dict(dtype=torch.int32, device="cuda")
+    if layers == "most":
+        layers = 8 * torch.cuda.get_device_properties(0).multi_processor_count // (heads * S)
     g = torch.Generator(device="cuda")
     g.manual_seed(n)
     k = torch.randn((layers, S, heads, n, 128), generator=g, device="cuda").to(torch.bfloat16)
