@@ -410,8 +410,7 @@ tri_status tri_select_topk(const tri_model *model, const float *final_scores, co
         return TRI_ERR_INVALID_ARG;
     }
     if ((rc = check_limits(*model, *cache, budget, "tri_select_topk")) != TRI_OK) return rc;
-    return launch_select(*model, final_scores, nullptr, nullptr, MomentLayout{1, 1, nullptr}, nullptr, *cache, budget,
-                         kept_idx, kept_cnt,
+    return launch_select(*model, final_scores, nullptr, MomentLayout{1, 1, nullptr}, nullptr, *cache, budget, kept_idx, kept_cnt,
                          (hipStream_t)stream);
 }
 
@@ -475,8 +474,7 @@ static tri_status run_step(const tri_model *model, const float *centers, const t
     // evicting in place with the fewest moves, the selection's workgroups do the moves themselves where they can
     const FillTail fill{new_seq_len};
     bool filled = false;
-    if ((rc = launch_select(*model, nullptr, reinterpret_cast<float *>(ws + wl.raw),
-                            moments.partials, moments,
+    if ((rc = launch_select(*model, nullptr, reinterpret_cast<float *>(ws + wl.raw), moments,
                             reinterpret_cast<uint32_t *>(ws + wl.final_), *src, budget, kept_idx, kept_cnt,
                             (hipStream_t)stream, dst ? nullptr : &fill, &filled)) != TRI_OK)
         return rc;

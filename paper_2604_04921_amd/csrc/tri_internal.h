@@ -211,8 +211,8 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
 struct FillTail {
     int32_t *new_seq_len;   // [S] or NULL
 };
-tri_status launch_select(const tri_model &m, const float *final_scores, float *raw, const double *partials, MomentLayout moments, uint32_t *hist, const tri_cache &c,
-                         int32_t budget, int32_t *kept_idx, int32_t *kept_cnt, hipStream_t st,
+tri_status launch_select(const tri_model &m, const float *final_scores, float *raw, MomentLayout moments, uint32_t *hist,
+                         const tri_cache &c, int32_t budget, int32_t *kept_idx, int32_t *kept_cnt, hipStream_t st,
                          const FillTail *fill = nullptr, bool *fill_taken = nullptr);
 tri_status launch_compact(const tri_model &m, const tri_cache &src, const tri_cache &dst, int32_t budget,
                           const int32_t *kept_idx, const int32_t *kept_cnt, int32_t *new_seq_len,

@@ -243,85 +243,85 @@ __global__ __launch_bounds__(kScoreThreads, 4) void score_kernel(ScoreArgs a)
     float *rw = a.raw + (((int64_t)l * c.n_seqs + s) * Hq + (int64_t)h * G) * c.max_seq_len;
     const float *const tb = tab;
     for (int m0 = n0; m0 < n1; m0 += kPartKeys) {
-    if (m0 > n0) __syncthreads();   // the sums of the part before have been read
+        if (m0 > n0) __syncthreads();   // the sums of the part before have been read
 #pragma unroll
-    for (int i = 0; i < kLoads; ++i) {
-        const int ci = i * kScoreThreads + tid;
-        lds[ci / ROW16 * STRIDE16 + ci % ROW16] = kd[i];
-    }
-    const double pd = (double)p_next;
-    __syncthreads();
-    if (m0 + kPartKeys < n1) load(m0 + kPartKeys);   // on its way during this part's arithmetic
-    const int n = m0 + key;
-    const bool valid = n < N;
-    float acc[G];
+        for (int i = 0; i < kLoads; ++i) {
+            const int ci = i * kScoreThreads + tid;
+            lds[ci / ROW16 * STRIDE16 + ci % ROW16] = kd[i];
+        }
+        const double pd = (double)p_next;
+        __syncthreads();
+        if (m0 + kPartKeys < n1) load(m0 + kPartKeys);   // on its way during this part's arithmetic
+        const int n = m0 + key;
+        const bool valid = n < N;
+        float acc[G];
 #pragma unroll
-    for (int g = 0; g < G; ++g) acc[g] = 0.f;
-    const uint4 *row = lds + key * STRIDE16;
-    constexpr int kBandsEach = kBands / kScoreSplit;
+        for (int g = 0; g < G; ++g) acc[g] = 0.f;
+        const uint4 *row = lds + key * STRIDE16;
+        constexpr int kBandsEach = kBands / kScoreSplit;
 
-    if constexpr (sizeof(T) == 2 && PAIRS == TRI_PAIR_INTERLEAVED) {
+        if constexpr (sizeof(T) == 2 && PAIRS == TRI_PAIR_INTERLEAVED) {
 #pragma unroll 2
-        for (int j = quarter * (kBandsEach / 4); j < (quarter + 1) * (kBandsEach / 4); ++j) {
-            uint4 q = row[j];
-            const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+            for (int j = quarter * (kBandsEach / 4); j < (quarter + 1) * (kBandsEach / 4); ++j) {
+                uint4 q = row[j];
+                const uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                int f = 4 * j + i;
-                band_update<G>(acc, tb + f * 3 * G, pd, rev[f], bf16_lo(w[i]), bf16_hi(w[i]));
+                for (int i = 0; i < 4; ++i) {
+                    int f = 4 * j + i;
+                    band_update<G>(acc, tb + f * 3 * G, pd, rev[f], bf16_lo(w[i]), bf16_hi(w[i]));
+                }
+            }
+        } else if constexpr (sizeof(T) == 2) {
+#pragma unroll
+            for (int j = quarter * (kBandsEach / 8); j < (quarter + 1) * (kBandsEach / 8); ++j) {
+                uint4 qr = row[j], qi = row[j + 8];
+                const uint32_t wr[4] = {qr.x, qr.y, qr.z, qr.w}, wi[4] = {qi.x, qi.y, qi.z, qi.w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    int f = 8 * j + 2 * i;
+                    band_update<G>(acc, tb + f * 3 * G, pd, rev[f], bf16_lo(wr[i]), bf16_lo(wi[i]));
+                    band_update<G>(acc, tb + (f + 1) * 3 * G, pd, rev[f + 1], bf16_hi(wr[i]), bf16_hi(wi[i]));
+                }
+            }
+        } else if constexpr (PAIRS == TRI_PAIR_INTERLEAVED) {
+#pragma unroll 2
+            for (int j = quarter * (kBandsEach / 2); j < (quarter + 1) * (kBandsEach / 2); ++j) {
+                uint4 q = row[j];
+                int f = 2 * j;
+                band_update<G>(acc, tb + f * 3 * G, pd, rev[f], __uint_as_float(q.x), __uint_as_float(q.y));
+                band_update<G>(acc, tb + (f + 1) * 3 * G, pd, rev[f + 1], __uint_as_float(q.z), __uint_as_float(q.w));
+            }
+        } else {
+#pragma unroll 2
+            for (int j = quarter * (kBandsEach / 4); j < (quarter + 1) * (kBandsEach / 4); ++j) {
+                uint4 qr = row[j], qi = row[j + 16];
+                const uint32_t wr[4] = {qr.x, qr.y, qr.z, qr.w}, wi[4] = {qi.x, qi.y, qi.z, qi.w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    int f = 4 * j + i;
+                    band_update<G>(acc, tb + f * 3 * G, pd, rev[f], __uint_as_float(wr[i]), __uint_as_float(wi[i]));
+                }
             }
         }
-    } else if constexpr (sizeof(T) == 2) {
-#pragma unroll
-        for (int j = quarter * (kBandsEach / 8); j < (quarter + 1) * (kBandsEach / 8); ++j) {
-            uint4 qr = row[j], qi = row[j + 8];
-            const uint32_t wr[4] = {qr.x, qr.y, qr.z, qr.w}, wi[4] = {qi.x, qi.y, qi.z, qi.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                int f = 8 * j + 2 * i;
-                band_update<G>(acc, tb + f * 3 * G, pd, rev[f], bf16_lo(wr[i]), bf16_lo(wi[i]));
-                band_update<G>(acc, tb + (f + 1) * 3 * G, pd, rev[f + 1], bf16_hi(wr[i]), bf16_hi(wi[i]));
-            }
-        }
-    } else if constexpr (PAIRS == TRI_PAIR_INTERLEAVED) {
-#pragma unroll 2
-        for (int j = quarter * (kBandsEach / 2); j < (quarter + 1) * (kBandsEach / 2); ++j) {
-            uint4 q = row[j];
-            int f = 2 * j;
-            band_update<G>(acc, tb + f * 3 * G, pd, rev[f], __uint_as_float(q.x), __uint_as_float(q.y));
-            band_update<G>(acc, tb + (f + 1) * 3 * G, pd, rev[f + 1], __uint_as_float(q.z), __uint_as_float(q.w));
-        }
-    } else {
-#pragma unroll 2
-        for (int j = quarter * (kBandsEach / 4); j < (quarter + 1) * (kBandsEach / 4); ++j) {
-            uint4 qr = row[j], qi = row[j + 16];
-            const uint32_t wr[4] = {qr.x, qr.y, qr.z, qr.w}, wi[4] = {qi.x, qi.y, qi.z, qi.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                int f = 4 * j + i;
-                band_update<G>(acc, tb + f * 3 * G, pd, rev[f], __uint_as_float(wr[i]), __uint_as_float(wi[i]));
-            }
-        }
-    }
 
-    // the quarters' sums together, in their order
-    __syncthreads();   // nobody reads the keys any more
-    float *const sums = reinterpret_cast<float *>(lds);   // [quarter - 1][head][key]
-    if (quarter > 0) {
+        // the quarters' sums together, in their order
+        __syncthreads();   // nobody reads the keys any more
+        float *const sums = reinterpret_cast<float *>(lds);   // [quarter - 1][head][key]
+        if (quarter > 0) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) sums[((quarter - 1) * G + g) * kPartKeys + key] = acc[g];
-    }
-    __syncthreads();
-    if (quarter == 0) {
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-#pragma unroll
-            for (int q = 1; q < kScoreSplit; ++q) acc[g] += sums[((q - 1) * G + g) * kPartKeys + key];
-            before[g] = last[g];
-            last[g] = valid ? acc[g] : 0.f;
-            if (valid) rw[(int64_t)g * c.max_seq_len + n] = acc[g];
+            for (int g = 0; g < G; ++g) sums[((quarter - 1) * G + g) * kPartKeys + key] = acc[g];
         }
-    }
+        __syncthreads();
+        if (quarter == 0) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+#pragma unroll
+                for (int q = 1; q < kScoreSplit; ++q) acc[g] += sums[((q - 1) * G + g) * kPartKeys + key];
+                before[g] = last[g];
+                last[g] = valid ? acc[g] : 0.f;
+                if (valid) rw[(int64_t)g * c.max_seq_len + n] = acc[g];
+            }
+        }
     }
     // the tile's sum and sum of squares per query head (double, fixed order)
     if (quarter == 0) {

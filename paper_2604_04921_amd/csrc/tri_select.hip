@@ -234,6 +234,7 @@ constexpr int kFromKeys = -1;
 template <int SRC, bool VEC, bool HELD, int THREADS>
 __global__ __launch_bounds__(THREADS, HELD ? (THREADS == kSelThreads ? 4 : 5) : 8) void select_kernel(SelectArgs a, int64_t key_row)
 {
+    static_assert(VEC || SRC == 0, "the workspace's rows allow 16-byte loads whatever their length");
     constexpr int kWaves = THREADS / 64;
     constexpr int kBinsPerThread = kSelBins / THREADS;
     constexpr int kHeads = SRC > 0 ? SRC : 1;
@@ -360,7 +361,7 @@ __global__ __launch_bounds__(THREADS, HELD ? (THREADS == kSelThreads ? 4 : 5) : 
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int n = min(n0 + 4 * lane + i, N - 1);
-                u[i] = SRC == 0 ? order_key(ranked(src[n])) : ks[n];
+                u[i] = order_key(ranked(src[n]));
             }
         }
     };
@@ -605,15 +606,14 @@ tri_status launch_select_g(const SelectArgs &sa, int n_inst, int n_cu, hipStream
 
 }  // namespace
 
-tri_status launch_select(const tri_model &m, const float *final_scores, float *raw, const double *partials,
-                         MomentLayout moments, uint32_t *hist, const tri_cache &c,
-                         int32_t budget, int32_t *kept_idx, int32_t *kept_cnt, hipStream_t st, const FillTail *fill,
+tri_status launch_select(const tri_model &m, const float *final_scores, float *raw, MomentLayout moments, uint32_t *hist,
+                         const tri_cache &c, int32_t budget, int32_t *kept_idx, int32_t *kept_cnt, hipStream_t st, const FillTail *fill,
                          bool *fill_taken)
 {
     if (fill_taken) *fill_taken = false;
     const int n_inst = m.n_layers * c.n_seqs * m.n_kv_heads;
     if (n_inst <= 0) return TRI_OK;
-    SelectArgs sa{final_scores, raw, partials, moments.n_tiles, moments.tile_keys, hist, c.seq_len, kept_idx,
+    SelectArgs sa{final_scores, raw, moments.partials, moments.n_tiles, moments.tile_keys, hist, c.seq_len, kept_idx,
                   kept_cnt, c.n_seqs, m.n_kv_heads, c.max_seq_len, budget, 1, 1, m.head_budgets};
     sa.fill = 0;
     // Short sequences: the eviction in place rides along (its move list takes the keys' place in LDS) -- on small batches, whose
