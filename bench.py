@@ -49,7 +49,7 @@ def score_kernel_name(group, instances, n, n_cu, mfma, half_split, paged, post_r
         keys = -(-(-(-n // pieces)) // tile) * tile
         last = keys <= 512
         keys = max(keys, 512)
-        cost = -(-instances * -(-n // keys) // n_cu) * (keys + 768)
+        cost = -(-instances * -(-n // keys) // n_cu) * (keys + 448)
         if best is None or cost < best:
             item, best = keys, cost
         if last:
