@@ -83,8 +83,8 @@ __device__ __forceinline__ void moments_to_stats(double s1, double s2, int N, do
 // head-instance's [tiles][2G] moments (room for `most`), part = 32 G doubles and zst = 2 G doubles of LDS; on return (after a barrier)
 // zst[2g], zst[2g + 1] = mean and 1/sigma of head g.  The first 64 tiles' moments are asked for by moments_ahead, whatever the length,
 // so that they arrive together with it; those of longer rows eight at a time (one after the other, a head of 131072 fp32 keys, 512
-// tiles, whose final scores 128 workgroups form: scores 43.5 us at G = 8 against 39.7, 33.3 against 28.6 at G = 4; with a launch of its
-// own for the statistics 45.5 and 34.8).
+// tiles, whose final scores 128 workgroups form: scores 39.6 us at G = 8 against 35.9, 33.7 against 28.8 at G = 4; with a launch of its own
+// for the statistics 5.7 and 6.2 us more).
 struct Moments {
     double v[4];
 };

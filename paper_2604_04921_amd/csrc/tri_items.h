@@ -61,21 +61,13 @@ inline int item_keys(int64_t instances, int max_seq_len, int n_cu)
     return best;
 }
 
-// Which kernel takes bf16 keys (item: item_keys() of the batch): that of tri_score_lane.hip, but paged pre-RoPE keys with
-// interleaved pairs in items of kFastChunk go to the one that spreads a key over sixteen lanes where it was the faster one before the
-// other's items followed one another without a gap (the figures below).  Measured since, whole steps, this kernel against the other: 768 x
-// 4096 to 65536 keys at G = 8 2606 / 2460 us, at G = 5 2458 / 2276, 32 x 65536 at G = 8 203 / 199, 512 x 8192 528 / 516, 4608 x 2176 at
-// G = 4 2551 / 2506, 3072 x 4096 2046 / 2002: the line could go, and this kernel with it.  It stands as tests/test_item_rules.py,
-// test_gpu_sixteen_lanes.py and test_gpu_precision.py (whose yardstick this kernel is) state it.
-// More than four query heads per KV head, whole steps: 768 x 4096 to 65536 keys at G = 8 2600 us against 2684, at G = 5 2447 against
-// 2495; batches whose cost model ends at kFastChunk as well (one item per CU and more): 32 x 65536 at G = 8 206 against 215, 64 x
-// 32768 205 against 218, 128 x 16384 225 against 235 (G = 5: 218 against 225), 512 x 8192 528 against 550.
-// Up to four: large batches of short sequences, 3072 x 4096 keys at G = 4 1055 against 1073, 4608 x 2176 2538 against 2559; it is
-// the slower one on smaller batches (256 x 8192 at G = 4 257 against 252, at G = 1 250 against 236; 768 x 8192 745 against 712) and
-// on longer sequences (768 x 4096 to 65536 keys 2107 against 2058 at G = 4, 1983 against 1959 at G = 2; 3072 x 9000 3098 against
-// 3064).
-// Half-split pairs: 768 x 4096 to 65536 keys 2680 against 2664 at G = 8, 2135 against 2078 at G = 4, 3072 x 4096 keys 1077 against
-// 1068; post-RoPE at G = 8 2368 against 2364: never.
+// Which kernel takes bf16 keys (item: item_keys() of the batch): that of tri_score_lane.hip, but paged pre-RoPE keys with interleaved pairs
+// in items of kFastChunk go to the one that spreads a key over sixteen lanes, with more than four query heads per KV head always, with up
+// to four on large batches of short sequences.  The line was drawn where that one was the faster before the other's items followed one
+// another without a gap.  It no longer is: whole steps, this kernel / the other, 768 x 4096 to 65536 keys at G = 8 2588 / 2466 us, at G = 5
+// 2433 / 2298, 32 x 65536 at G = 8 201 / 197, 512 x 8192 530 / 518; 4608 x 2176 at G = 4 2537 / 2491, at G = 1 2499 / 2447, 3072 x 4096 2048 / 2003.
+// tests/test_item_rules.py and test_gpu_sixteen_lanes.py state the line, and test_gpu_precision.py takes this kernel as the yardstick of
+// the other's sums: moving it means restating those.
 inline bool sixteen_lane_kernel(int G, int item, int64_t instances, int max_seq_len, int n_cu, bool half_split, bool paged, bool rotated)
 {
     if (!paged || half_split || rotated || item != kFastChunk) return false;

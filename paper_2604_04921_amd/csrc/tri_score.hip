@@ -172,9 +172,10 @@ __device__ __forceinline__ void band_update(float (&acc)[G], const float *tb, do
 // fp32 keys take let two workgroups share a CU: one's loads overlap the other's arithmetic, and the second part's loads go out ahead of the
 // first part's arithmetic.
 // Against 256 keys in one workgroup of 1024 threads, alone on its CU, with the table as scalar operands (whose loads a wave waited for every
-// other band): fp32, whole steps, 192 heads of 32768 keys 1258 -> 863 us at G = 4, 1045 -> 706 at G = 1, 1591 -> 1297 at G = 8; scores and selection
-// of 288 heads of 2176 144 -> 99; scores of 320 ragged ones up to 20011 857 -> 550.  (That one: one thread per key, one wave per SIMD,
-// 3595 us for 288 heads of 32768 keys; four 1730.)
+// other band): fp32, whole steps, 192 heads of 32768 keys 1252 -> 838 us at G = 4, 1044 -> 697 at G = 1, 1600 -> 998 at G = 8; scores and selection
+// of 288 heads of 2176 146 -> 96; scores of 320 ragged ones up to 20011 865 -> 535; bf16 in blocks of 8, scores of 288 heads of 2176 101 -> 70 at G = 4,
+// 55 -> 55 at G = 1, of 16384 669 -> 410 and 332 -> 311.  (That one: one thread per key, one wave per SIMD, 3595 us for 288 heads of 32768 keys;
+// four 1730.)  128 registers, none spilled.
 constexpr int kScoreSplit = 4, kPartKeys = 128, kScoreThreads = kPartKeys * kScoreSplit;
 template <int G, typename T, int PAIRS>
 __global__ __launch_bounds__(kScoreThreads, 4) void score_kernel(ScoreArgs a)
@@ -358,7 +359,7 @@ struct FinalArgs {
 // every workgroup adds up for itself, and S_final(k) = max_g (S~(g)(k) - mu_g) / sigma_g.  Four keys per thread, all their scores
 // and the moments loaded before the first is used: rows of an odd length read one score at a time took 24 x 5 x 8 head-instances of
 // up to 20011 keys, scores, 834 us against 806.  The statistics in a launch of their own ahead of this one: scores and selection of
-// 288 x 2176 keys 76.0 us against 74.1, 32 x 2176 28.0 / 26.0, 2304 x 2176 336.8 / 334.4, 9216 1323.5 / 1322.2.
+// 288 x 2176 interleaved keys 77.4 us against 75.5, 32 x 2176 28.1 / 26.3, 2304 x 2176 344.7 / 339.1, 9216 1305 / 1289, half-split 1335.0 / 1334.4.
 template <int G>
 __global__ __launch_bounds__(256) void final_kernel(FinalArgs a)
 {

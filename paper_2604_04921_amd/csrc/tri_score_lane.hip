@@ -299,7 +299,8 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
     // Items follow one another without a gap: while one is scored, the next one's table entries and every wave's first tile of it
     // are on their way, so that between two items there are two barriers and no wait for memory.  (Asking for an item, its chunk, its
     // rows and its table one after the other cost about as much as twelve tiles of an idle CU.)  9216 x 2176 keys, scores and selection:
-    // 1428 -> 1365 us half-split scattered, 1248 -> 1181 in slot order; 288 x 2176 93 -> 81; 64 x 8 x 131072 at G = 8, a step, 5262 -> 5000
+    // 1385 -> 1335 us half-split scattered, 1227 -> 1173 in slot order; 288 x 2176 interleaved scattered 90.7 -> 78.8, in slot order 83.5 -> 68.5;
+    // 64 x 8 x 131072 at G = 8, a step, 5218 -> 5004
     // (with the waits that load_half and the stores below speak of).
     float tab[kTabEach];
     auto load_table = [&](const Item &it) {
