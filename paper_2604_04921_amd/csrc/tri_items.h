@@ -10,7 +10,6 @@ namespace tri {
 constexpr int kFastChunk = 8192;
 constexpr int kMinChunk = 512;
 constexpr int kItemCost = 448;
-constexpr int lane_waves(int G) { return G > 4 ? 8 : 12; }   // waves per workgroup of the kernel of tri_score_lane.hip
 // Waves per workgroup of the sixteen-lane kernel: with more than four query heads per KV head a wave needs more than 128
 // registers, so only three waves fit a SIMD; 12-wave workgroups fill them (8-wave ones would leave one of three unused).
 constexpr int fast_waves(int G) { return G > 4 ? 12 : 8; }

@@ -2,10 +2,11 @@
 //
 // A wave takes 64 consecutive slots of a head-instance -- a tile -- in two steps, and scores them against all query heads of the
 // group.  The contraction over (band, component) x query head runs on v_mfma_f32_4x4x1_16b_f32: block b of the instruction
-// holds lanes 4b..4b+3, its rows are those four lanes' keys (operand A: the lane's own rotated component or modulus of the band
-// in turn), its columns four query heads (operand B: lane 4b+j supplies the folded table entry of head j).  The accumulator of
-// lane (b, j) ends up with the scores of four keys for head j: no cross-lane reduction over keys or heads, and one 16-byte
-// store per lane writes them.  Two ways to hand out the work (rows_layout()):
+// holds lanes 4b..4b+3, its columns are those four lanes' keys (operand B: the lane's own rotated component or modulus of the band
+// in turn), its rows four query heads (operand A: the folded table's entries, held in registers by one block and broadcast by the
+// instruction to the others).  Lane l of the accumulator ends up with key l's scores of four heads: no cross-lane reduction over keys
+// or heads; turned within the blocks (four keys of one head per lane), they leave in one 16-byte store per lane.  Two ways to hand
+// out the work (rows_layout()):
 //   * half rows: a lane owns one key; step 0 takes bands 0-31 of the 64 keys, step 1 bands 32-63.  Needs the two components of a
 //     band in the same half of the row, i.e. interleaved pairs.
 //   * rows: step 0 takes keys 0-31 of the tile, step 1 keys 32-63, and two lanes share a key: lane l has its bands 0-31 (l < 32)
@@ -13,10 +14,7 @@
 //     keys.  With whole rows in LDS the pair layouts differ in which pieces a lane reads and in nothing else.
 // Half-split pairs need the second; post-RoPE keys, which have the registers for it, gain 1 - 2 % from its whole-row loads (24 x 5 x 8
 // ragged head-instances up to 20011 keys, scores only: 848 -> 834 us; 36 x 2 x 8 x 32768, a step: 1261 -> 1245).  Pre-RoPE interleaved
-// keys keep the first: equal or 0.7 % slower in position order, but the second's extra registers spill and cost 1 % at sparse or
-// scattered positions (1362 -> 1377), 1.6 % at G = 8 (5247 -> 5330), 4 % on one sequence at steady state.  Half-split pre-RoPE kernels
-// have no choice and do spill: 3 - 6 of their 168 registers at G <= 4 contiguous, 1 - 7 paged, 2 of 256 contiguous at G > 5; paged
-// interleaved ones 2 - 4 at G <= 4; all others none.
+// keys keep the first: equal or 0.7 % slower in position order, 1 - 4 % at sparse or scattered positions.
 //
 // What it takes to get there:
 //   * K rows reach their lanes through LDS: the wave loads half rows (128 bytes per key, whole cache lines) or rows with coalesced
@@ -25,11 +23,16 @@
 //     rows or one row) and the reads (16 lanes = 16 keys, one piece) touch every bank once.
 //   * Rotation of the key (Appendix B.2): k e^{i w p} = (k e^{i w r}) e^{i w base} with base a position in the middle of
 //     the tile's positions and |r| < 64.  e^{i w |r|} comes from a table in LDS (one 16-byte read per two bands; a
-//     negative r flips the sign of the sine), e^{-i w base} is folded into the wave's copy of the head-instance's table,
-//     which it rewrites for every tile (lane = band: one sine / cosine pair and 2 G complex products per lane) or, rows, for a
-//     step.  A tile (rows: also either step) whose positions span 127 or more takes the direct path (phase in double, v_sin_f32 /
-//     v_cos_f32 per lane and band).
-//   * Operand B is read from that copy in LDS, four bands per read.
+//     negative r flips the sign of the sine), e^{-i w base} is folded into the head-instance's table, for every tile or, rows, for a
+//     step: a lane works out one band's sine / cosine pair, hands it to the other three of its block, and forms its entries, four complex
+//     products per quad of heads.  A tile (rows: also either step) whose positions span 127 or more takes the direct path (phase in
+//     double, v_sin_f32 / v_cos_f32 per lane and band).
+//   * The table lies in registers, 12 per quad of heads, a band's four entries in the lanes of one block: a matrix instruction names the
+//     block (cbsz, abid).  Read from LDS four bands at a time by every lane instead, it took 48 (G > 4: 96) of a tile's 104 (152) LDS
+//     reads, 26 KB of LDS, and the registers of two pieces' entries: 64 x 8 x 131072 keys at G = 8, a step, 4999 -> 4662 us (half of it from
+//     the third wave per SIMD that now fits), 6 x 16 x 8 x 4096 to 65536 paged 1827 -> 1799, 9216 x 2176 half-split scattered, scores and selection,
+//     1346 -> 1316, one layer of 8 x 12289 half-split 35.5 -> 34.7, 36 x 8 x 8 x 32768 equal (bound by its reads and the raw scores' writes).  Nothing spills now
+//     (half-split kernels had 1 - 7 registers spilled).
 // The vector instructions of four bands are issued first and their twelve (24) matrix instructions in one run after
 // them: a wave that alternates between the two kinds loses about 3.5 clocks per matrix instruction.
 #include <algorithm>
@@ -59,15 +62,42 @@ constexpr bool rows_layout(bool rotated, bool half_split) { return rotated || ha
 // there but costs 2 %.
 constexpr bool short_chains(bool paged, bool rotated, bool half_split) { return paged || rotated || half_split; }
 constexpr int chain_pieces(bool rotated, bool half_split, bool table) { return rotated || (!half_split && !table) ? 2 : 3; }
-constexpr int kTabRow = kBands + 4;                             // floats per (component, head) row: 16 bytes of skew
 
-// (lane_waves(G): LDS decides -- 33 KB of phasors + a stage and a table per wave)
-constexpr int lane_heads(int G) { return 4 * ((G + 3) / 4); }   // table rows: query heads rounded up to whole quads
-constexpr int lane_wave_bytes(int G) { return kStageBytes + 2 * lane_heads(G) * kTabRow * 4; }   // stage + (re, im) rows
-constexpr int lane_lds_bytes(int G, bool rotated)
+// The folded table as the matrix instructions take it: a register per (component, quad of heads, quarter v of the lane's bands) whose lane
+// (b, j) holds head 4 q + j's entry of band table_band(lane, v).  An instruction broadcasts one block's four lanes to all sixteen blocks
+// (half rows) or to the eight of its half of the wave (rows).
+constexpr int table_block(bool rows, int band) { return rows ? 8 * (band / 32) + band % 8 : band % 16; }   // the block that holds a band
+constexpr int table_quarter(bool rows, int band) { return rows ? band % 32 / 8 : band / 16; }
+constexpr int kTabQuad = 64 * 4;                                // floats per (component, quad of heads): four a lane
+constexpr int lane_quads(int G) { return (G + 3) / 4; }
+// Waves per workgroup: three per SIMD where their registers allow it (168 each).
+constexpr int lane_waves(int G, bool paged, bool rotated, bool half_split) { return G <= 4 || !(paged || rotated || half_split) ? 12 : 8; }
+constexpr int lane_lds_bytes(int G, bool paged, bool rotated, bool half_split)
 {
-    return (rotated ? 0 : kLanePhasorBytes) + lane_heads(G) * kTabRow * 4 + lane_waves(G) * lane_wave_bytes(G);
+    return (rotated ? 0 : kLanePhasorBytes) + 3 * lane_quads(G) * kTabQuad * 4 + lane_waves(G, paged, rotated, half_split) * kStageBytes;
 }
+// acc + (four heads' entries of block BLOCK, lanes 4 BLOCK ..) x (every lane's key): lane l of the result holds key l's products
+template <bool ROWS, int BLOCK>
+__device__ __forceinline__ float4v head_products(float entries, float key, float4v acc)
+{
+    return __builtin_amdgcn_mfma_f32_4x4x1f32(entries, key, acc, ROWS ? 3 : 4, BLOCK, 0);
+}
+template <int I, int N, typename F>
+__device__ __forceinline__ void static_for(F f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
+    }
+}
+// v of lane 4 b + K in all four lanes of a block; v of lane ^ 1, ^ 2
+template <int CTRL>
+__device__ __forceinline__ float quad_lane(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+constexpr int quad_same(int k) { return k * 0x55; }
+constexpr int kQuadXor1 = 0xb1, kQuadXor2 = 0x4e;
 
 // Byte offset of 16-byte piece p of key k in a wave's staging area, such that 16 lanes that hold whole rows or half rows (the
 // writes) or one piece of 16 keys (the reads) fall into 16 different groups of four banks.  Half rows: rows k and k ^ 1 swap
@@ -100,15 +130,13 @@ __device__ __forceinline__ HalfExtremes half_extremes(int v)
 
 // ROTATED: the keys are stored post-RoPE (no rotation, no positions).  PAGED: block_size >= 16.  HALF: half-split pairs.
 template <int G, bool PAGED, bool ROTATED, bool HALF>
-__global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArgs a)
+__global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void score_lane_kernel(ScoreArgs a)
 {
-    constexpr int NG = (G + 3) / 4, HR = lane_heads(G), W = lane_waves(G), kThreads = W * 64;
-    constexpr int kTabBytes = HR * kTabRow * 4;          // one component's rows
+    constexpr int NG = lane_quads(G), W = lane_waves(G, PAGED, ROTATED, HALF), kThreads = W * 64;
     constexpr bool ROWS = rows_layout(ROTATED, HALF), kShortChains = short_chains(PAGED, ROTATED, HALF);
     extern __shared__ __align__(16) char lds[];
     __shared__ double red[W][2 * 4 * NG];
     __shared__ double lds_rev[kBands];                    // omega_f / 2pi
-    __shared__ float q_tab[2][G][kBands];                 // E[q] e^{..} of the head-instance, (re, im) x head x band
     __shared__ int lds_item;
 
     const CacheView &c = a.c;
@@ -117,10 +145,8 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
     const int j = lane & 3, b = lane >> 2;                // column (query head within a quad) and block of the lane
 
     char *const ph_base = lds;                                                  // phasor table (absent when ROTATED)
-    char *const cn_base = lds + (ROTATED ? 0 : kLanePhasorBytes);               // norm-term rows, shared by the waves
-    char *const my_base = cn_base + kTabBytes + wave * lane_wave_bytes(G);
-    char *const stage = my_base;                                                // this wave's rows
-    char *const tab_re = my_base + kStageBytes, *const tab_im = tab_re + kTabBytes;
+    float *const item_tab = reinterpret_cast<float *>(lds + (ROTATED ? 0 : kLanePhasorBytes));   // the head-instance's table, [component][quad][lane][v]
+    char *const stage = reinterpret_cast<char *>(item_tab + 3 * NG * kTabQuad) + wave * kStageBytes;   // this wave's rows
 
     // the phasor table: all of a thread's entries asked for at once, stored further down
     constexpr int kPhasors = ROTATED ? 0 : (kLanePhasorBytes / 16 + kThreads - 1) / kThreads;
@@ -128,9 +154,9 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
 #pragma unroll
     for (int k = 0; k < kPhasors; ++k) ph[k] = reinterpret_cast<const uint4v *>(a.phasors)[min(tid + k * kThreads, kLanePhasorBytes / 16 - 1)];
     const double rev = a.band_rev[tid % kBands];
-    // rows of heads that do not exist (G not a multiple of four) stay zero for the whole launch
-    for (int k = lane; k < 2 * HR * kTabRow; k += 64) reinterpret_cast<float *>(tab_re)[k] = 0.f;
-    for (int k = tid; k < HR * kTabRow; k += kThreads) reinterpret_cast<float *>(cn_base)[k] = 0.f;
+    // entries of heads that do not exist (G not a multiple of four) stay zero for the whole launch
+    if constexpr (G % 4 != 0)
+        for (int k = tid; k < 3 * NG * kTabQuad; k += kThreads) item_tab[k] = 0.f;
 
     // (constant for the whole launch, unlike the counter in front of it: scalar loads)
     typedef const __attribute__((address_space(4))) int32_t *ConstInts;
@@ -160,8 +186,8 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
     const int hh = ROWS ? lane >> 5 : 0;   // rows: which half of the bands
     const int st_wr0 = stage_offset<ROWS>(ld_key, ld_piece), st_wr1 = ROWS ? 0 : stage_offset<ROWS>(8 + ld_key, ld_piece) - 1024;
     const int st_rd = ROWS ? stage_offset<ROWS>(lane & 31, HALF ? 4 * hh : 8 * hh) : stage_offset<ROWS>(lane, 0);
-    // byte offset of the lane's head row, from its first band on, inside a quad of table rows
-    const int tab_lane = (j * kTabRow + 32 * hh) * 4;
+    // the band whose phase the lane works out when a base is folded in: table_band(lane, j)
+    const int my_band = ROWS ? 32 * hh + 8 * j + (b & 7) : 16 * j + b;
 
     // A work item: a chunk of a head-instance's slots.  Everything here is wave-uniform.
     struct Item {
@@ -308,24 +334,16 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
 #pragma unroll
         for (int k = 0; k < kTabEach; ++k) tab[k] = tbl[min(tid + k * kThreads, kBands * 3 * G - 1)];
     };
-    // the norm-term rows, shared by the waves, and the folded table per band
     auto store_table = [&]() {
 #pragma unroll
         for (int k = 0; k < kTabEach; ++k) {
             const int e = tid + k * kThreads, f = e / (3 * G), comp = e / G - 3 * f, g = e % G;
             if (kBands * 3 * G % kThreads != 0 && e >= kBands * 3 * G) break;
-            if (comp == 2) {
-                reinterpret_cast<float *>(cn_base)[g * kTabRow + f] = tab[k];
-            } else if constexpr (ROTATED) {   // no base to fold in: every wave's copy is written once per item
-                for (int w = 0; w < W; ++w) {
-                    char *const wb = cn_base + kTabBytes + w * lane_wave_bytes(G) + kStageBytes + comp * kTabBytes;
-                    reinterpret_cast<float *>(wb)[g * kTabRow + f] = tab[k];
-                }
-            } else {
-                q_tab[comp][g][f] = tab[k];
-            }
+            item_tab[((comp * NG + g / 4) * 64 + 4 * table_block(ROWS, f) + g % 4) * 4 + table_quarter(ROWS, f)] = tab[k];
         }
     };
+    // the lane's four entries of a component and quad of heads
+    auto table_of = [&](int comp, int q) { return *reinterpret_cast<const float4v *>(item_tab + ((comp * NG + q) * 64 + lane) * 4); };
     auto load_first = [&](const Tile &ti) {
         bt_cur = load_blocks(ti);
         pos_next = load_pos(ti, bt_cur);   // (ahead of the rows: needed first)
@@ -346,8 +364,13 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
         const Item nxt = item_of(__builtin_amdgcn_readfirstlane(lds_item));
         if (nxt.n_tiles > 0) load_table(nxt);
         double s1[NG], s2[NG];
+        float4v t_re[NG], t_im[NG], t_m[NG];   // the table, with the tile's base folded in
 #pragma unroll
-        for (int q = 0; q < NG; ++q) s1[q] = s2[q] = 0.0;
+        for (int q = 0; q < NG; ++q) {
+            s1[q] = s2[q] = 0.0;
+            t_m[q] = table_of(2, q);
+            if constexpr (ROTATED) t_re[q] = table_of(0, q), t_im[q] = table_of(1, q);
+        }
         float *rw = a.raw + cur.inst * G * c.max_seq_len;
         // (16-byte stores need floats' alignment only; the rows' bytes fit 32 bits with room above them: mfma_path)
         constexpr uint32_t kNowhere = 0xffffffe0u;
@@ -375,18 +398,22 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
             // ---- the tile's base
             int base = 0, base1 = 0;   // rows: step 1's may be one of its own
             bool in_table = true, mirrored = false;   // wave-uniform
-            // fold e^{-i w base} into the wave's table: lane = band.  (The phase in [-1/2, 1/2] revolutions: in fp32 twice as
-            // fine as in [0, 1].)
+            // fold e^{-i w base} into the wave's table: a lane works out one band's phasor and hands it to the other three of its
+            // block.  (The phase in [-1/2, 1/2] revolutions: in fp32 twice as fine as in [0, 1].)
             auto fold_base = [&]() {
-                const double turns = (double)base * lds_rev[lane];
+                const double turns = (double)base * lds_rev[my_band];
                 const float x = (float)(turns - __builtin_rint(turns));
                 const float bs = __builtin_amdgcn_sinf(x), bc = __builtin_amdgcn_cosf(x);
+                static_for<0, 4>([&](auto quarter) {
+                    constexpr int v = quarter;
+                    const float s = quad_lane<quad_same(v)>(bs), c = quad_lane<quad_same(v)>(bc);
 #pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    const float qr = q_tab[0][g][lane], qi = q_tab[1][g][lane];
-                    reinterpret_cast<float *>(tab_re)[g * kTabRow + lane] = qr * bc + qi * bs;
-                    reinterpret_cast<float *>(tab_im)[g * kTabRow + lane] = qi * bc - qr * bs;
-                }
+                    for (int q = 0; q < NG; ++q) {
+                        const float qr = table_of(0, q)[v], qi = table_of(1, q)[v];
+                        t_re[q][v] = qr * c + qi * s;
+                        t_im[q][v] = qi * c - qr * s;
+                    }
+                });
             };
             if constexpr (!ROTATED) {
                 // Usual case: slots in the order of their positions, all within 64 of the first: base = the first, r >= 0.
@@ -449,7 +476,6 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                 uint4 kq;   // interleaved: four bands; half-split: the real parts of eight
                 uint4 ki;   // half-split: their imaginary parts
                 float4 e0, e1;
-                float4 br[NG], bi[NG], bc[NG];
             };
             auto fetch = [&](const Piece &prev, int half, int pc, auto table_tag) {
                 constexpr bool TABLE = decltype(table_tag)::value;
@@ -465,19 +491,12 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                     o.e0 = *reinterpret_cast<const float4 *>(ph_lane + (f0 / 2) * kLanePairStride);
                     o.e1 = *reinterpret_cast<const float4 *>(ph_lane + (f0 / 2 + 1) * kLanePairStride);
                 }
-#pragma unroll
-                for (int q = 0; q < NG; ++q) {
-                    const int off = tab_lane + (4 * q * kTabRow + f0) * 4;
-                    o.br[q] = *reinterpret_cast<const float4 *>(tab_re + off);
-                    o.bi[q] = *reinterpret_cast<const float4 *>(tab_im + off);
-                    o.bc[q] = *reinterpret_cast<const float4 *>(cn_base + off);
-                }
                 return o;
             };
             // The vector instructions of the piece first, then its matrix instructions in one run.
-            auto score_piece = [&](const Piece &pz, int half, int pc, auto table_tag, auto mirror_tag) {
+            auto score_piece = [&](const Piece &pz, auto half, auto pc, auto table_tag, auto mirror_tag) {
                 constexpr bool TABLE = decltype(table_tag)::value, MIRROR = decltype(mirror_tag)::value;
-                const int f0 = (ROWS ? 0 : 32 * half) + 4 * pc;
+                constexpr int f0 = (ROWS ? 0 : 32 * half) + 4 * pc;
                 const uint32_t w[4] = {pz.kq.x, pz.kq.y, pz.kq.z, pz.kq.w};
                 const uint32_t wi[4] = {pz.ki.x, pz.ki.y, pz.ki.z, pz.ki.w};
                 float cs[4] = {1.f, 1.f, 1.f, 1.f}, sn[4] = {0.f, 0.f, 0.f, 0.f};
@@ -521,33 +540,25 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                 // head-instances of 32768 keys 7.90 -> 7.60 ms, sparse positions 8.51 -> 8.01, G = 8 (64 x 8 of 131072 keys)
                 // 4.63 -> 4.38; the other way round gains half of that, the levels themselves (1 / 0, 3 / 0, 2 / 1) nothing.
                 __builtin_amdgcn_s_setprio(0);
+                static_for<0, 4>([&](auto k) {
+                    constexpr int f = f0 + k, v = table_quarter(ROWS, f), kBlock = table_block(ROWS, f);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
+                    for (int q = 0; q < NG; ++q) acc[q] = head_products<ROWS, kBlock>(t_re[q][v], kr[k], acc[q]);
 #pragma unroll
-                    for (int q = 0; q < NG; ++q) {
-                        const float t_[4] = {pz.br[q].x, pz.br[q].y, pz.br[q].z, pz.br[q].w};
-                        acc[q] = __builtin_amdgcn_mfma_f32_4x4x1f32(kr[k], t_[k], acc[q], 0, 0, 0);
-                    }
-#pragma unroll
-                    for (int q = 0; q < NG; ++q) {
-                        const float t_[4] = {pz.bi[q].x, pz.bi[q].y, pz.bi[q].z, pz.bi[q].w};
-                        acc2[q] = __builtin_amdgcn_mfma_f32_4x4x1f32(ki[k], t_[k], acc2[q], 0, 0, 0);
-                    }
+                    for (int q = 0; q < NG; ++q) acc2[q] = head_products<ROWS, kBlock>(t_im[q][v], ki[k], acc2[q]);
 #pragma unroll
                     for (int q = 0; q < NG; ++q) {
-                        const float t_[4] = {pz.bc[q].x, pz.bc[q].y, pz.bc[q].z, pz.bc[q].w};
                         float4v &to = kShortChains ? acc_m[q] : acc[q];
-                        to = __builtin_amdgcn_mfma_f32_4x4x1f32(m[k], t_[k], to, 0, 0, 0);
+                        to = head_products<ROWS, kBlock>(t_m[q][v], m[k], to);
                     }
-                }
+                });
                 __builtin_amdgcn_s_setprio(2);
                 __builtin_amdgcn_sched_barrier(0x4 | 0x20 | 0x100);
             };
             auto score_tile = [&](auto table_tag, auto mirror_tag) {
                 constexpr int kPieces = ROWS ? 8 : 16;   // of a sum
                 constexpr int kChain = chain_pieces(ROTATED, HALF, decltype(table_tag)::value);
-#pragma unroll
-                for (int half = 0; half < 2; ++half) {
+                static_for<0, 2>([&](auto half) {
                     stage_half(kd);   // waits for the step's loads, then 8 LDS writes
                     if constexpr (ROWS && !ROTATED) {
                         if constexpr (decltype(mirror_tag)::value)   // (nowhere else do the steps' bases differ)
@@ -556,7 +567,7 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                                 fold_base();
                             }
                         const auto p = __builtin_amdgcn_permlane32_swap((uint32_t)p_key, (uint32_t)p_key, false, false);
-                        take_position((int)p[half]);
+                        take_position((int)p[(int)half]);
                     }
                     if (ROWS || half == 0)
 #pragma unroll
@@ -569,13 +580,12 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                         load_half(nt, 0, kd, bt_next);
                     }
                     Piece cur = fetch(Piece{}, half, 0, table_tag);
-#pragma unroll
-                    for (int pc = 0; pc < 8; ++pc) {
+                    static_for<0, 8>([&](auto pc) {
                         Piece nxt = cur;
                         if (pc + 1 < 8) nxt = fetch(cur, half, pc + 1, table_tag);
                         score_piece(cur, half, pc, table_tag, mirror_tag);
                         cur = nxt;
-                        const int done = (ROWS ? 0 : 8 * half) + pc + 1;   // pieces of this sum scored so far
+                        constexpr int done = (ROWS ? 0 : 8 * half) + pc + 1;   // pieces of this sum scored so far
                         if (kShortChains && (done % kChain == 0 || done == kPieces)) {
 #pragma unroll
                             for (int q = 0; q < NG; ++q) {
@@ -584,13 +594,13 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                                 acc[q] = acc2[q] = float4v{0.f, 0.f, 0.f, 0.f};
                             }
                         }
-                    }
+                    });
 #pragma unroll
                     for (int q = 0; q < NG; ++q) {
                         if (ROWS || half == 1) acc[q] = kShortChains ? sum[q] + acc_m[q] : acc[q] + acc2[q];
                         if (ROWS && half == 0) first[q] = acc[q];
                     }
-                }
+                });
             };
             if (ROTATED || !in_table) score_tile(std::false_type{}, std::false_type{});
             else if (mirrored) score_tile(std::true_type{}, std::true_type{});
@@ -605,7 +615,16 @@ __global__ __launch_bounds__(lane_waves(G) * 64) void score_lane_kernel(ScoreArg
                     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(first[q][k]), __float_as_uint(acc[q][k]), false, false);
                     acc[q][k] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
                 }
-            // ---- lane (b, j) holds keys n0 + 4b .. + 3 for head 4q + j
+            // ---- lane l holds key n0 + l for heads 4q .. 4q + 3: turned within the blocks, lane (b, j) holds keys n0 + 4b .. + 3 for head 4q + j
+#pragma unroll
+            for (int q = 0; q < NG; ++q) {
+                const bool odd = j & 1, high = j & 2;
+                const float4v r = acc[q];
+                const float4v x = {quad_lane<kQuadXor1>(r[0]), quad_lane<kQuadXor1>(r[1]), quad_lane<kQuadXor1>(r[2]), quad_lane<kQuadXor1>(r[3])};
+                const float4v t = {odd ? x[1] : r[0], odd ? r[1] : x[0], odd ? x[3] : r[2], odd ? r[3] : x[2]};
+                const float4v y = {quad_lane<kQuadXor2>(t[0]), quad_lane<kQuadXor2>(t[1]), quad_lane<kQuadXor2>(t[2]), quad_lane<kQuadXor2>(t[3])};
+                acc[q] = float4v{high ? y[2] : t[0], high ? y[3] : t[1], high ? t[2] : y[0], high ? t[3] : y[1]};
+            }
 #pragma unroll
             for (int q = 0; q < NG; ++q) {
                 const int g = 4 * q + j, live = g < G ? min(4, cnt - 4 * b) : 0;   // keys of this lane that exist
@@ -673,7 +692,7 @@ tri_status launch_lane_g(const ScoreArgs &sa, bool half_split, hipStream_t st)
                        : (paged ? score_lane_kernel<G, true, false, H> : score_lane_kernel<G, false, false, H>);
     };
     auto kern = half_split ? pick(std::true_type{}) : pick(std::false_type{});
-    const int lds = lane_lds_bytes(G, rotated);
+    const int lds = lane_lds_bytes(G, paged, rotated, half_split), threads = lane_waves(G, paged, rotated, half_split) * 64;
     if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
         return hip_status("hipFuncSetAttribute(score_lane_kernel)");
     static std::atomic<int> resident[2][2][2][kMaxDevices];
@@ -688,7 +707,7 @@ tri_status launch_lane_g(const ScoreArgs &sa, bool half_split, hipStream_t st)
     if (slots == 0) {
         int n_cu = 0, per_cu = 0;
         if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kern, lane_waves(G) * 64, lds) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kern, threads, lds) != hipSuccess ||
             n_cu <= 0 || per_cu <= 0) {
             (void)hipGetLastError();
             set_error("score: occupancy query failed");
@@ -710,7 +729,7 @@ tri_status launch_lane_g(const ScoreArgs &sa, bool half_split, hipStream_t st)
             sb.first_mult = p;
             break;
         }
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(lane_waves(G) * 64), lds, st, sb);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), lds, st, sb);
     return hip_status("score_lane_kernel");
 }
 
