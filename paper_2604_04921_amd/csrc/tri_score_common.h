@@ -96,7 +96,7 @@ tri_status launch_score_fast(int G, const ScoreArgs &sa, hipStream_t st);
 tri_status launch_score_lane(int G, const ScoreArgs &sa, bool half_split, hipStream_t st);
 // The general kernel's table of e^{i w r}: entry (band pair bp, r) = (cos, sin) of bands 2bp and 2bp+1 at relative position r, at byte
 // bp * kLanePairStride + 16 r.  The fold kernel writes it with kLaneTablePhasors extra threads.
-constexpr int kLaneRange = 64;                                  // relative positions 0 .. 63
+constexpr int kLaneRange = 88;                                  // relative positions 0 .. 87: what LDS has room for
 constexpr int kLanePairStride = kLaneRange * 16 + 16;           // bytes per band pair (16 bytes of skew)
 constexpr int kLanePhasorBytes = (kBands / 2) * kLanePairStride;
 constexpr int kLaneTablePhasors = kBands * kLaneRange;

@@ -22,11 +22,13 @@
 //     bands, or the real or imaginary parts of eight.  The area is XOR-swizzled so that both the writes (16 lanes = 2 half
 //     rows or one row) and the reads (16 lanes = 16 keys, one piece) touch every bank once.
 //   * Rotation of the key (Appendix B.2): k e^{i w p} = (k e^{i w r}) e^{i w base} with base a position in the middle of
-//     the tile's positions and |r| < 64.  e^{i w |r|} comes from a table in LDS (one 16-byte read per two bands; a
+//     the tile's positions and |r| < kLaneRange.  e^{i w |r|} comes from a table in LDS (one 16-byte read per two bands; a
 //     negative r flips the sign of the sine), e^{-i w base} is folded into the head-instance's table, for every tile or, rows, for a
 //     step: a lane works out one band's sine / cosine pair, hands it to the other three of its block, and forms its entries, four complex
-//     products per quad of heads.  A tile (rows: also either step) whose positions span 127 or more takes the direct path (phase in
-//     double, v_sin_f32 / v_cos_f32 per lane and band).
+//     products per quad of heads.  A tile (rows: also either step) whose positions span 2 kLaneRange - 1 or more takes the direct path
+//     (phase in double, v_sin_f32 / v_cos_f32 per lane and band).  88 positions: with 64, about half of the tiles of a cache that has kept
+//     one position in two took the direct path (36 x 2 x 8 x 32768 sparse keys, a step, 1287 -> 1264 us, at G = 8 16 x 8 x 131072 1304 -> 1216,
+//     one layer of 8 x 32768 52.0 -> 50.3; dense and scattered ones equal).
 //   * The table lies in registers, 12 per quad of heads, a band's four entries in the lanes of one block: a matrix instruction names the
 //     block (cbsz, abid).  Read from LDS four bands at a time by every lane instead, it took 48 (G > 4: 96) of a tile's 104 (152) LDS
 //     reads, 26 KB of LDS, and the registers of two pieces' entries: 64 x 8 x 131072 keys at G = 8, a step, 4999 -> 4662 us (half of it from
@@ -416,7 +418,7 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
                 });
             };
             if constexpr (!ROTATED) {
-                // Usual case: slots in the order of their positions, all within 64 of the first: base = the first, r >= 0.
+                // Usual case: slots in the order of their positions, all within the table's range of the first: base = the first, r >= 0.
                 // (The lowest and highest position of every tile through twelve LDS shuffles, each waiting for the one before,
                 // cost 64 x 8 head-instances of 131072 keys at G = 8 1 %.)
                 base = base1 = __builtin_amdgcn_readfirstlane(p_key);
@@ -425,8 +427,8 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
                     const HalfExtremes lo = half_extremes<false>(p_key), hi = half_extremes<true>(p_key);
                     base = min(lo.v[0], lo.v[1]);
                     const int64_t span = (int64_t)max(hi.v[0], hi.v[1]) - (int64_t)base;
-                    // positions within 64 of the lowest: base = the lowest, r >= 0.  Else base = the middle and the table
-                    // serves |r| (a negative r flips the sine), as long as the span stays below 127.
+                    // positions within the range of the lowest: base = the lowest, r >= 0.  Else base = the middle and the table
+                    // serves |r| (a negative r flips the sine), as long as the span stays below twice the range.
                     mirrored = span >= kLaneRange;
                     in_table = span < 2 * kLaneRange - 1;
                     if (mirrored) base = (int)((int64_t)base + (span >> 1));
