@@ -7,7 +7,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtri.so")
-SOURCES = ["tri_api.hip", "tri_centers.hip", "tri_score.hip", "tri_score_mfma.hip", "tri_score_lane.hip", "tri_select.hip", "tri_compact.hip"]
+SOURCES = ["tri_api.hip", "tri_centers.hip", "tri_score.hip", "tri_score_mfma.hip", "tri_select.hip", "tri_compact.hip"]
+# (source, flags): the general score kernel's variants, a compilation per group size
+UNITS = [("tri_score_lane.hip", ["-DTRI_LANE_GROUP=%d" % g]) for g in (8, 7, 6, 5, 4, 3, 2, 1)] + [(s, []) for s in SOURCES]
 
 # packed fp32 VALU forms are switched off for every kernel of this library
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
@@ -27,17 +29,18 @@ def build(verbose=False, extra=()):
         return "\n".join(l for l in text.splitlines() if "packed-fp32-ops" not in l)
 
     with tempfile.TemporaryDirectory(prefix="libtri_build_") as tmp:
-        def compile_one(src):
-            obj = os.path.join(tmp, src.replace(".hip", ".o"))
-            cmd = [hipcc(), *HIPCC_FLAGS, *extra, "-c", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+        def compile_one(unit):
+            src, flags = unit
+            obj = os.path.join(tmp, "%d_%s" % (UNITS.index(unit), src.replace(".hip", ".o")))
+            cmd = [hipcc(), *HIPCC_FLAGS, *extra, *flags, "-c", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
                    os.path.join(CSRC, src), "-o", obj]
             if verbose:
                 print(" ".join(cmd), flush=True)
             res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
             return src, obj, res.returncode, clean(res.stdout)
 
-        with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1)) as ex:
-            results = list(ex.map(compile_one, SOURCES))
+        with ThreadPoolExecutor(max_workers=min(len(UNITS), os.cpu_count() or 1)) as ex:
+            results = list(ex.map(compile_one, UNITS))
         for src, _, rc, out in results:
             if rc != 0:
                 raise RuntimeError("hipcc failed on %s:\n%s" % (src, out))

@@ -124,6 +124,10 @@ __device__ __forceinline__ void block_stats(const Moments &ahead, const double *
     __syncthreads();
 }
 
+// Entries of a head-instance of N keys among its n_tiles: those of tile_keys keys each that exist, or (tile_keys 0) all of them, some
+// of which are zero.
+__device__ __forceinline__ int moment_entries(int n_tiles, int tile_keys, int N) { return tile_keys > 0 ? (N + tile_keys - 1) / tile_keys : n_tiles; }
+
 typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
 // 16 bytes that a step reads once / writes and does not read again: non-temporal hint (measured on this GPU: a
 // streaming read reaches 7.0 TB/s with it and 6.2 TB/s without; the gather runs 10 % faster with such stores)
@@ -198,7 +202,7 @@ tri_status launch_diagnostics(const tri_model &m, const float *q_centers, const 
 // moments) and no statistics are formed here: the selection does that itself.
 struct MomentLayout {
     int32_t n_tiles;     // entries per head-instance
-    int32_t tile_keys;   // keys per entry
+    int32_t tile_keys;   // keys per entry, or 0 (moment_entries)
     const double *partials;   // where they are
 };
 tri_status launch_score(const tri_model &m, const float *centers, const tri_cache &c, float *final_out,

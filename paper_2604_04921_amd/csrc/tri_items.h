@@ -60,6 +60,64 @@ inline int item_keys(int64_t instances, int max_seq_len, int n_cu)
     return best;
 }
 
+// Where work items leave some CUs with more than others, the general MFMA kernel takes stretches instead: the tiles of all head-instances,
+// (layer, KV head) by (layer, KV head) and in them sequence by sequence, one after the other, are cut into stretches of equal length (to
+// a tile), the same number for every CU, whatever head-instances they begin and end in.  The lengths are known on the device only, which
+// cuts a batch there (plan_stretches).
+constexpr int kStretchTile = 64;
+constexpr int kStretchSeqs = 1024;   // sequences at most: one workgroup counts their tiles
+constexpr int64_t kStretchTiles = (int64_t)1 << 30;   // tiles of all head-instances stay below
+// Stretches per CU, or 0: work items.  Both sides measured in one process, us with items / with stretches.  Scores and selection of 288 x 2176
+// scattered keys 75 / 61, half-split 76 / 61, 576 x 2176 115 / 102, 1152 192 / 179, 2016 305 / 299; scores of 960 ragged post-RoPE
+// head-instances up to 20011 684 / 651, of 160 140 / 122; steps on 768 ragged paged ones of 4096 to 65536 1795 / 1761, on 128 375 / 332, on
+// 576, 864, 1152 x 32768 1271 / 1244, 1911 / 1850, 2494 / 2430.  Items stay where
+//  - a CU has sixteen tiles at most: they begin sooner (8 x 12289 half-split, a step, 33.8 / 35.0, 64 x 2176 29.4 / 30.5);
+//  - the batch is large and the sequences are short (4608 x 2176 668 / 673, 9216 half-split 1331 / 1336), or there are more than four query heads (240 x
+//    131072 at G = 8 2225 / 2250: less arithmetic to spare for reads in a less even order), or 32 items per CU and more are even enough
+//    (2304 x 32768 4885 / 4929).
+// 64 tiles in a stretch: neighbouring workgroups then read 1 MB from one another (288 x 32768, a step, 635 with 64, 650 with 96, 649 with 128 and
+// 665 with 256; paged 768 1762, 1778, 1778; 576 x 8192 scattered half-split, the other way, 328, 319, 320).
+inline int stretch_rounds(int G, int64_t instances, int max_seq_len, int n_cu)
+{
+    const int64_t cus = n_cu > 0 ? n_cu : 1, tiles = instances * (((int64_t)max_seq_len + kStretchTile - 1) / kStretchTile);
+    if (tiles <= 16 * cus || tiles >= kStretchTiles) return 0;
+    if (large_batch(instances, max_seq_len, n_cu) && (G > 4 || max_seq_len < kFastChunk || tiles >= 32 * cus * (kFastChunk / kStretchTile))) return 0;
+    return (int)((tiles + 64 * cus - 1) / (64 * cus));
+}
+// tiles of a stretch at least: eight, more where a stretch has more anyway and a row would have more than sixty entries of moments
+inline int stretch_least(int64_t instances, int max_seq_len, int64_t stretches)
+{
+    const int64_t tiles = ((int64_t)max_seq_len + kStretchTile - 1) / kStretchTile, each = instances * tiles / stretches;
+    const int64_t few = (tiles + 59) / 60, least = each < few ? each : few;
+    return least > 8 ? (int)least : 8;
+}
+// stretches of `total` tiles; the first tile of stretch i; the stretch that holds a tile
+constexpr uint32_t stretch_count(uint32_t total, uint32_t least, uint32_t most)
+{
+    const uint32_t fit = total / least;
+    return total == 0 ? 0 : fit < 1 ? 1 : fit < most ? fit : most;
+}
+struct Stretches {
+    uint32_t count, least, longer;   // the first `longer` ones have least + 1 tiles, the others least
+};
+constexpr Stretches stretches_of(uint32_t total, uint32_t least, uint32_t most)
+{
+    const uint32_t count = stretch_count(total, least, most), per = count > 0 ? count : 1;
+    return Stretches{count, total / per, total % per};
+}
+constexpr uint32_t stretch_begin(const Stretches &st, uint32_t i) { return i * st.least + (i < st.longer ? i : st.longer); }
+constexpr uint32_t stretch_of(const Stretches &st, uint32_t tile)
+{
+    const uint32_t split = st.longer * (st.least + 1);
+    return tile < split ? tile / (st.least + 1) : st.longer + (tile - split) / st.least;
+}
+// stretches that a head-instance of max_seq_len keys can lie in, at most
+constexpr int stretch_entries(int max_seq_len, int least)
+{
+    const int tiles = (max_seq_len + kStretchTile - 1) / kStretchTile;
+    return tiles < 2 ? 1 : (tiles - 2) / least + 2;
+}
+
 // Which kernel takes bf16 keys (item: item_keys() of the batch): that of tri_score_lane.hip, but paged pre-RoPE keys with interleaved pairs
 // in items of kFastChunk go to the one that spreads a key over sixteen lanes, with more than four query heads per KV head always, with up
 // to four on large batches of short sequences.  The line was drawn where that one was the faster before the other's items followed one

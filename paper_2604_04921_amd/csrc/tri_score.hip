@@ -28,6 +28,10 @@ struct FoldArgs {
     const int32_t *seq_len; // [S]
     int32_t *work;          // work list of the MFMA score kernels, or NULL when the generic kernel runs
     int32_t chunk_keys;     // keys per entry of that list
+    StretchPlan *stretches; // stretches of the general MFMA kernel instead, or NULL; its moments are cleared here
+    int32_t n_stretches, stretch_least, n_first, n_entries;
+    double *partials;       // [L][S][Hkv][n_entries][2G]
+    int32_t L;
     float4 *phasors;        // relative-position phasor table of the MFMA score kernel, filled in by extra workgroups
     int32_t lane_kernel;    // its layout: that of tri_score_lane.hip or the sixteen-lane kernel's
     int32_t max_seq_len;
@@ -60,9 +64,9 @@ constexpr int kFoldThreads = 512;
 // thread per band went through the offsets one after the other, and a second one for the tables took 5.8 + 4.6 us (10.6 + 5.1
 // with 32 offsets); with this one a step on one head's 4096 keys takes 35.6 us instead of 39.5, on one layer of eight heads
 // x 32768 keys 74.3 instead of 78.4.
-// The extra workgroups of the first layer's row have nothing to do with the tables: the first lists the chunks of the MFMA score kernels and
-// writes the band frequencies (a launch of its own would cost more than the list), those after it fill the MFMA score
-// kernel's phasor table when it needs one, an entry per thread.
+// The extra workgroups of the first layer's row have nothing to do with the tables: the first writes the band frequencies, the second lists
+// the stretches or chunks of the MFMA score kernels (a launch of its own would cost more than the list; behind the first one's pow it cost small
+// calls 0.5 us), those after it fill the MFMA score kernel's phasor table when it needs one, an entry per thread.
 __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
 {
     extern __shared__ __align__(16) double fold_lds[];
@@ -75,8 +79,13 @@ __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
     const int f = tid % kBands;
     const int extra = (int)blockIdx.x - n_fold;   // uniform over the workgroup
     if (extra >= 0 && l > 0) return;
-    if (extra > 0) {
-        const int t = (extra - 1) * kFoldThreads + tid;   // (an entry holds two bands: a thread each)
+    if (extra == 1) {
+        if (a.stretches) plan_stretches(a.seq_len, a.S, a.max_seq_len, a.L, a.Hkv, a.stretch_least, a.n_stretches, a.n_first, a.work, a.stretches);
+        else if (a.work) build_work_list(a.seq_len, a.S, a.max_seq_len, a.chunk_keys, a.work);
+        return;
+    }
+    if (extra > 1) {
+        const int t = (extra - 2) * kFoldThreads + tid;   // (an entry holds two bands: a thread each)
         if (a.lane_kernel) lane_phasor(a.theta, t, reinterpret_cast<float2 *>(a.phasors));
         else fast_phasor(a.theta, t, reinterpret_cast<float2 *>(a.phasors));
         return;
@@ -84,7 +93,6 @@ __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
     const double rev = pow(a.theta, -2.0 * (double)f / (double)kHeadDim) / kTwoPi;
     if (extra == 0) {
         if (tid < kBands) a.band_rev[f] = rev;
-        if (a.work) build_work_list(a.seq_len, a.S, a.max_seq_len, a.chunk_keys, a.work);
         return;
     }
     const int h = blockIdx.x / a.seq_blocks, sb = blockIdx.x - h * a.seq_blocks;
@@ -95,6 +103,11 @@ __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
     const float *ct = a.centers + (((int64_t)l * a.Hq + h * a.G + g) * kBands + fb) * 3;
     const float c0 = ct[0], c1 = ct[1], c2 = ct[2];
     const int s0 = sb * a.fold_seqs, n_seq = min(a.S - s0, a.fold_seqs);
+    if (a.stretches)   // an entry that no stretch of the head-instance's writes counts as nothing
+        for (int j = 0; j < n_seq; ++j) {
+            double *const m = a.partials + (((int64_t)l * a.S + s0 + j) * a.Hkv + h) * a.n_entries * (2 * a.G);
+            for (int k = tid; k < a.n_entries * 2 * a.G; k += kFoldThreads) m[k] = 0.0;
+        }
     for (int k = tid; k < a.n_off * kBands; k += kFoldThreads) {
         double c, s;
         unit_phasor((double)a.offsets[k / kBands], rev, &c, &s);
@@ -387,7 +400,7 @@ __global__ __launch_bounds__(256) void final_kernel(FinalArgs a)
             for (int k = 0; k < 4; ++k) v[g][k] = row[min(n + k, N - 1)];
         }
     }
-    block_stats<G>(ahead, pt, (N + a.tile_keys - 1) / a.tile_keys, N, threadIdx.x, zpart, zst);
+    block_stats<G>(ahead, pt, moment_entries(a.n_tiles, a.tile_keys, N), N, threadIdx.x, zpart, zst);
     if (n0 >= N) return;
     float best[4];
 #pragma unroll
@@ -467,12 +480,13 @@ tri_status launch_score_g(const tri_model &m, const tri_cache &c, ScoreArgs sa, 
         }
         sa.chunk_keys = tile_keys;
     }
-    sa.n_tiles = (c.max_seq_len + tile_keys - 1) / tile_keys;
+    if (sa.stretches) tile_keys = 0;   // (sa.n_tiles: launch_score)
+    else sa.n_tiles = (c.max_seq_len + tile_keys - 1) / tile_keys;
     hipEvent_t ev0, ev1;
     const bool timed = timing_next(&ev0, &ev1);
     if (timed) (void)hipEventRecord(ev0, st);
     if (lane_kernel) {
-        rc = launch_score_lane(G, sa, m.pairs == TRI_PAIR_HALF, st);
+        rc = launch_score_lane<G>(sa, m.pairs == TRI_PAIR_HALF, st);
     } else if (fast) {
         rc = launch_score_fast(G, sa, st);
     } else {
@@ -569,13 +583,28 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     const bool lane_kernel = fo.work && !sixteen;
     const int table_entries = !fo.work || c.k_rotated ? 0 : lane_kernel ? kLaneTablePhasors : kFastTablePhasors;
     fo.phasors = reinterpret_cast<float4 *>(ws + wl.phasors);
+    const int64_t n_inst = (int64_t)m.n_layers * c.n_seqs * m.n_kv_heads;
+    const int rounds = lane_kernel && c.n_seqs <= kStretchSeqs ? stretch_rounds(G, n_inst, c.max_seq_len, n_cu) : 0;
+    if (rounds > 0) {
+        const int count = rounds * n_cu, least = stretch_least(n_inst, c.max_seq_len, count), entries = stretch_entries(c.max_seq_len, least);
+        if ((size_t)n_inst * entries * 2 * G * sizeof(double) <= wl.raw - wl.partials &&
+            kStretchPlanAt + sizeof(StretchPlan) + (size_t)n_cu * sizeof(StretchStart) <= (size_t)kPhasorAreaBytes) {
+            fo.stretches = reinterpret_cast<StretchPlan *>(ws + wl.phasors + kStretchPlanAt);
+            fo.n_stretches = count;
+            fo.stretch_least = least;
+            fo.n_first = n_cu;
+            fo.n_entries = entries;
+            fo.partials = reinterpret_cast<double *>(ws + wl.partials);
+            fo.L = m.n_layers;
+        }
+    }
     fo.lane_kernel = lane_kernel;
     const size_t fold_lds = (size_t)(m.n_offsets + std::min(fo.fold_seqs, c.n_seqs)) * kBands * 2 * sizeof(double);
     constexpr int kFoldLdsLimit = (kMaxOffsets + kFoldSeqsMost) * kBands * 2 * (int)sizeof(double);   // the most any call asks for
     if (fold_lds > 48 * 1024 &&
         hipFuncSetAttribute((const void *)fold_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kFoldLdsLimit) != hipSuccess)
         return hip_status("hipFuncSetAttribute(fold_kernel)");
-    hipLaunchKernelGGL(fold_kernel, dim3(m.n_kv_heads * fo.seq_blocks + 1 + table_entries / kFoldThreads, m.n_layers),
+    hipLaunchKernelGGL(fold_kernel, dim3(m.n_kv_heads * fo.seq_blocks + (fo.work ? 2 : 1) + table_entries / kFoldThreads, m.n_layers),
                        dim3(kFoldThreads), fold_lds, st, fo);
     if ((rc = hip_status("fold_kernel")) != TRI_OK) return rc;
 
@@ -589,6 +618,11 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     sa.work = reinterpret_cast<int32_t *>(ws + wl.work);
     sa.n_layers = m.n_layers;
     sa.chunk_keys = chunk_keys;
+    sa.stretches = reinterpret_cast<const int32_t *>(fo.stretches);
+    sa.n_stretches = fo.n_stretches;
+    sa.stretch_least = fo.stretch_least;
+    sa.n_first = fo.n_first;
+    sa.n_tiles = fo.n_entries;
     FinalArgs fa{};
     fa.raw = sa.raw;
     fa.final_ = final_out;

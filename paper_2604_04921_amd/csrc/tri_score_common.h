@@ -17,6 +17,8 @@ struct ScoreArgs {
     int32_t first_mult;      // MFMA kernel only: workgroup b starts on item (b * first_mult) mod grid size
     int32_t *work;           // MFMA kernel only: item counter and work list (fast_work_ints(S, Nmax) ints)
     int32_t chunk_keys;      // MFMA kernels only: keys per work item (= keys per entry of `partials`)
+    const int32_t *stretches;   // general MFMA kernel: a StretchPlan instead of a work list, or NULL
+    int32_t n_stretches, stretch_least, n_first;   // at most, tiles each at least, how many of them the plan has
 };
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
@@ -68,6 +70,61 @@ __device__ __forceinline__ void build_work_list(const int32_t *seq_len, int n_se
     }
 }
 
+// The stretches of a batch (tri_items.h): how many tiles a (layer, KV head) has, how many of them lie ahead of each sequence, and where the
+// first `first` stretches begin, worked out by one workgroup of kStretchSeqs / 2 threads.
+struct StretchStart {
+    int32_t lh, s, off, entry, tiles;   // layer << 16 | KV head; from tile off of sequence s on; which of its head-instance's moments; length
+};
+constexpr int kStretchInts = 5;
+struct StretchPlan {   // in the phasor table's area, behind the table
+    int32_t before[kStretchSeqs];
+    StretchStart start[1];
+};
+constexpr size_t kStretchPlanAt = 48 * 1024;
+// where stretch i begins
+template <typename Ints>
+__device__ __forceinline__ StretchStart stretch_start(uint32_t i, const Stretches &st, uint32_t per_lh, int n_seqs, uint32_t n_kv_heads, Ints before)
+{
+    const uint32_t begin = stretch_begin(st, i), lh = begin / per_lh, l = lh / n_kv_heads;
+    const int r = (int)(begin - lh * per_lh);
+    int s = 0;   // the last sequence with no more than r tiles ahead of it: r lies in it (those behind an empty one have as many)
+    for (int step = n_seqs > 1 ? 1 << (31 - __builtin_clz(n_seqs - 1)) : 0; step > 0; step >>= 1)
+        if (s + step < n_seqs && before[s + step] <= r) s += step;
+    const int off = r - before[s];
+    return StretchStart{(int32_t)(l << 16 | (lh - l * n_kv_heads)), s, off, (int32_t)(i - stretch_of(st, begin - off)), (int32_t)(st.least + (i < st.longer ? 1 : 0))};
+}
+__device__ __forceinline__ void plan_stretches(const int32_t *seq_len, int n_seqs, int max_seq_len, int n_layers, int n_kv_heads, int least, int most,
+                                               int first, int32_t *work, StretchPlan *plan)
+{
+    __shared__ int before[kStretchSeqs], wave_sum[kStretchSeqs / 128];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    auto tiles = [&](int s) { return s < n_seqs ? (clamp_len(seq_len[s], max_seq_len) + kStretchTile - 1) / kStretchTile : 0; };
+    const int t0 = tiles(2 * tid), t1 = tiles(2 * tid + 1);
+    int cum = t0 + t1;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(cum, o, 64);
+        if (lane >= o) cum += t;
+    }
+    if (lane == 63) wave_sum[wave] = cum;
+    __syncthreads();
+    int per_lh = 0;
+#pragma unroll
+    for (int w = 0; w < kStretchSeqs / 128; ++w) {
+        if (w < wave) cum += wave_sum[w];
+        per_lh += wave_sum[w];
+    }
+    before[2 * tid] = cum - t0 - t1;
+    before[2 * tid + 1] = cum - t1;
+    if (2 * tid < n_seqs) plan->before[2 * tid] = cum - t0 - t1;
+    if (2 * tid + 1 < n_seqs) plan->before[2 * tid + 1] = cum - t1;
+    if (tid == 0) work[0] = 0, work[1] = per_lh;
+    __syncthreads();
+    const Stretches st = stretches_of((uint32_t)per_lh * (uint32_t)(n_layers * n_kv_heads), least, most);
+    for (int i = tid; i < first; i += kStretchSeqs / 2)
+        plan->start[i] = i < (int)st.count ? stretch_start(i, st, per_lh, n_seqs, n_kv_heads, before) : StretchStart{};
+}
+
 // (cos, sin) of band f at relative position r, in double
 __device__ __forceinline__ void relative_phasor(double theta, int f, int r, float *c, float *s)
 {
@@ -93,7 +150,8 @@ __device__ __forceinline__ void fast_phasor(double theta, int t, float2 *out)
 // bf16 keys; G in 1..8.  launch_score_lane (tri_score_lane.hip): the general one; launch_score_fast (tri_score_mfma.hip): paged,
 // interleaved pairs, pre-RoPE.  Each has its own phasor table layout.
 tri_status launch_score_fast(int G, const ScoreArgs &sa, hipStream_t st);
-tri_status launch_score_lane(int G, const ScoreArgs &sa, bool half_split, hipStream_t st);
+template <int G>
+tri_status launch_score_lane(const ScoreArgs &sa, bool half_split, hipStream_t st);
 // The general kernel's table of e^{i w r}: entry (band pair bp, r) = (cos, sin) of bands 2bp and 2bp+1 at relative position r, at byte
 // bp * kLanePairStride + 16 r.  The fold kernel writes it with kLaneTablePhasors extra threads.
 constexpr int kLaneRange = 88;                                  // relative positions 0 .. 87: what LDS has room for

@@ -74,9 +74,10 @@ constexpr int kTabQuad = 64 * 4;                                // floats per (c
 constexpr int lane_quads(int G) { return (G + 3) / 4; }
 // Waves per workgroup: three per SIMD where their registers allow it (168 each).
 constexpr int lane_waves(int G, bool paged, bool rotated, bool half_split) { return G <= 4 || !(paged || rotated || half_split) ? 12 : 8; }
-constexpr int lane_lds_bytes(int G, bool paged, bool rotated, bool half_split)
+constexpr int lane_slots(int G) { return G > 4 ? 2 : 4; }   // pieces of an item: as many tables as LDS has room for
+constexpr int lane_lds_bytes(int G, bool paged, bool rotated, bool half_split, bool stretch)
 {
-    return (rotated ? 0 : kLanePhasorBytes) + 3 * lane_quads(G) * kTabQuad * 4 + lane_waves(G, paged, rotated, half_split) * kStageBytes;
+    return (rotated ? 0 : kLanePhasorBytes) + (stretch ? lane_slots(G) : 1) * 3 * lane_quads(G) * kTabQuad * 4 + lane_waves(G, paged, rotated, half_split) * kStageBytes;
 }
 // acc + (four heads' entries of block BLOCK, lanes 4 BLOCK ..) x (every lane's key): lane l of the result holds key l's products
 template <bool ROWS, int BLOCK>
@@ -131,15 +132,19 @@ __device__ __forceinline__ HalfExtremes half_extremes(int v)
 }
 
 // ROTATED: the keys are stored post-RoPE (no rotation, no positions).  PAGED: block_size >= 16.  HALF: half-split pairs.
-template <int G, bool PAGED, bool ROTATED, bool HALF>
+template <int G, bool PAGED, bool ROTATED, bool HALF, bool STRETCH>
 __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void score_lane_kernel(ScoreArgs a)
 {
     constexpr int NG = lane_quads(G), W = lane_waves(G, PAGED, ROTATED, HALF), kThreads = W * 64;
+    constexpr int P = STRETCH ? lane_slots(G) : 1, kSlot = 3 * NG * kTabQuad;   // pieces of an item, floats of a piece's table
     constexpr bool ROWS = rows_layout(ROTATED, HALF), kShortChains = short_chains(PAGED, ROTATED, HALF);
     extern __shared__ __align__(16) char lds[];
-    __shared__ double red[W][2 * 4 * NG];
+    constexpr int kSums = 2 * 4 * NG;
+    __shared__ double red[W][P * kSums];
     __shared__ double lds_rev[kBands];                    // omega_f / 2pi
-    __shared__ int lds_item;
+    constexpr int kPieceInts = 8;   // lh, sequence, first tile, entry of the moments, end of the keys, end of the item's tiles, rotation
+    __shared__ __align__(16) int lds_piece[3][P][kPieceInts];   // an item's pieces,
+    __shared__ int lds_size[3][2];                              // its tiles and how many pieces
 
     const CacheView &c = a.c;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -147,8 +152,8 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
     const int j = lane & 3, b = lane >> 2;                // column (query head within a quad) and block of the lane
 
     char *const ph_base = lds;                                                  // phasor table (absent when ROTATED)
-    float *const item_tab = reinterpret_cast<float *>(lds + (ROTATED ? 0 : kLanePhasorBytes));   // the head-instance's table, [component][quad][lane][v]
-    char *const stage = reinterpret_cast<char *>(item_tab + 3 * NG * kTabQuad) + wave * kStageBytes;   // this wave's rows
+    float *const item_tab = reinterpret_cast<float *>(lds + (ROTATED ? 0 : kLanePhasorBytes));   // the pieces' tables, [piece][component][quad][lane][v]
+    char *const stage = reinterpret_cast<char *>(item_tab + P * kSlot) + wave * kStageBytes;   // this wave's rows
 
     // the phasor table: all of a thread's entries asked for at once, stored further down
     constexpr int kPhasors = ROTATED ? 0 : (kLanePhasorBytes / 16 + kThreads - 1) / kThreads;
@@ -158,13 +163,14 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
     const double rev = a.band_rev[tid % kBands];
     // entries of heads that do not exist (G not a multiple of four) stay zero for the whole launch
     if constexpr (G % 4 != 0)
-        for (int k = tid; k < 3 * NG * kTabQuad; k += kThreads) item_tab[k] = 0.f;
+        for (int k = tid; k < P * kSlot; k += kThreads) item_tab[k] = 0.f;
 
     // (constant for the whole launch, unlike the counter in front of it: scalar loads)
     typedef const __attribute__((address_space(4))) int32_t *ConstInts;
     const ConstInts work_list = (ConstInts)a.work, seq_len = (ConstInts)c.seq_len;
-    const int per_lh = work_list[1];
-    const int n_items = per_lh * a.n_layers * c.n_kv_heads;
+    const int per_lh = work_list[1];   // items, or tiles, of a (layer, KV head)
+    const Stretches cut = STRETCH ? stretches_of((uint32_t)per_lh * (uint32_t)(a.n_layers * c.n_kv_heads), a.stretch_least, a.n_stretches) : Stretches{};
+    const int n_items = STRETCH ? (int)cut.count : per_lh * a.n_layers * c.n_kv_heads;
     // A workgroup's first two items are its own: a permutation of its index, and the same behind the grid's first ones; the others come
     // from the counter.
     const int first_item = (int)(((uint32_t)blockIdx.x * (uint32_t)a.first_mult) % gridDim.x);
@@ -191,45 +197,123 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
     // the band whose phase the lane works out when a base is folded in: table_band(lane, j)
     const int my_band = ROWS ? 32 * hh + 8 * j + (b & 7) : 16 * j + b;
 
-    // A work item: a chunk of a head-instance's slots.  Everything here is wave-uniform.
-    struct Item {
+    // A piece: consecutive tiles of a head-instance.  An item: one piece (a chunk from the list), or the next P at most of a stretch.
+    // Everything here is wave-uniform, and of a stretch as little as possible is held: a piece is worked out again where it is needed again.
+    struct Walk {
+        uint32_t lh;                // layer << 16 | KV head
+        int s, off, entry, rem;     // `rem` tiles from tile `off` of sequence s on; which of the head-instance's entries the first piece has
+    };
+    struct Piece {
         const char *krow;
         const int32_t *prow, *bt;
-        int64_t inst;
-        int chunk, c0, c_len, n_tiles, rot;   // n_tiles 0: none
-        __device__ int tile_at(int t) const { const int u = t + rot; return u >= n_tiles ? u - n_tiles : u; }
+        int inst, off, c_end, t0, t1, slot, rot;   // from tile off on, keys up to c_end; its tiles are the item's [t0, t1), in an order rotated by rot
     };
-    auto item_of = [&](int id) {
-        Item it{};
-        if (id >= n_items) return it;
-        const int lh = id / per_lh, wi = id - lh * per_lh;
-        const int l = lh / c.n_kv_heads, h = lh - l * c.n_kv_heads;
-        const int s = work_list[kWorkHeader + 2 * wi];
-        it.chunk = work_list[kWorkHeader + 2 * wi + 1];
-        it.inst = ((int64_t)l * c.n_seqs + s) * c.n_kv_heads + h;
-        it.krow = (const char *)c.k + ((int64_t)l * c.stride_layer + (int64_t)h * c.stride_head) * 2 + (PAGED ? 0 : (int64_t)s * c.stride_sb * 2);
-        it.prow = c.pos + (int64_t)l * c.pos_stride_layer + (int64_t)h * c.pos_stride_head + (PAGED ? 0 : (int64_t)s * c.pos_stride_sb);
-        it.bt = PAGED ? c.block_table + (int64_t)s * c.max_blocks : nullptr;
-        it.c0 = it.chunk * a.chunk_keys;
-        it.c_len = min(clamp_len(seq_len[s], c.max_seq_len) - it.c0, a.chunk_keys);
-        it.n_tiles = (it.c_len + kTileKeys - 1) / kTileKeys;
-        // Item i takes its tiles in an order rotated by 5 i: workgroups that run side by side work on neighbouring
-        // chunks and would otherwise read the same offset of their chunk (addresses one chunk apart) at the same
-        // time, all the way through.  Measured on 36 x 16 x 8 head-instances of 32768 keys in one process: 8.13 ->
-        // 7.97 ms and 7.74 -> 7.53 ms (steps of 2 to 6 tiles alike, 1, 11 to 37 less, 7 and 9 little or nothing); with more
-        // than four query heads the kernel is bound by its arithmetic and the rotation costs 0.7 %, so it stays off.
-        it.rot = G <= 4 ? (int)(((unsigned)id * 5u) % (unsigned)it.n_tiles) : 0;
-        return it;
+    // what follows the piece that begins at w and has n tiles
+    auto behind = [&](Walk w, int n) {
+        w.rem -= n;
+        w.off = w.entry = 0;
+        if (++w.s == c.n_seqs) {
+            w.s = 0;
+            w.lh = (w.lh & 0xffffu) + 1u == (uint32_t)c.n_kv_heads ? (w.lh & 0xffff0000u) + 0x10000u : w.lh + 1u;
+            if ((int)(w.lh >> 16) >= a.n_layers) w.rem = 0;
+        }
+        if constexpr (!STRETCH) w.rem = 0;
+        return w;
     };
-    // A tile of an item: where its rows, positions and block-table entries are, its first slot, its keys that exist.
+    // w moved to where its next piece begins (past empty sequences); the piece's length in tiles (0: there is none), and where its keys end
+    auto settle = [&](Walk &w, int &c_end) {
+        int len = clamp_len(seq_len[w.s], c.max_seq_len), n = (len + kTileKeys - 1) / kTileKeys - w.off;
+        while (n <= 0 && w.rem > 0) {
+            w = behind(w, 0);
+            len = clamp_len(seq_len[w.s], c.max_seq_len);
+            n = (len + kTileKeys - 1) / kTileKeys;
+        }
+        n = max(min(n, w.rem), 0);
+        c_end = min(len, (w.off + n) * kTileKeys);
+        return n;
+    };
+    auto instance_of = [&](uint32_t lh, int s) { return ((int)(lh >> 16) * c.n_seqs + s) * c.n_kv_heads + (int)(lh & 0xffffu); };
+    auto piece_from = [&](uint32_t lh, int s, int off, int c_end, int t0, int t1, int slot, int rot) {
+        const int l = (int)(lh >> 16), h = (int)(lh & 0xffffu);
+        Piece p;
+        p.inst = instance_of(lh, s);
+        p.krow = (const char *)c.k + ((int64_t)l * c.stride_layer + (int64_t)h * c.stride_head) * 2 + (PAGED ? 0 : (int64_t)s * c.stride_sb * 2);
+        p.prow = c.pos + (int64_t)l * c.pos_stride_layer + (int64_t)h * c.pos_stride_head + (PAGED ? 0 : (int64_t)s * c.pos_stride_sb);
+        p.bt = PAGED ? c.block_table + (int64_t)s * c.max_blocks : nullptr;
+        p.off = off, p.c_end = c_end, p.t0 = t0, p.t1 = t1, p.slot = slot, p.rot = rot;
+        return p;
+    };
+    // Item i takes a piece's tiles in an order rotated by 5 i: workgroups that run side by side work on neighbouring
+    // chunks and would otherwise read the same offset of their chunk (addresses one chunk apart) at the same
+    // time, all the way through.  Measured on 36 x 16 x 8 head-instances of 32768 keys in one process: 8.13 ->
+    // 7.97 ms and 7.74 -> 7.53 ms (steps of 2 to 6 tiles alike, 1, 11 to 37 less, 7 and 9 little or nothing); with more
+    // than four query heads the kernel is bound by its arithmetic and the rotation costs 0.7 %, so it stays off.
+    auto rotation = [&](int id, int n) { return G <= 4 ? (int)(((unsigned)id * 5u) % (unsigned)max(n, 1)) : 0; };
+    // where item id (of a stretch: its first) begins
+    auto start_of = [&](int id) {
+        if constexpr (STRETCH) {
+            const ConstInts plan = (ConstInts)a.stretches;
+            if (id < a.n_first) {   // (its length is 0 where there are fewer stretches)
+                const ConstInts st = plan + kStretchSeqs + kStretchInts * id;
+                return Walk{(uint32_t)st[0], st[1], st[2], st[3], st[4]};
+            }
+            if (id >= n_items) return Walk{};
+            const StretchStart st = stretch_start((uint32_t)id, cut, (uint32_t)per_lh, c.n_seqs, (uint32_t)c.n_kv_heads, plan);
+            return Walk{(uint32_t)st.lh, st.s, st.off, st.entry, st.tiles};
+        }
+        if (id >= n_items) return Walk{};
+        const int lh = id / per_lh, wi = id - lh * per_lh, l = lh / c.n_kv_heads, per = a.chunk_keys / kTileKeys;
+        const int s = work_list[kWorkHeader + 2 * wi], chunk = work_list[kWorkHeader + 2 * wi + 1];
+        return Walk{(uint32_t)l << 16 | (uint32_t)(lh - l * c.n_kv_heads), s, chunk * per, chunk, per};
+    };
+    // One wave lists an item's pieces, an item ahead of all others, which read them from LDS.  (Every wave for itself: a wait for the
+    // length and some sixty scalar instructions per piece, three times an item.)  Leaves w behind them.
+    auto list_item = [&](Walk &w, int id, int buf) {
+        int n_tiles = 0, n_pieces = 0;
+#pragma unroll 1
+        for (; n_pieces < P && w.rem > 0; ++n_pieces) {
+            int c_end;
+            const int n = settle(w, c_end);
+            if (n == 0) break;
+            n_tiles += n;
+            if (lane == 0) {
+                int *const o = lds_piece[buf][n_pieces];
+                *reinterpret_cast<int4 *>(o) = make_int4((int)w.lh, w.s, w.off, w.entry);
+                *reinterpret_cast<int4 *>(o + 4) = make_int4(c_end, n_tiles, rotation(id, n), 0);
+            }
+            w = behind(w, n);
+        }
+        if (lane == 0) lds_size[buf][0] = n_tiles, lds_size[buf][1] = n_pieces;
+    };
+    auto spent = [&](const Walk &w) { return !STRETCH || w.rem <= 0; };
+    struct Item {
+        int buf, n_tiles, n_pieces;   // n_tiles 0: none
+    };
+    auto item_in = [&](int buf) {
+        return Item{buf, __builtin_amdgcn_readfirstlane(lds_size[buf][0]), __builtin_amdgcn_readfirstlane(lds_size[buf][1])};
+    };
+    auto listed = [&](int buf, int k, int i) { return __builtin_amdgcn_readfirstlane(lds_piece[buf][k][i]); };
+    // the piece that holds the item's tile t (t < n_tiles)
+    auto piece_of = [&](const Item &it, int t) {
+        int k = 0, t0 = 0, t1 = STRETCH ? listed(it.buf, 0, 5) : it.n_tiles;
+#pragma unroll 1
+        while (k + 1 < P && t >= t1) {
+            ++k;
+            t0 = t1;
+            t1 = listed(it.buf, k, 5);
+        }
+        return piece_from((uint32_t)listed(it.buf, k, 0), listed(it.buf, k, 1), listed(it.buf, k, 2), listed(it.buf, k, 4), t0, t1, k, listed(it.buf, k, 6));
+    };
+    // A tile: where its rows, positions and block-table entries are, its first slot, its keys that exist.
     struct Tile {
         const char *krow;
         const int32_t *prow, *bt;
         int n0, cnt;
     };
-    auto tile_of = [&](const Item &it, int t) {
-        const int n0 = it.c0 + it.tile_at(t) * kTileKeys;
-        return Tile{it.krow, it.prow, it.bt, n0, min(kTileKeys, it.c0 + it.c_len - n0)};
+    // tile t of the item, which lies in piece p
+    auto tile_of = [&](const Piece &p, int t) {
+        const int t0 = STRETCH ? p.t0 : 0, n = p.t1 - t0, u = t - t0 + p.rot, n0 = (p.off + (u >= n ? u - n : u)) * kTileKeys;
+        return Tile{p.krow, p.prow, p.bt, n0, min(kTileKeys, p.c_end - n0)};
     };
 
     // what step `half` takes of the tile at slot n0 (cnt keys exist): eight 16-byte loads per lane.  For a whole tile every address is a
@@ -324,78 +408,128 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
     uint4 kd[8];
     int pos_next = 0, bt_cur = 0, bt_next = 0;
     const bool whole_lines = (c.max_seq_len & 31) == 0 && ((uintptr_t)a.raw & 127) == 0;   // a tile's 64 scores start on a 128-byte line
-    // Items follow one another without a gap: while one is scored, the next one's table entries and every wave's first tile of it
-    // are on their way, so that between two items there are two barriers and no wait for memory.  (Asking for an item, its chunk, its
+    // Items follow one another without a gap: while one is scored, the next one's table entries (of each of its pieces) and every wave's first
+    // tile of it are on their way, so that between two items there are two barriers and no wait for memory.  (Asking for an item, its chunk, its
     // rows and its table one after the other cost about as much as twelve tiles of an idle CU.)  9216 x 2176 keys, scores and selection:
     // 1385 -> 1335 us half-split scattered, 1227 -> 1173 in slot order; 288 x 2176 interleaved scattered 90.7 -> 78.8, in slot order 83.5 -> 68.5;
     // 64 x 8 x 131072 at G = 8, a step, 5218 -> 5004
     // (with the waits that load_half and the stores below speak of).
-    float tab[kTabEach];
-    auto load_table = [&](const Item &it) {
-        const float *tbl = a.table + it.inst * (kBands * 3 * G);
+    float tab[P][kTabEach];
+    auto load_table = [&](int i, int inst) {
+        const float *tbl = a.table + (int64_t)inst * (kBands * 3 * G);
 #pragma unroll
-        for (int k = 0; k < kTabEach; ++k) tab[k] = tbl[min(tid + k * kThreads, kBands * 3 * G - 1)];
+        for (int k = 0; k < kTabEach; ++k) tab[i][k] = tbl[min(tid + k * kThreads, kBands * 3 * G - 1)];
     };
-    auto store_table = [&]() {
+    auto load_tables = [&](const Item &it) {
 #pragma unroll
-        for (int k = 0; k < kTabEach; ++k) {
-            const int e = tid + k * kThreads, f = e / (3 * G), comp = e / G - 3 * f, g = e % G;
-            if (kBands * 3 * G % kThreads != 0 && e >= kBands * 3 * G) break;
-            item_tab[((comp * NG + g / 4) * 64 + 4 * table_block(ROWS, f) + g % 4) * 4 + table_quarter(ROWS, f)] = tab[k];
+        for (int i = 0; i < P; ++i) {
+            if (i >= it.n_pieces) break;
+            load_table(i, instance_of((uint32_t)listed(it.buf, i, 0), listed(it.buf, i, 1)));
+        }
+    };
+    auto store_tables = [&](const Item &it) {
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            if (i >= it.n_pieces) break;
+#pragma unroll
+            for (int k = 0; k < kTabEach; ++k) {
+                const int e = tid + k * kThreads, f = e / (3 * G), comp = e / G - 3 * f, g = e % G;
+                if (kBands * 3 * G % kThreads != 0 && e >= kBands * 3 * G) break;
+                item_tab[i * kSlot + ((comp * NG + g / 4) * 64 + 4 * table_block(ROWS, f) + g % 4) * 4 + table_quarter(ROWS, f)] = tab[i][k];
+            }
         }
     };
     // the lane's four entries of a component and quad of heads
-    auto table_of = [&](int comp, int q) { return *reinterpret_cast<const float4v *>(item_tab + ((comp * NG + q) * 64 + lane) * 4); };
+    const float *piece_tab = item_tab;
+    auto table_of = [&](int comp, int q) { return *reinterpret_cast<const float4v *>(piece_tab + ((comp * NG + q) * 64 + lane) * 4); };
     auto load_first = [&](const Tile &ti) {
         bt_cur = load_blocks(ti);
         pos_next = load_pos(ti, bt_cur);   // (ahead of the rows: needed first)
         load_half(ti, 0, kd, bt_cur);
     };
-    Item cur = item_of(first_item);
+    // The first item: every wave for itself.
+    Walk rest = start_of(first_item);   // (the listing wave's) where what it lists next begins
+    int id = first_item;                // (the listing wave's) and of which item or stretch that is
+    Piece at{};                         // that of the wave's tile
+    Item cur{0, 0, 0};
+    {
+        Walk w = rest;
+        bool found = false;
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            if (w.rem <= 0) break;
+            int c_end;
+            const int n = settle(w, c_end);
+            if (n == 0) break;
+            load_table(i, instance_of(w.lh, w.s));
+            if (!found) at = piece_from(w.lh, w.s, w.off, c_end, cur.n_tiles, cur.n_tiles + n, i, rotation(id, n));
+            cur.n_tiles += n;
+            cur.n_pieces = i + 1;
+            found = found || wave < cur.n_tiles;
+            w = behind(w, n);
+        }
+    }
     if (cur.n_tiles == 0) return;   // (the whole workgroup)
-    load_table(cur);
-    load_first(tile_of(cur, min(wave, cur.n_tiles - 1)));   // (a wave without a tile: no branch that the wait for the table would have to allow for)
+    load_first(tile_of(at, min(wave, at.t1 - 1)));   // (a wave without a tile: no branch that the wait for the table would have to allow for)
+    constexpr int kLister = W - 1;   // the wave that most often has a tile less than others
+    if (wave == kLister) {
+        list_item(rest, id, 0);
+        if (spent(rest)) id = (int)gridDim.x + first_item, rest = start_of(id);
+        list_item(rest, id, 1);
+    }
 #pragma unroll
     for (int k = 0; k < kPhasors; ++k) reinterpret_cast<uint4v *>(ph_base)[min(tid + k * kThreads, kLanePhasorBytes / 16 - 1)] = ph[k];
     if (tid < kBands) lds_rev[tid] = rev;
     __syncthreads();   // (the zeros are written)
-    store_table();
-    if (tid == 0) lds_item = (int)gridDim.x + first_item;
+    store_tables(cur);
     __syncthreads();
+    // the counter's answer to the listing wave: the item or stretch behind those that are the workgroup's own
+    auto ask = [&]() {
+        if (lane == 0) later_item = atomicAdd(a.work + own_zero, 1);
+    };
+    bool own_next = STRETCH && id == first_item;   // (the listing wave's) the workgroup's second one is still to come
     for (;;) {
-        const Item nxt = item_of(__builtin_amdgcn_readfirstlane(lds_item));
-        if (nxt.n_tiles > 0) load_table(nxt);
+        const Item nxt = item_in(cur.buf == 2 ? 0 : cur.buf + 1);
+        const bool asks = wave == kLister && spent(rest) && !own_next;
+        if (nxt.n_tiles > 0) load_tables(nxt);
+        if (lane < P * kSums) red[wave][lane] = 0.0;   // (pieces without a tile of this wave's)
         double s1[NG], s2[NG];
         float4v t_re[NG], t_im[NG], t_m[NG];   // the table, with the tile's base folded in
+        auto begin_piece = [&]() {
+            if constexpr (STRETCH) piece_tab = item_tab + at.slot * kSlot;
 #pragma unroll
-        for (int q = 0; q < NG; ++q) {
-            s1[q] = s2[q] = 0.0;
-            t_m[q] = table_of(2, q);
-            if constexpr (ROTATED) t_re[q] = table_of(0, q), t_im[q] = table_of(1, q);
-        }
-        float *rw = a.raw + cur.inst * G * c.max_seq_len;
-        // (16-byte stores need floats' alignment only; the rows' bytes fit 32 bits with room above them: mfma_path)
-        constexpr uint32_t kNowhere = 0xffffffe0u;
-        constexpr int kNonTemporal = 2;
-        const __amdgpu_buffer_rsrc_t raw_rows = __builtin_amdgcn_make_buffer_rsrc(rw, 0, (uint32_t)G * (uint32_t)c.max_seq_len * 4u, 0x00027000);
+            for (int q = 0; q < NG; ++q) {
+                s1[q] = s2[q] = 0.0;
+                t_m[q] = table_of(2, q);
+                if constexpr (ROTATED) t_re[q] = table_of(0, q), t_im[q] = table_of(1, q);
+            }
+        };
+        begin_piece();
         if (wave >= cur.n_tiles) {
             // No tile of this item to load the next one's first behind.  (What is asked for here is waited for here, where the wave has
             // nothing else to do: left pending, it would have to be waited for wherever the other waves' path joins this one.)
-            if (wave < nxt.n_tiles) load_first(tile_of(nxt, wave));
+            if (wave < nxt.n_tiles) {
+                at = piece_of(nxt, wave);
+                load_first(tile_of(at, wave));
+            }
+            if (asks) ask();
             __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
         } else for (int t_idx = wave;;) {
-            const Tile now = tile_of(cur, t_idx);
+            const Tile now = tile_of(at, t_idx);
             const int n0 = now.n0, cnt = now.cnt;
             int p_key = pos_next;
-            // the wave's next tile: of this item, or its first of the next one
-            const bool last = t_idx + W >= cur.n_tiles, ahead = !last || wave < nxt.n_tiles;
-            const Tile nt = last ? tile_of(nxt, wave) : tile_of(cur, t_idx + W);
+            // the wave's next tile: of this piece, of a later one, or its first of the next item
+            const bool last = t_idx + W >= cur.n_tiles, ahead = !last || wave < nxt.n_tiles, leaves = t_idx + W >= at.t1;
+            Tile nt;
+            if (!leaves || !ahead) nt = tile_of(at, t_idx + W);
+            else if (last) nt = tile_of(piece_of(nxt, wave), wave);
+            else nt = tile_of(piece_of(cur, t_idx + W), t_idx + W);
             asm volatile("" : "+v"(p_key));   // (waits for the position here, and not for a copy between registers further down)
             if (ahead) {
                 if constexpr (PAGED) bt_next = load_blocks(nt);   // needed when its first loads go out, half a tile from now
                 else pos_next = load_pos(nt, 0);
             }
-            if (tid == 0 && last) later_item = atomicAdd(a.work + own_zero, 1);
+            if (last && asks) ask();
 
             // ---- the tile's base
             int base = 0, base1 = 0;   // rows: step 1's may be one of its own
@@ -617,6 +751,11 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
                     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(first[q][k]), __float_as_uint(acc[q][k]), false, false);
                     acc[q][k] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
                 }
+            // (16-byte stores need floats' alignment only; the rows' bytes fit 32 bits with room above them: mfma_path)
+            constexpr uint32_t kNowhere = 0xffffffe0u;
+            constexpr int kNonTemporal = 2;
+            float *const rw = a.raw + (int64_t)at.inst * G * c.max_seq_len;
+            const __amdgpu_buffer_rsrc_t raw_rows = __builtin_amdgcn_make_buffer_rsrc(rw, 0, (uint32_t)G * (uint32_t)c.max_seq_len * 4u, 0x00027000);
             // ---- lane l holds key n0 + l for heads 4q .. 4q + 3: turned within the blocks, lane (b, j) holds keys n0 + 4b .. + 3 for head 4q + j
 #pragma unroll
             for (int q = 0; q < NG; ++q) {
@@ -652,34 +791,48 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
                     s2[q] += v * v;
                 }
             }
-            if (last) break;
             t_idx += W;
-        }
-
-        // per-head sums over the wave's keys: lanes with equal lane % 4 hold the same head
+            if (!leaves) continue;
+            // per-head sums over the wave's keys of the piece: lanes with equal lane % 4 hold the same head
 #pragma unroll
-        for (int q = 0; q < NG; ++q) {
+            for (int q = 0; q < NG; ++q) {
 #pragma unroll
-            for (int o = 4; o < 64; o <<= 1) {
-                s1[q] += __shfl_xor(s1[q], o, 64);
-                s2[q] += __shfl_xor(s2[q], o, 64);
+                for (int o = 4; o < 64; o <<= 1) {
+                    s1[q] += __shfl_xor(s1[q], o, 64);
+                    s2[q] += __shfl_xor(s2[q], o, 64);
+                }
+                if (lane < 4) {
+                    red[wave][(STRETCH ? at.slot * kSums : 0) + (4 * q + lane) * 2 + 0] = s1[q];
+                    red[wave][(STRETCH ? at.slot * kSums : 0) + (4 * q + lane) * 2 + 1] = s2[q];
+                }
             }
-            if (lane < 4) {
-                red[wave][(4 * q + lane) * 2 + 0] = s1[q];
-                red[wave][(4 * q + lane) * 2 + 1] = s2[q];
+            if (last) {
+                if (ahead) at = piece_of(nxt, wave);
+                break;
             }
+            at = piece_of(cur, t_idx);
+            begin_piece();
         }
-        __syncthreads();   // nobody reads this item's table any more
-        if (tid < 2 * G) {
-            const int g = tid % G, which = tid / G;
+        if (wave == kLister) {   // the item after the next
+            if (spent(rest)) {
+                id = own_next ? (int)gridDim.x + first_item : 2 * (int)gridDim.x + __builtin_amdgcn_readfirstlane(later_item);
+                own_next = false;
+                rest = start_of(id);
+            }
+            list_item(rest, id, cur.buf == 0 ? 2 : cur.buf - 1);
+        }
+        __syncthreads();   // nobody reads this item's tables any more
+        if (tid < 2 * G * cur.n_pieces) {   // the waves' sums of a piece, in their order
+            const int *const o = lds_piece[cur.buf][tid / (2 * G)];
+            const int64_t to = ((int64_t)instance_of((uint32_t)o[0], o[1]) * a.n_tiles + o[3]) * (2 * G) + tid % (2 * G);
+            const int e = tid % (2 * G), g = e % G, which = e / G;
             double v = 0.0;
-            for (int w_ = 0; w_ < W; ++w_) v += red[w_][g * 2 + which];
-            a.partials[(cur.inst * a.n_tiles + cur.chunk) * (2 * G) + tid] = v;
+            for (int w_ = 0; w_ < W; ++w_) v += red[w_][tid / (2 * G) * kSums + g * 2 + which];
+            a.partials[to] = v;
         }
         if (nxt.n_tiles == 0) break;
         cur = nxt;
-        store_table();
-        if (tid == 0) lds_item = 2 * (int)gridDim.x + later_item;
+        store_tables(cur);
         __syncthreads();
     }
 }
@@ -688,23 +841,26 @@ template <int G>
 tri_status launch_lane_g(const ScoreArgs &sa, bool half_split, hipStream_t st)
 {
     const bool paged = sa.c.block_shift >= 0, rotated = sa.c.k_rotated != 0;
-    auto pick = [&](auto half) {
-        constexpr bool H = decltype(half)::value;
-        return rotated ? (paged ? score_lane_kernel<G, true, true, H> : score_lane_kernel<G, false, true, H>)
-                       : (paged ? score_lane_kernel<G, true, false, H> : score_lane_kernel<G, false, false, H>);
+    const bool stretch = sa.stretches != nullptr;
+    auto pick = [&](auto half, auto str) {
+        constexpr bool H = decltype(half)::value, S = decltype(str)::value;
+        return rotated ? (paged ? score_lane_kernel<G, true, true, H, S> : score_lane_kernel<G, false, true, H, S>)
+                       : (paged ? score_lane_kernel<G, true, false, H, S> : score_lane_kernel<G, false, false, H, S>);
     };
-    auto kern = half_split ? pick(std::true_type{}) : pick(std::false_type{});
-    const int lds = lane_lds_bytes(G, paged, rotated, half_split), threads = lane_waves(G, paged, rotated, half_split) * 64;
+    using std::true_type, std::false_type;
+    auto kern = stretch ? (half_split ? pick(true_type{}, true_type{}) : pick(false_type{}, true_type{}))
+                        : (half_split ? pick(true_type{}, false_type{}) : pick(false_type{}, false_type{}));
+    const int lds = lane_lds_bytes(G, paged, rotated, half_split, stretch), threads = lane_waves(G, paged, rotated, half_split) * 64;
     if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
         return hip_status("hipFuncSetAttribute(score_lane_kernel)");
-    static std::atomic<int> resident[2][2][2][kMaxDevices];
+    static std::atomic<int> resident[2][2][2][2][kMaxDevices];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) {
         (void)hipGetLastError();
         set_error("score: no current device below %d", kMaxDevices);
         return TRI_ERR_HIP;
     }
-    std::atomic<int> &cached = resident[half_split ? 1 : 0][rotated ? 1 : 0][paged ? 1 : 0][dev];
+    std::atomic<int> &cached = resident[stretch ? 1 : 0][half_split ? 1 : 0][rotated ? 1 : 0][paged ? 1 : 0][dev];
     int slots = cached.load(std::memory_order_relaxed);
     if (slots == 0) {
         int n_cu = 0, per_cu = 0;
@@ -723,7 +879,7 @@ tri_status launch_lane_g(const ScoreArgs &sa, bool half_split, hipStream_t st)
         set_error("score: %lld chunks of %d keys exceed the 32-bit work counter", (long long)max_items, sa.chunk_keys);
         return TRI_ERR_UNSUPPORTED;
     }
-    const int grid = (int)std::min<int64_t>((int64_t)slots, max_items);
+    const int grid = stretch ? std::min(slots, sa.n_stretches) : (int)std::min<int64_t>((int64_t)slots, max_items);
     ScoreArgs sb = sa;
     sb.first_mult = 1;
     for (int p : {197, 199, 211, 223})
@@ -737,20 +893,11 @@ tri_status launch_lane_g(const ScoreArgs &sa, bool half_split, hipStream_t st)
 
 }  // namespace
 
-tri_status launch_score_lane(int G, const ScoreArgs &sa, bool half_split, hipStream_t st)
+// (compiled once per group size: TRI_LANE_GROUP)
+template <>
+tri_status launch_score_lane<TRI_LANE_GROUP>(const ScoreArgs &sa, bool half_split, hipStream_t st)
 {
-    switch (G) {
-        case 1: return launch_lane_g<1>(sa, half_split, st);
-        case 2: return launch_lane_g<2>(sa, half_split, st);
-        case 3: return launch_lane_g<3>(sa, half_split, st);
-        case 4: return launch_lane_g<4>(sa, half_split, st);
-        case 5: return launch_lane_g<5>(sa, half_split, st);
-        case 6: return launch_lane_g<6>(sa, half_split, st);
-        case 7: return launch_lane_g<7>(sa, half_split, st);
-        case 8: return launch_lane_g<8>(sa, half_split, st);
-    }
-    set_error("group size %d not built (1 to 8)", G);
-    return TRI_ERR_UNSUPPORTED;
+    return launch_lane_g<TRI_LANE_GROUP>(sa, half_split, st);
 }
 
 }  // namespace tri

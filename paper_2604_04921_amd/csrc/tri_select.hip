@@ -80,7 +80,7 @@ template <int G>
 __device__ __forceinline__ void load_zparams(const SelectArgs &a, const Moments &ahead, int inst, int N, int tid, double *zpart, double *zst,
                                              ZParams (&zp)[G])
 {
-    block_stats<G>(ahead, a.partials + (int64_t)inst * a.n_tiles * (2 * G), (N + a.tile_keys - 1) / a.tile_keys, N, tid, zpart, zst);
+    block_stats<G>(ahead, a.partials + (int64_t)inst * a.n_tiles * (2 * G), moment_entries(a.n_tiles, a.tile_keys, N), N, tid, zpart, zst);
 #pragma unroll
     for (int g = 0; g < G; ++g) zp[g] = z_params(zst[2 * g], zst[2 * g + 1]);
 }

@@ -1,0 +1,42 @@
+"""Batches that the score kernel cuts into stretches, raw and final scores against the oracle on head-instances spread over the batch:
+stretches that begin and end inside head-instances, hold more of them than a workgroup has tables for at a time, or pass over empty
+sequences."""
+import numpy as np
+import pytest
+
+from workload import recipe
+
+import tri_harness as H
+from test_gpu_parity import run_and_check
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("group,layers,heads,lens,pairs,rotated,paged", [
+    (4, 5, 8, [2176] * 4, 0, False, False),                                   # pieces of 2 to 32 tiles
+    (3, 2, 2, [(37 * i) % 130 if i % 3 else 0 for i in range(700)], 0, False, False),   # tiny and empty sequences, groups of four
+    (8, 3, 4, [2000, 700, 1, 2100, 0, 64, 65, 2101, 900, 1300, 1999], 0, False, False),
+    (4, 5, 8, [2100, 300, 2175, 0, 1000], 1, False, False),
+    (4, 5, 8, [2100, 300, 2175, 0, 1000], 0, False, True),
+    (5, 5, 8, [2100, 300, 2175, 0, 1000], 1, True, False),
+    (2, 5, 8, [2100, 300, 2175, 0, 1000], 1, False, True),
+])
+def test_stretches(oracle, group, layers, heads, lens, pairs, rotated, paged):
+    cfg = recipe.scaled(recipe.CONFIGS["c4_paged" if paged else "c2_layer"], n_layers=layers, n_seqs=len(lens), n_q_heads=heads * group,
+                        n_kv_heads=heads, seq_len=max(lens), min_seq_len=0, budget=60 if max(lens) < 200 else 500, n_calib=16,
+                        positions="dense", block_size=16 if paged else 0, seed=7 + group)
+    rng = np.random.default_rng(3)
+    last = layers * len(lens) * heads - 1
+    picks = sorted({0, last} | set(rng.integers(0, last, size=22).tolist()))
+    instances = [(i // (len(lens) * heads), i // heads % len(lens), i % heads) for i in picks]
+
+    def mutate(w):
+        w["seq_len"][:] = lens
+        if pairs:
+            for name in ("k", "q_samples"):
+                x = w[name]
+                w[name] = np.ascontiguousarray(np.concatenate([x[..., 0::2], x[..., 1::2]], axis=-1))
+        if rotated:
+            w["k"] = H.to_post_rope(w["k"], w["pos"], cfg.rope_theta, pairs, cfg.dtype)
+
+    run_and_check(oracle, cfg, instances=instances, paged=paged, pairs=pairs, mutate=mutate, rotated=rotated)

@@ -1,0 +1,83 @@
+"""How the score kernel's batches are cut into stretches (csrc/tri_items.h, no GPU needed): every tile in one stretch, a head-instance's
+pieces in entries of their own that the workspace has room for, and where the lines of the rule lie."""
+import ctypes
+import os
+import random
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CUS = 256
+WRAPPER = """
+#include "tri_items.h"
+using namespace tri;
+extern "C" {
+int rounds(int G, long long instances, int n, int n_cu) { return stretch_rounds(G, instances, n, n_cu); }
+int least(long long instances, int n, long long stretches) { return stretch_least(instances, n, stretches); }
+int entries(int n, int least) { return stretch_entries(n, least); }
+unsigned count(unsigned total, unsigned least, unsigned most) { return stretches_of(total, least, most).count; }
+unsigned begin(unsigned total, unsigned least, unsigned most, unsigned i) { return stretch_begin(stretches_of(total, least, most), i); }
+unsigned of(unsigned total, unsigned least, unsigned most, unsigned tile) { return stretch_of(stretches_of(total, least, most), tile); }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("stretches")
+    src, so = str(tmp / "s.cpp"), str(tmp / "s.so")
+    with open(src, "w") as f:
+        f.write(WRAPPER)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-I" + os.path.join(ROOT, "paper_2604_04921_amd", "csrc"),
+                    src, "-o", so], check=True)
+    so = ctypes.CDLL(so)
+    so.rounds.argtypes = [ctypes.c_int, ctypes.c_longlong, ctypes.c_int, ctypes.c_int]
+    so.least.argtypes = [ctypes.c_longlong, ctypes.c_int, ctypes.c_longlong]
+    for f in (so.count, so.begin, so.of):
+        f.restype = ctypes.c_uint
+    return so
+
+
+def test_every_tile_once_and_room_for_the_moments(lib):
+    rng = random.Random(11)
+    taken = 0
+    for _ in range(400):
+        n, seqs, lh = int(2 ** rng.uniform(0, 17)), rng.randint(1, 12), rng.randint(1, 300)
+        r = lib.rounds(4, lh * seqs, n, CUS)
+        if r == 0:
+            continue
+        taken += 1
+        most = r * CUS
+        least = lib.least(lh * seqs, n, most)
+        entries = lib.entries(n, least)
+        assert entries <= -(-n // 256) + 1   # an entry per 256 keys and one more: what workspaces are sized for
+        lens = [rng.choice([0, 1, n, rng.randint(0, n), rng.randint(0, n)]) for _ in range(seqs)]
+        tiles = [-(-x // 64) for x in lens]
+        total = sum(tiles) * lh
+        count = lib.count(total, least, most)
+        assert count <= most and (count > 0) == (total > 0)
+        starts = [lib.begin(total, least, most, i) for i in range(count + 1)]
+        assert starts[0] == 0 and starts[-1] == total if total else True
+        sizes = [b - a for a, b in zip(starts, starts[1:])]
+        assert max(sizes) - min(sizes) <= 1 if sizes else True
+        at = 0
+        for _ in range(min(lh, 3)):
+            for t in tiles:
+                if t:
+                    first = lib.of(total, least, most, at)
+                    last = lib.of(total, least, most, at + t - 1)
+                    assert starts[first] <= at < starts[first + 1] and starts[last] <= at + t - 1 < starts[last + 1]
+                    assert last - first + 1 <= entries, (n, least, t)
+                at += t
+    assert taken > 100
+
+
+@pytest.mark.parametrize("group,instances,n,stretches", [
+    (4, 121, 2176, True), (4, 120, 2176, False),             # more than sixteen tiles per CU
+    (4, 2047, 2176, True), (4, 2048, 2176, False),           # short sequences: not in large batches
+    (4, 2047, 32768, True), (4, 2048, 32768, False),         # 32 items per CU and more
+    (4, 2304, 8192, True), (4, 8192, 8192, False),
+    (8, 511, 32768, True), (8, 512, 32768, False)])          # more than four query heads: not in large batches
+def test_where_the_lines_lie(lib, group, instances, n, stretches):
+    assert (lib.rounds(group, instances, n, CUS) > 0) == stretches
