@@ -21,20 +21,24 @@ struct CentersArgs {
 constexpr int kCenterThreads = 256;
 constexpr int kCenterWaves = kCenterThreads / 64;
 
-// The 16-byte pieces that hold (re, im) of bands 8q..8q+7 of the head vector at element `row`: two (bf16) or four (fp32), 32
-// or 64 contiguous bytes with interleaved pairs, two halves 64 elements apart with half-split ones.
-template <bool BF16, bool HALF>
+// (re, im) of eight bands of a head vector in 16-byte pieces, two (bf16) or four (fp32): with interleaved pairs one run of pieces, with
+// half-split ones a run of real and one of imaginary parts.  The O lanes that share 8 O bands (from octet q0 on) take the pieces of a run in
+// turn, so that a load instruction reads O neighbouring ones.  (A lane with its pieces side by side read every line by two or four
+// instructions, some of them from memory again: 4096 tokens x 36 x 32 heads, interleaved, 310 -> 243 us; 18 x 32 in fp32 450 -> 203, half-split 275 -> 202.)
+template <bool BF16, bool HALF, int O>
 struct Octet {
-    static constexpr int kPieces = BF16 ? 2 : 4;
+    static constexpr int kPieces = BF16 ? 2 : 4, kPer = BF16 ? 8 : 4;   // pieces, elements per piece
+    static constexpr int kRun = HALF ? kPieces / 2 : kPieces, kPieceBands = HALF ? kPer : kPer / 2;
     uint4 p[kPieces];
+    // which of the O lanes' bands is the k-th of lane q
+    static __device__ __forceinline__ int band(int q, int k) { return (k / kPieceBands * O + q) * kPieceBands + k % kPieceBands; }
     // ONCE: nobody else reads these bytes
     template <bool ONCE>
-    __device__ __forceinline__ void load(const void *base, int64_t row, int q)
+    __device__ __forceinline__ void load(const void *base, int64_t row, int q0, int q)
     {
-        constexpr int kPer = BF16 ? 8 : 4;   // elements per piece
 #pragma unroll
         for (int k = 0; k < kPieces; ++k) {
-            const int e = HALF ? (k / (kPieces / 2)) * kBands + 8 * q + (k % (kPieces / 2)) * kPer : 16 * q + k * kPer;
+            const int e = k / kRun * kBands + (q0 * kRun + k % kRun * O + q) * kPer;
             const char *at = (const char *)base + (row + e) * (BF16 ? 2 : 4);
             p[k] = ONCE ? load_stream16(at) : *reinterpret_cast<const uint4 *>(at);
         }
@@ -65,12 +69,21 @@ __device__ __forceinline__ double root(double s)
     return s > 0.0 && s < __builtin_inf() ? g : s;   // 0, infinity and NaN are their own
 }
 
+// The same for a sum that is not infinite, and NaN for one that is: one step of third order, and zero's root through a finite reciprocal
+// instead of a comparison (a quarter of the clocks of a sample and band: 4096 tokens x 36 x 32 half-split heads in bf16 257 -> 222 us).
+__device__ __forceinline__ double finite_root(double s)
+{
+    const double r = __builtin_amdgcn_rsq(fmax(s, 1e-300));   // (the least square of an fp32 value other than 0 is 2e-90)
+    const double g = s * r, e = fma(-g, r, 1.0);
+    return fma(g * e, fma(0.375, e, 0.5), g);
+}
+
 // Block 256: thread = (band octet of the workgroup's O, token residue); O neighbouring threads read O/8 of a head vector with
 // 16-byte loads, the next token's on their way while one is summed.  Grid: 8 / O workgroups per (layer, head), eight apart in the
 // launch, so that those that share cache lines run on one XCD, side by side (workgroups go to the eight XCDs in turn).  Double sums in a fixed order: per thread
 // over its tokens, then a butterfly over the residues of a wave, then the waves in order.
-// Bound by its double arithmetic and the memory stream together: 4096 tokens x 36 x 32 heads in bf16 (1.2 GB) 421 -> 265 us with the root
-// above and 256 threads where 512 with the library's square root stood, in fp32 (18 x 32 heads) 684 -> 277.
+// Bound by its double arithmetic in bf16 (4096 tokens x 36 x 32 heads, 1.2 GB: 245 us half-split, 243 interleaved, 4.9 TB/s, where 282 and 302 stood before
+// finite_root and the order of the pieces) and by the memory stream in fp32 (18 x 32 heads, as many bytes: 202, 6.0 TB/s).
 template <bool BF16, bool HALF, int O>
 __global__ __launch_bounds__(kCenterThreads) void centers_kernel(CentersArgs a)
 {
@@ -82,22 +95,30 @@ __global__ __launch_bounds__(kCenterThreads) void centers_kernel(CentersArgs a)
     const int q0 = (int)(blockIdx.x / 8) % kParts * O;
     if (lh >= a.heads) return;
     double sre[8], sim[8], sab[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) sre[k] = sim[k] = sab[k] = 0.0;
     auto row = [&](int64_t t) { return (t * a.heads + lh) * kHeadDim; };
-    Octet<BF16, HALF> cur, nxt;
-    if (r < a.T) cur.template load<O == 8>(a.q, row(r), q0 + q);
-    for (int64_t t = r; t < a.T; t += kResidues) {
-        nxt.template load<O == 8>(a.q, row(t + kResidues < a.T ? t + kResidues : t), q0 + q);
+    auto sum_up = [&](auto root_of) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const double x = (double)cur.re(k), y = (double)cur.im(k);
-            sre[k] += x;
-            sim[k] += y;
-            sab[k] += root(fma(x, x, y * y));
+        for (int k = 0; k < 8; ++k) sre[k] = sim[k] = sab[k] = 0.0;
+        Octet<BF16, HALF, O> cur, nxt;
+        if (r < a.T) cur.template load<O == 8>(a.q, row(r), q0, q);
+        for (int64_t t = r; t < a.T; t += kResidues) {
+            nxt.template load<O == 8>(a.q, row(t + kResidues < a.T ? t + kResidues : t), q0, q);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const double x = (double)cur.re(k), y = (double)cur.im(k);
+                sre[k] += x;
+                sim[k] += y;
+                sab[k] += root_of(fma(x, x, y * y));
+                __builtin_amdgcn_sched_barrier(0);   // one band after the other: 84 registers instead of 116 (bf16, half-split)
+            }
+            cur = nxt;
         }
-        cur = nxt;
-    }
+    };
+    sum_up([](double v) { return finite_root(v); });
+    bool finite = true;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) finite = finite && sab[k] == sab[k];
+    if (!finite) sum_up([](double v) { return root(v); });   // an infinite or not a numerical sample among the thread's
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
 #pragma unroll
@@ -107,9 +128,10 @@ __global__ __launch_bounds__(kCenterThreads) void centers_kernel(CentersArgs a)
             sab[k] += __shfl_xor(sab[k], o, 64);
         }
         if ((threadIdx.x & 63) < O) {
-            part[wave][8 * q + k][0] = sre[k];
-            part[wave][8 * q + k][1] = sim[k];
-            part[wave][8 * q + k][2] = sab[k];
+            const int f = Octet<BF16, HALF, O>::band(q, k);
+            part[wave][f][0] = sre[k];
+            part[wave][f][1] = sim[k];
+            part[wave][f][2] = sab[k];
         }
     }
     __syncthreads();
