@@ -268,6 +268,15 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
     };
     // One wave lists an item's pieces, an item ahead of all others, which read them from LDS.  (Every wave for itself: a wait for the
     // length and some sixty scalar instructions per piece, three times an item.)  Leaves w behind them.
+    auto list_piece = [&](int buf, int k, const Walk &w, int c_end, int t1, int rot) {
+        if (lane != 0) return;
+        int *const o = lds_piece[buf][k];
+        *reinterpret_cast<int4 *>(o) = make_int4((int)w.lh, w.s, w.off, w.entry);
+        *reinterpret_cast<int4 *>(o + 4) = make_int4(c_end, t1, rot, 0);
+    };
+    auto list_size = [&](int buf, int n_tiles, int n_pieces) {
+        if (lane == 0) lds_size[buf][0] = n_tiles, lds_size[buf][1] = n_pieces;
+    };
     auto list_item = [&](Walk &w, int id, int buf) {
         int n_tiles = 0, n_pieces = 0;
 #pragma unroll 1
@@ -276,14 +285,10 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
             const int n = settle(w, c_end);
             if (n == 0) break;
             n_tiles += n;
-            if (lane == 0) {
-                int *const o = lds_piece[buf][n_pieces];
-                *reinterpret_cast<int4 *>(o) = make_int4((int)w.lh, w.s, w.off, w.entry);
-                *reinterpret_cast<int4 *>(o + 4) = make_int4(c_end, n_tiles, rotation(id, n), 0);
-            }
+            list_piece(buf, n_pieces, w, c_end, n_tiles, rotation(id, n));
             w = behind(w, n);
         }
-        if (lane == 0) lds_size[buf][0] = n_tiles, lds_size[buf][1] = n_pieces;
+        list_size(buf, n_tiles, n_pieces);
     };
     auto spent = [&](const Walk &w) { return !STRETCH || w.rem <= 0; };
     struct Item {
@@ -448,12 +453,13 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
         load_half(ti, 0, kd, bt_cur);
     };
     // The first item: every wave for itself.
+    constexpr int kLister = W - 1;      // the wave that most often has a tile less than others
     Walk rest = start_of(first_item);   // (the listing wave's) where what it lists next begins
     int id = first_item;                // (the listing wave's) and of which item or stretch that is
     Piece at{};                         // that of the wave's tile
     Item cur{0, 0, 0};
     {
-        Walk w = rest;
+        Walk &w = rest;
         bool found = false;
 #pragma unroll
         for (int i = 0; i < P; ++i) {
@@ -462,8 +468,10 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
             const int n = settle(w, c_end);
             if (n == 0) break;
             load_table(i, instance_of(w.lh, w.s));
-            if (!found) at = piece_from(w.lh, w.s, w.off, c_end, cur.n_tiles, cur.n_tiles + n, i, rotation(id, n));
+            const int rot = rotation(id, n);
+            if (!found) at = piece_from(w.lh, w.s, w.off, c_end, cur.n_tiles, cur.n_tiles + n, i, rot);
             cur.n_tiles += n;
+            if (wave == kLister) list_piece(0, i, w, c_end, cur.n_tiles, rot);
             cur.n_pieces = i + 1;
             found = found || wave < cur.n_tiles;
             w = behind(w, n);
@@ -471,9 +479,8 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
     }
     if (cur.n_tiles == 0) return;   // (the whole workgroup)
     load_first(tile_of(at, min(wave, at.t1 - 1)));   // (a wave without a tile: no branch that the wait for the table would have to allow for)
-    constexpr int kLister = W - 1;   // the wave that most often has a tile less than others
     if (wave == kLister) {
-        list_item(rest, id, 0);
+        list_size(0, cur.n_tiles, cur.n_pieces);
         if (spent(rest)) id = (int)gridDim.x + first_item, rest = start_of(id);
         list_item(rest, id, 1);
     }
@@ -490,7 +497,7 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
     bool own_next = STRETCH && id == first_item;   // (the listing wave's) the workgroup's second one is still to come
     for (;;) {
         const Item nxt = item_in(cur.buf == 2 ? 0 : cur.buf + 1);
-        const bool asks = wave == kLister && spent(rest) && !own_next;
+        const bool asks = wave == kLister && nxt.n_tiles > 0 && spent(rest) && !own_next;
         if (nxt.n_tiles > 0) load_tables(nxt);
         if (lane < P * kSums) red[wave][lane] = 0.0;   // (pieces without a tile of this wave's)
         double s1[NG], s2[NG];
@@ -813,7 +820,7 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
             at = piece_of(cur, t_idx);
             begin_piece();
         }
-        if (wave == kLister) {   // the item after the next
+        if (wave == kLister && nxt.n_tiles > 0) {   // the item after the next (behind the last one nothing is waited for: 1 us of small calls)
             if (spent(rest)) {
                 id = own_next ? (int)gridDim.x + first_item : 2 * (int)gridDim.x + __builtin_amdgcn_readfirstlane(later_item);
                 own_next = false;
