@@ -70,6 +70,22 @@ __device__ __forceinline__ float bin_place(float score) { return fmaf(score, 128
 __device__ __forceinline__ int linear_bin(float score) { return (int)__builtin_amdgcn_fmed3f(bin_place(score), 0.0f, 2047.0f); }
 __device__ __forceinline__ int linear_bin(uint32_t u) { return linear_bin(key_to_float(u)); }
 
+// The least key whose score lies at or above a place: bins are ranges of keys, since places rise with keys.  All lanes of the wave take
+// part, a sixty-fourth of the range left each.
+__device__ __forceinline__ uint32_t first_key(float place, int lane)
+{
+    uint32_t first = 0u;   // no key below it reaches the place
+#pragma unroll 1
+    for (int shift = 26; shift > -6; shift -= 6) {
+        const int sh = max(shift, 0);
+        const uint32_t u = first + ((uint32_t)(lane + 1) << sh) - 1u;   // the last key of the lane's part
+        // (patterns below that of -infinity and above that of infinity are no scores')
+        const bool below = u < 0x007fffffu || bin_place(key_to_float(u)) < place;
+        first += (uint32_t)__popcll(__ballot(below)) << sh;
+    }
+    return first;
+}
+
 // Mean and 1/sigma of a head-instance's heads from the moments (block_stats; every thread of the workgroup calls).
 template <int G>
 __device__ __forceinline__ Moments load_moments(const SelectArgs &a, int inst, int tid)
@@ -449,22 +465,32 @@ __global__ __launch_bounds__(THREADS, HELD ? (THREADS == kSelThreads ? 4 : 5) : 
     // ---- gather the selected bin's keys (any order; the ranks below do not depend on it), count the keys above it
     uint32_t above_bin = 0u;
     // (places below the first bin and beyond the last one belong to them; a slot past the end, key 0, is no number and no score's)
-    const float bin_lo = sel_bin == 0 ? -__builtin_inff() : (float)sel_bin, bin_hi = sel_bin == kSelBins - 1 ? __builtin_inff() : (float)(sel_bin + 1);
-    const bool last_bin = sel_bin == kSelBins - 1;
-    for_rows([&](int n0, const uint32_t (&u)[4]) {
+    auto gather_bin = [&](auto above, auto inside) {
+        for_rows([&](int n0, const uint32_t (&u)[4]) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float place = bin_place(key_to_float(u[i]));
-            above_bin += place >= bin_hi && !last_bin ? 1u : 0u;
-            if (place >= bin_lo && (place < bin_hi || last_bin)) {
-                const uint32_t pos = atomicAdd(&sh[2], 1u);
-                if (pos < (uint32_t)kCand) {
-                    cand_key[pos] = u[i];
-                    cand_idx[pos] = (uint32_t)(n0 + 4 * lane + i);
+            for (int i = 0; i < 4; ++i) {
+                above_bin += above(u[i]) ? 1u : 0u;
+                if (inside(u[i])) {
+                    const uint32_t pos = atomicAdd(&sh[2], 1u);
+                    if (pos < (uint32_t)kCand) {
+                        cand_key[pos] = u[i];
+                        cand_idx[pos] = (uint32_t)(n0 + 4 * lane + i);
+                    }
                 }
             }
-        }
-    });
+        });
+    };
+    const bool last_bin = sel_bin == kSelBins - 1;
+    if constexpr (HELD) {
+        const float bin_lo = sel_bin == 0 ? -__builtin_inff() : (float)sel_bin, bin_hi = last_bin ? __builtin_inff() : (float)(sel_bin + 1);
+        gather_bin([&](uint32_t u) { return bin_place(key_to_float(u)) >= bin_hi && !last_bin; },
+                   [&](uint32_t u) { const float place = bin_place(key_to_float(u)); return place >= bin_lo && (place < bin_hi || last_bin); });
+    } else {
+        // Long rows: compared as keys, with the bin's ends found once (1 us, which rows in LDS don't win back: one of 4096 keys 7.2 -> 8.2), and not
+        // key by key as places.  With the single comparison of the emit below, 8 rows of 131072 keys 40.6 -> 36.4 us.
+        const uint32_t first = sel_bin == 0 ? 1u : first_key((float)sel_bin, lane), end = last_bin ? ~0u : first_key((float)(sel_bin + 1), lane);
+        gather_bin([&](uint32_t u) { return u >= end; }, [&](uint32_t u) { return u - first < end - first; });
+    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) above_bin += __shfl_xor(above_bin, o, 64);
     if (lane == 0) wave_gt[wave] = above_bin;
@@ -522,6 +548,28 @@ __global__ __launch_bounds__(THREADS, HELD ? (THREADS == kSelThreads ? 4 : 5) : 
 
     // ---- ordered emit: the wave starts behind the kept slots of the waves before it
     uint32_t g_run = sum_before<kWaves>(wave_gt, wave), e_run = sum_before<kWaves>(wave_eq, wave);
+    // Every threshold tie is kept (mostly there is one): one comparison per key (8 rows of 32768 keys, this launch, 21.7 -> 20.4 us, 576 of them
+    // 90 -> 86, 8 of 12289 11.9 -> 11.5; short ones 0.2 us either way).
+    if (sum_before<kWaves>(wave_eq, kWaves) == need) {
+        uint32_t run = g_run + e_run;
+        for_rows([&](int n0, const uint32_t (&u)[4]) {
+            uint32_t at = run;   // kept keys before the lane's first slot
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint64_t m = __ballot(u[i] >= thr);
+                at = lanes_below(m, at);
+                run += (uint32_t)__popcll(m);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const bool kept = u[i] >= thr;
+                if (kept && at < (uint32_t)B) out[at] = n0 + 4 * lane + i;
+                at += kept ? 1u : 0u;
+            }
+        });
+        fill_tail(B);
+        return;
+    }
     for_rows([&](int n0, const uint32_t (&u)[4]) {
         uint32_t g_at = g_run, e_at = e_run;   // kept / threshold keys before the lane's first slot
         uint64_t eq_any = 0ull;
