@@ -38,6 +38,7 @@ struct FoldArgs {
     int32_t S, Hq, Hkv, G;
     int32_t fold_seqs;      // sequences per workgroup
     int32_t seq_blocks;     // workgroups per (layer, KV head)
+    int32_t band_shift;     // each once per 64 >> band_shift parts of 1 << band_shift bands
     double theta;
     int32_t n_off;
     int32_t variant;        // tri_score_variant
@@ -56,14 +57,15 @@ constexpr int kFoldSeqs = 8;      // sequences per workgroup, more where workgro
 constexpr int kFoldSeqsMost = 32; // at most this many
 constexpr int kFoldThreads = 512;
 
-// The folded tables of one (layer, KV head) and fold_seqs sequences per workgroup: grid (Hkv * seq_blocks + extra, L),
-// block 512.  The phasors a fold needs depend on the band and on the offsets or the query position only, and every
-// workgroup evaluates them for itself: (offset, band) and (sequence, band) pairs spread over its threads, three double-precision
-// sincos per thread for 16 offsets and 8 sequences, the offsets then added in their order by one thread per band.  The
+// The folded tables of one (layer, KV head), fold_seqs sequences and 1 << band_shift bands per workgroup: grid (Hkv * seq_blocks *
+// (64 >> band_shift) + extra, L), block 512.  The phasors a fold needs depend on the band and on the offsets or the query position only, and every
+// workgroup evaluates them for itself: (offset or sequence, band) pairs spread over its threads, three double-precision
+// sincos per thread for 16 offsets and 8 sequences and all bands, the offsets then added in their order by one thread per band.  The
 // kernel is bound by that chain of software sincos and pow, not by its work: a launch of its own for the phasors, in which one
 // thread per band went through the offsets one after the other, and a second one for the tables took 5.8 + 4.6 us (10.6 + 5.1
 // with 32 offsets); with this one a step on one head's 4096 keys takes 35.6 us instead of 39.5, on one layer of eight heads
-// x 32768 keys 74.3 instead of 78.4.
+// x 32768 keys 74.3 instead of 78.4.  Where workgroups are few the bands of each go to two or four (launch_score), a sincos per thread: the
+// same steps 22.6 -> 22.2 and 47.4 -> 46.9 us, 32 x 2176 keys, scores and selection, 26.4 -> 26.0.
 // The extra workgroups of the first layer's row have nothing to do with the tables: the first writes the band frequencies, the second lists
 // the stretches or chunks of the MFMA score kernels (a launch of its own would cost more than the list; behind the first one's pow it cost small
 // calls 0.5 us), those after it fill the MFMA score kernel's phasor table when it needs one, an entry per thread.
@@ -71,12 +73,11 @@ __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
 {
     extern __shared__ __align__(16) double fold_lds[];
     double (*const off_ph)[2] = reinterpret_cast<double (*)[2]>(fold_lds);   // e^{i w delta_j}: entry (j, band); row 0 then holds their mean
-    double (*const cur_ph)[2] = off_ph + a.n_off * kBands;                   // e^{i w cur_pos[s]}
-    const int tid = threadIdx.x;
-    const int n_fold = a.Hkv * a.seq_blocks, l = blockIdx.y;
-    // Section 2.1: omega_f = theta^(-2f/d); kept as revolutions per position.  (kFoldThreads is a multiple of F: a
-    // thread's band is the same in every loop below)
-    const int f = tid % kBands;
+    const int tid = threadIdx.x, bands = 1 << a.band_shift, parts = kBands >> a.band_shift;
+    double (*const cur_ph)[2] = off_ph + a.n_off * bands;                    // e^{i w cur_pos[s]}
+    const int n_fold = a.Hkv * a.seq_blocks * parts, l = blockIdx.y;
+    // Section 2.1: omega_f = theta^(-2f/d); kept as revolutions per position.  (kFoldThreads is a multiple of the
+    // workgroup's bands: a thread's band is the same in every loop below)
     const int extra = (int)blockIdx.x - n_fold;   // uniform over the workgroup
     if (extra >= 0 && l > 0) return;
     if (extra == 1) {
@@ -90,58 +91,54 @@ __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
         else fast_phasor(a.theta, t, reinterpret_cast<float2 *>(a.phasors));
         return;
     }
+    const int f0 = extra == 0 ? 0 : (blockIdx.x & (parts - 1)) << a.band_shift, f = extra == 0 ? tid % kBands : f0 + (tid & (bands - 1));
     const double rev = pow(a.theta, -2.0 * (double)f / (double)kHeadDim) / kTwoPi;
     if (extra == 0) {
         if (tid < kBands) a.band_rev[f] = rev;
         return;
     }
-    const int h = blockIdx.x / a.seq_blocks, sb = blockIdx.x - h * a.seq_blocks;
+    const int x = blockIdx.x >> (6 - a.band_shift), h = x / a.seq_blocks, sb = x - h * a.seq_blocks;
     // the thread's (band, query head) pair, the head fastest: neighbouring threads write neighbouring entries of [F][3][G].  Its
     // statistics are asked for ahead of the phasors.
     static_assert(kBands * kMaxGroup <= kFoldThreads, "a pair per thread");
-    const int fb = min(tid / a.G, kBands - 1), g = tid - tid / a.G * a.G;
+    const int fl = min(tid / a.G, bands - 1), fb = f0 + fl, g = tid - tid / a.G * a.G;
     const float *ct = a.centers + (((int64_t)l * a.Hq + h * a.G + g) * kBands + fb) * 3;
     const float c0 = ct[0], c1 = ct[1], c2 = ct[2];
     const int s0 = sb * a.fold_seqs, n_seq = min(a.S - s0, a.fold_seqs);
-    if (a.stretches)   // an entry that no stretch of the head-instance's writes counts as nothing
+    if (a.stretches && f0 == 0)   // an entry that no stretch of the head-instance's writes counts as nothing
         for (int j = 0; j < n_seq; ++j) {
             double *const m = a.partials + (((int64_t)l * a.S + s0 + j) * a.Hkv + h) * a.n_entries * (2 * a.G);
             for (int k = tid; k < a.n_entries * 2 * a.G; k += kFoldThreads) m[k] = 0.0;
         }
-    for (int k = tid; k < a.n_off * kBands; k += kFoldThreads) {
+    for (int k = tid; k < (a.n_off + n_seq) * bands; k += kFoldThreads) {   // (the sequences' phasors lie behind the offsets')
+        const int j = k >> a.band_shift;
         double c, s;
-        unit_phasor((double)a.offsets[k / kBands], rev, &c, &s);
+        unit_phasor(j < a.n_off ? (double)a.offsets[j] : (double)a.cur_pos[s0 + j - a.n_off], rev, &c, &s);
         off_ph[k][0] = c;
         off_ph[k][1] = s;
     }
-    for (int k = tid; k < n_seq * kBands; k += kFoldThreads) {
-        double c, s;
-        unit_phasor((double)a.cur_pos[s0 + k / kBands], rev, &c, &s);
-        cur_ph[k][0] = c;
-        cur_ph[k][1] = s;
-    }
     __syncthreads();
-    if (tid < kBands) {   // mean over the offsets, in their order
+    if (tid < bands) {   // mean over the offsets, in their order
         double er = 0.0, ei = 0.0;
 #pragma unroll 8
         for (int j = 0; j < a.n_off; ++j) {
-            er += off_ph[j * kBands + f][0];
-            ei += off_ph[j * kBands + f][1];
+            er += off_ph[j * bands + tid][0];
+            ei += off_ph[j * bands + tid][1];
         }
-        off_ph[f][0] = er / (double)a.n_off;
-        off_ph[f][1] = ei / (double)a.n_off;
+        off_ph[tid][0] = er / (double)a.n_off;
+        off_ph[tid][1] = ei / (double)a.n_off;
     }
     __syncthreads();
     // the ablation variants (Section 5) only change the table: no trig part, no norm part, or the norm
     // part without its (1 - R_f) weight, i.e. S_norm^(0) of Section 4.1
     const bool trig_on = a.variant != TRI_SCORE_NORM_ONLY, norm_on = a.variant != TRI_SCORE_TRIG_ONLY;
-    if (tid < kBands * a.G) {
-        const double er = off_ph[fb][0], ei = off_ph[fb][1];
+    if (tid < bands * a.G) {
+        const double er = off_ph[fl][0], ei = off_ph[fl][1];
         const double qr = (double)c0, qi = (double)c1, qa = (double)c2;
         const double ar = trig_on ? qr * er - qi * ei : 0.0, ai = trig_on ? qr * ei + qi * er : 0.0;
         const double cn = !norm_on ? 0.0 : a.variant == TRI_SCORE_NORM_UNWEIGHTED ? qa : qa - hypot(qr, qi);
         for (int j = 0; j < n_seq; ++j) {
-            const double c = cur_ph[j * kBands + fb][0], sn = cur_ph[j * kBands + fb][1];
+            const double c = cur_ph[j * bands + fl][0], sn = cur_ph[j * bands + fl][1];
             float *t = a.table + (((((int64_t)l * a.S + s0 + j) * a.Hkv + h) * kBands + fb) * 3) * a.G;
             t[0 * a.G + g] = (float)(ar * c - ai * sn);
             t[1 * a.G + g] = (float)(ar * sn + ai * c);
@@ -571,6 +568,9 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     while (fo.fold_seqs < kFoldSeqsMost && (int64_t)m.n_layers * m.n_kv_heads * ((c.n_seqs + 2 * fo.fold_seqs - 1) / (2 * fo.fold_seqs)) >= 2 * n_cu)
         fo.fold_seqs *= 2;
     fo.seq_blocks = (c.n_seqs + fo.fold_seqs - 1) / fo.fold_seqs;
+    fo.band_shift = 6;   // (half as many workgroups as CUs at most: 64 head-instances of 2176 keys, scores and selection, 29.5 -> 29.3 us with two parts)
+    const int64_t n_fold = (int64_t)m.n_layers * m.n_kv_heads * fo.seq_blocks;
+    while (fo.band_shift > 4 && n_fold * (kBands >> fo.band_shift) * 2 <= n_cu / 2) --fo.band_shift;
     fo.Hq = m.n_q_heads;
     fo.Hkv = m.n_kv_heads;
     fo.G = G;
@@ -604,7 +604,7 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     if (fold_lds > 48 * 1024 &&
         hipFuncSetAttribute((const void *)fold_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kFoldLdsLimit) != hipSuccess)
         return hip_status("hipFuncSetAttribute(fold_kernel)");
-    hipLaunchKernelGGL(fold_kernel, dim3(m.n_kv_heads * fo.seq_blocks + (fo.work ? 2 : 1) + table_entries / kFoldThreads, m.n_layers),
+    hipLaunchKernelGGL(fold_kernel, dim3(m.n_kv_heads * fo.seq_blocks * (kBands >> fo.band_shift) + (fo.work ? 2 : 1) + table_entries / kFoldThreads, m.n_layers),
                        dim3(kFoldThreads), fold_lds, st, fo);
     if ((rc = hip_status("fold_kernel")) != TRI_OK) return rc;
 
