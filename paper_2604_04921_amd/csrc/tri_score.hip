@@ -25,24 +25,24 @@ struct FoldArgs {
     float *table;           // [L][S][Hkv][F][3][G]
     double *band_rev;       // [F]
     const int32_t *cur_pos; // [S]
-    const int32_t *seq_len; // [S]
-    int32_t *work;          // work list of the MFMA score kernels, or NULL when the generic kernel runs
-    int32_t chunk_keys;     // keys per entry of that list
-    StretchPlan *stretches; // stretches of the general MFMA kernel instead, or NULL; its moments are cleared here
-    int32_t n_stretches, stretch_least, n_first, n_entries;
-    double *partials;       // [L][S][Hkv][n_entries][2G]
-    int32_t L;
-    float4 *phasors;        // relative-position phasor table of the MFMA score kernel, filled in by extra workgroups
-    int32_t lane_kernel;    // its layout: that of tri_score_lane.hip or the sixteen-lane kernel's
-    int32_t max_seq_len;
+    double theta;
+    int32_t n_off;
+    int32_t variant;        // tri_score_variant
     int32_t S, Hq, Hkv, G;
     int32_t fold_seqs;      // sequences per workgroup
     int32_t seq_blocks;     // workgroups per (layer, KV head)
     int32_t band_shift;     // each once per 64 >> band_shift parts of 1 << band_shift bands
-    double theta;
-    int32_t n_off;
-    int32_t variant;        // tri_score_variant
+    int32_t lane_kernel;    // layout of the phasor table: that of tri_score_lane.hip or the sixteen-lane kernel's
+    float4 *phasors;        // relative-position phasor table of the MFMA score kernel, filled in by extra workgroups
+    StretchPlan *stretches; // stretches of the general MFMA kernel, or NULL; its moments are cleared here
     int64_t offsets[kMaxOffsets];
+    const int32_t *seq_len; // [S]
+    int32_t *work;          // work list of the MFMA score kernels, or NULL when the generic kernel runs
+    double *partials;       // [L][S][Hkv][n_entries][2G]
+    int32_t chunk_keys;     // keys per entry of that list
+    int32_t n_stretches, stretch_least, n_first, n_entries;
+    int32_t L;
+    int32_t max_seq_len;
 };
 
 // exp(2 pi i * frac(t * rev)) in double; t * rev is exact enough for |t| < 2^62 * 2^-53 relative
