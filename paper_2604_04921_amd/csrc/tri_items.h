@@ -33,7 +33,7 @@ inline bool large_batch(int64_t instances, int max_seq_len, int n_cu)
 // 126 -> 109, 36 layers 693 -> 674; one layer of eight x 12289, half-split, 150 -> 44.5.  The cost was 768 keys while an item also
 // waited for its list entry, table and first rows; with those asked for an item ahead 448 is the better one: 144 x 2176 keys, scores
 // and selection, 53.1 -> 47.8 us, 576 129.5 -> 122, 288 x 1400 70.4 -> 62.4, 288 x 3000 97.7 -> 91.6, 288 x 17000, a step, 393 -> 385, the
-// others of 27 shapes equal; 256 is equal everywhere.  Counting an item's waves without a last tile as half or as whole idle ones takes 288 x
+// others of 27 shapes equal; 256 is equal everywhere.  (Batches that take stretches now among them: stretch_rounds.)  Counting an item's waves without a last tile as half or as whole idle ones takes 288 x
 // 2176 from 81.0 to 76.2, but 576 from 122 to 130, 288 x 3000 from 91.6 to 98 and 288 x 32768, a step, from 640 to 658.
 inline int item_keys(int64_t instances, int max_seq_len, int n_cu)
 {

@@ -33,8 +33,9 @@
 //     block (cbsz, abid).  Read from LDS four bands at a time by every lane instead, it took 48 (G > 4: 96) of a tile's 104 (152) LDS
 //     reads, 26 KB of LDS, and the registers of two pieces' entries: 64 x 8 x 131072 keys at G = 8, a step, 4999 -> 4662 us (half of it from
 //     the third wave per SIMD that now fits), 6 x 16 x 8 x 4096 to 65536 paged 1827 -> 1799, 9216 x 2176 half-split scattered, scores and selection,
-//     1346 -> 1316, one layer of 8 x 12289 half-split 35.5 -> 34.7, 36 x 8 x 8 x 32768 equal (bound by its reads and the raw scores' writes).  Nothing spills now
-//     (half-split kernels had 1 - 7 registers spilled).
+//     1346 -> 1316, one layer of 8 x 12289 half-split 35.5 -> 34.7, 36 x 8 x 8 x 32768 equal (bound by its reads and the raw scores' writes).  Half-split
+//     kernels, which had 1 - 7 registers spilled, spill none in work items and 2 - 4 (paged 2) in stretches; above four heads contiguous
+//     interleaved ones 2 - 4.
 // The vector instructions of four bands are issued first and their twelve (24) matrix instructions in one run after
 // them: a wave that alternates between the two kinds loses about 3.5 clocks per matrix instruction.
 #include <algorithm>
@@ -324,10 +325,9 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
     // what step `half` takes of the tile at slot n0 (cnt keys exist): eight 16-byte loads per lane.  For a whole tile every address is a
     // wave-uniform pointer (sixteen keys never straddle a block) plus the lane's constant offset; in the last, partial tile a key past
     // the end repeats the last one.  Kernels short of registers keep that constant and cut it off at the last row (tile_first,
-    // tile_last), a minimum per load, instead of a row number per load: half-split contiguous ones spill 3 - 6 registers so, not 17 - 22
-    // (9216 x 2176 scattered, scores and selection, 1336 -> 1318 us, 288 x 2170 85.7 -> 78.7, one layer of 8 x 12289 36.7 -> 34.9); the others lose
-    // 0.3 us with it on small calls.  Paged ones, the shortest, go that way with every tile (a branch of its own for the last one: 13 - 17
-    // registers spilled, 1.5 - 2 % half-split, 0.5 % interleaved).
+    // tile_last), a minimum per load, instead of a row number per load: half-split contiguous ones spill six registers more without it (9216 x
+    // 2176 scattered, scores and selection, 1301 / 1306 us); the others lose 0.3 us with it on small calls.  Paged ones go that way with every tile (a
+    // branch of its own for the last one took registers that were spilled: 1.5 - 2 % half-split, 0.5 % interleaved).
     // Paged caches: lane j of `btv` holds the physical block of keys n0 + 16 j .. + 15 (load_blocks; a block holds
     // 16 slots or more), asked for a tile ahead like the positions, so that no load here waits for a block-table
     // entry.
