@@ -32,6 +32,7 @@ struct FoldArgs {
     int32_t fold_seqs;      // sequences per workgroup
     int32_t seq_blocks;     // workgroups per (layer, KV head)
     int32_t band_shift;     // each once per 64 >> band_shift parts of 1 << band_shift bands
+    int32_t extra, extra_each;   // workgroups for everything but the tables, and how many of them a layer's row holds
     int32_t lane_kernel;    // layout of the phasor table: that of tri_score_lane.hip or the sixteen-lane kernel's
     float4 *phasors;        // relative-position phasor table of the MFMA score kernel, filled in by extra workgroups
     StretchPlan *stretches; // stretches of the general MFMA kernel, or NULL; its moments are cleared here
@@ -58,7 +59,7 @@ constexpr int kFoldSeqsMost = 32; // at most this many
 constexpr int kFoldThreads = 512;
 
 // The folded tables of one (layer, KV head), fold_seqs sequences and 1 << band_shift bands per workgroup: grid (Hkv * seq_blocks *
-// (64 >> band_shift) + extra, L), block 512.  The phasors a fold needs depend on the band and on the offsets or the query position only, and every
+// (64 >> band_shift) + extra_each, L), block 512.  The phasors a fold needs depend on the band and on the offsets or the query position only, and every
 // workgroup evaluates them for itself: (offset or sequence, band) pairs spread over its threads, three double-precision
 // sincos per thread for 16 offsets and 8 sequences and all bands, the offsets then added in their order by one thread per band.  The
 // kernel is bound by that chain of software sincos and pow, not by its work: a launch of its own for the phasors, in which one
@@ -66,9 +67,11 @@ constexpr int kFoldThreads = 512;
 // with 32 offsets); with this one a step on one head's 4096 keys takes 35.6 us instead of 39.5, on one layer of eight heads
 // x 32768 keys 74.3 instead of 78.4.  Where workgroups are few the bands of each go to two or four (launch_score), a sincos per thread: the
 // same steps 22.6 -> 22.2 and 47.4 -> 46.9 us, 32 x 2176 keys, scores and selection, 26.4 -> 26.0.
-// The extra workgroups of the first layer's row have nothing to do with the tables: the first writes the band frequencies, the second lists
-// the stretches or chunks of the MFMA score kernels (a launch of its own would cost more than the list; behind the first one's pow it cost small
-// calls 0.5 us), those after it fill the MFMA score kernel's phasor table when it needs one, an entry per thread.
+// The extra workgroups have nothing to do with the tables: the first writes the band frequencies, the second lists the stretches or
+// chunks of the MFMA score kernels (a launch of its own would cost more than the list; behind the first one's pow it cost small
+// calls 0.5 us), those after it fill the MFMA score kernel's phasor table when it needs one, an entry per thread.  They are spread over the
+// layers' rows.  (All of them in every row, where only the first row's had work, is a grid of 528 workgroups instead of 165 for 33 x 4
+// head-instances: scores of 64 keys each 17.4 us instead of 14.7, 64 x 1000 keys 19.3 / 17.3, 40 x 2 x 568 at G = 8 22.8 / 20.6.)
 __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
 {
     extern __shared__ __align__(16) double fold_lds[];
@@ -78,8 +81,9 @@ __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
     const int n_fold = a.Hkv * a.seq_blocks * parts, l = blockIdx.y;
     // Section 2.1: omega_f = theta^(-2f/d); kept as revolutions per position.  (kFoldThreads is a multiple of the
     // workgroup's bands: a thread's band is the same in every loop below)
-    const int extra = (int)blockIdx.x - n_fold;   // uniform over the workgroup
-    if (extra >= 0 && l > 0) return;
+    const bool folds = (int)blockIdx.x < n_fold;   // (uniform over the workgroup)
+    const int extra = folds ? -1 : l * a.extra_each + (int)blockIdx.x - n_fold;
+    if (extra >= a.extra) return;
     if (extra == 1) {
         if (a.stretches) plan_stretches(a.seq_len, a.S, a.max_seq_len, a.L, a.Hkv, a.stretch_least, a.n_stretches, a.n_first, a.work, a.stretches);
         else if (a.work) build_work_list(a.seq_len, a.S, a.max_seq_len, a.chunk_keys, a.work);
@@ -604,7 +608,9 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     if (fold_lds > 48 * 1024 &&
         hipFuncSetAttribute((const void *)fold_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kFoldLdsLimit) != hipSuccess)
         return hip_status("hipFuncSetAttribute(fold_kernel)");
-    hipLaunchKernelGGL(fold_kernel, dim3(m.n_kv_heads * fo.seq_blocks * (kBands >> fo.band_shift) + (fo.work ? 2 : 1) + table_entries / kFoldThreads, m.n_layers),
+    fo.extra = (fo.work ? 2 : 1) + table_entries / kFoldThreads;
+    fo.extra_each = (fo.extra + m.n_layers - 1) / m.n_layers;
+    hipLaunchKernelGGL(fold_kernel, dim3(m.n_kv_heads * fo.seq_blocks * (kBands >> fo.band_shift) + fo.extra_each, m.n_layers),
                        dim3(kFoldThreads), fold_lds, st, fo);
     if ((rc = hip_status("fold_kernel")) != TRI_OK) return rc;
 

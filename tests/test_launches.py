@@ -37,3 +37,14 @@ def test_calibration_launches_fit_the_grid(layers, heads):
         assert "centers_kernel" in name and x * threads < 2 ** 32 and y == z == 1
         covered += x
     assert covered >= layers * heads
+
+
+@pytest.mark.parametrize("layers,heads,rotated,dtype", [(1, 1, 0, 1), (1, 8, 0, 1), (13, 2, 0, 1), (36, 8, 0, 1), (36, 8, 1, 1), (61, 8, 0, 0)])
+def test_every_workgroup_of_the_fold_has_work(layers, heads, rotated, dtype):
+    """A workgroup per (layer, KV head) -- or per part of its bands, where there are few -- and those that list the batch, write the frequencies
+    and fill the phasor table (13 at most) once, not once per layer: less than one per layer leaves without work."""
+    [(status, launches, _)] = launch_probe.run([dict(entry="score", layers=layers, kv_heads=heads, group=2, n=500, rotated=rotated, dtype=dtype)])
+    assert status == 0
+    [(x, y, z)] = [grid for name, grid, _, _ in launches if "fold_kernel" in name]
+    assert y == layers and z == 1
+    assert any(layers * heads * parts <= x * y < layers * heads * parts + 13 + layers for parts in (1, 2, 4))
