@@ -57,6 +57,8 @@ __device__ __forceinline__ void unit_phasor(double t, double rev, double *c, dou
 constexpr int kFoldSeqs = 8;      // sequences per workgroup, more where workgroups abound,
 constexpr int kFoldSeqsMost = 32; // at most this many
 constexpr int kFoldThreads = 512;
+constexpr int kBandShift = 6;
+static_assert(kBands == 1 << kBandShift, "bands");
 
 // The folded tables of one (layer, KV head), fold_seqs sequences and 1 << band_shift bands per workgroup: grid (Hkv * seq_blocks *
 // (64 >> band_shift) + extra_each, L), block 512.  The phasors a fold needs depend on the band and on the offsets or the query position only, and every
@@ -66,17 +68,19 @@ constexpr int kFoldThreads = 512;
 // thread per band went through the offsets one after the other, and a second one for the tables took 5.8 + 4.6 us (10.6 + 5.1
 // with 32 offsets); with this one a step on one head's 4096 keys takes 35.6 us instead of 39.5, on one layer of eight heads
 // x 32768 keys 74.3 instead of 78.4.  Where workgroups are few the bands of each go to two or four (launch_score), a sincos per thread: the
-// same steps 22.6 -> 22.2 and 47.4 -> 46.9 us, 32 x 2176 keys, scores and selection, 26.4 -> 26.0.
+// same steps 22.6 -> 22.2 and 47.4 -> 46.9 us, 32 x 2176 keys, scores and selection, 26.4 -> 26.0.  SPLIT: only there are the
+// bands of a workgroup a variable (a constant saves the others 0.15 us: scores of 36 x 8 x 300 fp32 keys 28.2 -> 28.0, bf16 25.35 -> 25.2).
 // The extra workgroups have nothing to do with the tables: the first writes the band frequencies, the second lists the stretches or
 // chunks of the MFMA score kernels (a launch of its own would cost more than the list; behind the first one's pow it cost small
 // calls 0.5 us), those after it fill the MFMA score kernel's phasor table when it needs one, an entry per thread.  They are spread over the
 // layers' rows.  (All of them in every row, where only the first row's had work, is a grid of 528 workgroups instead of 165 for 33 x 4
 // head-instances: scores of 64 keys each 17.4 us instead of 14.7, 64 x 1000 keys 19.3 / 17.3, 40 x 2 x 568 at G = 8 22.8 / 20.6.)
+template <bool SPLIT>
 __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
 {
     extern __shared__ __align__(16) double fold_lds[];
     double (*const off_ph)[2] = reinterpret_cast<double (*)[2]>(fold_lds);   // e^{i w delta_j}: entry (j, band); row 0 then holds their mean
-    const int tid = threadIdx.x, bands = 1 << a.band_shift, parts = kBands >> a.band_shift;
+    const int tid = threadIdx.x, band_shift = SPLIT ? a.band_shift : kBandShift, bands = 1 << band_shift, parts = kBands >> band_shift;
     double (*const cur_ph)[2] = off_ph + a.n_off * bands;                    // e^{i w cur_pos[s]}
     const int n_fold = a.Hkv * a.seq_blocks * parts, l = blockIdx.y;
     // Section 2.1: omega_f = theta^(-2f/d); kept as revolutions per position.  (kFoldThreads is a multiple of the
@@ -95,13 +99,13 @@ __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
         else fast_phasor(a.theta, t, reinterpret_cast<float2 *>(a.phasors));
         return;
     }
-    const int f0 = extra == 0 ? 0 : (blockIdx.x & (parts - 1)) << a.band_shift, f = extra == 0 ? tid % kBands : f0 + (tid & (bands - 1));
+    const int f0 = extra == 0 ? 0 : (blockIdx.x & (parts - 1)) << band_shift, f = extra == 0 ? tid % kBands : f0 + (tid & (bands - 1));
     const double rev = pow(a.theta, -2.0 * (double)f / (double)kHeadDim) / kTwoPi;
     if (extra == 0) {
         if (tid < kBands) a.band_rev[f] = rev;
         return;
     }
-    const int x = blockIdx.x >> (6 - a.band_shift), h = x / a.seq_blocks, sb = x - h * a.seq_blocks;
+    const int x = blockIdx.x >> (kBandShift - band_shift), h = x / a.seq_blocks, sb = x - h * a.seq_blocks;
     // the thread's (band, query head) pair, the head fastest: neighbouring threads write neighbouring entries of [F][3][G].  Its
     // statistics are asked for ahead of the phasors.
     static_assert(kBands * kMaxGroup <= kFoldThreads, "a pair per thread");
@@ -115,7 +119,7 @@ __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
             for (int k = tid; k < a.n_entries * 2 * a.G; k += kFoldThreads) m[k] = 0.0;
         }
     for (int k = tid; k < (a.n_off + n_seq) * bands; k += kFoldThreads) {   // (the sequences' phasors lie behind the offsets')
-        const int j = k >> a.band_shift;
+        const int j = k >> band_shift;
         double c, s;
         unit_phasor(j < a.n_off ? (double)a.offsets[j] : (double)a.cur_pos[s0 + j - a.n_off], rev, &c, &s);
         off_ph[k][0] = c;
@@ -572,7 +576,7 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     while (fo.fold_seqs < kFoldSeqsMost && (int64_t)m.n_layers * m.n_kv_heads * ((c.n_seqs + 2 * fo.fold_seqs - 1) / (2 * fo.fold_seqs)) >= 2 * n_cu)
         fo.fold_seqs *= 2;
     fo.seq_blocks = (c.n_seqs + fo.fold_seqs - 1) / fo.fold_seqs;
-    fo.band_shift = 6;   // (half as many workgroups as CUs at most: 64 head-instances of 2176 keys, scores and selection, 29.5 -> 29.3 us with two parts)
+    fo.band_shift = kBandShift;   // (half as many workgroups as CUs at most: 64 head-instances of 2176 keys, scores and selection, 29.5 -> 29.3 us with two parts)
     const int64_t n_fold = (int64_t)m.n_layers * m.n_kv_heads * fo.seq_blocks;
     while (fo.band_shift > 4 && n_fold * (kBands >> fo.band_shift) * 2 <= n_cu / 2) --fo.band_shift;
     fo.Hq = m.n_q_heads;
@@ -605,12 +609,13 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     fo.lane_kernel = lane_kernel;
     const size_t fold_lds = (size_t)(m.n_offsets + std::min(fo.fold_seqs, c.n_seqs)) * kBands * 2 * sizeof(double);
     constexpr int kFoldLdsLimit = (kMaxOffsets + kFoldSeqsMost) * kBands * 2 * (int)sizeof(double);   // the most any call asks for
+    auto fold = fo.band_shift < kBandShift ? fold_kernel<true> : fold_kernel<false>;
     if (fold_lds > 48 * 1024 &&
-        hipFuncSetAttribute((const void *)fold_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kFoldLdsLimit) != hipSuccess)
+        hipFuncSetAttribute((const void *)fold, hipFuncAttributeMaxDynamicSharedMemorySize, kFoldLdsLimit) != hipSuccess)
         return hip_status("hipFuncSetAttribute(fold_kernel)");
     fo.extra = (fo.work ? 2 : 1) + table_entries / kFoldThreads;
     fo.extra_each = (fo.extra + m.n_layers - 1) / m.n_layers;
-    hipLaunchKernelGGL(fold_kernel, dim3(m.n_kv_heads * fo.seq_blocks * (kBands >> fo.band_shift) + fo.extra_each, m.n_layers),
+    hipLaunchKernelGGL(fold, dim3(m.n_kv_heads * fo.seq_blocks * (kBands >> fo.band_shift) + fo.extra_each, m.n_layers),
                        dim3(kFoldThreads), fold_lds, st, fo);
     if ((rc = hip_status("fold_kernel")) != TRI_OK) return rc;
 

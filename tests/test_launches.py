@@ -45,6 +45,7 @@ def test_every_workgroup_of_the_fold_has_work(layers, heads, rotated, dtype):
     and fill the phasor table (13 at most) once, not once per layer: less than one per layer leaves without work."""
     [(status, launches, _)] = launch_probe.run([dict(entry="score", layers=layers, kv_heads=heads, group=2, n=500, rotated=rotated, dtype=dtype)])
     assert status == 0
-    [(x, y, z)] = [grid for name, grid, _, _ in launches if "fold_kernel" in name]
+    [(name, (x, y, z))] = [(name, grid) for name, grid, _, _ in launches if "fold_kernel" in name]
     assert y == layers and z == 1
-    assert any(layers * heads * parts <= x * y < layers * heads * parts + 13 + layers for parts in (1, 2, 4))
+    [parts] = [p for p in (1, 2, 4) if layers * heads * p <= x * y < layers * heads * p + 13 + layers]
+    assert ("ILb1E" in name) == (parts > 1), name   # the bands of a workgroup are a variable only where they have to be
