@@ -10,6 +10,7 @@
 // (keys_kernel).
 #include <algorithm>
 
+#include "tri_bins.h"
 #include "tri_fill.h"
 
 namespace tri {
@@ -66,24 +67,16 @@ __device__ __forceinline__ float key_to_float(uint32_t u)
     return __uint_as_float(u ^ ((uint32_t)((int32_t)~u >> 31) | 0x80000000u));
 }
 // 2048 bins over [-4, 12): where a score lies in them, and its bin (scores beyond go to the first and the last one)
-__device__ __forceinline__ float bin_place(float score) { return fmaf(score, 128.0f, 512.0f); }
+__device__ __forceinline__ float bin_place(float score) { return fmaf(score, (float)kBinsPerUnit, (float)kBinOfZero); }
 __device__ __forceinline__ int linear_bin(float score) { return (int)__builtin_amdgcn_fmed3f(bin_place(score), 0.0f, 2047.0f); }
 __device__ __forceinline__ int linear_bin(uint32_t u) { return linear_bin(key_to_float(u)); }
 
-// The least key whose score lies at or above a place: bins are ranges of keys, since places rise with keys.  All lanes of the wave take
-// part, a sixty-fourth of the range left each.
-__device__ __forceinline__ uint32_t first_key(float place, int lane)
+// The least key of bin `bin` (1 to 2047) and those above it: bins are ranges of keys, since places rise with keys.
+__device__ __forceinline__ uint32_t first_key(int bin)
 {
-    uint32_t first = 0u;   // no key below it reaches the place
-#pragma unroll 1
-    for (int shift = 26; shift > -6; shift -= 6) {
-        const int sh = max(shift, 0);
-        const uint32_t u = first + ((uint32_t)(lane + 1) << sh) - 1u;   // the last key of the lane's part
-        // (patterns below that of -infinity and above that of infinity are no scores')
-        const bool below = u < 0x007fffffu || bin_place(key_to_float(u)) < place;
-        first += (uint32_t)__popcll(__ballot(below)) << sh;
-    }
-    return first;
+    const double edge = bin_edge(bin);
+    const float f = (float)edge;
+    return order_key(f) + ((double)f < edge ? 1u : 0u);
 }
 
 // Mean and 1/sigma of a head-instance's heads from the moments (block_stats; every thread of the workgroup calls).
@@ -486,9 +479,10 @@ __global__ __launch_bounds__(THREADS, HELD ? (THREADS == kSelThreads ? 4 : 5) : 
         gather_bin([&](uint32_t u) { return bin_place(key_to_float(u)) >= bin_hi && !last_bin; },
                    [&](uint32_t u) { const float place = bin_place(key_to_float(u)); return place >= bin_lo && (place < bin_hi || last_bin); });
     } else {
-        // Long rows: compared as keys, with the bin's ends found once (1 us, which rows in LDS don't win back: one of 4096 keys 7.2 -> 8.2), and not
-        // key by key as places.  With the single comparison of the emit below, 8 rows of 131072 keys 40.6 -> 36.4 us.
-        const uint32_t first = sel_bin == 0 ? 1u : first_key((float)sel_bin, lane), end = last_bin ? ~0u : first_key((float)(sel_bin + 1), lane);
+        // Long rows: compared as keys, with the bin's ends worked out once, and not key by key as places.  With the single comparison of the emit
+        // below, a selection of 8 rows of 131072 keys 54.1 -> 45.8 us.  (Ends that the wave searches for in twelve rounds: 47.2, and 8 sequences of 2176
+        // keys in rows of 131072 7.0 instead of 6.3, where the places take 6.2.)
+        const uint32_t first = sel_bin == 0 ? 1u : first_key(sel_bin), end = last_bin ? ~0u : first_key(sel_bin + 1);
         gather_bin([&](uint32_t u) { return u >= end; }, [&](uint32_t u) { return u - first < end - first; });
     }
 #pragma unroll
