@@ -527,10 +527,11 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
             int p_key = pos_next;
             // the wave's next tile: of this piece, of a later one, or its first of the next item
             const bool last = t_idx + W >= cur.n_tiles, ahead = !last || wave < nxt.n_tiles, leaves = t_idx + W >= at.t1;
-            Tile nt;
-            if (!leaves || !ahead) nt = tile_of(at, t_idx + W);
-            else if (last) nt = tile_of(piece_of(nxt, wave), wave);
-            else nt = tile_of(piece_of(cur, t_idx + W), t_idx + W);
+            // (Worked out here for the loads and once more behind the tile, pieces cost 1 - 4 % of short items: scores, us, 5760 x 655 post-RoPE keys at
+            // G = 4 222.2 -> 218.0, 5760 x 279 165.6 -> 160.6, 4608 x 300 half-split 141.2 -> 136.5; 2048 x 2176 equal.)
+            const int inst = at.inst, slot = at.slot;   // this tile's; `at` is the next one's piece from here on
+            if (leaves && ahead) at = last ? piece_of(nxt, wave) : piece_of(cur, t_idx + W);
+            const Tile nt = tile_of(at, last && ahead ? wave : t_idx + W);
             asm volatile("" : "+v"(p_key));   // (waits for the position here, and not for a copy between registers further down)
             if (ahead) {
                 if constexpr (PAGED) bt_next = load_blocks(nt);   // needed when its first loads go out, half a tile from now
@@ -761,7 +762,7 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
             // (16-byte stores need floats' alignment only; the rows' bytes fit 32 bits with room above them: mfma_path)
             constexpr uint32_t kNowhere = 0xffffffe0u;
             constexpr int kNonTemporal = 2;
-            float *const rw = a.raw + (int64_t)at.inst * G * c.max_seq_len;
+            float *const rw = a.raw + (int64_t)inst * G * c.max_seq_len;
             const __amdgpu_buffer_rsrc_t raw_rows = __builtin_amdgcn_make_buffer_rsrc(rw, 0, (uint32_t)G * (uint32_t)c.max_seq_len * 4u, 0x00027000);
             // ---- lane l holds key n0 + l for heads 4q .. 4q + 3: turned within the blocks, lane (b, j) holds keys n0 + 4b .. + 3 for head 4q + j
 #pragma unroll
@@ -809,15 +810,11 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
                     s2[q] += __shfl_xor(s2[q], o, 64);
                 }
                 if (lane < 4) {
-                    red[wave][(STRETCH ? at.slot * kSums : 0) + (4 * q + lane) * 2 + 0] = s1[q];
-                    red[wave][(STRETCH ? at.slot * kSums : 0) + (4 * q + lane) * 2 + 1] = s2[q];
+                    red[wave][(STRETCH ? slot * kSums : 0) + (4 * q + lane) * 2 + 0] = s1[q];
+                    red[wave][(STRETCH ? slot * kSums : 0) + (4 * q + lane) * 2 + 1] = s2[q];
                 }
             }
-            if (last) {
-                if (ahead) at = piece_of(nxt, wave);
-                break;
-            }
-            at = piece_of(cur, t_idx);
+            if (last) break;
             begin_piece();
         }
         if (wave == kLister && nxt.n_tiles > 0) {   // the item after the next (behind the last one nothing is waited for: 1 us of small calls)
