@@ -527,11 +527,19 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
             int p_key = pos_next;
             // the wave's next tile: of this piece, of a later one, or its first of the next item
             const bool last = t_idx + W >= cur.n_tiles, ahead = !last || wave < nxt.n_tiles, leaves = t_idx + W >= at.t1;
-            // (Worked out here for the loads and once more behind the tile, pieces cost 1 - 4 % of short items: scores, us, 5760 x 655 post-RoPE keys at
-            // G = 4 222.2 -> 218.0, 5760 x 279 165.6 -> 160.6, 4608 x 300 half-split 141.2 -> 136.5; 2048 x 2176 equal.)
-            const int inst = at.inst, slot = at.slot;   // this tile's; `at` is the next one's piece from here on
-            if (leaves && ahead) at = last ? piece_of(nxt, wave) : piece_of(cur, t_idx + W);
-            const Tile nt = tile_of(at, last && ahead ? wave : t_idx + W);
+            // Work items: `at` is the next tile's piece from here on.  (Worked out for the loads and once more behind the tile, pieces cost 1 - 4 % of
+            // short items: scores, us, 5760 x 655 post-RoPE keys at G = 4 222.2 -> 218.0, 5760 x 279 165.6 -> 160.6, 4608 x 300 half-split 141.2 -> 136.5;
+            // 2048 x 2176 equal.  Stretches, whose pieces take more registers, spill up to six more of them so and lose 2 % at G = 1.)
+            const int inst = at.inst;   // this tile's
+            Tile nt;
+            if constexpr (STRETCH) {
+                if (!leaves || !ahead) nt = tile_of(at, t_idx + W);
+                else if (last) nt = tile_of(piece_of(nxt, wave), wave);
+                else nt = tile_of(piece_of(cur, t_idx + W), t_idx + W);
+            } else {
+                if (last && ahead) at = piece_of(nxt, wave);
+                nt = tile_of(at, last && ahead ? wave : t_idx + W);
+            }
             asm volatile("" : "+v"(p_key));   // (waits for the position here, and not for a copy between registers further down)
             if (ahead) {
                 if constexpr (PAGED) bt_next = load_blocks(nt);   // needed when its first loads go out, half a tile from now
@@ -810,11 +818,15 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
                     s2[q] += __shfl_xor(s2[q], o, 64);
                 }
                 if (lane < 4) {
-                    red[wave][(STRETCH ? slot * kSums : 0) + (4 * q + lane) * 2 + 0] = s1[q];
-                    red[wave][(STRETCH ? slot * kSums : 0) + (4 * q + lane) * 2 + 1] = s2[q];
+                    red[wave][(STRETCH ? at.slot * kSums : 0) + (4 * q + lane) * 2 + 0] = s1[q];
+                    red[wave][(STRETCH ? at.slot * kSums : 0) + (4 * q + lane) * 2 + 1] = s2[q];
                 }
             }
-            if (last) break;
+            if (last) {
+                if (STRETCH && ahead) at = piece_of(nxt, wave);
+                break;
+            }
+            if (STRETCH) at = piece_of(cur, t_idx);   // (an item of its own has one piece)
             begin_piece();
         }
         if (wave == kLister && nxt.n_tiles > 0) {   // the item after the next (behind the last one nothing is waited for: 1 us of small calls)
