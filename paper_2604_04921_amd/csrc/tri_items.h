@@ -60,51 +60,80 @@ inline int item_keys(int64_t instances, int max_seq_len, int n_cu)
     return best;
 }
 
+// Waves per workgroup of the general MFMA kernel: three per SIMD where their registers allow it (168 each).
+constexpr int lane_waves(int G, bool paged, bool rotated, bool half_split) { return G <= 4 || !(paged || rotated || half_split) ? 12 : 8; }
+
 // Where work items leave some CUs with more than others, the general MFMA kernel takes stretches instead: the tiles of all head-instances,
 // (layer, KV head) by (layer, KV head) and in them sequence by sequence, one after the other, are cut into stretches of equal length (to
 // a tile), the same number for every CU, whatever head-instances they begin and end in.  The lengths are known on the device only, which
 // cuts a batch there (plan_stretches).
 constexpr int kStretchTile = 64;
+constexpr int kStretchLong = 64;     // tiles of a stretch where all sequences are max_seq_len long and a CU has several
 constexpr int kStretchSeqs = 1024;   // sequences at most: one workgroup counts their tiles
 constexpr int64_t kStretchTiles = (int64_t)1 << 30;   // tiles of all head-instances stay below
-// Stretches per CU, or 0: work items.  Both sides measured in one process, us with items / with stretches.  Scores and selection of 288 x 2176
-// scattered keys 75 / 61, half-split 76 / 61, 576 x 2176 115 / 102, 1152 192 / 179, 2016 305 / 299; scores of 960 ragged post-RoPE
-// head-instances up to 20011 684 / 651, of 160 140 / 122; steps on 768 ragged paged ones of 4096 to 65536 1795 / 1761, on 128 375 / 332, on
-// 576, 864, 1152 x 32768 1271 / 1244, 1911 / 1850, 2494 / 2430.  Items stay where
+// Stretches per CU where all sequences are max_seq_len long, and at most, or 0: work items.  Both sides measured in one process, us with items /
+// with stretches.  Scores and selection of 288 x 2176 scattered keys 72.7 / 59.9; scores of 1152 x 2176 half-split 178 / 167, of 960 ragged post-RoPE
+// head-instances up to 20011 587 / 564, of 114 ragged ones up to 21284 116 / 82; steps on 768 ragged paged ones of 4096 to 65536 1592 / 1548, on 576 and
+// 1152 x 32768 1254 / 1226, 2476 / 2433.  Over 260 drawn batches of one to 60 sequences that come here, scores with stretches take 0.99 of items' time
+// where all sequences are max_seq_len long, 0.83 where they are ragged, 0.82 where they end far below it.  (What the host cannot see is that items are
+// even for the lengths at hand; stretches then cost what they begin with, about 1 us, or up to 3 % (20 x 4 x 8 x 3854 post-RoPE 127.4 / 132.0), above
+// four heads, where an item of a stretch holds two pieces, up to 8 % of short sequences: 1584 x 2502 at G = 8 297 / 322.)  Items stay where
 //  - a CU has sixteen tiles at most: they begin sooner (8 x 12289 half-split, a step, 33.8 / 35.0, 64 x 2176 29.4 / 30.5);
 //  - the batch is large and the sequences are short (4608 x 2176 668 / 673, 9216 half-split 1331 / 1336), or there are more than four query heads (240 x
 //    131072 at G = 8 2225 / 2250: less arithmetic to spare for reads in a less even order), or 32 items per CU and more are even enough
 //    (2304 x 32768 4885 / 4929).
-// 64 tiles in a stretch: neighbouring workgroups then read 1 MB from one another (288 x 32768, a step, 635 with 64, 650 with 96, 649 with 128 and
-// 665 with 256; paged 768 1762, 1778, 1778; 576 x 8192 scattered half-split, the other way, 328, 319, 320).
 inline int stretch_rounds(int G, int64_t instances, int max_seq_len, int n_cu)
 {
     const int64_t cus = n_cu > 0 ? n_cu : 1, tiles = instances * (((int64_t)max_seq_len + kStretchTile - 1) / kStretchTile);
     if (tiles <= 16 * cus || tiles >= kStretchTiles) return 0;
     if (large_batch(instances, max_seq_len, n_cu) && (G > 4 || max_seq_len < kFastChunk || tiles >= 32 * cus * (kFastChunk / kStretchTile))) return 0;
-    return (int)((tiles + 64 * cus - 1) / (64 * cus));
+    return (int)((tiles + kStretchLong * cus - 1) / (kStretchLong * cus));
 }
-// tiles of a stretch at least: eight, more where a stretch has more anyway and a row would have more than sixty entries of moments
-inline int stretch_least(int64_t instances, int max_seq_len, int64_t stretches)
+// What a row's entries of moments are counted on: tiles of a stretch at least, eight, more where a CU has more anyway and a row would have more than
+// sixty entries.
+inline int stretch_least(int64_t instances, int max_seq_len, int n_cu)
 {
-    const int64_t tiles = ((int64_t)max_seq_len + kStretchTile - 1) / kStretchTile, each = instances * tiles / stretches;
+    const int64_t tiles = ((int64_t)max_seq_len + kStretchTile - 1) / kStretchTile, each = instances * tiles / (n_cu > 0 ? n_cu : 1);
     const int64_t few = (tiles + 59) / 60, least = each < few ? each : few;
     return least > 8 ? (int)least : 8;
 }
-// stretches of `total` tiles; the first tile of stretch i; the stretch that holds a tile
-constexpr uint32_t stretch_count(uint32_t total, uint32_t least, uint32_t most)
+// The number of stretches, as the device works it out from the lengths.  Long batches keep the number that max_seq_len asks for as long as that leaves
+// 24 tiles to a stretch: where lengths differ, shorter stretches even out better (steps on 768 ragged paged head-instances of 4096 to 65536 keys, 34
+// tiles to a stretch, 1552 us, with 60 1569).  Others, and sequences further below it, get as many per CU as make a stretch five rounds of twelve waves
+// or eight of eight, one more or less by what a CU needs for them: rounds of its waves, and seven tiles' time for a stretch's beginning and end (1 x 2 x 8
+// x 76303 scattered keys at G = 5, 75 tiles per CU, a step, 149.7 us as two stretches of a CU, 142.7 as one; six sequences of 22293 x 8 heads 80.6 / 73.9).
+constexpr uint32_t stretch_cost(uint32_t each, uint32_t stretches, uint32_t waves)
 {
-    const uint32_t fit = total / least;
-    return total == 0 ? 0 : fit < 1 ? 1 : fit < most ? fit : most;
+    const uint32_t tiles = (each + stretches - 1) / stretches;
+    return stretches * ((tiles + waves - 1) / waves * waves + 7);
+}
+// total: tiles of the batch, longest: of its longest sequence; most: what stretch_rounds says, for all CUs.  Fewer than asked for where a
+// head-instance would lie in more than `entries` of them, or they would have fewer than eight tiles although every CU has a stretch; a multiple of the
+// CUs as long as all have one.
+// (With the least length and the number counted on from max_seq_len alone, sequences far below it were cut into the wrong number: 8 x 2176 keys in
+// rows of 131072 into 7 stretches, 288 x 2176 into 279, 512 x 1000 in 32768 into 910.  Scores and selection, work items / that / now: 37.7 / 40.6 /
+// 23.5 us, 101.6 / 106.2 / 88.9 and 70.0 / 81.9 / 75.6.)
+constexpr uint32_t stretch_count(uint32_t total, uint32_t longest, uint32_t entries, uint32_t most, uint32_t cus, uint32_t waves)
+{
+    if (total == 0) return 0;
+    const uint32_t room = longest > 2 && entries > 1 ? (longest - 2) / (entries - 1) + 1 : 1;   // (stretch_entries)
+    const uint32_t few = total >= 8 * cus ? 8 : total >= cus ? total / cus : 1;
+    const uint32_t fit = total / (room > few ? room : few), each = (total + cus - 1) / cus;
+    const uint32_t goal = waves == 12 ? 60 : 64, low = each / goal > 0 ? each / goal : 1;
+    uint32_t rounds = most / cus;
+    if (rounds < 4 || each < 24 * rounds) rounds = stretch_cost(each, low + 1, waves) < stretch_cost(each, low, waves) ? low + 1 : low;
+    const uint32_t want = rounds * cus < most ? rounds * cus : most;
+    return fit >= want ? want : fit >= cus ? fit / cus * cus : fit > 0 ? fit : 1;
 }
 struct Stretches {
     uint32_t count, least, longer;   // the first `longer` ones have least + 1 tiles, the others least
 };
-constexpr Stretches stretches_of(uint32_t total, uint32_t least, uint32_t most)
+constexpr Stretches stretches_of(uint32_t total, uint32_t count)
 {
-    const uint32_t count = stretch_count(total, least, most), per = count > 0 ? count : 1;
+    const uint32_t per = count > 0 ? count : 1;
     return Stretches{count, total / per, total % per};
 }
+// the first tile of stretch i; the stretch that holds a tile
 constexpr uint32_t stretch_begin(const Stretches &st, uint32_t i) { return i * st.least + (i < st.longer ? i : st.longer); }
 constexpr uint32_t stretch_of(const Stretches &st, uint32_t tile)
 {

@@ -41,7 +41,7 @@ struct FoldArgs {
     int32_t *work;          // work list of the MFMA score kernels, or NULL when the generic kernel runs
     double *partials;       // [L][S][Hkv][n_entries][2G]
     int32_t chunk_keys;     // keys per entry of that list
-    int32_t n_stretches, stretch_least, n_first, n_entries;
+    int32_t n_stretches, n_first, n_entries, stretch_waves;
     int32_t L;
     int32_t max_seq_len;
 };
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
     const int extra = folds ? -1 : l * a.extra_each + (int)blockIdx.x - n_fold;
     if (extra >= a.extra) return;
     if (extra == 1) {
-        if (a.stretches) plan_stretches(a.seq_len, a.S, a.max_seq_len, a.L, a.Hkv, a.stretch_least, a.n_stretches, a.n_first, a.work, a.stretches);
+        if (a.stretches) plan_stretches(a.seq_len, a.S, a.max_seq_len, a.L, a.Hkv, a.n_entries, a.n_stretches, a.n_first, a.stretch_waves, a.work, a.stretches);
         else if (a.work) build_work_list(a.seq_len, a.S, a.max_seq_len, a.chunk_keys, a.work);
         return;
     }
@@ -113,8 +113,8 @@ __global__ __launch_bounds__(kFoldThreads) void fold_kernel(FoldArgs a)
     const float *ct = a.centers + (((int64_t)l * a.Hq + h * a.G + g) * kBands + fb) * 3;
     const float c0 = ct[0], c1 = ct[1], c2 = ct[2];
     const int s0 = sb * a.fold_seqs, n_seq = min(a.S - s0, a.fold_seqs);
-    if (a.stretches && f0 == 0)   // an entry that no stretch of the head-instance's writes counts as nothing
-        for (int j = 0; j < n_seq; ++j) {
+    if (a.stretches)   // an entry that no stretch of the head-instance's writes counts as nothing
+        for (int j = f0 >> band_shift; j < n_seq; j += parts) {
             double *const m = a.partials + (((int64_t)l * a.S + s0 + j) * a.Hkv + h) * a.n_entries * (2 * a.G);
             for (int k = tid; k < a.n_entries * 2 * a.G; k += kFoldThreads) m[k] = 0.0;
         }
@@ -594,13 +594,13 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     const int64_t n_inst = (int64_t)m.n_layers * c.n_seqs * m.n_kv_heads;
     const int rounds = lane_kernel && c.n_seqs <= kStretchSeqs ? stretch_rounds(G, n_inst, c.max_seq_len, n_cu) : 0;
     if (rounds > 0) {
-        const int count = rounds * n_cu, least = stretch_least(n_inst, c.max_seq_len, count), entries = stretch_entries(c.max_seq_len, least);
+        const int count = rounds * n_cu, least = stretch_least(n_inst, c.max_seq_len, n_cu), entries = stretch_entries(c.max_seq_len, least);
         if ((size_t)n_inst * entries * 2 * G * sizeof(double) <= wl.raw - wl.partials &&
             kStretchPlanAt + sizeof(StretchPlan) + (size_t)n_cu * sizeof(StretchStart) <= (size_t)kPhasorAreaBytes) {
             fo.stretches = reinterpret_cast<StretchPlan *>(ws + wl.phasors + kStretchPlanAt);
             fo.n_stretches = count;
-            fo.stretch_least = least;
             fo.n_first = n_cu;
+            fo.stretch_waves = lane_waves(G, c.block_size != 0, c.k_rotated != 0, m.pairs == TRI_PAIR_HALF);
             fo.n_entries = entries;
             fo.partials = reinterpret_cast<double *>(ws + wl.partials);
             fo.L = m.n_layers;
@@ -631,7 +631,6 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     sa.chunk_keys = chunk_keys;
     sa.stretches = reinterpret_cast<const int32_t *>(fo.stretches);
     sa.n_stretches = fo.n_stretches;
-    sa.stretch_least = fo.stretch_least;
     sa.n_first = fo.n_first;
     sa.n_tiles = fo.n_entries;
     FinalArgs fa{};

@@ -18,7 +18,7 @@ struct ScoreArgs {
     int32_t *work;           // MFMA kernel only: item counter and work list (fast_work_ints(S, Nmax) ints)
     int32_t chunk_keys;      // MFMA kernels only: keys per work item (= keys per entry of `partials`)
     const int32_t *stretches;   // general MFMA kernel: a StretchPlan instead of a work list, or NULL
-    int32_t n_stretches, stretch_least, n_first;   // at most, tiles each at least, how many of them the plan has
+    int32_t n_stretches, n_first;   // at most; how many of them the plan has
 };
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
@@ -93,34 +93,37 @@ __device__ __forceinline__ StretchStart stretch_start(uint32_t i, const Stretche
     const int off = r - before[s];
     return StretchStart{(int32_t)(l << 16 | (lh - l * n_kv_heads)), s, off, (int32_t)(i - stretch_of(st, begin - off)), (int32_t)(st.least + (i < st.longer ? 1 : 0))};
 }
-__device__ __forceinline__ void plan_stretches(const int32_t *seq_len, int n_seqs, int max_seq_len, int n_layers, int n_kv_heads, int least, int most,
-                                               int first, int32_t *work, StretchPlan *plan)
+__device__ __forceinline__ void plan_stretches(const int32_t *seq_len, int n_seqs, int max_seq_len, int n_layers, int n_kv_heads, int entries, int most,
+                                               int first, int waves, int32_t *work, StretchPlan *plan)
 {
-    __shared__ int before[kStretchSeqs], wave_sum[kStretchSeqs / 128];
+    __shared__ int before[kStretchSeqs], wave_sum[kStretchSeqs / 128], wave_most[kStretchSeqs / 128];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     auto tiles = [&](int s) { return s < n_seqs ? (clamp_len(seq_len[s], max_seq_len) + kStretchTile - 1) / kStretchTile : 0; };
     const int t0 = tiles(2 * tid), t1 = tiles(2 * tid + 1);
-    int cum = t0 + t1;
+    int cum = t0 + t1, longest = max(t0, t1);
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
         const int t = __shfl_up(cum, o, 64);
         if (lane >= o) cum += t;
+        longest = max(longest, __shfl_xor(longest, o, 64));
     }
-    if (lane == 63) wave_sum[wave] = cum;
+    if (lane == 63) wave_sum[wave] = cum, wave_most[wave] = longest;
     __syncthreads();
     int per_lh = 0;
 #pragma unroll
     for (int w = 0; w < kStretchSeqs / 128; ++w) {
         if (w < wave) cum += wave_sum[w];
         per_lh += wave_sum[w];
+        longest = max(longest, wave_most[w]);
     }
     before[2 * tid] = cum - t0 - t1;
     before[2 * tid + 1] = cum - t1;
     if (2 * tid < n_seqs) plan->before[2 * tid] = cum - t0 - t1;
     if (2 * tid + 1 < n_seqs) plan->before[2 * tid + 1] = cum - t1;
-    if (tid == 0) work[0] = 0, work[1] = per_lh;
+    const uint32_t total = (uint32_t)per_lh * (uint32_t)(n_layers * n_kv_heads);
+    const Stretches st = stretches_of(total, stretch_count(total, longest, entries, most, first, waves));
+    if (tid == 0) work[0] = 0, work[1] = per_lh, work[2] = (int)st.count;
     __syncthreads();
-    const Stretches st = stretches_of((uint32_t)per_lh * (uint32_t)(n_layers * n_kv_heads), least, most);
     for (int i = tid; i < first; i += kStretchSeqs / 2)
         plan->start[i] = i < (int)st.count ? stretch_start(i, st, per_lh, n_seqs, n_kv_heads, before) : StretchStart{};
 }

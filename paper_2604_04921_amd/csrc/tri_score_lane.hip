@@ -73,8 +73,6 @@ constexpr int table_block(bool rows, int band) { return rows ? 8 * (band / 32) +
 constexpr int table_quarter(bool rows, int band) { return rows ? band % 32 / 8 : band / 16; }
 constexpr int kTabQuad = 64 * 4;                                // floats per (component, quad of heads): four a lane
 constexpr int lane_quads(int G) { return (G + 3) / 4; }
-// Waves per workgroup: three per SIMD where their registers allow it (168 each).
-constexpr int lane_waves(int G, bool paged, bool rotated, bool half_split) { return G <= 4 || !(paged || rotated || half_split) ? 12 : 8; }
 constexpr int lane_slots(int G) { return G > 4 ? 2 : 4; }   // pieces of an item: as many tables as LDS has room for
 constexpr int lane_lds_bytes(int G, bool paged, bool rotated, bool half_split, bool stretch)
 {
@@ -170,7 +168,7 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
     typedef const __attribute__((address_space(4))) int32_t *ConstInts;
     const ConstInts work_list = (ConstInts)a.work, seq_len = (ConstInts)c.seq_len;
     const int per_lh = work_list[1];   // items, or tiles, of a (layer, KV head)
-    const Stretches cut = STRETCH ? stretches_of((uint32_t)per_lh * (uint32_t)(a.n_layers * c.n_kv_heads), a.stretch_least, a.n_stretches) : Stretches{};
+    const Stretches cut = STRETCH ? stretches_of((uint32_t)per_lh * (uint32_t)(a.n_layers * c.n_kv_heads), (uint32_t)work_list[2]) : Stretches{};
     const int n_items = STRETCH ? (int)cut.count : per_lh * a.n_layers * c.n_kv_heads;
     // A workgroup's first two items are its own: a permutation of its index, and the same behind the grid's first ones; the others come
     // from the counter.

@@ -40,3 +40,30 @@ def test_stretches(oracle, group, layers, heads, lens, pairs, rotated, paged):
             w["k"] = H.to_post_rope(w["k"], w["pos"], cfg.rope_theta, pairs, cfg.dtype)
 
     run_and_check(oracle, cfg, instances=instances, paged=paged, pairs=pairs, mutate=mutate, rotated=rotated)
+
+
+@pytest.mark.parametrize("group,lens,n,pairs,rotated,paged", [
+    (4, [130, 700, 64, 0, 1, 900], 4096, 0, False, False),    # fewer tiles than eight per CU
+    (4, [64, 1, 0, 0, 63, 2], 4096, 1, False, True),          # fewer than one per CU
+    (8, [2000, 1500, 0, 1700, 64, 1999], 4096, 0, False, False),
+    (2, [3, 4000, 0, 0, 64, 65], 4096, 0, True, True)])
+def test_lengths_far_below_the_reserved_one(oracle, group, lens, n, pairs, rotated, paged):
+    layers, heads = 3, 8
+    cfg = recipe.scaled(recipe.CONFIGS["c4_paged" if paged else "c2_layer"], n_layers=layers, n_seqs=len(lens), n_q_heads=heads * group,
+                        n_kv_heads=heads, seq_len=n, min_seq_len=0, budget=100, n_calib=16, positions="sparse", block_size=16 if paged else 0,
+                        seed=17 + group)
+    rng = np.random.default_rng(5)
+    last = layers * len(lens) * heads - 1
+    picks = sorted({0, last} | set(rng.integers(0, last, size=30).tolist()))
+
+    def mutate(w):
+        w["seq_len"][:] = lens
+        if pairs:
+            for name in ("k", "q_samples"):
+                x = w[name]
+                w[name] = np.ascontiguousarray(np.concatenate([x[..., 0::2], x[..., 1::2]], axis=-1))
+        if rotated:
+            w["k"] = H.to_post_rope(w["k"], w["pos"], cfg.rope_theta, pairs, cfg.dtype)
+
+    run_and_check(oracle, cfg, instances=[(i // (len(lens) * heads), i // heads % len(lens), i % heads) for i in picks], paged=paged, pairs=pairs,
+                  mutate=mutate, rotated=rotated)
