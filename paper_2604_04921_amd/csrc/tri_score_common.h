@@ -155,6 +155,23 @@ __device__ __forceinline__ void fast_phasor(double theta, int t, float2 *out)
 tri_status launch_score_fast(int G, const ScoreArgs &sa, hipStream_t st);
 template <int G>
 tri_status launch_score_lane(const ScoreArgs &sa, bool half_split, hipStream_t st);
+// (each group size is a compilation of its own)
+template <>
+tri_status launch_score_lane<1>(const ScoreArgs &sa, bool half_split, hipStream_t st);
+template <>
+tri_status launch_score_lane<2>(const ScoreArgs &sa, bool half_split, hipStream_t st);
+template <>
+tri_status launch_score_lane<3>(const ScoreArgs &sa, bool half_split, hipStream_t st);
+template <>
+tri_status launch_score_lane<4>(const ScoreArgs &sa, bool half_split, hipStream_t st);
+template <>
+tri_status launch_score_lane<5>(const ScoreArgs &sa, bool half_split, hipStream_t st);
+template <>
+tri_status launch_score_lane<6>(const ScoreArgs &sa, bool half_split, hipStream_t st);
+template <>
+tri_status launch_score_lane<7>(const ScoreArgs &sa, bool half_split, hipStream_t st);
+template <>
+tri_status launch_score_lane<8>(const ScoreArgs &sa, bool half_split, hipStream_t st);
 // The general kernel's table of e^{i w r}: entry (band pair bp, r) = (cos, sin) of bands 2bp and 2bp+1 at relative position r, at byte
 // bp * kLanePairStride + 16 r.  The fold kernel writes it with kLaneTablePhasors extra threads.
 constexpr int kLaneRange = 88;                                  // relative positions 0 .. 87: what LDS has room for
