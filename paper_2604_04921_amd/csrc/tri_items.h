@@ -89,13 +89,19 @@ inline int stretch_rounds(int G, int64_t instances, int max_seq_len, int n_cu)
     if (large_batch(instances, max_seq_len, n_cu) && (G > 4 || max_seq_len < kFastChunk || tiles >= 32 * cus * (kFastChunk / kStretchTile))) return 0;
     return (int)((tiles + kStretchLong * cus - 1) / (kStretchLong * cus));
 }
-// What a row's entries of moments are counted on: tiles of a stretch at least, eight, more where a CU has more anyway and a row would have more than
-// sixty entries.
-inline int stretch_least(int64_t instances, int max_seq_len, int n_cu)
+// What a row's entries of moments are counted on: tiles of a stretch at least, eight, more where a stretch has more anyway and a row would have more
+// than sixty entries.
+inline int stretch_least(int64_t instances, int max_seq_len, int64_t stretches)
 {
-    const int64_t tiles = ((int64_t)max_seq_len + kStretchTile - 1) / kStretchTile, each = instances * tiles / (n_cu > 0 ? n_cu : 1);
+    const int64_t tiles = ((int64_t)max_seq_len + kStretchTile - 1) / kStretchTile, each = instances * tiles / stretches;
     const int64_t few = (tiles + 59) / 60, least = each < few ? each : few;
     return least > 8 ? (int)least : 8;
+}
+// stretches of `total` tiles, of `least` each at least
+constexpr uint32_t stretch_count(uint32_t total, uint32_t least, uint32_t most)
+{
+    const uint32_t fit = total / least;
+    return total == 0 ? 0 : fit < 1 ? 1 : fit < most ? fit : most;
 }
 // The number of stretches, as the device works it out from the lengths.  Long batches keep the number that max_seq_len asks for as long as that leaves
 // 24 tiles to a stretch: where lengths differ, shorter stretches even out better (steps on 768 ragged paged head-instances of 4096 to 65536 keys, 34
@@ -113,24 +119,24 @@ constexpr uint32_t stretch_cost(uint32_t each, uint32_t stretches, uint32_t wave
 // (With the least length and the number counted on from max_seq_len alone, sequences far below it were cut into the wrong number: 8 x 2176 keys in
 // rows of 131072 into 7 stretches, 288 x 2176 into 279, 512 x 1000 in 32768 into 910.  Scores and selection, work items / that / now: 37.7 / 40.6 /
 // 23.5 us, 101.6 / 106.2 / 88.9 and 70.0 / 81.9 / 75.6.)
-constexpr uint32_t stretch_count(uint32_t total, uint32_t longest, uint32_t entries, uint32_t most, uint32_t cus, uint32_t waves)
+constexpr uint32_t stretches_wanted(uint32_t total, uint32_t longest, uint32_t entries, uint32_t most, uint32_t cus, uint32_t waves)
 {
     if (total == 0) return 0;
     const uint32_t room = longest > 2 && entries > 1 ? (longest - 2) / (entries - 1) + 1 : 1;   // (stretch_entries)
     const uint32_t few = total >= 8 * cus ? 8 : total >= cus ? total / cus : 1;
-    const uint32_t fit = total / (room > few ? room : few), each = (total + cus - 1) / cus;
+    const uint32_t fit = stretch_count(total, room > few ? room : few, total), each = (total + cus - 1) / cus;
     const uint32_t goal = waves == 12 ? 60 : 64, low = each / goal > 0 ? each / goal : 1;
     uint32_t rounds = most / cus;
     if (rounds < 4 || each < 24 * rounds) rounds = stretch_cost(each, low + 1, waves) < stretch_cost(each, low, waves) ? low + 1 : low;
     const uint32_t want = rounds * cus < most ? rounds * cus : most;
-    return fit >= want ? want : fit >= cus ? fit / cus * cus : fit > 0 ? fit : 1;
+    return fit >= want ? want : fit >= cus ? fit / cus * cus : fit;
 }
 struct Stretches {
     uint32_t count, least, longer;   // the first `longer` ones have least + 1 tiles, the others least
 };
-constexpr Stretches stretches_of(uint32_t total, uint32_t count)
+constexpr Stretches stretches_of(uint32_t total, uint32_t least, uint32_t most)
 {
-    const uint32_t per = count > 0 ? count : 1;
+    const uint32_t count = stretch_count(total, least, most), per = count > 0 ? count : 1;
     return Stretches{count, total / per, total % per};
 }
 // the first tile of stretch i; the stretch that holds a tile

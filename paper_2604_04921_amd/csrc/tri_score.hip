@@ -594,7 +594,7 @@ tri_status launch_score(const tri_model &m, const float *centers, const tri_cach
     const int64_t n_inst = (int64_t)m.n_layers * c.n_seqs * m.n_kv_heads;
     const int rounds = lane_kernel && c.n_seqs <= kStretchSeqs ? stretch_rounds(G, n_inst, c.max_seq_len, n_cu) : 0;
     if (rounds > 0) {
-        const int count = rounds * n_cu, least = stretch_least(n_inst, c.max_seq_len, n_cu), entries = stretch_entries(c.max_seq_len, least);
+        const int count = rounds * n_cu, least = stretch_least(n_inst, c.max_seq_len, count), entries = stretch_entries(c.max_seq_len, least);
         if ((size_t)n_inst * entries * 2 * G * sizeof(double) <= wl.raw - wl.partials &&
             kStretchPlanAt + sizeof(StretchPlan) + (size_t)n_cu * sizeof(StretchStart) <= (size_t)kPhasorAreaBytes) {
             fo.stretches = reinterpret_cast<StretchPlan *>(ws + wl.phasors + kStretchPlanAt);

@@ -121,7 +121,7 @@ __device__ __forceinline__ void plan_stretches(const int32_t *seq_len, int n_seq
     if (2 * tid < n_seqs) plan->before[2 * tid] = cum - t0 - t1;
     if (2 * tid + 1 < n_seqs) plan->before[2 * tid + 1] = cum - t1;
     const uint32_t total = (uint32_t)per_lh * (uint32_t)(n_layers * n_kv_heads);
-    const Stretches st = stretches_of(total, stretch_count(total, longest, entries, most, first, waves));
+    const Stretches st = stretches_of(total, 1, stretches_wanted(total, longest, entries, most, first, waves));
     if (tid == 0) work[0] = 0, work[1] = per_lh, work[2] = (int)st.count;
     __syncthreads();
     for (int i = tid; i < first; i += kStretchSeqs / 2)

@@ -168,7 +168,7 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
     typedef const __attribute__((address_space(4))) int32_t *ConstInts;
     const ConstInts work_list = (ConstInts)a.work, seq_len = (ConstInts)c.seq_len;
     const int per_lh = work_list[1];   // items, or tiles, of a (layer, KV head)
-    const Stretches cut = STRETCH ? stretches_of((uint32_t)per_lh * (uint32_t)(a.n_layers * c.n_kv_heads), (uint32_t)work_list[2]) : Stretches{};
+    const Stretches cut = STRETCH ? stretches_of((uint32_t)per_lh * (uint32_t)(a.n_layers * c.n_kv_heads), 1, (uint32_t)work_list[2]) : Stretches{};
     const int n_items = STRETCH ? (int)cut.count : per_lh * a.n_layers * c.n_kv_heads;
     // A workgroup's first two items are its own: a permutation of its index, and the same behind the grid's first ones; the others come
     // from the counter.

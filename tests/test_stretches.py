@@ -14,14 +14,15 @@ WRAPPER = """
 using namespace tri;
 extern "C" {
 int rounds(int G, long long instances, int n, int n_cu) { return stretch_rounds(G, instances, n, n_cu); }
-int least(long long instances, int n, int n_cu) { return stretch_least(instances, n, n_cu); }
+int least(long long instances, int n, long long stretches) { return stretch_least(instances, n, stretches); }
 int entries(int n, int least) { return stretch_entries(n, least); }
-unsigned count(unsigned total, unsigned longest, unsigned entries, unsigned most, unsigned n_cu, unsigned waves)
+unsigned count(unsigned total, unsigned least, unsigned most) { return stretches_of(total, least, most).count; }
+unsigned wanted(unsigned total, unsigned longest, unsigned entries, unsigned most, unsigned n_cu, unsigned waves)
 {
-    return stretch_count(total, longest, entries, most, n_cu, waves);
+    return stretches_wanted(total, longest, entries, most, n_cu, waves);
 }
-unsigned begin(unsigned total, unsigned count, unsigned i) { return stretch_begin(stretches_of(total, count), i); }
-unsigned of(unsigned total, unsigned count, unsigned tile) { return stretch_of(stretches_of(total, count), tile); }
+unsigned begin(unsigned total, unsigned least, unsigned most, unsigned i) { return stretch_begin(stretches_of(total, least, most), i); }
+unsigned of(unsigned total, unsigned least, unsigned most, unsigned tile) { return stretch_of(stretches_of(total, least, most), tile); }
 }
 """
 
@@ -36,7 +37,7 @@ def lib(tmp_path_factory):
                     src, "-o", so], check=True)
     so = ctypes.CDLL(so)
     so.rounds.argtypes = [ctypes.c_int, ctypes.c_longlong, ctypes.c_int, ctypes.c_int]
-    so.least.argtypes = [ctypes.c_longlong, ctypes.c_int, ctypes.c_int]
+    so.least.argtypes = [ctypes.c_longlong, ctypes.c_int, ctypes.c_longlong]
     for f in (so.count, so.begin, so.of):
         f.restype = ctypes.c_uint
     return so
@@ -52,16 +53,15 @@ def test_every_tile_once_and_room_for_the_moments(lib):
             continue
         taken += 1
         most = r * CUS
-        least = lib.least(lh * seqs, n, CUS)
+        least = lib.least(lh * seqs, n, most)
         entries = lib.entries(n, least)
         assert entries <= -(-n // 256) + 1   # an entry per 256 keys and one more: what workspaces are sized for
-        top = rng.choice([n, n, rng.randint(0, n), int(n ** rng.random())])   # lengths up to the reserved one, or far below it
-        lens = [rng.choice([0, 1, top, rng.randint(0, top), rng.randint(0, top)]) for _ in range(seqs)]
+        lens = [rng.choice([0, 1, n, rng.randint(0, n), rng.randint(0, n)]) for _ in range(seqs)]
         tiles = [-(-x // 64) for x in lens]
         total = sum(tiles) * lh
-        count = lib.count(total, max(tiles), entries, most, CUS, rng.choice([8, 12]))
+        count = lib.count(total, least, most)
         assert count <= most and (count > 0) == (total > 0)
-        starts = [lib.begin(total, count, i) for i in range(count + 1)]
+        starts = [lib.begin(total, least, most, i) for i in range(count + 1)]
         assert starts[0] == 0 and starts[-1] == total if total else True
         sizes = [b - a for a, b in zip(starts, starts[1:])]
         assert max(sizes) - min(sizes) <= 1 if sizes else True
@@ -69,10 +69,10 @@ def test_every_tile_once_and_room_for_the_moments(lib):
         for _ in range(min(lh, 3)):
             for t in tiles:
                 if t:
-                    first = lib.of(total, count, at)
-                    last = lib.of(total, count, at + t - 1)
+                    first = lib.of(total, least, most, at)
+                    last = lib.of(total, least, most, at + t - 1)
                     assert starts[first] <= at < starts[first + 1] and starts[last] <= at + t - 1 < starts[last + 1]
-                    assert last - first + 1 <= entries, (n, count, t)
+                    assert last - first + 1 <= entries, (n, least, t)
                 at += t
     assert taken > 100
 
@@ -87,13 +87,38 @@ def test_where_the_lines_lie(lib, group, instances, n, stretches):
     assert (lib.rounds(group, instances, n, CUS) > 0) == stretches
 
 
+def test_the_number_that_the_lengths_ask_for(lib):
+    """Lengths up to the reserved one, and far below it: every stretch has a tile, and a head-instance's lie in as many as it has entries for."""
+    rng = random.Random(12)
+    taken = 0
+    for _ in range(600):
+        n, seqs, lh = int(2 ** rng.uniform(0, 17)), rng.randint(1, 12), rng.randint(1, 300)
+        r = lib.rounds(4, lh * seqs, n, CUS)
+        if r == 0:
+            continue
+        taken += 1
+        most = r * CUS
+        entries = lib.entries(n, lib.least(lh * seqs, n, most))
+        top = rng.choice([n, n, rng.randint(0, n), int(n ** rng.random())])
+        tiles = [-(-x // 64) for x in (rng.choice([0, 1, top, rng.randint(0, top), rng.randint(0, top)]) for _ in range(seqs))]
+        total = sum(tiles) * lh
+        count = lib.wanted(total, max(tiles), entries, most, CUS, rng.choice([8, 12]))
+        assert count <= min(most, total) and (count > 0) == (total > 0)
+        assert count % CUS == 0 or count < CUS
+        at = 0
+        for _ in range(min(lh, 3)):
+            for t in tiles:
+                if t:
+                    assert lib.of(total, 1, count, at + t - 1) - lib.of(total, 1, count, at) + 1 <= entries, (n, count, t)
+                at += t
+    assert taken > 100
+
+
 @pytest.mark.parametrize("instances,tiles,n", [
     (8, 34, 131072), (288, 34, 131072), (72, 34, 131072), (512, 16, 32768), (512, 1, 1665), (136, 3, 2547), (288, 128, 32768), (1152, 64, 32768)])
 def test_lengths_far_below_the_reserved_one(lib, instances, tiles, n):
     """Every CU has its share of the tiles that there are, also where max_seq_len says little about them."""
-    rounds = lib.rounds(4, instances, n, CUS)
-    assert rounds > 0
-    most, total = rounds * CUS, instances * tiles
-    count = lib.count(total, tiles, lib.entries(n, lib.least(instances, n, CUS)), most, CUS, 12)
-    assert count % CUS == 0 or count < CUS
+    most, total = lib.rounds(4, instances, n, CUS) * CUS, instances * tiles
+    assert most > 0
+    count = lib.wanted(total, tiles, lib.entries(n, lib.least(instances, n, most)), most, CUS, 12)
     assert -(-count // CUS) * -(-total // count) <= 1.15 * -(-total // CUS) + 1, count   # tiles of the CU that has the most
