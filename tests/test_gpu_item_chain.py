@@ -1,5 +1,5 @@
 """Work items that follow one another in a workgroup: thousands of head-instances of ragged lengths, so that every workgroup takes
-several items, many of them with fewer tiles than the workgroup has waves, and rows of raw scores that start on cache lines
+several items or stretches, many of the items with fewer tiles than the workgroup has waves, and rows of raw scores that start on cache lines
 or do not; and the generic kernel's tiles of one and of two parts.  Raw and final scores of every length against the oracle.  The layers
 share one layer's keys (stride 0) and differ in their query statistics."""
 import numpy as np
@@ -15,10 +15,11 @@ pytestmark = pytest.mark.gpu
 LENS = [1, 64, 65, 129, 0, 511, 640, 700, 767, 768, 769, 900, 1023, 1024, 300, 1000]
 
 
-def check(oracle, lens, per_cu, group, pairs, paged, rotated, n, dtype="bf16", block=16):
+def check(oracle, lens, per_cu, group, pairs, paged, rotated, n, dtype="bf16", block=16, path=None):
     from paper_2604_04921_amd import binding as T
     kv_heads, S, n_cu = 4, len(lens), torch.cuda.get_device_properties(0).multi_processor_count
-    layers = max(1, -(-per_cu * n_cu // (S * kv_heads)))
+    layers = max(1, int(-(-per_cu * n_cu // (S * kv_heads))))
+    assert path is None or H.score_path(layers, S, kv_heads, group, n, pairs, paged, rotated) == path
     cfg = recipe.scaled(recipe.CONFIGS["c4_paged"], n_layers=1, n_seqs=S, n_q_heads=kv_heads * group, n_kv_heads=kv_heads, seq_len=n,
                         min_seq_len=None, budget=40, n_calib=64, positions="sparse" if group == 4 else "dense", block_size=block, dtype=dtype, seed=77 + group)
     w = recipe.generate(cfg)
@@ -61,8 +62,22 @@ def check(oracle, lens, per_cu, group, pairs, paged, rotated, n, dtype="bf16", b
 @pytest.mark.parametrize("group,pairs,paged,rotated,n", [(4, 0, False, False, 1024), (4, 1, False, False, 1031), (3, 1, True, False, 1028),
                                                          (1, 0, True, False, 1056), (8, 0, False, False, 1025), (6, 1, True, True, 1024),
                                                          (4, 0, False, True, 1030)])
-def test_chained_items(oracle, group, pairs, paged, rotated, n):
-    check(oracle, LENS, 6, group, pairs, paged, rotated, n)
+@pytest.mark.parametrize("per_cu,path", [(6, "stretches"), (8, "items")])   # eight head-instances per CU: a large batch
+def test_chained_items(oracle, group, pairs, paged, rotated, n, per_cu, path):
+    if path == "items" and paged and not pairs and not rotated:
+        path = "sixteen"
+    check(oracle, LENS, per_cu, group, pairs, paged, rotated, n, path=path)
+
+
+# three stretches per workgroup and more: its own two, then the counter's
+@pytest.mark.parametrize("group,pairs,paged,rotated", [(4, 0, False, False), (3, 1, True, False), (8, 0, False, False), (2, 1, True, True)])
+def test_chained_stretches(oracle, group, pairs, paged, rotated):
+    lens = [2047, 2000, 1999, 1984, 1, 0, 2046, 1900, 1800, 1700, 64, 2047, 1930, 1111, 2045, 2040]
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    layers = int(-(-7.5 * n_cu // (len(lens) * 4)))
+    tiles = sum(-(-m // 64) for m in lens) * layers * 4
+    assert H.stretches(layers * len(lens) * 4, group, lens, tiles, 2047, pairs, paged, rotated) >= 3 * n_cu
+    check(oracle, lens, 7.5, group, pairs, paged, rotated, 2047, path="stretches")
 
 
 # many head-instances: tiles of two parts; few: of one, the moments in the phasor table's place

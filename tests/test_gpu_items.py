@@ -25,6 +25,7 @@ def test_half_split_items(oracle, group, lens, paged, rotated):
                         block_size=16 if paged else 0, seed=77 + group)
 
     assert H.item_keys(2 * len(lens), max(lens)) == 512
+    assert H.score_path(1, len(lens), 2, group, max(lens), 1, paged, rotated) == "items"
 
     def mutate(w):
         for name in ("k", "q_samples"):

@@ -339,20 +339,19 @@ def test_chunk_boundaries(oracle):
     cfg = recipe.scaled(recipe.CONFIGS["c2_layer"], n_layers=1, n_seqs=7, n_q_heads=8, n_kv_heads=1, seq_len=16901,
                         min_seq_len=16901, budget=500, n_calib=128)
     k = H.item_keys(7, cfg.seq_len)
-    assert k == 512
+    assert k == 512 and H.score_path(1, 7, 1, 8, cfg.seq_len) == "items"
 
     def lens(w):
         w["seq_len"][:] = np.array([k - 1, k, k + 1, 16 * k - 1, 16 * k, 16 * k + 1, 16901], dtype=np.int32)
     run_and_check(oracle, cfg, mutate=lens)
 
 
-def test_work_items_of_two_rounds(oracle):
-    """Work items of whole sequences (as many head-instances as CUs): 2 layers x 16 sequences x 8 KV heads of up to 6200 keys,
-    lengths around two, four and six rounds of a workgroup's twelve waves (768 keys each); a dozen head-instances go through
+def test_whole_sequences_in_stretches(oracle):
+    """As many head-instances as CUs, cut into stretches: 2 layers x 16 sequences x 8 KV heads of up to 6200 keys, lengths around two, four and six rounds of a workgroup's twelve waves (768 keys each); a dozen head-instances go through
     the oracle, all of them through the compaction check's index rules."""
     cfg = recipe.scaled(recipe.CONFIGS["c2_layer"], n_layers=2, n_seqs=16, n_q_heads=32, n_kv_heads=8, seq_len=6200,
                         min_seq_len=6200, budget=300, n_calib=128)
-    assert H.item_keys(256, cfg.seq_len) >= cfg.seq_len
+    assert H.score_path(2, 16, 8, 4, cfg.seq_len) == "stretches"
 
     def lens(w):
         w["seq_len"][:] = np.array([1535, 1536, 1537, 3071, 3072, 3073, 4608, 6200, 6144, 100, 0, 1600, 5000, 2999, 64, 6199],
@@ -362,13 +361,13 @@ def test_work_items_of_two_rounds(oracle):
 
 
 @pytest.mark.parametrize("group,rotated", [(4, False), (4, True), (8, False)])
-def test_work_items_between_the_extremes(oracle, group, rotated):
-    """A batch large enough for work items above 512 keys and small enough not to reach 8192 or whole sequences (10 x 8
-    head-instances of up to 6200 keys: three items of 2112 on 256 CUs), lengths on either side of one and two items."""
+def test_parts_of_sequences_in_stretches(oracle, group, rotated):
+    """A batch of 10 x 8 head-instances of up to 6200 keys, stretches that hold a part of a sequence, lengths on either side of a third and
+    two thirds of it (what items of it would hold)."""
     cfg = recipe.scaled(recipe.CONFIGS["c2_layer"], n_layers=1, n_seqs=10, n_q_heads=8 * group, n_kv_heads=8, seq_len=6200,
                         min_seq_len=6200, budget=300, n_calib=64)
     k = H.item_keys(80, cfg.seq_len)
-    assert 512 < k < 8192 and 2 * k + 1 < cfg.seq_len
+    assert 512 < k < 8192 and 2 * k + 1 < cfg.seq_len and H.score_path(1, 10, 8, group, cfg.seq_len, rotated=rotated) == "stretches"
 
     def mutate(w):
         w["seq_len"][:] = np.array([k - 1, k, k + 1, 2 * k - 1, 2 * k, 2 * k + 1, 6200, 64, 0, k + 500], dtype=np.int32)
@@ -396,16 +395,16 @@ def test_all_sequences_empty():
     assert torch.equal(run.k.view(torch.int16), k0.view(torch.int16))
 
 
-def test_repeated_calls_give_the_same_bits():
-    """Work items reach the workgroups through a shared counter, in an order that differs from launch to launch; the
-    raw and final scores, the moments behind them and the kept sets must not depend on it.  4 x 16 x 8 head-instances
-    of ragged lengths up to 20000 keys generated on the device (up to three work items per sequence, about four per workgroup
-    the GPU holds), five calls of tri_score and of the fused step compared bit for bit."""
+@pytest.mark.parametrize("layers,seq_len,min_len,budget,path", [(4, 20000, 3000, 1024, "stretches"), (16, 1500, 400, 300, "items")])
+def test_repeated_calls_give_the_same_bits(layers, seq_len, min_len, budget, path):
+    """Work items and stretches reach the workgroups through a shared counter, in an order that differs from launch to launch; the
+    raw and final scores, the moments behind them and the kept sets must not depend on it.  512 head-instances of ragged lengths
+    up to 20000 keys (a dozen stretches per workgroup) and 2048 of up to 1500 (eight items per workgroup) generated on the device, five calls of tri_score and of the fused step compared bit for bit."""
     from paper_2604_04921_amd import binding as B
     from workload import device
-    cfg = recipe.scaled(recipe.CONFIGS["c2_layer"], n_layers=4, n_seqs=16, n_q_heads=32, n_kv_heads=8, seq_len=20000,
-                        min_seq_len=3000, budget=1024, n_calib=128)
-    assert -(-cfg.seq_len // H.item_keys(cfg.n_layers * cfg.n_seqs * cfg.n_kv_heads, cfg.seq_len)) >= 3
+    cfg = recipe.scaled(recipe.CONFIGS["c2_layer"], n_layers=layers, n_seqs=16, n_q_heads=32, n_kv_heads=8, seq_len=seq_len,
+                        min_seq_len=min_len, budget=budget, n_calib=128)
+    assert H.score_path(layers, 16, 8, 4, seq_len) == path
     w = device.generate(cfg, positions="sparse", layers=cfg.n_layers)
     L, S, Hq, Hkv, d, Bk = cfg.n_layers, cfg.n_seqs, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, cfg.budget
     model = B.Model(L, Hq, Hkv, d, cfg.rope_theta, cfg.offsets)
@@ -434,7 +433,7 @@ def test_repeated_calls_give_the_same_bits():
         if first is None:
             first = got
             assert int(kept_cnt.min()) == Bk and int(kept_cnt.max()) == Bk
-            assert not bool(torch.isnan(raw[0, 0, 0, :3000]).any())
+            assert not bool(torch.isnan(raw[0, 0, 0, :min_len]).any())
         else:
             for a, b in zip(first, got):
                 assert torch.equal(a, b), "call %d differs from the first" % rep

@@ -1,7 +1,10 @@
 """Launches as the library would make them, seen through a fake HIP runtime (no GPU needed)."""
+import random
+
 import pytest
 
 import launch_probe
+import tri_rules as R
 
 
 def test_lds_limits_do_not_depend_on_the_call():
@@ -49,3 +52,26 @@ def test_every_workgroup_of_the_fold_has_work(layers, heads, rotated, dtype):
     assert y == layers and z == 1
     [parts] = [p for p in (1, 2, 4) if layers * heads * p <= x * y < layers * heads * p + 13 + layers]
     assert ("ILb1E" in name) == (parts > 1), name   # the bands of a workgroup are a variable only where they have to be
+
+
+def test_the_score_kernel_that_the_rules_name():
+    """What R.score_path says, by which the GPU tests know the path that they take, against the kernels that the library launches."""
+    rng = random.Random(9)
+    calls, paths = [], []
+    while len(calls) < 300:
+        layers, seqs, heads, group = rng.randint(1, 40), rng.choice([rng.randint(1, 60), 1023, 1024, 1025]), rng.choice([1, 2, 4, 8]), rng.randint(1, 8)
+        n, block = int(2 ** rng.uniform(0, 17)), rng.choice([0, 0, 16, 32])
+        if layers * seqs * heads * -(-n // 256) >= 2 ** 31 or group * n * 4 >= 2 ** 31:
+            continue
+        pairs, rotated = int(rng.random() < 0.4), int(rng.random() < 0.3)
+        calls.append(dict(entry="score", layers=layers, seqs=seqs, kv_heads=heads, group=group, n=n, block=block, pairs=pairs, rotated=rotated))
+        paths.append((group, R.score_path(group, layers * seqs * heads, n, 256, seqs, bool(pairs), bool(block), bool(rotated)), pairs, block, rotated))
+    for c, (group, path, pairs, block, rotated), (status, launches, _) in zip(calls, paths, launch_probe.run(calls)):
+        assert status == 0, c
+        [name] = [name for name, _, _, _ in launches if "score_" in name]
+        if path == "sixteen":
+            assert "score_mfma_kernel" in name, (c, name)
+        else:
+            flags = "".join("Lb%dE" % bool(x) for x in (block, rotated, pairs, path == "stretches"))
+            assert "score_lane_kernelILi%dE%s" % (group, flags) in name, (c, name)
+    assert {p[1] for p in paths} == {"sixteen", "stretches", "items"}

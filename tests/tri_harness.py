@@ -17,6 +17,18 @@ def item_keys(instances, n):
     return tri_rules.item_keys(instances, n, torch.cuda.get_device_properties(0).multi_processor_count)
 
 
+def score_path(layers, n_seqs, heads, group, n, pairs=0, paged=False, rotated=False):
+    """tri_rules.score_path on this GPU."""
+    return tri_rules.score_path(group, layers * n_seqs * heads, n, torch.cuda.get_device_properties(0).multi_processor_count, n_seqs, bool(pairs),
+                                paged, rotated)
+
+
+def stretches(instances, group, lens, tiles, n, pairs=0, paged=False, rotated=False):
+    """How many stretches a batch of `tiles` tiles, its sequences `lens` long, is cut into on this GPU."""
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    return tri_rules.library().stretches(group, instances, n, n_cu, tiles, -(-max(lens) // 64), int(bool(pairs)), int(paged), int(rotated))
+
+
 def to_torch(a, dtype, device="cuda"):
     """numpy storage array (uint16 bf16 bits or float32) -> torch tensor on the device."""
     if dtype == "bf16":
