@@ -24,7 +24,8 @@ constexpr int kCenterWaves = kCenterThreads / 64;
 // (re, im) of eight bands of a head vector in 16-byte pieces, two (bf16) or four (fp32): with interleaved pairs one run of pieces, with
 // half-split ones a run of real and one of imaginary parts.  The O lanes that share 8 O bands (from octet q0 on) take the pieces of a run in
 // turn, so that a load instruction reads O neighbouring ones.  (A lane with its pieces side by side read every line by two or four
-// instructions, some of them from memory again: 4096 tokens x 36 x 32 heads, interleaved, 310 -> 243 us; 18 x 32 in fp32 450 -> 203, half-split 275 -> 202.)
+// instructions, some of them from memory again: 4096 tokens x 36 x 32 heads in bf16, interleaved, 298 -> 230 us, half-split equal; 18 x 32 in fp32
+// 455 -> 204, half-split 278 -> 203.)
 template <bool BF16, bool HALF, int O>
 struct Octet {
     static constexpr int kPieces = BF16 ? 2 : 4, kPer = BF16 ? 8 : 4;   // pieces, elements per piece
@@ -70,7 +71,7 @@ __device__ __forceinline__ double root(double s)
 }
 
 // The same for a sum that is not infinite, and NaN for one that is: one step of third order, and zero's root through a finite reciprocal
-// instead of a comparison (a quarter of the clocks of a sample and band: 4096 tokens x 36 x 32 half-split heads in bf16 257 -> 222 us).
+// instead of a comparison (a quarter of the clocks of a sample and band: 4096 tokens x 36 x 32 heads in bf16 262 -> 235 us half-split, 271 -> 230 interleaved).
 __device__ __forceinline__ double finite_root(double s)
 {
     const double r = __builtin_amdgcn_rsq(fmax(s, 1e-300));   // (the least square of an fp32 value other than 0 is 2e-90)
@@ -82,8 +83,8 @@ __device__ __forceinline__ double finite_root(double s)
 // 16-byte loads, the next token's on their way while one is summed.  Grid: 8 / O workgroups per (layer, head), eight apart in the
 // launch, so that those that share cache lines run on one XCD, side by side (workgroups go to the eight XCDs in turn).  Double sums in a fixed order: per thread
 // over its tokens, then a butterfly over the residues of a wave, then the waves in order.
-// Bound by its double arithmetic in bf16 (4096 tokens x 36 x 32 heads, 1.2 GB: 245 us half-split, 243 interleaved, 4.9 TB/s, where 282 and 302 stood before
-// finite_root and the order of the pieces) and by the memory stream in fp32 (18 x 32 heads, as many bytes: 202, 6.0 TB/s).
+// Bound by its double arithmetic in bf16 (4096 tokens x 36 x 32 heads, 1.2 GB: 235 us half-split, 230 interleaved, 5.2 TB/s, where 271 both stood before
+// finite_root and the order of the pieces) and by the memory stream in fp32 (18 x 32 heads, as many bytes: 203, 6.0 TB/s).
 template <bool BF16, bool HALF, int O>
 __global__ __launch_bounds__(kCenterThreads) void centers_kernel(CentersArgs a)
 {

@@ -155,11 +155,12 @@ constexpr int stretch_entries(int max_seq_len, int least)
 
 // Which kernel takes bf16 keys (item: item_keys() of the batch): that of tri_score_lane.hip, but paged pre-RoPE keys with interleaved pairs
 // in items of kFastChunk go to the one that spreads a key over sixteen lanes, with more than four query heads per KV head always, with up
-// to four on large batches of short sequences.  The line was drawn where that one was the faster before the other's items followed one
-// another without a gap.  It no longer is: whole steps, this kernel / the other, 768 x 4096 to 65536 keys at G = 8 2588 / 2466 us, at G = 5
-// 2433 / 2298, 32 x 65536 at G = 8 201 / 197, 512 x 8192 530 / 518; 4608 x 2176 at G = 4 2537 / 2491, at G = 1 2499 / 2447, 3072 x 4096 2048 / 2003.
-// tests/test_item_rules.py and test_gpu_sixteen_lanes.py state the line, and test_gpu_precision.py takes this kernel as the yardstick of
-// the other's sums: moving it means restating those.
+// to four on large batches of short sequences.  It is the slower one there, by 0 - 10 % on long dense sequences and up to twice on short ones
+// (scores and selection, this kernel / the other, us: 96 x 8 x 4096 to 65536 keys at G = 8 2147 / 2005, at G = 5 2047 / 1871, 32 x 65536 at G = 8 186 /
+// 189, 512 x 8192 332 / 310, scattered 431 / 361, 4608 x 2176 at G = 4 624 / 582, scattered 797 / 673, 4096 x 19 to 300 217 / 112), and the nearer one to
+// 64 bits on short dense ones: its raw scores by 1 - 2 % of their error, the final ones by up to 2 % above four heads (1024 keys, G = 8, dense and
+// sparse, 9.25e-8 / 9.38e-8 and 9.24e-8 / 9.43e-8; 65536 keys, the other way, 9.85e-8 / 9.66e-8).  These calls keep its sums until the other's are as
+// near there.
 inline bool sixteen_lane_kernel(int G, int item, int64_t instances, int max_seq_len, int n_cu, bool half_split, bool paged, bool rotated)
 {
     if (!paged || half_split || rotated || item != kFastChunk) return false;

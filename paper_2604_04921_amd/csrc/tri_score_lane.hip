@@ -32,10 +32,11 @@
 //   * The table lies in registers, 12 per quad of heads, a band's four entries in the lanes of one block: a matrix instruction names the
 //     block (cbsz, abid).  Read from LDS four bands at a time by every lane instead, it took 48 (G > 4: 96) of a tile's 104 (152) LDS
 //     reads, 26 KB of LDS, and the registers of two pieces' entries: 64 x 8 x 131072 keys at G = 8, a step, 4999 -> 4662 us (half of it from
-//     the third wave per SIMD that now fits), 6 x 16 x 8 x 4096 to 65536 paged 1827 -> 1799, 9216 x 2176 half-split scattered, scores and selection,
-//     1346 -> 1316, one layer of 8 x 12289 half-split 35.5 -> 34.7, 36 x 8 x 8 x 32768 equal (bound by its reads and the raw scores' writes).  Half-split
-//     kernels, which had 1 - 7 registers spilled, spill none in work items and 2 - 4 (paged 2) in stretches; above four heads contiguous
-//     interleaved ones 2 - 4.
+//     the third wave per SIMD that now fits), 9216 x 2176 half-split scattered, scores and selection,
+//     1346 -> 1316, one layer of 8 x 12289 half-split 35.5 -> 34.7, 6 x 16 x 8 x 4096 to 65536 paged within what its caches' places cost from process to
+//     process, 36 x 8 x 8 x 32768 equal (bound by its reads and the raw scores' writes).  Pre-RoPE kernels that spill vector registers: contiguous interleaved ones
+//     above four heads 2 - 4, half-split stretches of up to four heads 2 contiguous, 4 (8 at G = 1) paged, paged interleaved stretches at G = 1 2.
+//     Scalar ones go to vector registers in all of them, 4 - 27 in work items, 30 - 58 in stretches, most of them between items (post-RoPE 0 - 2 and 10 - 28).
 // The vector instructions of four bands are issued first and their twelve (24) matrix instructions in one run after
 // them: a wave that alternates between the two kinds loses about 3.5 clocks per matrix instruction.
 #include <algorithm>

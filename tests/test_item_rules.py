@@ -12,7 +12,8 @@ CUS = 256
 @pytest.mark.parametrize("instances,n", [(32, 65536), (16, 131072), (64, 32768), (128, 16384), (256, 8192), (512, 8192)])
 def test_whole_items_do_not_make_a_batch_large(instances, n):
     """Batches far below eight items per CU whose cost model ends at 8192 keys: up to four query heads per KV head they stay on
-    the kernel that takes every other small batch, above that the sixteen-lane kernel is the faster one."""
+    the kernel that takes every other small batch; above that they keep the sixteen-lane one, the slower of the two, whose sums are nearer to 64 bits
+    on short dense sequences."""
     assert R.item_keys(instances, n, CUS) == 8192 and not R.large_batch(instances, n, CUS)
     for group in (1, 2, 3, 4):
         assert not R.sixteen_lane_kernel(group, instances, n, CUS)
