@@ -76,8 +76,8 @@ constexpr int64_t kStretchTiles = (int64_t)1 << 30;   // tiles of all head-insta
 // head-instances up to 20011 587 / 564, of 114 ragged ones up to 21284 116 / 82; steps on 768 ragged paged ones of 4096 to 65536 1592 / 1548, on 576 and
 // 1152 x 32768 1254 / 1226, 2476 / 2433.  Over 260 drawn batches of one to 60 sequences that come here, scores with stretches take 0.99 of items' time
 // where all sequences are max_seq_len long, 0.83 where they are ragged, 0.82 where they end far below it.  (What the host cannot see is that items are
-// even for the lengths at hand; stretches then cost what they begin with, about 1 us, or up to 3 % (20 x 4 x 8 x 3854 post-RoPE 127.4 / 132.0), above
-// four heads, where an item of a stretch holds two pieces, up to 8 % of short sequences: 1584 x 2502 at G = 8 297 / 322.)  Items stay where
+// even for the lengths at hand; stretches then cost what they begin with, about 1 us, or up to 4 %: 20 x 4 x 8 x 3854 post-RoPE 136.5 / 141.4, 1152 x 4096 at
+// G = 8 298 / 310.)  Items stay where
 //  - a CU has sixteen tiles at most: they begin sooner (8 x 12289 half-split, a step, 33.8 / 35.0, 64 x 2176 29.4 / 30.5);
 //  - the batch is large and the sequences are short (4608 x 2176 668 / 673, 9216 half-split 1331 / 1336), or there are more than four query heads (240 x
 //    131072 at G = 8 2225 / 2250: less arithmetic to spare for reads in a less even order), or 32 items per CU and more are even enough
@@ -152,6 +152,15 @@ constexpr int stretch_entries(int max_seq_len, int least)
     const int tiles = (max_seq_len + kStretchTile - 1) / kStretchTile;
     return tiles < 2 ? 1 : (tiles - 2) / least + 2;
 }
+
+// Whether the stretch that a workgroup takes behind stretch `id` is its own (id + grid) or the counter's.  The counter is asked an item ahead,
+// and a stretch of more pieces than an item holds is two items, so that of workgroups that do as much work some ask a stretch ahead of others: of
+// three stretches per CU some took four and others two.  Up to eight per CU, which every batch of full sequences shorter than kStretchLong tiles stays below, all
+// are their workgroup's own; beyond, the counter's evenness is worth more than the one stretch that it may get wrong.  Scores, us, two own and the
+// others asked for / eight own: 1056 x 2433 half-split scattered keys at G = 8 281 / 236, 2016 x 2176 429 / 392, 1008 x 2562 at G = 5 270 / 226, 1584 x 2502
+// interleaved 311 / 288; all own: 1152 x 32768 at G = 4 2057 / 2096, 768 ragged paged ones of 4096 to 65536 1594 / 1621.
+constexpr int kOwnStretches = 8;
+constexpr bool own_stretch(int id, int grid, int stretches) { return id < grid || stretches <= kOwnStretches * grid; }
 
 // Which kernel takes bf16 keys (item: item_keys() of the batch): that of tri_score_lane.hip, but paged pre-RoPE keys with interleaved pairs
 // in items of kFastChunk go to the one that spreads a key over sixteen lanes, with more than four query heads per KV head always, with up

@@ -36,7 +36,7 @@
 //     1346 -> 1316, one layer of 8 x 12289 half-split 35.5 -> 34.7, 6 x 16 x 8 x 4096 to 65536 paged within what its caches' places cost from process to
 //     process, 36 x 8 x 8 x 32768 equal (bound by its reads and the raw scores' writes).  Pre-RoPE kernels that spill vector registers: contiguous interleaved ones
 //     above four heads 2 - 4, half-split stretches of up to four heads 2 contiguous, 4 (8 at G = 1) paged, paged interleaved stretches at G = 1 2.
-//     Scalar ones go to vector registers in all of them, 4 - 27 in work items, 30 - 58 in stretches, most of them between items (post-RoPE 0 - 2 and 10 - 28).
+//     Scalar ones go to vector registers in all of them, 4 - 27 in work items, 25 - 56 in stretches, most of them between items (post-RoPE 0 - 2 and 7 - 26).
 // The vector instructions of four bands are issued first and their twelve (24) matrix instructions in one run after
 // them: a wave that alternates between the two kinds loses about 3.5 clocks per matrix instruction.
 #include <algorithm>
@@ -172,7 +172,7 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
     const Stretches cut = STRETCH ? stretches_of((uint32_t)per_lh * (uint32_t)(a.n_layers * c.n_kv_heads), 1, (uint32_t)work_list[2]) : Stretches{};
     const int n_items = STRETCH ? (int)cut.count : per_lh * a.n_layers * c.n_kv_heads;
     // A workgroup's first two items are its own: a permutation of its index, and the same behind the grid's first ones; the others come
-    // from the counter.
+    // from the counter (own_stretch: those of a few stretches are all its own).
     const int first_item = (int)(((uint32_t)blockIdx.x * (uint32_t)a.first_mult) % gridDim.x);
     int later_item = 0;   // (thread 0's) the counter's answer for the item after the next
     // (zero, which the compiler does not know to be uniform: it would wait for the counter's answer at once to hand it to all lanes)
@@ -493,10 +493,11 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
     auto ask = [&]() {
         if (lane == 0) later_item = atomicAdd(a.work + own_zero, 1);
     };
-    bool own_next = STRETCH && id == first_item;   // (the listing wave's) the workgroup's second one is still to come
+    // (the listing wave's) whether the stretch behind `id` is the workgroup's own too
+    auto own_next = [&]() { return STRETCH && own_stretch(id, (int)gridDim.x, n_items); };
     for (;;) {
         const Item nxt = item_in(cur.buf == 2 ? 0 : cur.buf + 1);
-        const bool asks = wave == kLister && nxt.n_tiles > 0 && spent(rest) && !own_next;
+        const bool asks = wave == kLister && nxt.n_tiles > 0 && spent(rest) && !own_next();
         if (nxt.n_tiles > 0) load_tables(nxt);
         if (lane < P * kSums) red[wave][lane] = 0.0;   // (pieces without a tile of this wave's)
         double s1[NG], s2[NG];
@@ -830,8 +831,7 @@ __global__ __launch_bounds__(lane_waves(G, PAGED, ROTATED, HALF) * 64) void scor
         }
         if (wave == kLister && nxt.n_tiles > 0) {   // the item after the next (behind the last one nothing is waited for: 1 us of small calls)
             if (spent(rest)) {
-                id = own_next ? (int)gridDim.x + first_item : 2 * (int)gridDim.x + __builtin_amdgcn_readfirstlane(later_item);
-                own_next = false;
+                id = own_next() ? id + (int)gridDim.x : 2 * (int)gridDim.x + __builtin_amdgcn_readfirstlane(later_item);
                 rest = start_of(id);
             }
             list_item(rest, id, cur.buf == 0 ? 2 : cur.buf - 1);

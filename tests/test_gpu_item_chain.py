@@ -69,7 +69,7 @@ def test_chained_items(oracle, group, pairs, paged, rotated, n, per_cu, path):
     check(oracle, LENS, per_cu, group, pairs, paged, rotated, n, path=path)
 
 
-# three stretches per workgroup and more: its own two, then the counter's
+# three stretches per workgroup and more, all of them its own
 @pytest.mark.parametrize("group,pairs,paged,rotated", [(4, 0, False, False), (3, 1, True, False), (8, 0, False, False), (2, 1, True, True)])
 def test_chained_stretches(oracle, group, pairs, paged, rotated):
     lens = [2047, 2000, 1999, 1984, 1, 0, 2046, 1900, 1800, 1700, 64, 2047, 1930, 1111, 2045, 2040]
@@ -78,6 +78,17 @@ def test_chained_stretches(oracle, group, pairs, paged, rotated):
     tiles = sum(-(-m // 64) for m in lens) * layers * 4
     assert H.stretches(layers * len(lens) * 4, group, lens, tiles, 2047, pairs, paged, rotated) >= 3 * n_cu
     check(oracle, lens, 7.5, group, pairs, paged, rotated, 2047, path="stretches")
+
+
+# more than eight: its own two, then the counter's
+@pytest.mark.parametrize("group,pairs,paged,rotated", [(4, 0, False, False), (3, 1, True, False), (8, 0, False, False), (2, 1, True, True)])
+def test_counted_stretches(oracle, group, pairs, paged, rotated):
+    lens = [8100, 8191, 7000, 7936, 1, 0, 8000, 7700, 6400, 8191, 64, 7999, 8190, 1111, 8064, 8129]
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    layers = int(-(-7.5 * n_cu // (len(lens) * 4)))
+    tiles = sum(-(-m // 64) for m in lens) * layers * 4
+    assert H.stretches(layers * len(lens) * 4, group, lens, tiles, 8191, pairs, paged, rotated) > 8 * n_cu
+    check(oracle, lens, 7.5, group, pairs, paged, rotated, 8191, path="stretches")
 
 
 # many head-instances: tiles of two parts; few: of one, the moments in the phasor table's place

@@ -21,6 +21,7 @@ unsigned wanted(unsigned total, unsigned longest, unsigned entries, unsigned mos
 {
     return stretches_wanted(total, longest, entries, most, n_cu, waves);
 }
+int own(int id, int grid, int stretches) { return own_stretch(id, grid, stretches); }
 unsigned begin(unsigned total, unsigned least, unsigned most, unsigned i) { return stretch_begin(stretches_of(total, least, most), i); }
 unsigned of(unsigned total, unsigned least, unsigned most, unsigned tile) { return stretch_of(stretches_of(total, least, most), tile); }
 }
@@ -122,3 +123,43 @@ def test_lengths_far_below_the_reserved_one(lib, instances, tiles, n):
     assert most > 0
     count = lib.wanted(total, tiles, lib.entries(n, lib.least(instances, n, most)), most, CUS, 12)
     assert -(-count // CUS) * -(-total // count) <= 1.15 * -(-total // CUS) + 1, count   # tiles of the CU that has the most
+
+
+@pytest.mark.parametrize("instances,tiles,waves,slots", [(1056, 39, 8, 2), (1056, 40, 8, 2), (1008, 41, 8, 2), (2016, 34, 8, 2), (1584, 40, 12, 2), (1152, 64, 12, 2),
+                                                         (2016, 20, 12, 4), (2016, 13, 12, 4)])
+def test_every_workgroup_has_its_share(lib, instances, tiles, waves, slots):
+    """The stretches that workgroups end up with where some of them are one item and others, of more pieces than an item holds, two: each item in the time
+    of its tiles (and seven), the number of a later stretch asked for at the beginning of an item, where the next one is its stretch's last."""
+    total, n = instances * tiles, tiles * 64
+    count = lib.wanted(total, tiles, lib.entries(n, lib.least(instances, n, lib.rounds(8, instances, n, CUS) * CUS)), lib.rounds(8, instances, n, CUS) * CUS,
+                       CUS, waves)
+    assert count % CUS == 0
+
+    def items(i):   # tiles of the items of stretch i
+        at, end, sizes = lib.begin(total, 1, count, i), lib.begin(total, 1, count, i + 1), []
+        while at < end:
+            cut = min(end, (at // tiles + 1) * tiles)
+            sizes.append(cut - at)
+            at = cut
+        return [sum(sizes[j:j + slots]) for j in range(0, len(sizes), slots)]
+
+    counter, taken = 2 * CUS, [[w] for w in range(CUS)]
+    listed = [[(t, w) for t in items(w)] for w in range(CUS)]   # the items that a workgroup knows of
+    last = list(range(CUS))
+    clock = [(0, w) for w in range(CUS)]
+    while clock:
+        now, w = min(clock)
+        clock.remove((now, w))
+        while last[w] < count and len(listed[w]) < 3:   # the item at hand, the next one, the one after it
+            if lib.own(last[w], CUS, count):
+                nxt = last[w] + CUS
+            else:
+                nxt, counter = counter, counter + 1
+            last[w] = nxt
+            if nxt < count:
+                taken[w].append(nxt)
+                listed[w] += [(t, nxt) for t in items(nxt)]
+        if listed[w]:
+            clock.append((now + listed[w].pop(0)[0] + 7, w))
+    assert sorted(i for t in taken for i in t) == list(range(count))
+    assert all(len(t) == count // CUS for t in taken), sorted(set(len(t) for t in taken))
